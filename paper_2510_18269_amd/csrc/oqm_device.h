@@ -36,6 +36,11 @@ __device__ __forceinline__ float dpp_f32(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+
 // All-reduce (min and max at once) over aligned sets of LANES lanes, LANES in {1,2,4,8,16}.
 template <int LANES>
 __device__ __forceinline__ void group_minmax(float& mn, float& mx) {

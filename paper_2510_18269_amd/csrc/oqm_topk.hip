@@ -1,28 +1,58 @@
 // Selection of the k best frame-groups per layer (paper Eq. 12 TopK; the
 // supplement keeps the selected indices in sorted, i.e. temporal, order).
 //
-// One workgroup of 1024 threads per row.  The k-th largest score is found by a
-// 4-pass, 8-bit most-significant-digit radix select over order-preserving
-// 32-bit keys (LDS histograms), which is O(T) and exact.  The winners are then
+// Ascending index order (what the retrieval uses) and rows of up to 4096 scores: the row is held
+// in registers and the threshold is found bit by bit with ballots (oqm_select.h).  The launch is
+// bound by the latency of its serial steps (and by fetching its own code: unrolling 16 keys per
+// lane costs more than the barriers it saves), so rows of up to 256 scores take one wave without
+// any barrier, longer ones the fewest waves that keep a lane at 4 (8 above 1024) keys.  Kernel
+// time at 28 rows, this form against the radix select below: 256 scores 3.6 / 5.6 us, 1024
+// 6.0 / 6.3 us, 3600 8.4 / 10.6 us; one row: 2.5 / 4.6, 4.0 / 5.3, 5.7 / 9.6 us.  At 1024 scores
+// one wave with 16 keys takes 7.6 us; at 4096 four waves with 16 keys 9.7 us against 7.9 us.
+//
+// Longer rows, and the best-first order: one workgroup of 1024 threads per row.  The k-th
+// largest score is found by a 4-pass, 8-bit most-significant-digit radix select over
+// order-preserving 32-bit keys (LDS histograms), which is O(T) and exact.  The winners are then
 // compacted in index order with wave ballots, which yields the ascending-index
 // output directly and resolves equal scores by lowest index: of the entries
 // equal to the threshold only the first `need` (by index) are taken.  For the
 // score-descending order the k winners are sorted with an LDS bitonic network.
-// The step is latency-bound: T <= a few thousand scores per row.
+#include <type_traits>
+
 #include "oqm_common.h"
 #include "oqm_device.h"
+#include "oqm_select.h"
 
 namespace oqm {
 namespace {
 
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkWaves = kTopkThreads / 64;
+constexpr int kTopkMaxInRegisters = 4096;
 constexpr int kCachedKeys = 2 * kTopkMaxSortedK;  // keys kept in LDS when the row fits
 
-// Larger float <=> larger unsigned key; -0 and +0 map to the same key.
-__device__ __forceinline__ uint32_t orderable(float s) {
-    const uint32_t u = __float_as_uint(s + 0.0f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+template <int WAVES, int KEYS>
+__global__ void __launch_bounds__(64 * WAVES)
+topk_ascending_kernel(const float* __restrict__ scores, const int64_t stride, const int n, const int k,
+                      const int k_eff, int32_t* __restrict__ idx) {
+    __shared__ uint32_t slots[2][WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t* out = idx + (int64_t)blockIdx.x * k;
+    if (k_eff == n) {  // everything is chosen
+        for (int i = threadIdx.x; i < n; i += 64 * WAVES) out[i] = i;
+        return;
+    }
+    const float* s = scores + (int64_t)blockIdx.x * stride;
+    float x[KEYS];
+#pragma unroll
+    for (int c = 0; c < KEYS; ++c) x[c] = s[(uint32_t)min((wave * KEYS + c) * 64 + lane, n - 1)];
+    uint32_t key[KEYS];
+#pragma unroll
+    for (int c = 0; c < KEYS; ++c) {
+        asm volatile("" : "+v"(x[c]));  // all loads in flight before the first is used (the compiler would branch around each)
+        key[c] = (wave * KEYS + c) * 64 + lane < n ? orderable(x[c]) : 0u;
+    }
+    select_largest<WAVES, KEYS>(key, k_eff, wave, lane, out, slots);
 }
 
 __global__ void __launch_bounds__(kTopkThreads)
@@ -179,6 +209,17 @@ topk_kernel(const float* __restrict__ scores, const int64_t stride, const int n,
 hipError_t launch_topk(const float* scores, int64_t stride, int n_rows, int n_groups, int k,
                        int k_eff, int order, int32_t* idx, hipStream_t s) {
     if (n_rows == 0 || k_eff == 0) return hipSuccess;
+    if (order == TOM_ORDER_INDEX_ASC && n_groups <= kTopkMaxInRegisters) {
+        auto go = [&](auto waves, auto keys) {
+            constexpr int W = decltype(waves)::value, C = decltype(keys)::value;
+            topk_ascending_kernel<W, C><<<dim3(n_rows), dim3(64 * W), 0, s>>>(scores, stride, n_groups, k, k_eff, idx);
+        };
+        using std::integral_constant;
+        if (n_groups <= 256) go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+        else if (n_groups <= 1024) go(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+        else go(integral_constant<int, 8>{}, integral_constant<int, 8>{});
+        return hipGetLastError();
+    }
     topk_kernel<<<dim3(n_rows), dim3(kTopkThreads), 0, s>>>(scores, stride, n_groups, k, k_eff,
                                                             order, idx);
     return hipGetLastError();

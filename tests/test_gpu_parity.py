@@ -343,6 +343,21 @@ def test_topk_against_oracle(oqm, T, k):
         assert np.all(got[:, k_eff:] == -7)
 
 
+@pytest.mark.parametrize("T", [2, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 4095, 4096, 4097])
+def test_topk_at_the_edges_of_its_row_lengths(oqm, T):
+    """Each form of the selection at the shortest and longest row it takes, k from one to all."""
+    g = torch.Generator().manual_seed(T)
+    s = torch.randn(4, T, generator=g)
+    s[1] = torch.round(s[1] * 2) / 2                               # ties across lanes and waves
+    s[2] = -s[2].abs() - 1.0                                       # all negative
+    s[3] = torch.where(s[3] > 0, float("inf"), float("-inf"))
+    for k in sorted({1, min(2, T), T // 2, T - 1, T}):
+        idx = torch.full((4, k), -7, dtype=torch.int32, device="cuda")
+        assert oqm.tom_oqm_topk(s.cuda(), T, 4, T, k, idx) == k
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), H.orc.topk(s.numpy(), k, oqm.TOM_ORDER_INDEX_ASC)[0])
+
+
 def test_topk_all_equal_and_monotone_rows(oqm):
     s = torch.zeros(2, 500)
     s[1] = torch.arange(500, dtype=torch.float32)
