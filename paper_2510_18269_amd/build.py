@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libtom_oqm.so")
 OBJ = os.path.join(HERE, "_build")
+BINDING = os.path.join(HERE, "_oqm_binding.so")
 SELFCHECK = os.path.join(HERE, "selfcheck_division.bin")
 
 SOURCES = ["oqm_api.hip", "oqm_quantize.hip", "oqm_quantize_tokens.hip", "oqm_dequant.hip", "oqm_score.hip",
@@ -52,6 +54,13 @@ def build(verbose: bool = False) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    # the Python side's argument marshalling: host code only, linked against the library beside it
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-I", INCLUDE,
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "oqm_binding.cpp"), "-o", BINDING,
+           "-L", HERE, "-ltom_oqm", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"binding build failed:\n{r.stdout}\n{r.stderr}")
     cmd = ["hipcc", *COMMON, "-shared", os.path.join(CSRC, "bench_probe.hip"), "-o", BENCH_LIB]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -1,9 +1,10 @@
-"""Thin ctypes binding of libtom_oqm.so (the C ABI in include/tom_oqm.h).
+"""Thin binding of libtom_oqm.so (the C ABI in include/tom_oqm.h).
 
 Argument marshalling only: every step of the path runs in the library's HIP
-kernels.  PyTorch is used for device memory (`torch.empty`, `.data_ptr()`) and
-for the current HIP stream, nothing else.  If the library has not been built,
-importing this module raises: there is no CPU fallback.
+kernels.  The hot-path calls go through `_oqm_binding` (csrc/oqm_binding.cpp), the
+others through ctypes.  PyTorch is used for device memory (`torch.empty`,
+`.data_ptr()`) and for the current HIP stream, nothing else.  If the library or the
+binding has not been built, importing this module raises: there is no CPU fallback.
 """
 from __future__ import annotations
 
@@ -95,6 +96,8 @@ def _load():
 
 lib = _load()
 
+from . import _oqm_binding as _native  # noqa: E402  (linked against the library that was just loaded)
+
 _DTYPE_OF_TORCH = {torch.float32: TOM_F32, torch.bfloat16: TOM_BF16, torch.float16: TOM_F16}
 _TORCH_OF_DTYPE = {v: k for k, v in _DTYPE_OF_TORCH.items()}
 
@@ -117,13 +120,22 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
-def _stream(stream) -> int:
-    if stream is None:
-        # without a GPU only argument validation can run; it never reaches a launch
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
-    if isinstance(stream, int):
-        return stream
-    return stream.cuda_stream
+def _raise(status: int) -> None:
+    raise TomError(status, tom_last_error())
+
+
+def _first_stream() -> int:
+    """The current stream where the device has not been initialised yet."""
+    # without a GPU only argument validation can run; it never reaches a launch
+    return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0
+
+
+def _no_device(*_) -> int:
+    raise RuntimeError("this build of PyTorch has no device support")
+
+
+_native.setup(_raise, C.ArgumentError, torch.cuda.is_initialized, getattr(torch._C, "_cuda_getDevice", _no_device),
+              getattr(torch._C, "_cuda_getCurrentRawStream", _no_device), _first_stream)
 
 
 def tom_oqm_query_sizes(cfg: tom_oqm_config_t) -> tom_oqm_sizes_t:
@@ -151,7 +163,7 @@ def tom_oqm_num_groups(h: int) -> int:
 
 
 def tom_oqm_set_num_groups(h: int, n: int) -> None:
-    _check(lib.tom_oqm_set_num_groups(h, n))
+    _native.set_num_groups(h, n)
 
 
 def tom_oqm_destroy(h: int) -> None:
@@ -168,17 +180,9 @@ def tom_oqm_quantize_append(h: int, layer0: int, n_layers: int, n_frames: int, k
     """k, v: device tensors (or raw device pointers).  `strides` = (frame, layer, head, token)
     in elements; None means a contiguous [n_frames][n_layers][H_k][G][d] tensor.
     Returns the first group slot written."""
-    if strides is None:
-        s = k.stride()
-        assert k.dim() == 5 and s[4] == 1, "contiguous channel axis expected"
-        strides = (s[0], s[1], s[2], s[3])
-        assert tuple(v.stride()) == tuple(k.stride())
-    sarr = (C.c_int64 * 4)(*strides)
-    first = C.c_int32(-1)
-    _check(lib.tom_oqm_quantize_append(h, layer0, n_layers, n_frames, _ptr(k), _ptr(v),
-                                       _ptr(k_for_summary), sarr, 1 if commit else 0,
-                                       _stream(stream), C.byref(first)))
-    return first.value
+    if strides is not None:
+        strides = tuple((C.c_int64 * 4)(*strides))
+    return _native.quantize_append(h, layer0, n_layers, n_frames, k, v, k_for_summary, strides, commit, stream)
 
 
 def tom_oqm_score_workspace_bytes(h: int, n_layers: int, t_q: int, path: int = TOM_SCORE_AUTO,
@@ -191,32 +195,24 @@ def tom_oqm_score_groups(h: int, layer0: int, n_layers: int, q, t_q: int, scores
                          workspace=None, stream=None, q_dtype: int | None = None) -> None:
     if q_dtype is None:
         q_dtype = _DTYPE_OF_TORCH[q.dtype]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib.tom_oqm_score_groups(h, layer0, n_layers, _ptr(q), q_dtype, t_q, _ptr(scores),
-                                    score_stride, _ptr(token_scores), path, _ptr(workspace),
-                                    ws_bytes, _stream(stream)))
+    _native.score_groups(h, layer0, n_layers, q, q_dtype, t_q, scores, score_stride, token_scores, path, workspace,
+                         stream)
 
 
 def tom_oqm_topk(scores, score_stride: int, n_rows: int, n_groups: int, k: int, idx,
                  order: int = TOM_ORDER_INDEX_ASC, stream=None) -> int:
     """Returns k_eff = min(k, n_groups)."""
-    k_eff = C.c_int32(-1)
-    _check(lib.tom_oqm_topk(_ptr(scores), score_stride, n_rows, n_groups, k, order, _ptr(idx),
-                            C.byref(k_eff), _stream(stream)))
-    return k_eff.value
+    return _native.topk(scores, score_stride, n_rows, n_groups, k, order, idx, stream)
 
 
 def tom_oqm_dequant_gather(h: int, layer0: int, n_layers: int, idx, k: int, k_eff: int, k_out,
                            v_out, stream=None) -> None:
-    _check(lib.tom_oqm_dequant_gather(h, layer0, n_layers, _ptr(idx), k, k_eff, _ptr(k_out),
-                                      _ptr(v_out), _stream(stream)))
+    _native.dequant_gather(h, layer0, n_layers, idx, k, k_eff, k_out, v_out, stream)
 
 
 def tom_oqm_assemble_active(h: int, layer0: int, n_layers: int, idx, k: int, k_eff: int,
                             prefix_rows: int, sys_k, sys_v, k_out, v_out, stream=None) -> None:
-    _check(lib.tom_oqm_assemble_active(h, layer0, n_layers, _ptr(idx), k, k_eff, prefix_rows,
-                                       _ptr(sys_k), _ptr(sys_v), _ptr(k_out), _ptr(v_out),
-                                       _stream(stream)))
+    _native.assemble_active(h, layer0, n_layers, idx, k, k_eff, prefix_rows, sys_k, sys_v, k_out, v_out, stream)
 
 
 def tom_oqm_retrieve(h: int, layer0: int, n_layers: int, q, t_q: int, k: int, scores,
@@ -226,13 +222,8 @@ def tom_oqm_retrieve(h: int, layer0: int, n_layers: int, q, t_q: int, k: int, sc
     """score -> top-k -> assemble in one call.  Returns k_eff."""
     if q_dtype is None:
         q_dtype = _DTYPE_OF_TORCH[q.dtype]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    k_eff = C.c_int32(-1)
-    _check(lib.tom_oqm_retrieve(h, layer0, n_layers, _ptr(q), q_dtype, t_q, k, path, _ptr(scores),
-                                score_stride, _ptr(idx), prefix_rows, _ptr(sys_k), _ptr(sys_v),
-                                _ptr(k_out), _ptr(v_out), _ptr(workspace), ws_bytes,
-                                C.byref(k_eff), _stream(stream)))
-    return k_eff.value
+    return _native.retrieve(h, layer0, n_layers, q, q_dtype, t_q, k, path, scores, score_stride, idx, prefix_rows,
+                            sys_k, sys_v, k_out, v_out, workspace, stream)
 
 
 def tom_oqm_retrieve_noalloc(h: int, layer0: int, n_layers: int, q, t_q: int, k: int, scores,
@@ -242,12 +233,8 @@ def tom_oqm_retrieve_noalloc(h: int, layer0: int, n_layers: int, q, t_q: int, k:
     """tom_oqm_retrieve without a workspace: the score scratch is the library's static array."""
     if q_dtype is None:
         q_dtype = _DTYPE_OF_TORCH[q.dtype]
-    k_eff = C.c_int32(-1)
-    _check(lib.tom_oqm_retrieve_noalloc(h, layer0, n_layers, _ptr(q), q_dtype, t_q, k, path,
-                                        _ptr(scores), score_stride, _ptr(idx), prefix_rows,
-                                        _ptr(sys_k), _ptr(sys_v), _ptr(k_out), _ptr(v_out),
-                                        C.byref(k_eff), _stream(stream)))
-    return k_eff.value
+    return _native.retrieve_noalloc(h, layer0, n_layers, q, q_dtype, t_q, k, path, scores, score_stride, idx,
+                                    prefix_rows, sys_k, sys_v, k_out, v_out, stream)
 
 
 def tom_oqm_static_scratch_bytes() -> int:

@@ -1,0 +1,83 @@
+"""The native argument marshalling (csrc/oqm_binding.cpp) takes and refuses what the ctypes
+prototypes of the same functions do.  No GPU: every call ends in the library's validation."""
+import ctypes as C
+
+import pytest
+import torch
+
+
+@pytest.fixture()
+def store():
+    from paper_2510_18269_amd import oqm
+    h = oqm.tom_oqm_create(oqm.make_config(2, 2, 4, 64, 4, 32, 8))
+    oqm.tom_oqm_bind(h, 0x1000, 0x1000, 0x1000)
+    yield oqm, h
+    oqm.tom_oqm_destroy(h)
+
+
+class FakeTensor:
+    """What the binding reads of a tensor: its place, its strides, its size."""
+    def __init__(self, strides=(), is_cuda=True, numel=0):
+        self.strides, self.is_cuda, self.n = strides, is_cuda, numel
+    def data_ptr(self): return 0x1000
+    def dim(self): return len(self.strides)
+    def stride(self): return self.strides
+    def numel(self): return self.n
+    def element_size(self): return 1
+
+
+def test_arguments_that_ctypes_refuses(store):
+    oqm, h = store
+    for bad in (1.0, "1", None):
+        with pytest.raises(C.ArgumentError):
+            oqm.tom_oqm_topk(0x1000, 8, bad, 0, 1, 0x1000)
+        with pytest.raises(C.ArgumentError):
+            oqm.tom_oqm_set_num_groups(h, bad)
+    with pytest.raises(AssertionError, match="device tensor"):
+        oqm.tom_oqm_topk(torch.zeros(8), 8, 1, 8, 1, 0x1000)
+    with pytest.raises(AttributeError):
+        oqm.tom_oqm_topk(object(), 8, 1, 8, 1, 0x1000)
+    with pytest.raises(AttributeError):
+        oqm.tom_oqm_retrieve(h, 0, 2, 0x1000, 1, 1, 0x1000, 8, 0x1000, 0x1000, 0x1000, 0x1000, q_dtype=oqm.TOM_F32)
+
+
+def test_integers_are_truncated_like_c_int32(store):
+    oqm, h = store
+    oqm.tom_oqm_set_num_groups(h, (1 << 32) + 3)
+    assert oqm.tom_oqm_num_groups(h) == 3
+    with pytest.raises(oqm.TomError) as e:
+        oqm.tom_oqm_set_num_groups(h, -1)
+    assert e.value.status == oqm.TOM_ERR_INVALID_ARG and "n = -1" in str(e.value)
+    assert oqm.tom_oqm_topk(0, 8, 0, 8, 3, 0) == 3        # no rows: nothing launched, k_eff returned
+    with pytest.raises(oqm.TomError, match="handle is NULL"):
+        oqm.tom_oqm_set_num_groups(None, 0)
+
+
+def test_strides_of_tensors_and_of_raw_pointers(store):
+    oqm, h = store
+    good = (2 * 2 * 4 * 64, 2 * 4 * 64, 4 * 64, 64, 1)
+    with pytest.raises(AssertionError, match="contiguous channel"):
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, FakeTensor(good[1:]), FakeTensor(good[1:]))
+    with pytest.raises(AssertionError, match="contiguous channel"):
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, FakeTensor(good[:4] + (2,)), FakeTensor(good[:4] + (2,)))
+    with pytest.raises(AssertionError):
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, FakeTensor(good), FakeTensor((4,) + good[1:]))
+    with pytest.raises(oqm.TomError, match="strides"):    # an odd frame stride, from the tensor and as given
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, FakeTensor((3,) + good[1:]), FakeTensor((3,) + good[1:]))
+    with pytest.raises(oqm.TomError, match=r"strides\[0\] = 3"):
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, 0x1000, 0x1000, strides=[3, 1024, 256, 64])
+    with pytest.raises(oqm.TomError, match="token stride 0"):   # fewer than four: the rest are 0, as in a C array
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, 0x1000, 0x1000, strides=(2048, 1024, 256))
+    with pytest.raises(IndexError):
+        oqm.tom_oqm_quantize_append(h, 0, 2, 1, 0x1000, 0x1000, strides=(1, 2, 3, 4, 5))
+    assert oqm.tom_oqm_quantize_append(h, 0, 2, 0, FakeTensor(good), FakeTensor(good)) == 0
+
+
+def test_workspace_size_is_that_of_the_tensor(store):
+    oqm, h = store
+    oqm.tom_oqm_set_num_groups(h, 4)
+    need = oqm.tom_oqm_score_workspace_bytes(h, 2, 1)
+    with pytest.raises(oqm.TomError, match=f"{need} bytes needed, {need - 1} given"):
+        oqm.tom_oqm_score_groups(h, 0, 2, 0x1000, 1, 0x1000, 8, workspace=FakeTensor(numel=need - 1), q_dtype=oqm.TOM_F32)
+    with pytest.raises(oqm.TomError, match="0 given"):
+        oqm.tom_oqm_score_groups(h, 0, 2, 0x1000, 1, 0x1000, 8, q_dtype=oqm.TOM_F32)
