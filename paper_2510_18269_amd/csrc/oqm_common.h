@@ -72,7 +72,10 @@ inline uint32_t reciprocal_u32(uint32_t d) { return d <= 1 ? 0xffffffffu : (uint
 struct DequantArgs {
     const uint8_t* codes;
     const void* meta;
-    const int32_t* idx;  // [n_layers][k]
+    const int32_t* idx;  // [n_layers][k]; unused when all_idx is given
+    int32_t* all_idx;    // every stored group is taken in order, and these indices are written; or NULL
+    const char* sys_k;   // source of the prefix rows [n_layers][H_k][prefix_rows][d], or NULL
+    const char* sys_v;
     void* k_out;
     void* v_out;
     int32_t n_kv_heads, head_dim, group_tokens, qgroup, capacity_groups;
@@ -85,6 +88,7 @@ struct DequantArgs {
     // reciprocal floor(2^32 / chunks) for oqm::div_by.
     int32_t chunks, rows_per_chunk;
     uint32_t inv_chunks;
+    int32_t prefix_blocks;  // workgroups per (layer, K|V, head) that copy prefix rows
 };
 
 struct ScoreArgs {
@@ -106,7 +110,9 @@ struct ScoreArgs {
 // ---- launchers (each validates nothing: the API layer has done that) ------
 hipError_t launch_quantize_append(const QuantArgs& a, int in_dtype, hipStream_t s);
 hipError_t launch_quantize_append_tokens(const QuantArgs& a, int in_dtype, hipStream_t s);
+// Copies the prefix rows too where a.sys_k is given.
 hipError_t launch_dequant_gather(const DequantArgs& a, int out_dtype, hipStream_t s);
+// The prefix rows alone.
 hipError_t launch_prefix_copy(const DequantArgs& a, const void* sys_k, const void* sys_v, int out_dtype,
                               hipStream_t s);
 hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s);

@@ -1,9 +1,9 @@
 // Reconstruction of the selected frame-groups into the bounded active KV buffer
 // (paper Sec. 3.4, Eq. 11 and Eq. 13; supplement "Cache reconstruction for decoding").
 //
-// Grid (rank * chunks + chunk, 2*head + K|V, layer): a workgroup of 256 threads owns
+// Grid (prefix blocks, then rank * chunks + chunk; 2*head + K|V; layer): a workgroup of 256 threads owns
 // up to three row passes (48 token rows at head_dim 128) of one head tile of one
-// selected group; consecutive workgroups write consecutive row blocks of the active
+// selected group (the first `prefix_blocks` copy system-token rows instead); consecutive workgroups write consecutive row blocks of the active
 // buffer.  It reads the group index from device memory (the index array never visits
 // the host), streams its rows' packed nibbles and (scale, zero) pairs, and writes them
 // to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns one
@@ -26,6 +26,13 @@
 namespace oqm {
 namespace {
 
+// System-token prefix (the part of the paper's dual-structure memory that stays in 16 bits): piece
+// `block` (256 lanes x 16 bytes) of the prefix rows of one head's active buffer, bit for bit.
+__device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t bytes, unsigned block) {
+    const int64_t off = ((int64_t)block * kBlock + threadIdx.x) * 16;
+    if (off < bytes) *reinterpret_cast<u32x4*>(dst + off) = *reinterpret_cast<const u32x4*>(src + off);
+}
+
 // kUnroll: rows per lane whose loads are issued before any is converted (the host cuts the tile
 // into chunks that one trip covers).
 template <typename OUT, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB>
@@ -34,15 +41,29 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     constexpr uint32_t CW = BITS;          // bytes of packed codes per lane and row (8 channels)
     constexpr uint32_t CMASK = (1u << BITS) - 1u;
     const int H = a.n_kv_heads, d = a.head_dim, G = a.group_tokens;
-    const int r = a.chunks > 1 ? (int)div_by(blockIdx.x, a.chunks, a.inv_chunks) : (int)blockIdx.x;
-    const int row_begin = ((int)blockIdx.x - r * a.chunks) * a.rows_per_chunk;
-    const int row_end = min(G, row_begin + a.rows_per_chunk);
     const int kv = blockIdx.y & 1;
     const int h = blockIdx.y >> 1;
     const int li = blockIdx.z;
+    const int64_t head = (int64_t)li * H + h;
+    const int64_t head_rows = (int64_t)a.prefix_rows + (int64_t)a.k * G;  // rows per head buffer
+    char* const head_out = static_cast<char*>(kv ? a.v_out : a.k_out) + head * head_rows * (int64_t)d * EB;
+    if ((int)blockIdx.x < a.prefix_blocks) {  // uniform
+        copy_prefix((kv ? a.sys_v : a.sys_k) + head * a.prefix_rows * (int64_t)d * EB, head_out,
+                    (int64_t)a.prefix_rows * d * EB, blockIdx.x);
+        return;
+    }
+    const int piece = (int)blockIdx.x - a.prefix_blocks;
+    const int r = a.chunks > 1 ? (int)div_by(piece, a.chunks, a.inv_chunks) : piece;
+    const int row_begin = (piece - r * a.chunks) * a.rows_per_chunk;
+    const int row_end = min(G, row_begin + a.rows_per_chunk);
 
-    const int t = a.idx[(int64_t)li * a.k + r];
-    if ((unsigned)t >= (unsigned)a.n_groups) return;  // not a stored group: leave the rows alone
+    int t = r;
+    if (a.all_idx) {  // uniform
+        if (blockIdx.y == 0 && row_begin == 0 && threadIdx.x == 0) a.all_idx[(int64_t)li * a.k + r] = r;
+    } else {
+        t = a.idx[(int64_t)li * a.k + r];
+        if ((unsigned)t >= (unsigned)a.n_groups) return;  // not a stored group: leave the rows alone
+    }
 
     const int lpr = d >> 3;
     const int rpp = kBlock / lpr;
@@ -63,9 +84,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
 #pragma unroll
         for (int i = 0; i < 8; ++i) ch[i] = widen_pair(meta_t[slot * 8 + i]);
     }
-    const int64_t head_rows = (int64_t)a.prefix_rows + (int64_t)a.k * G;  // rows per head buffer
-    char* out = static_cast<char*>(kv ? a.v_out : a.k_out) +
-                (((int64_t)li * H + h) * head_rows + a.prefix_rows + (int64_t)r * G) * (int64_t)d * EB;
+    char* out = head_out + ((int64_t)a.prefix_rows + (int64_t)r * G) * (int64_t)d * EB;
     // offsets inside one tile fit 32 bits (G * d * 4 < 2^31 is checked on the host)
     const uint32_t code_lane = ((uint32_t)row0 * lpr + slot) * CW;
     const int meta_lane = TOKEN_AXIS ? 0 : row0 * ng + slot / lpg;
@@ -101,17 +120,43 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     }
 }
 
-// System-token prefix (the part of the paper's dual-structure memory that stays in 16 bits):
-// rows [0, prefix_rows) of every head's active buffer are copied from
-// sys [n_layers][H_k][prefix_rows][d].  grid (chunks, H_k * n_layers, 2), 16 bytes per lane.
-__global__ void __launch_bounds__(kBlock) prefix_copy_kernel(const DequantArgs a, const char* sys_k,
-                                                             const char* sys_v, const int64_t head_bytes,
+// The prefix alone.  grid (chunks, H_k * n_layers, 2).
+__global__ void __launch_bounds__(kBlock) prefix_copy_kernel(const DequantArgs a, const int64_t head_bytes,
                                                              const int64_t prefix_bytes) {
-    const int64_t off = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 16;
-    if (off >= prefix_bytes) return;
-    const char* src = (blockIdx.z ? sys_v : sys_k) + (int64_t)blockIdx.y * prefix_bytes + off;
-    char* dst = static_cast<char*>(blockIdx.z ? a.v_out : a.k_out) + (int64_t)blockIdx.y * head_bytes + off;
-    *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(src);
+    copy_prefix((blockIdx.z ? a.sys_v : a.sys_k) + (int64_t)blockIdx.y * prefix_bytes,
+                static_cast<char*>(blockIdx.z ? a.v_out : a.k_out) + (int64_t)blockIdx.y * head_bytes, prefix_bytes,
+                blockIdx.x);
+}
+
+template <typename OUT>
+hipError_t prefix_copy(const DequantArgs& a, hipStream_t s) {
+    constexpr int64_t eb = elem_bytes<OUT>::value;
+    const int64_t prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;  // multiple of 16: d % 8 == 0
+    const int64_t head_bytes = ((int64_t)a.prefix_rows + (int64_t)a.k * a.group_tokens) * a.head_dim * eb;
+    if (prefix_bytes == 0 || a.n_layers == 0) return hipSuccess;
+    const int64_t chunks = (prefix_bytes / 16 + kBlock - 1) / kBlock;
+    if (chunks > 0x7fffffffLL || (int64_t)a.n_kv_heads * a.n_layers > 65535) return hipErrorInvalidValue;
+    prefix_copy_kernel<<<dim3((unsigned)chunks, a.n_kv_heads * a.n_layers, 2), dim3(kBlock), 0, s>>>(a, head_bytes,
+                                                                                                     prefix_bytes);
+    return hipGetLastError();
+}
+
+// Whether the prefix rows can be copied by blocks of the gather's own launch.  As a launch of its
+// own the copy costs 1.3 to 4.5 us for 14 rows (0.8 MB at 28 layers), inside the gather nothing
+// that can be measured.  Not where a grid dimension would pass 2^32 threads, nor where the source
+// overlaps the active buffer: the copy then has to come first.
+template <typename OUT>
+bool prefix_joins_gather(const DequantArgs& a) {
+    constexpr int64_t eb = elem_bytes<OUT>::value;
+    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
+    const int64_t prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;
+    const int64_t out_bytes = heads * ((int64_t)a.prefix_rows + (int64_t)a.k * a.group_tokens) * a.head_dim * eb;
+    if ((prefix_bytes / 16 + kBlock - 1) / kBlock + (int64_t)a.k_eff * a.chunks >= (1LL << 32) / kBlock) return false;
+    auto apart = [&](const void* sys, const void* out) {
+        const uintptr_t s = reinterpret_cast<uintptr_t>(sys), o = reinterpret_cast<uintptr_t>(out);
+        return s + (uintptr_t)(heads * prefix_bytes) <= o || o + (uintptr_t)out_bytes <= s;
+    };
+    return apart(a.sys_k, a.k_out) && apart(a.sys_k, a.v_out) && apart(a.sys_v, a.k_out) && apart(a.sys_v, a.v_out);
 }
 
 template <typename OUT>
@@ -125,7 +170,16 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     a.rows_per_chunk = (a.group_tokens + a.chunks - 1) / a.chunks;
     a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
     if ((int64_t)a.k_eff * a.chunks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(a.k_eff * a.chunks), 2 * a.n_kv_heads, a.n_layers), block(kBlock);
+    a.prefix_blocks = 0;
+    if (a.sys_k && a.prefix_rows > 0) {
+        if (prefix_joins_gather<OUT>(a)) {
+            const int64_t bytes = (int64_t)a.prefix_rows * a.head_dim * elem_bytes<OUT>::value;
+            a.prefix_blocks = (int32_t)((bytes / 16 + kBlock - 1) / kBlock);
+        } else if (hipError_t e = prefix_copy<OUT>(a, s)) {
+            return e;
+        }
+    }
+    const dim3 grid((unsigned)(a.prefix_blocks + a.k_eff * a.chunks), 2 * a.n_kv_heads, a.n_layers), block(kBlock);
     const int lpg = a.qgroup / 8;  // unused for the token axis
     const bool tok = a.qaxis == TOM_QAXIS_TOKENS;
     auto go = [&](auto unroll, auto bits, auto mb) {
@@ -149,17 +203,12 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_prefix_copy(const DequantArgs& a, const void* sys_k, const void* sys_v, int out_dtype,
+hipError_t launch_prefix_copy(const DequantArgs& args, const void* sys_k, const void* sys_v, int out_dtype,
                               hipStream_t s) {
-    const int64_t eb = out_dtype == TOM_F32 ? 4 : 2;
-    const int64_t prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;  // multiple of 16: d % 8 == 0
-    const int64_t head_bytes = ((int64_t)a.prefix_rows + (int64_t)a.k * a.group_tokens) * a.head_dim * eb;
-    if (prefix_bytes == 0 || a.n_layers == 0) return hipSuccess;
-    const int64_t chunks = (prefix_bytes / 16 + kBlock - 1) / kBlock;
-    if (chunks > 0x7fffffffLL || (int64_t)a.n_kv_heads * a.n_layers > 65535) return hipErrorInvalidValue;
-    prefix_copy_kernel<<<dim3((unsigned)chunks, a.n_kv_heads * a.n_layers, 2), dim3(kBlock), 0, s>>>(
-        a, static_cast<const char*>(sys_k), static_cast<const char*>(sys_v), head_bytes, prefix_bytes);
-    return hipGetLastError();
+    DequantArgs a = args;
+    a.sys_k = static_cast<const char*>(sys_k);
+    a.sys_v = static_cast<const char*>(sys_v);
+    return out_dtype == TOM_F32 ? prefix_copy<In_f32>(a, s) : prefix_copy<In_bf16>(a, s);
 }
 
 hipError_t launch_dequant_gather(const DequantArgs& a, int out_dtype, hipStream_t s) {
