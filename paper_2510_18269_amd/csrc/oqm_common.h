@@ -84,11 +84,13 @@ struct DequantArgs {
     int32_t bits;         // 4 or 2
     int32_t meta_bf16;    // (scale, zero) stored as bfloat16 pairs
     int32_t prefix_rows;  // rows of each head's active buffer that precede the gathered groups
-    // Filled in by the launcher: workgroups per tile, the token rows each takes, and the
-    // reciprocal floor(2^32 / chunks) for oqm::div_by.
-    int32_t chunks, rows_per_chunk;
-    uint32_t inv_chunks;
-    int32_t prefix_blocks;  // workgroups per (layer, K|V, head) that copy prefix rows
+    // Filled in by the launcher: the gather's decomposition and the byte sizes its addresses need.
+    uint32_t chunks, inv_chunks, chunk_items;  // workgroups per tile, floor(2^32 / chunks), items each takes
+    uint32_t step, tile_items;                 // items between two of a lane; items of a tile (G * d/8)
+    uint32_t lpg_shift, tile_meta_bytes;       // log2(items of a quant-group); bytes of a tile's pairs
+    uint32_t lanes_per_row, inv_lanes_per_row;
+    int64_t plane_tiles;                       // tiles of one (layer, K|V): capacity * H_k
+    int64_t prefix_bytes, head_out_bytes;      // of one head's active buffer: prefix rows, all rows
 };
 
 struct ScoreArgs {

@@ -1,23 +1,25 @@
 // Reconstruction of the selected frame-groups into the bounded active KV buffer
 // (paper Sec. 3.4, Eq. 11 and Eq. 13; supplement "Cache reconstruction for decoding").
 //
-// Grid (prefix blocks, then rank * chunks + chunk; 2*head + K|V; layer): a workgroup of 256 threads owns
-// up to three row passes (48 token rows at head_dim 128) of one head tile of one
-// selected group (the first `prefix_blocks` copy system-token rows instead); consecutive workgroups write consecutive row blocks of the active
+// Grid (rank * chunks + chunk, then prefix blocks; K|V * H_k + head; layer): a workgroup of 256
+// threads owns up to three passes (48 token rows at head_dim 128) of one head tile of one
+// selected group; consecutive workgroups write consecutive row blocks of the active
 // buffer.  It reads the group index from device memory (the index array never visits
-// the host), streams its rows' packed nibbles and (scale, zero) pairs, and writes them
+// the host), streams its rows' packed codes and (scale, zero) pairs, and writes them
 // to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns one
 // 32-bit word of codes (8 channels) into one 128-bit non-temporal store, so each store
 // instruction of a wave writes 1 KB of contiguous bf16.  HBM-bound: 0.5 + 8/gs bytes
 // read and 2 bytes written per element.
 //
-// Rows per workgroup, measured at 28 layers x 64 groups x 196 x 128 (944 MB, random
-// groups): whole tile (13 passes, all loads first) 171 us; 7 / 6 chunks 178 / 176 us;
-// 5 chunks of 40 rows 167 us; 3 chunks of 66 rows 168 us; 2 chunks 173 us; chunks of one
-// pass 216 us.  Chunks of unequal size whose count divides 8 are slow (3 x 64 + 4 rows:
-// 193 us): workgroup ids go round-robin over the eight XCDs, so all the short chunks land
-// on the same two.  With contiguous groups instead of random ones the same kernel takes
-// 152 us: what is left to a dense stream is the DRAM row locality of 12.5 KB pieces.
+// Measured at 28 layers x 64 random groups x 196 x 128 (944 MB): 162 us = 5.83 TB/s, where an
+// arithmetic-free linear stream of the same byte mix reaches 6.1.  In-kernel clocks: a workgroup
+// lives 3.5 us (index 0.2, loads 1.5, stores 1.7), 1520 of 2048 slots are taken at any time.  One to
+// five passes per workgroup, 256 or 512 threads and a barrier between loads and stores
+// all stay within 1 %; seven passes 171, 1024 threads 165, three or five workgroups per compute unit
+// instead of eight 230 / 181, and a persistent loop that loads the next piece before it
+// stores the current one 187 us: the memory system prefers workgroups whose reads and writes
+// are separate bursts.  All heads' K before all heads' V (162 us) is 1 % faster than K and V of a
+// head in turn; contiguous instead of random groups take 156 us.
 #include <type_traits>
 
 #include "oqm_common.h"
@@ -33,91 +35,83 @@ __device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t 
     if (off < bytes) *reinterpret_cast<u32x4*>(dst + off) = *reinterpret_cast<const u32x4*>(src + off);
 }
 
-// kUnroll: rows per lane whose loads are issued before any is converted (the host cuts the tile
-// into chunks that one trip covers).
+// The 8-channel items of a tile (one 32-bit word of 4-bit codes each) are numbered row by row: item
+// row * (d/8) + slot.  Codes and output are linear in that number, and so are the pairs of the
+// head_dim axis (d/8 is a multiple of the gs/8 lanes of a quant-group), so a chunk is a linear stream and the
+// kernel divides by nothing.  On the token axis a lane has to keep its channels: its items are
+// `step` = the largest multiple of d/8 below 256 apart, otherwise 256.
+// kUnroll: items per lane; all their loads are issued before the first is converted, and the host
+// cuts the tile into chunks that one trip covers.
 template <typename OUT, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB>
-__global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArgs a, const int lpg) {
+__global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArgs a) {
     constexpr int EB = elem_bytes<OUT>::value;
-    constexpr uint32_t CW = BITS;          // bytes of packed codes per lane and row (8 channels)
+    constexpr uint32_t CW = BITS;          // bytes of packed codes per item
     constexpr uint32_t CMASK = (1u << BITS) - 1u;
-    const int H = a.n_kv_heads, d = a.head_dim, G = a.group_tokens;
-    const int kv = blockIdx.y & 1;
-    const int h = blockIdx.y >> 1;
-    const int li = blockIdx.z;
-    const int64_t head = (int64_t)li * H + h;
-    const int64_t head_rows = (int64_t)a.prefix_rows + (int64_t)a.k * G;  // rows per head buffer
-    char* const head_out = static_cast<char*>(kv ? a.v_out : a.k_out) + head * head_rows * (int64_t)d * EB;
-    if ((int)blockIdx.x < a.prefix_blocks) {  // uniform
-        copy_prefix((kv ? a.sys_v : a.sys_k) + head * a.prefix_rows * (int64_t)d * EB, head_out,
-                    (int64_t)a.prefix_rows * d * EB, blockIdx.x);
+    typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
+    const uint32_t tid = threadIdx.x;
+    // everything the addresses need is requested at once, not behind the index
+    asm volatile("" ::"s"(a.codes), "s"(a.meta), "s"(a.plane_tiles), "s"(a.tile_meta_bytes), "s"(a.tile_items), "s"(a.step),
+                 "s"(a.prefix_bytes), "s"(a.head_out_bytes), "s"(a.chunk_items), "s"(a.layer0), "s"(a.lpg_shift), "s"(a.k_out),
+                 "s"(a.v_out), "s"(a.idx), "s"(a.all_idx), "s"(a.k), "s"(a.chunks));
+    const uint32_t kv = blockIdx.y >= (uint32_t)a.n_kv_heads ? 1u : 0u, h = blockIdx.y - kv * (uint32_t)a.n_kv_heads;
+    const uint32_t li = blockIdx.z;
+    const uint32_t r = div_by(blockIdx.x, a.chunks, a.inv_chunks);
+    char* const head_out =
+        static_cast<char*>(kv ? a.v_out : a.k_out) + (uint64_t)(li * (uint32_t)a.n_kv_heads + h) * (uint64_t)a.head_out_bytes;
+    if (r >= (uint32_t)a.k_eff) {  // uniform: one of the prefix blocks that end the x dimension
+        const int64_t prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * EB;
+        copy_prefix((kv ? a.sys_v : a.sys_k) + ((int64_t)li * a.n_kv_heads + h) * prefix_bytes, head_out, prefix_bytes,
+                    blockIdx.x - (uint32_t)a.k_eff * a.chunks);
         return;
     }
-    const int piece = (int)blockIdx.x - a.prefix_blocks;
-    const int r = a.chunks > 1 ? (int)div_by(piece, a.chunks, a.inv_chunks) : piece;
-    const int row_begin = (piece - r * a.chunks) * a.rows_per_chunk;
-    const int row_end = min(G, row_begin + a.rows_per_chunk);
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;  // not written by this launch where it is read
+    const uint32_t t = a.all_idx ? r : ((scalar_ptr)(uintptr_t)a.idx)[(uint64_t)li * (uint32_t)a.k + r];
+    if (t >= (uint32_t)a.n_groups) return;  // not a stored group: leave the rows alone
 
-    int t = r;
-    if (a.all_idx) {  // uniform
-        if (blockIdx.y == 0 && row_begin == 0 && threadIdx.x == 0) a.all_idx[(int64_t)li * a.k + r] = r;
-    } else {
-        t = a.idx[(int64_t)li * a.k + r];
-        if ((unsigned)t >= (unsigned)a.n_groups) return;  // not a stored group: leave the rows alone
-    }
-
-    const int lpr = d >> 3;
-    const int rpp = kBlock / lpr;
-    const int tid = threadIdx.x;
-    const int row0 = tid / lpr;
-    const int slot = tid - row0 * lpr;
-    if (row0 >= rpp) return;
-    const int ng = TOKEN_AXIS ? 0 : lpr / lpg;
-
-    const int64_t tile = (((int64_t)(a.layer0 + li) * 2 + kv) * a.capacity_groups + t) * H + h;
-    const char* codes_t = reinterpret_cast<const char*>(a.codes + tile * ((int64_t)G * d * BITS / 8));
-    // token axis (Eq. 9): one pair per channel, d pairs per tile; else G * d/gs pairs
-    typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
-    const meta_pair* meta_t =
-        reinterpret_cast<const meta_pair*>(a.meta) + tile * (TOKEN_AXIS ? (int64_t)d : (int64_t)G * ng);
+    const uint32_t begin = (blockIdx.x - r * a.chunks) * a.chunk_items;
+    const uint32_t end = min(a.tile_items, begin + a.chunk_items);
+    const uint64_t tile = (uint64_t)((a.layer0 + li) * 2u + kv) * a.plane_tiles + (uint64_t)t * (uint32_t)a.n_kv_heads + h;
+    const char* const codes_t = reinterpret_cast<const char*>(a.codes) + tile * (a.tile_items * CW);
+    const char* const meta_t = static_cast<const char*>(a.meta) + tile * a.tile_meta_bytes;
+    char* const out = head_out + a.prefix_bytes + (uint64_t)r * (a.tile_items * (8u * EB));
+    const uint32_t first = begin + tid;
+    const bool active = !TOKEN_AXIS || tid < a.step;
     f32x2 ch[8];  // token axis: the pairs of this lane's 8 channels, loaded once
     if (TOKEN_AXIS) {
+        const uint32_t slot = tid - div_by(tid, a.lanes_per_row, a.inv_lanes_per_row) * a.lanes_per_row;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ch[i] = widen_pair(meta_t[slot * 8 + i]);
+        for (int i = 0; i < 8; ++i) ch[i] = widen_pair(reinterpret_cast<const meta_pair*>(meta_t)[slot * 8u + i]);
     }
-    char* out = head_out + ((int64_t)a.prefix_rows + (int64_t)r * G) * (int64_t)d * EB;
-    // offsets inside one tile fit 32 bits (G * d * 4 < 2^31 is checked on the host)
-    const uint32_t code_lane = ((uint32_t)row0 * lpr + slot) * CW;
-    const int meta_lane = TOKEN_AXIS ? 0 : row0 * ng + slot / lpg;
-    const uint32_t out_lane = ((uint32_t)row0 * d + slot * 8u) * EB;
 
-    for (int r0 = row_begin; r0 + row0 < row_end; r0 += kUnroll * rpp) {
-        uint32_t w[kUnroll];
-        meta_pair sm[kUnroll];
+    uint32_t w[kUnroll];
+    meta_pair sm[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int rb = r0 + u * rpp;
-            w[u] = 0u;
-            sm[u] = meta_pair{};
-            if (rb + row0 < row_end) {
-                w[u] = load_codes8<BITS>(codes_t + (code_lane + (uint32_t)rb * lpr * CW));
-                if (!TOKEN_AXIS) sm[u] = meta_t[meta_lane + rb * ng];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int rb = r0 + u * rpp;
-            if (rb + row0 < row_end) {
-                float x[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float c = (float)((w[u] >> (BITS * i)) & CMASK);
-                    const f32x2 p = TOKEN_AXIS ? ch[i] : widen_pair(sm[u]);
-                    x[i] = __builtin_fmaf(c, p[0], p[1]);  // Eq. 11, rounded once to float32
-                }
-                store8(out + (out_lane + (uint32_t)rb * d * EB), OUT{}, x);
-            }
+    for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t item = first + u * a.step;
+        w[u] = 0u;
+        sm[u] = meta_pair{};
+        if (active && item < end) {
+            w[u] = load_codes8<BITS>(codes_t + item * CW);
+            if (!TOKEN_AXIS)
+                sm[u] = *reinterpret_cast<const meta_pair*>(meta_t + (item >> a.lpg_shift) * (uint32_t)sizeof(meta_pair));
         }
     }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const uint32_t item = first + u * a.step;
+        if (active && item < end) {
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float c = (float)((w[u] >> (BITS * i)) & CMASK);
+                const f32x2 p = TOKEN_AXIS ? ch[i] : widen_pair(sm[u]);
+                x[i] = __builtin_fmaf(c, p[0], p[1]);  // Eq. 11, rounded once to float32
+            }
+            store8(out + item * (8u * EB), OUT{}, x);
+        }
+    }
+    // last, so that the index load above stays a scalar load
+    if (a.all_idx && blockIdx.y == 0 && begin == 0 && tid == 0) a.all_idx[(int64_t)li * a.k + r] = (int32_t)r;
 }
 
 // The prefix alone.  grid (chunks, H_k * n_layers, 2).
@@ -163,30 +157,41 @@ template <typename OUT>
 hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.k_eff == 0) return hipSuccess;
     DequantArgs a = args;
-    const int rpp = kBlock / (a.head_dim / 8);
-    const int passes = (a.group_tokens + rpp - 1) / rpp;  // row passes per tile
-    // up to four passes: one workgroup per tile; more: equal chunks of at most three passes
+    constexpr uint32_t eb = elem_bytes<OUT>::value;
+    const bool tok = a.qaxis == TOM_QAXIS_TOKENS;
+    const uint32_t lpr = (uint32_t)a.head_dim / 8u, G = (uint32_t)a.group_tokens;
+    a.lanes_per_row = lpr;
+    a.inv_lanes_per_row = reciprocal_u32(lpr);
+    a.step = tok ? kBlock / lpr * lpr : kBlock;
+    a.tile_items = G * lpr;  // G * d * 4 < 2^31 is checked by the API layer
+    const uint32_t passes = (a.tile_items + a.step - 1) / a.step;
+    // up to four passes: one workgroup per tile; more: equal chunks (whole rows) of at most three passes
+    const uint32_t unroll = passes <= 4 ? 4 : 3;
     a.chunks = passes <= 4 ? 1 : (passes + 2) / 3;
-    a.rows_per_chunk = (a.group_tokens + a.chunks - 1) / a.chunks;
-    a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
+    while ((G + a.chunks - 1) / a.chunks * lpr > unroll * a.step) ++a.chunks;
+    a.chunk_items = (G + a.chunks - 1) / a.chunks * lpr;
+    a.inv_chunks = reciprocal_u32(a.chunks);
     if ((int64_t)a.k_eff * a.chunks > 0x7fffffffLL) return hipErrorInvalidValue;
-    a.prefix_blocks = 0;
+    a.lpg_shift = 0;
+    while (!tok && (8 << a.lpg_shift) < a.qgroup) ++a.lpg_shift;  // qgroup is a power of two
+    a.tile_meta_bytes = (tok ? (uint32_t)a.head_dim : G * (lpr >> a.lpg_shift)) * (a.meta_bf16 ? 4u : 8u);
+    a.plane_tiles = (int64_t)a.capacity_groups * a.n_kv_heads;
+    a.prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;
+    a.head_out_bytes = a.prefix_bytes + (int64_t)a.k * a.group_tokens * a.head_dim * eb;
+    uint32_t prefix_blocks = 0;
     if (a.sys_k && a.prefix_rows > 0) {
         if (prefix_joins_gather<OUT>(a)) {
-            const int64_t bytes = (int64_t)a.prefix_rows * a.head_dim * elem_bytes<OUT>::value;
-            a.prefix_blocks = (int32_t)((bytes / 16 + kBlock - 1) / kBlock);
+            prefix_blocks = (uint32_t)((a.prefix_bytes / 16 + kBlock - 1) / kBlock);
         } else if (hipError_t e = prefix_copy<OUT>(a, s)) {
             return e;
         }
     }
-    const dim3 grid((unsigned)(a.prefix_blocks + a.k_eff * a.chunks), 2 * a.n_kv_heads, a.n_layers), block(kBlock);
-    const int lpg = a.qgroup / 8;  // unused for the token axis
-    const bool tok = a.qaxis == TOM_QAXIS_TOKENS;
+    const dim3 grid((uint32_t)a.k_eff * a.chunks + prefix_blocks, 2 * a.n_kv_heads, a.n_layers), block(kBlock);
     auto go = [&](auto unroll, auto bits, auto mb) {
         constexpr int U = decltype(unroll)::value, B = decltype(bits)::value;
         constexpr bool M = decltype(mb)::value;
-        if (tok) dequant_gather_kernel<OUT, U, true, B, M><<<grid, block, 0, s>>>(a, 1);
-        else dequant_gather_kernel<OUT, U, false, B, M><<<grid, block, 0, s>>>(a, lpg);
+        if (tok) dequant_gather_kernel<OUT, U, true, B, M><<<grid, block, 0, s>>>(a);
+        else dequant_gather_kernel<OUT, U, false, B, M><<<grid, block, 0, s>>>(a);
     };
     auto with_meta = [&](auto unroll, auto bits) {
         if (a.meta_bf16) go(unroll, bits, std::true_type{});
@@ -196,7 +201,7 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
         if (a.bits == 2) with_meta(unroll, std::integral_constant<int, 2>{});
         else with_meta(unroll, std::integral_constant<int, 4>{});
     };
-    if (passes <= 4) with_bits(std::integral_constant<int, 4>{});
+    if (unroll == 4) with_bits(std::integral_constant<int, 4>{});
     else with_bits(std::integral_constant<int, 3>{});
     return hipGetLastError();
 }
