@@ -62,6 +62,93 @@ __device__ __forceinline__ void group_minmax(float& mn, float& mx) {
     }
 }
 
+// ---- reduction across the token rows of a wave ------------------------------
+// A wave holds 64 / LPR token rows of LPR lanes, 8 channels per lane.  reduce_rows combines v[0 .. 8)
+// over the rows and leaves each lane with LPR / 8 finished channels: v[j] is then channel
+// row * (LPR / 8) + j of the lane's 8.  spread_rows is the way back: every lane gets all 8.  A
+// permlane swap serves two channels at once (v_permlane32_swap exchanges the upper half of the first register with
+// the lower half of the second, v_permlane16_swap the odd rows of 16 lanes with the even ones),
+// so 8 channels take 4 + 2 (+ 1) exchanges and no LDS.
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+// lanes with bit 3 clear end with their a and that of lane + 8, the others with their b and that of lane - 8
+__device__ __forceinline__ void swap8(uint32_t& a, uint32_t& b) {
+    const bool upper = (__lane_id() & 8u) != 0;
+    const uint32_t other = dpp_u32<0x128>(upper ? a : b);  // row_ror:8 = lane ^ 8
+    const uint32_t keep = upper ? b : a;
+    a = upper ? other : keep;
+    b = upper ? keep : other;
+}
+template <int N>
+__device__ __forceinline__ void swap_lanes(uint32_t& a, uint32_t& b) {
+    if constexpr (N == 32) swap32(a, b);
+    else if constexpr (N == 16) swap16(a, b);
+    else swap8(a, b);
+}
+template <int N>
+__device__ __forceinline__ void swap_lanes(float& a, float& b) {
+    uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    swap_lanes<N>(x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <int N>
+__device__ __forceinline__ void swap_lanes(double& a, double& b) {
+    uint32_t al = (uint32_t)__double2loint(a), ah = (uint32_t)__double2hiint(a);
+    uint32_t bl = (uint32_t)__double2loint(b), bh = (uint32_t)__double2hiint(b);
+    swap_lanes<N>(al, bl);
+    swap_lanes<N>(ah, bh);
+    a = __hiloint2double((int)ah, (int)al);
+    b = __hiloint2double((int)bh, (int)bl);
+}
+template <int LPR, typename T, typename OP>
+__device__ __forceinline__ void reduce_rows(T (&v)[8], OP op) {
+    static_assert(LPR == 8 || LPR == 16 || LPR == 32, "lanes per token row");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        swap_lanes<32>(v[i], v[i + 4]);
+        v[i] = op(v[i], v[i + 4]);
+    }
+    if constexpr (LPR <= 16) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            swap_lanes<16>(v[i], v[i + 2]);
+            v[i] = op(v[i], v[i + 2]);
+        }
+    }
+    if constexpr (LPR <= 8) {
+        swap_lanes<8>(v[0], v[1]);
+        v[0] = op(v[0], v[1]);
+    }
+}
+template <int LPR>
+__device__ __forceinline__ void spread_rows(float (&v)[8]) {
+    if constexpr (LPR <= 8) {
+        v[1] = v[0];
+        swap_lanes<8>(v[0], v[1]);
+    }
+    if constexpr (LPR <= 16) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            v[i + 2] = v[i];
+            swap_lanes<16>(v[i], v[i + 2]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i + 4] = v[i];
+        swap_lanes<32>(v[i], v[i + 4]);
+    }
+}
+
 // Sum of a double over all 64 lanes of the wave (result valid in every lane).
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
@@ -122,6 +209,10 @@ __device__ __forceinline__ void zero_raw(Raw8<In_f32>& r) {
     r.a = f32x4{0.f, 0.f, 0.f, 0.f};
     r.b = r.a;
 }
+// Makes the compiler widen a held row again later instead of keeping the widened copy as well.
+__device__ __forceinline__ void forget_widened(Raw8<In_bf16>& r) { asm volatile("" : "+v"(r.a)); }
+__device__ __forceinline__ void forget_widened(Raw8<In_f16>& r) { asm volatile("" : "+v"(r.a)); }
+__device__ __forceinline__ void forget_widened(Raw8<In_f32>&) {}
 __device__ __forceinline__ void widen(const Raw8<In_bf16>& r, float (&x)[8]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {

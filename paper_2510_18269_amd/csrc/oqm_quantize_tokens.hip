@@ -2,14 +2,17 @@
 // head and channel, taken over the G tokens of the frame-group (Sec. 3.4, Eq. 8 and Eq. 9),
 // plus nibble packing and the summary key, for one head tile per workgroup.
 //
-// Same decomposition as the head_dim-axis kernel (grid (head, 2*layer + K|V, frame), lane =
+// The general form's decomposition: (grid (head, 2*layer + K|V, frame), lane =
 // 8 channels of one token row), but the min/max run down the token rows: each lane keeps
 // 8 running minima and maxima over its rows, the 256/(d/8) row slots of the workgroup are
 // combined through LDS, one thread per channel derives scale, reciprocal and zero point,
 // and a second sweep quantizes and packs.  When a lane's share of the tile fits a few
 // registers (HOLD rows: up to 13 x 16 B) the rows stay in registers between the sweeps;
-// otherwise the second sweep reads the tile again (from the caches: it was read a moment ago).  HBM traffic per element: 2 B read + 0.5 B written + 8/G B of
+// otherwise the second sweep reads the tile again (from the caches: it was read a moment ago).
+// HBM traffic per element: 2 B read + 0.5 B written + 8/G B of
 // (scale, zero) pairs.
+#include <type_traits>
+
 #include "oqm_common.h"
 #include "oqm_device.h"
 
@@ -187,6 +190,174 @@ __global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const Qu
     }
 }
 
+// The form for d = 64, 128, 256 (LPR = d/8 lanes per token row divides a wave).  As few waves as
+// can hold the tile at eight rows per lane own it; a wave reduces its rows with lane swaps, several
+// exchange one (min, max) and one key sum per channel through LDS behind a single barrier, one
+// alone needs neither.  Each phase of a launch this short is latency or vector work, not
+// bandwidth: fewer threads per tile mean more tiles in flight and fewer of the per-channel steps.
+// Measured (28 layers x 4 heads x 50 x 128, two waves of seven rows, against the 256-thread
+// form below): 8 FP16 frames 9.3 / 9.9 us, 32 bf16 frames 25.6 / 30.1 us = 4.6 TB/s.  At 32 frames one wave of 13 rows takes
+// 29.1 us, three waves of five 28.4, four of four 29.8; skipping the dead rows by a branch per row
+// 27.5 (no v_min3 across rows), keeping the widened rows for the second sweep 26.4.
+template <typename IN, int LPR, int HOLD, int BITS, bool MB>
+__global__ void __launch_bounds__(1024) quantize_append_rows_kernel(const QuantArgs a, const int waves) {
+    constexpr int EB = elem_bytes<IN>::value;
+    constexpr uint32_t CW = BITS;  // bytes of packed codes per lane and row (8 channels)
+    constexpr int R = 64 / LPR, D = 8 * LPR, CH = LPR / 8;  // rows and channels of a wave's pass; channels a lane finishes
+    typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
+    extern __shared__ double lds_sum[];             // [waves][D] key sums, then [waves][D] (min, max)
+    f32x2* const lds_mm = reinterpret_cast<f32x2*>(lds_sum + waves * D);
+    const int H = a.n_kv_heads, G = a.group_tokens;
+    const int h = blockIdx.x, kv = blockIdx.y & 1, li = blockIdx.y >> 1, f = blockIdx.z;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int row0 = wave * R + lane / LPR, slot = lane % LPR;
+    const int step = waves * R;  // token rows per pass
+    const int c0 = slot * 8 + (lane / LPR) * CH;  // first channel this lane finishes
+
+    const int64_t in_off = f * a.stride_frame + li * a.stride_layer + h * a.stride_head;
+    const char* src = static_cast<const char*>(kv ? a.v : a.k) + in_off * EB;
+    const int64_t group = (int64_t)a.first_group + f;
+    const int64_t tile = (((int64_t)(a.layer0 + li) * 2 + kv) * a.capacity_groups + group) * H + h;
+    char* codes_t = reinterpret_cast<char*>(a.codes) + tile * ((int64_t)G * (D * BITS / 8));
+    meta_pair* meta_t = static_cast<meta_pair*>(a.meta) + tile * D;
+    const uint32_t in_row_bytes = (uint32_t)a.stride_token * EB;
+    const bool do_sum = kv == 0, own_sum = do_sum && a.ksum != a.k;
+
+    // pass u covers rows [u * step, (u + 1) * step); rows past G repeat the last one (in the cache already)
+    Raw8<IN> held[HOLD];
+#pragma unroll
+    for (int u = 0; u < HOLD; ++u)
+        load_raw(src + ((uint32_t)min(u * step + row0, G - 1) * in_row_bytes + (uint32_t)slot * (8u * EB)), held[u]);
+
+    double acc[8];
+    float mn[8], mx[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        acc[i] = 0.0;
+        mn[i] = __builtin_inff();
+        mx[i] = -__builtin_inff();
+    }
+#pragma unroll
+    for (int u = 0; u < HOLD; ++u) {
+        float x[8];
+        widen(held[u], x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            mn[i] = fminf(mn[i], x[i]);
+            mx[i] = fmaxf(mx[i], x[i]);
+        }
+    }
+    if (do_sum && !own_sum) {
+#pragma unroll
+        for (int u = 0; u < HOLD; ++u) {
+            float x[8];
+            widen(held[u], x);
+            if (u * step + row0 < G) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
+            }
+        }
+    }
+    if (own_sum) {  // the keys to average come from another tensor
+        const char* ssrc = static_cast<const char*>(a.ksum) + in_off * EB;
+        for (int row = row0; row < G; row += step) {
+            float x[8];
+            load8(ssrc + ((uint32_t)row * in_row_bytes + (uint32_t)slot * (8u * EB)), IN{}, x);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
+        }
+    }
+    reduce_rows<LPR>(mn, [](float p, float q) { return fminf(p, q); });
+    reduce_rows<LPR>(mx, [](float p, float q) { return fmaxf(p, q); });
+    if (do_sum) reduce_rows<LPR>(acc, [](double p, double q) { return p + q; });
+    if (waves > 1) {  // uniform
+#pragma unroll
+        for (int j = 0; j < CH; ++j) lds_mm[wave * D + c0 + j] = f32x2{mn[j], mx[j]};
+        if (do_sum) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) lds_sum[wave * D + c0 + j] = acc[j];
+        }
+        __syncthreads();
+        for (int w = 0; w < waves; ++w) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const f32x2 m = lds_mm[w * D + c0 + j];
+                mn[j] = fminf(mn[j], m[0]);
+                mx[j] = fmaxf(mx[j], m[1]);
+            }
+        }
+    }
+
+    // Eq. 9 over the whole token axis, for this lane's channels; then all 8 of its slot
+    float zm[8], zi[8];
+#pragma unroll
+    for (int j = 0; j < CH; ++j) {
+        float m = mn[j] + 0.0f;  // never store -0 as a zero point
+        float s = div_levels_exact<BITS>(__fsub_rn(mx[j], m));
+        if (!(s >= 1.17549435e-38f)) s = 0.0f;
+        meta_pair stored;
+        if constexpr (MB) stored = round_pair_bf16(s, m);  // the codes follow the rounded pair
+        else stored = f32x2{s, m};
+        if (wave == 0) meta_t[c0 + j] = stored;
+        zm[j] = m;
+        zi[j] = s >= 1.17549435e-38f ? rcp_scale<BITS>(s) : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < HOLD; ++u) forget_widened(held[u]);
+    spread_rows<LPR>(zm);
+    spread_rows<LPR>(zi);
+#pragma unroll
+    for (int u = 0; u < HOLD; ++u) {
+        float x[8], tq[8];
+        widen(held[u], x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            tq[i] = __builtin_fmaf(__fsub_rn(x[i], zm[i]), zi[i], 8388608.0f);
+            if constexpr (MB) tq[i] = clamp_code<BITS>(tq[i]);  // m may lie above the minimum
+        }
+        const int row = u * step + row0;
+        if (row < G) store_codes8<BITS>(codes_t + ((uint32_t)row * LPR + slot) * CW, tq);
+    }
+
+    if (!do_sum || wave != 0) return;
+    float* key = a.keys + (((int64_t)(a.layer0 + li) * a.capacity_groups + group) * H + h) * D;
+    for (int w = 1; w < waves; ++w) {
+#pragma unroll
+        for (int j = 0; j < CH; ++j) acc[j] += lds_sum[w * D + c0 + j];
+    }
+#pragma unroll
+    for (int j = 0; j < CH; ++j) key[c0 + j] = (float)(acc[j] / (double)G);
+}
+
+constexpr int kMostRows = 8;                 // rows a lane holds
+constexpr int kMostPasses = 16 * kMostRows;  // row passes of one wave that 16 waves hold
+
+template <typename IN, int LPR, int HOLD>
+hipError_t launch_rows_h(const QuantArgs& a, int waves, hipStream_t s) {
+    const dim3 grid(a.n_kv_heads, 2 * a.n_layers, a.n_frames), block(64 * waves);
+    const size_t lds = waves > 1 ? (size_t)waves * LPR * 8 * (sizeof(double) + sizeof(f32x2)) : 0;
+    auto go = [&](auto bits, auto mb) {
+        quantize_append_rows_kernel<IN, LPR, HOLD, decltype(bits)::value, decltype(mb)::value><<<grid, block, lds, s>>>(a, waves);
+    };
+    using std::integral_constant;
+    if (a.bits == 2 && a.meta_bf16) go(integral_constant<int, 2>{}, std::true_type{});
+    else if (a.bits == 2) go(integral_constant<int, 2>{}, std::false_type{});
+    else if (a.meta_bf16) go(integral_constant<int, 4>{}, std::true_type{});
+    else go(integral_constant<int, 4>{}, std::false_type{});
+    return hipGetLastError();
+}
+
+template <typename IN, int LPR>
+hipError_t launch_rows(const QuantArgs& a, hipStream_t s) {
+    const int passes = (a.group_tokens + 64 / LPR - 1) / (64 / LPR);
+    const int waves = (passes + kMostRows - 1) / kMostRows;
+    const int rows = (passes + waves - 1) / waves;
+    if (rows <= 4) return launch_rows_h<IN, LPR, 4>(a, waves, s);
+    if (rows <= 6) return launch_rows_h<IN, LPR, 6>(a, waves, s);
+    if (rows == 7) return launch_rows_h<IN, LPR, 7>(a, waves, s);
+    return launch_rows_h<IN, LPR, 8>(a, waves, s);
+}
+
 template <typename IN, int HOLD, int BITS, bool MB>
 hipError_t launch_m(const QuantArgs& a, hipStream_t s) {
     const dim3 grid(a.n_kv_heads, 2 * a.n_layers, a.n_frames);
@@ -207,7 +378,12 @@ hipError_t launch_h(const QuantArgs& a, hipStream_t s) {
 template <typename IN>
 hipError_t launch_t(const QuantArgs& a, hipStream_t s) {
     if (a.n_frames == 0 || a.n_layers == 0) return hipSuccess;
-    const int rpp = kBlock / (a.head_dim / 8);
+    const int lpr = a.head_dim / 8;
+    // tiles that 16 waves of 8 rows per lane hold (at most 64 KB of LDS for their exchange): the form of row waves
+    if (lpr == 8 && a.group_tokens <= 8 * kMostPasses) return launch_rows<IN, 8>(a, s);
+    if (lpr == 16 && a.group_tokens <= 4 * kMostPasses) return launch_rows<IN, 16>(a, s);
+    if (lpr == 32 && a.group_tokens <= 2 * kMostPasses) return launch_rows<IN, 32>(a, s);
+    const int rpp = kBlock / lpr;
     const int trips = (a.group_tokens + rpp - 1) / rpp;  // rows per lane
     if (trips <= 4) return launch_h<IN, 4>(a, s);
     if (trips <= 8) return launch_h<IN, 8>(a, s);
