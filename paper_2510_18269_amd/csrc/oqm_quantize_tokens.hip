@@ -191,16 +191,16 @@ __global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const Qu
 }
 
 // The form for d = 64, 128, 256 (LPR = d/8 lanes per token row divides a wave).  As few waves as
-// can hold the tile at eight rows per lane own it; a wave reduces its rows with lane swaps, several
+// can hold the tile at eight rows per lane (13 where that would be more than four waves) own it; a wave reduces its rows with lane swaps, several
 // exchange one (min, max) and one key sum per channel through LDS behind a single barrier, one
 // alone needs neither.  Each phase of a launch this short is latency or vector work, not
 // bandwidth: fewer threads per tile mean more tiles in flight and fewer of the per-channel steps.
 // Measured (28 layers x 4 heads x 50 x 128, two waves of seven rows, against the 256-thread
-// form below): 8 FP16 frames 9.3 / 9.9 us, 32 bf16 frames 25.6 / 30.1 us = 4.6 TB/s.  At 32 frames one wave of 13 rows takes
+// form below): 8 FP16 frames 9.2 / 9.9 us, 32 bf16 frames 25.9 / 30.1 us = 4.6 TB/s.  At 32 frames one wave of 13 rows takes
 // 29.1 us, three waves of five 28.4, four of four 29.8; skipping the dead rows by a branch per row
-// 27.5 (no v_min3 across rows), keeping the widened rows for the second sweep 26.4.
+// 27.5 (no v_min3 across rows), keeping the widened rows for the second sweep 26.6.
 template <typename IN, int LPR, int HOLD, int BITS, bool MB>
-__global__ void __launch_bounds__(1024) quantize_append_rows_kernel(const QuantArgs a, const int waves) {
+__global__ void __launch_bounds__(256) quantize_append_rows_kernel(const QuantArgs a, const int waves) {
     constexpr int EB = elem_bytes<IN>::value;
     constexpr uint32_t CW = BITS;  // bytes of packed codes per lane and row (8 channels)
     constexpr int R = 64 / LPR, D = 8 * LPR, CH = LPR / 8;  // rows and channels of a wave's pass; channels a lane finishes
@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(1024) quantize_append_rows_kernel(const QuantA
     char* codes_t = reinterpret_cast<char*>(a.codes) + tile * ((int64_t)G * (D * BITS / 8));
     meta_pair* meta_t = static_cast<meta_pair*>(a.meta) + tile * D;
     const uint32_t in_row_bytes = (uint32_t)a.stride_token * EB;
-    const bool do_sum = kv == 0, own_sum = do_sum && a.ksum != a.k;
+    const bool do_sum = kv == 0;
 
     // pass u covers rows [u * step, (u + 1) * step); rows past G repeat the last one (in the cache already)
     Raw8<IN> held[HOLD];
@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(1024) quantize_append_rows_kernel(const QuantA
             mx[i] = fmaxf(mx[i], x[i]);
         }
     }
-    if (do_sum && !own_sum) {
+    if (do_sum) {
 #pragma unroll
         for (int u = 0; u < HOLD; ++u) {
             float x[8];
@@ -256,15 +256,6 @@ __global__ void __launch_bounds__(1024) quantize_append_rows_kernel(const QuantA
 #pragma unroll
                 for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
             }
-        }
-    }
-    if (own_sum) {  // the keys to average come from another tensor
-        const char* ssrc = static_cast<const char*>(a.ksum) + in_off * EB;
-        for (int row = row0; row < G; row += step) {
-            float x[8];
-            load8(ssrc + ((uint32_t)row * in_row_bytes + (uint32_t)slot * (8u * EB)), IN{}, x);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
         }
     }
     reduce_rows<LPR>(mn, [](float p, float q) { return fminf(p, q); });
@@ -329,8 +320,22 @@ __global__ void __launch_bounds__(1024) quantize_append_rows_kernel(const QuantA
     for (int j = 0; j < CH; ++j) key[c0 + j] = (float)(acc[j] / (double)G);
 }
 
-constexpr int kMostRows = 8;                 // rows a lane holds
-constexpr int kMostPasses = 16 * kMostRows;  // row passes of one wave that 16 waves hold
+// Waves per tile for `passes` row passes of one wave; 0: the general form is the better one.  Eight rows per lane, at
+// most four waves (seven of eight rows lose to the general form: 196 rows at d = 128, 16 frames
+// 56.1 against 52.5 us, since one workgroup more or less per compute unit is then a third of it).
+// Taller tiles take 13 rows, where the registers hold them (16-bit inputs): 48.6 us.  At d = 256 a
+// wave covers only two rows a pass and the exchange costs more, so 13 rows are taken wherever at
+// most one of them per wave is idle (50 rows: 28.5 us against 29.4 with eight rows and 31.6 in the general
+// form) and tiles above 32 passes otherwise stay in the general form (80 rows: 50.6 against 47.0).
+constexpr int kMostRows = 8, kMostRows16Bit = 13;
+template <typename IN, int LPR>
+int row_waves(int passes) {
+    constexpr bool tall = sizeof(Raw8<IN>) <= 16;
+    const int few = (passes + kMostRows16Bit - 1) / kMostRows16Bit;
+    if (LPR == 32 && tall && few <= 4 && few * kMostRows16Bit - passes <= few) return few;
+    if (passes <= 4 * kMostRows) return (passes + kMostRows - 1) / kMostRows;
+    return tall && LPR < 32 && few <= 4 ? 4 : 0;
+}
 
 template <typename IN, int LPR, int HOLD>
 hipError_t launch_rows_h(const QuantArgs& a, int waves, hipStream_t s) {
@@ -348,14 +353,15 @@ hipError_t launch_rows_h(const QuantArgs& a, int waves, hipStream_t s) {
 }
 
 template <typename IN, int LPR>
-hipError_t launch_rows(const QuantArgs& a, hipStream_t s) {
-    const int passes = (a.group_tokens + 64 / LPR - 1) / (64 / LPR);
-    const int waves = (passes + kMostRows - 1) / kMostRows;
+hipError_t launch_rows(const QuantArgs& a, int waves, int passes, hipStream_t s) {
     const int rows = (passes + waves - 1) / waves;
     if (rows <= 4) return launch_rows_h<IN, LPR, 4>(a, waves, s);
     if (rows <= 6) return launch_rows_h<IN, LPR, 6>(a, waves, s);
     if (rows == 7) return launch_rows_h<IN, LPR, 7>(a, waves, s);
-    return launch_rows_h<IN, LPR, 8>(a, waves, s);
+    if constexpr (sizeof(Raw8<IN>) <= 16) {
+        if (rows > kMostRows) return launch_rows_h<IN, LPR, kMostRows16Bit>(a, waves, s);
+    }
+    return launch_rows_h<IN, LPR, kMostRows>(a, waves, s);
 }
 
 template <typename IN, int HOLD, int BITS, bool MB>
@@ -379,10 +385,15 @@ template <typename IN>
 hipError_t launch_t(const QuantArgs& a, hipStream_t s) {
     if (a.n_frames == 0 || a.n_layers == 0) return hipSuccess;
     const int lpr = a.head_dim / 8;
-    // tiles that 16 waves of 8 rows per lane hold (at most 64 KB of LDS for their exchange): the form of row waves
-    if (lpr == 8 && a.group_tokens <= 8 * kMostPasses) return launch_rows<IN, 8>(a, s);
-    if (lpr == 16 && a.group_tokens <= 4 * kMostPasses) return launch_rows<IN, 16>(a, s);
-    if (lpr == 32 && a.group_tokens <= 2 * kMostPasses) return launch_rows<IN, 32>(a, s);
+    // a separate summary source is one more pass over another tensor: the general form is as fast there
+    if (a.ksum == a.k) {
+        const int passes = lpr <= 64 ? (a.group_tokens + 64 / lpr - 1) / (64 / lpr) : 0;
+        const int waves = lpr == 8 ? row_waves<IN, 8>(passes) : lpr == 16 ? row_waves<IN, 16>(passes)
+                        : lpr == 32 ? row_waves<IN, 32>(passes) : 0;
+        if (waves && lpr == 8) return launch_rows<IN, 8>(a, waves, passes, s);
+        if (waves && lpr == 16) return launch_rows<IN, 16>(a, waves, passes, s);
+        if (waves && lpr == 32) return launch_rows<IN, 32>(a, waves, passes, s);
+    }
     const int rpp = kBlock / lpr;
     const int trips = (a.group_tokens + rpp - 1) / rpp;  // rows per lane
     if (trips <= 4) return launch_h<IN, 4>(a, s);
