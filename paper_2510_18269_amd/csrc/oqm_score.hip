@@ -7,7 +7,8 @@
 //                            against the folded query: a float64 GEMV that streams the
 //                            summary keys once; HBM-bound (H_k*d*4 bytes per group).
 //   score_token_gemm_kernel  per-token scores [T_q x H_k*d] x [H_k*d x T] on the matrix
-//                            cores (v_mfma_f64_16x16x4_f64), then the token mean.
+//                            cores (v_mfma_f64_16x16x4_f64), then the token mean; small launches
+//                            split the contraction over waves (score_token_split_kernel).
 //
 // Everything accumulates in float64 (the CDNA vector and matrix pipes run it at
 // full rate), so the float32 scores handed to top-k agree with a float64
@@ -375,6 +376,128 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     }
 }
 
+// The same contraction for launches of at most kSplitUnits units of 16 groups, where the 64 x 64 form
+// leaves compute units idle and each of its few workgroups walks the whole contraction through
+// barriers (1.2 us per 32 channels).  Unit of work = (layer, 16
+// consecutive groups), all query tokens in passes of 16 * MT: the eight waves of a workgroup split the contraction,
+// wave w taking the blocks w, w + 8, ... of 16 channels, and add their tiles up in LDS at the end.
+// Operands go from memory straight into the MFMA registers: the order of a contraction is free,
+// so lane (fi, kk) takes channels 4 kk .. 4 kk + 3 of a block for its four MFMA steps and every load is 16 bytes
+// wide; kAhead blocks are requested before the first is used (four: no faster, one at a time: 3 to 8 us slower).
+// A whole question on the device (fold, this, top-k, gather of 4 groups) at 4 heads of 128, against the 64 x 64 form:
+// 1 layer x 256 groups x 32 tokens 18.1 / 28.0 us, x 64 tokens 25.8 / 39.3; 8 x 1024 (512 units)
+// x 32 25.3 / 31.0, x 64 40.1 / 42.9; but 28 x 400 (700 units) x 32 33.0 / 33.0, x 64 55.2 / 45.9: from three
+// units per compute unit on the query block is read too often.
+constexpr int kSplitUnits = 512;
+constexpr int kSplitWaves = 8, kSplitThreads = 64 * kSplitWaves, kAhead = 2;
+
+template <int MT>
+__global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const ScoreArgs a) {
+    __shared__ double red[kSplitWaves][2 * 256];  // two 16 x 16 tiles of every wave
+    __shared__ double col[2][kSplitWaves][16];
+    const int unit = (int)(blockIdx.x & 7u) * a.gemm_units_per_xcd + (int)(blockIdx.x >> 3);
+    if (unit >= a.gemm_units) return;  // uniform per workgroup
+    const int li = div_by(unit, a.gemm_tiles_per_layer, a.inv_gemm_tiles_per_layer);
+    const int n0 = (unit - li * a.gemm_tiles_per_layer) * 16;
+    const int HD = a.n_kv_heads * a.head_dim;
+    const int T = a.n_groups, Tq = a.t_q;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fi = lane & 15, kk = lane >> 4;
+    const int blocks = (HD + 15) >> 4;
+    // groups past T and tokens past T_q repeat the last one and are dropped at the end
+    const float* const key = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups + min(n0 + fi, T - 1)) * HD;
+    const double* const qtok = a.ws_qtok + (int64_t)li * Tq * HD;
+
+    double csum = 0.0, nk2 = 0.0;
+    for (int m0 = 0; m0 < Tq; m0 += 16 * MT) {
+        const double* row[MT];
+        f64x4 acc[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            row[m] = qtok + (int64_t)min(m0 + m * 16 + fi, Tq - 1) * HD;
+            acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+        }
+        for (int b0 = wave; b0 < blocks; b0 += kAhead * kSplitWaves) {
+            f64x2 ra[kAhead][MT][2];
+            f32x4 rb[kAhead];
+#pragma unroll
+            for (int p = 0; p < kAhead; ++p) {
+                const int b = b0 + p * kSplitWaves;
+                if (b < blocks) {  // uniform
+                    const int k = min(b * 16 + kk * 4, HD - 4);  // HD is a multiple of 8
+                    rb[p] = *reinterpret_cast<const f32x4*>(key + k);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        ra[p][m][0] = *reinterpret_cast<const f64x2*>(row[m] + k);
+                        ra[p][m][1] = *reinterpret_cast<const f64x2*>(row[m] + k + 2);
+                    }
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < kAhead; ++p) {
+                const int b = b0 + p * kSplitWaves;
+                if (b >= blocks) break;  // uniform
+                if (b * 16 + kk * 4 >= HD) {  // half a block: the upper lanes re-read the last channels
+                    rb[p] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) ra[p][m][0] = ra[p][m][1] = f64x2{0.0, 0.0};
+                }
+#pragma unroll
+                for (int st = 0; st < 4; ++st) {
+                    const double bv = (double)rb[p][st];
+                    if (m0 == 0) nk2 = fma(bv, bv, nk2);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(ra[p][m][st >> 1][st & 1], bv, acc[m], 0, 0, 0);
+                }
+            }
+        }
+        // add up the waves, two tiles at a time: thread (u, e) owns element e = v * 64 + lane of tile m + u
+#pragma unroll
+        for (int m = 0; m < MT; m += 2) {
+            if (m0 + m > 0) __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (m + u < MT) red[wave][u * 256 + v * 64 + lane] = acc[m + u < MT ? m + u : 0][v];
+            __syncthreads();
+            const int j = m0 + (m + (tid >> 8)) * 16 + mfma_d_row(lane, (tid >> 6) & 3);
+            if (m + (tid >> 8) < MT && j < Tq) {
+                double sum = 0.0;
+#pragma unroll
+                for (int w = 0; w < kSplitWaves; ++w) sum += red[w][tid];
+                csum += sum;
+                if (a.token_scores && n0 + fi < T) a.token_scores[((int64_t)li * Tq + j) * T + n0 + fi] = (float)sum;
+            }
+        }
+    }
+    // lanes fi, 16 + fi, 32 + fi, 48 + fi hold parts of group n0 + fi
+    csum += __shfl_xor(csum, 16, 64);
+    csum += __shfl_xor(csum, 32, 64);
+    nk2 += __shfl_xor(nk2, 16, 64);
+    nk2 += __shfl_xor(nk2, 32, 64);
+    if (kk == 0) {
+        col[0][wave][fi] = csum;
+        col[1][wave][fi] = nk2;
+    }
+    __syncthreads();
+    if (tid < 16 && n0 + tid < T) {
+        double s = 0.0, n2 = 0.0;
+        for (int w = 0; w < kSplitWaves; ++w) {
+            s += col[0][w][tid];
+            n2 += col[1][w][tid];
+        }
+        s = s / (double)Tq;
+        if (a.sim == TOM_SIM_COSINE) {
+            double nq2 = 0.0;
+            for (int hh = 0; hh < a.n_kv_heads; ++hh) nq2 += a.ws_qnorm2[(int64_t)li * a.n_kv_heads + hh];
+            s = s / (fmax(sqrt(nq2), 1e-12) * fmax(sqrt(n2), 1e-12));
+        }
+        a.scores[(int64_t)li * a.score_stride + n0 + tid] = (float)s;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s) {
@@ -399,19 +522,24 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-}  // namespace oqm
-
-namespace oqm {
 hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.n_groups == 0) return hipSuccess;
     ScoreArgs a = args;
-    a.gemm_tiles_per_layer = (a.n_groups + kGemmN - 1) / kGemmN;
+    const int64_t tiles16 = (a.n_groups + 15) / 16;
+    const bool split = tiles16 * a.n_layers <= kSplitUnits;
+    const int width = split ? 16 : kGemmN;
+    a.gemm_tiles_per_layer = (a.n_groups + width - 1) / width;
     a.inv_gemm_tiles_per_layer = reciprocal_u32((uint32_t)a.gemm_tiles_per_layer);
     const int64_t units = (int64_t)a.gemm_tiles_per_layer * a.n_layers;
     if (units > 0x7fffffffLL - 8) return hipErrorInvalidValue;  // 2^25 tiles x 65535 layers at most: never
     a.gemm_units = (int32_t)units;
     a.gemm_units_per_xcd = (int32_t)((units + 7) / 8);
-    score_token_gemm_kernel<<<dim3(8u * (unsigned)a.gemm_units_per_xcd), dim3(kBlock), 0, s>>>(a);
+    const dim3 grid(8u * (unsigned)a.gemm_units_per_xcd);
+    if (!split) score_token_gemm_kernel<<<grid, dim3(kBlock), 0, s>>>(a);
+    else if (a.t_q <= 16) score_token_split_kernel<1><<<grid, dim3(kSplitThreads), 0, s>>>(a);
+    else if (a.t_q <= 32) score_token_split_kernel<2><<<grid, dim3(kSplitThreads), 0, s>>>(a);
+    else if (a.t_q <= 48) score_token_split_kernel<3><<<grid, dim3(kSplitThreads), 0, s>>>(a);
+    else score_token_split_kernel<4><<<grid, dim3(kSplitThreads), 0, s>>>(a);
     return hipGetLastError();
 }
 }  // namespace oqm
