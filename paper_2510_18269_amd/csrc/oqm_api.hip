@@ -324,9 +324,7 @@ static tom_status_t score_impl(const tom_oqm_t* h, int32_t layer0, int32_t n_lay
     a.q_dtype = q_dtype;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     drop_stale_hip_error();
-    hipError_t e = launch_query_fold(a, rpath == TOM_SCORE_TOKEN_GEMM, s);
-    if (e != hipSuccess) return fail(TOM_ERR_HIP, "query_fold launch: %s", hipGetErrorString(e));
-    e = rpath == TOM_SCORE_TOKEN_GEMM ? launch_score_token_gemm(a, s) : launch_score_mean_query(a, s);
+    const hipError_t e = rpath == TOM_SCORE_TOKEN_GEMM ? launch_score_token_gemm(a, s) : launch_score_mean_query(a, s);
     if (e != hipSuccess) return fail(TOM_ERR_HIP, "score launch: %s", hipGetErrorString(e));
     return TOM_OK;
 }

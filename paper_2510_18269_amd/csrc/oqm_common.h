@@ -107,6 +107,8 @@ struct ScoreArgs {
     // Filled in by the launcher of the per-token contraction: its unit decomposition.
     int32_t gemm_units, gemm_units_per_xcd, gemm_tiles_per_layer;
     uint32_t inv_gemm_tiles_per_layer;
+    // Filled in by the launcher of the fused fold and score: row slots per KV head and the reciprocals for oqm::div_by.
+    uint32_t fold_slots, inv_fold_slots, inv_lanes_per_row, inv_head_dim;
 };
 
 // ---- launchers (each validates nothing: the API layer has done that) ------
@@ -117,7 +119,7 @@ hipError_t launch_dequant_gather(const DequantArgs& a, int out_dtype, hipStream_
 // The prefix rows alone.
 hipError_t launch_prefix_copy(const DequantArgs& a, const void* sys_k, const void* sys_v, int out_dtype,
                               hipStream_t s);
-hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s);
+// Both fold the query themselves.
 hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s);
 hipError_t launch_score_token_gemm(const ScoreArgs& a, hipStream_t s);
 hipError_t launch_topk(const float* scores, int64_t stride, int n_rows, int n_groups, int k,

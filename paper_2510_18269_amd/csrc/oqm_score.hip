@@ -6,6 +6,7 @@
 //   score_mean_query_kernel  one dot product (and one key norm) per stored frame-group
 //                            against the folded query: a float64 GEMV that streams the
 //                            summary keys once; HBM-bound (H_k*d*4 bytes per group).
+//   score_fold_query_kernel  both of these in one launch, for short questions.
 //   score_token_gemm_kernel  per-token scores [T_q x H_k*d] x [H_k*d x T] on the matrix
 //                            cores (v_mfma_f64_16x16x4_f64), then the token mean; small launches
 //                            split the contraction over waves (score_token_split_kernel).
@@ -134,7 +135,42 @@ __device__ __forceinline__ double row16_sum_f64(double v) {
     return v;
 }
 
+constexpr int kFoldThreads = 512;
 constexpr int kScoreChunks = 8;  // 16-byte key loads per lane that are in flight together
+
+// Dot product and norm of one group's key (its first kScoreChunks pieces already in kx) against the
+// staged query, and the score.  16 lanes work on a group.
+template <typename LOAD, typename NORM>
+__device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double* qbar, f32x4 (&kx)[kScoreChunks],
+                                               LOAD load_keys, int HD, int sub, int t, int li, NORM query_norm) {
+    double dot = 0.0, nk2 = 0.0;
+    for (int e0 = 0; e0 < HD; e0 += kScoreChunks * 64) {
+        f32x4 cur[kScoreChunks];
+#pragma unroll
+        for (int c = 0; c < kScoreChunks; ++c) cur[c] = kx[c];
+        if (e0 + kScoreChunks * 64 < HD) load_keys(e0 + kScoreChunks * 64);  // uniform
+#pragma unroll
+        for (int c = 0; c < kScoreChunks; ++c) {
+            const int e = e0 + c * 64 + sub * 4;
+            if (e < HD) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double kd = (double)cur[c][i];
+                    const double qv = qbar[(((2 * ((e0 >> 6) + c) + (i >> 1)) * 16 + sub) << 1) + (i & 1)];
+                    dot = fma(qv, kd, dot);
+                    nk2 = fma(kd, kd, nk2);
+                }
+            }
+        }
+    }
+    dot = row16_sum_f64(dot);
+    nk2 = row16_sum_f64(nk2);
+    if (sub == 0 && t < a.n_groups) {
+        double s = dot;
+        if (a.sim == TOM_SIM_COSINE) s = dot / (fmax(query_norm(), 1e-12) * fmax(sqrt(nk2), 1e-12));
+        a.scores[(int64_t)li * a.score_stride + t] = (float)s;
+    }
+}
 
 // grid (ceil(T / 16), n_layers); dynamic LDS: H_k*d doubles (q-bar).  16 lanes share one
 // frame-group: lane i of them takes floats [64c + 4i, 64c + 4i + 4) of the key for
@@ -172,33 +208,88 @@ __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArg
     const double nq = sqrt(nq2);
     __syncthreads();
 
-    double dot = 0.0, nk2 = 0.0;
-    for (int e0 = 0; e0 < HD; e0 += kScoreChunks * 64) {
-        f32x4 cur[kScoreChunks];
-#pragma unroll
-        for (int c = 0; c < kScoreChunks; ++c) cur[c] = kx[c];
-        if (e0 + kScoreChunks * 64 < HD) load_keys(e0 + kScoreChunks * 64);  // uniform
+    score_of_group(a, qbar, kx, load_keys, HD, sub, t, li, [&] { return nq; });
+}
+
+// Fold and score in one launch, for questions short enough that every workgroup can fold the query
+// of its layer by itself.  grid (ceil(T / 32), n_layers), 512 threads; dynamic LDS: H_k*d doubles.
+// The r * T_q rows of a KV head are contiguous in Q, so the mean over heads and tokens is one
+// sum over a run of rows: head h gets the same number of row slots (d/8 lanes each) of the
+// workgroup.  The key loads are in flight meanwhile.
+template <typename QT>
+__global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const ScoreArgs a) {
+    constexpr int EB = elem_bytes<QT>::value;
+    constexpr int kRows = 8;  // query rows per lane in flight
+    extern __shared__ double qbar[];
+    __shared__ double red[kFoldThreads * 8];
+    __shared__ double wsum[kFoldThreads / 64];
+    const int li = blockIdx.y;
+    const int H = a.n_kv_heads, d = a.head_dim, HD = H * d;
+    const int tid = threadIdx.x, sub = tid & 15;
+    const float* keys = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups) * HD;
+    const int t = blockIdx.x * (kFoldThreads / 16) + (tid >> 4);
+    const int tc = min(t, a.n_groups - 1);  // the tail re-reads the last group
+    const float* key = keys + (int64_t)tc * HD + sub * 4;
+    f32x4 kx[kScoreChunks];
+    auto load_keys = [&](int e0) {
 #pragma unroll
         for (int c = 0; c < kScoreChunks; ++c) {
-            const int e = e0 + c * 64 + sub * 4;
-            if (e < HD) {
+            kx[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (e0 + c * 64 + sub * 4 < HD) kx[c] = *reinterpret_cast<const f32x4*>(key + e0 + c * 64);
+        }
+    };
+    load_keys(0);
+
+    const int lpr = d >> 3;
+    const int s = div_by(tid, lpr, a.inv_lanes_per_row), slot = tid - s * lpr;
+    const int h = div_by(s, a.fold_slots, a.inv_fold_slots), part = s - h * a.fold_slots;
+    if (h < H) {
+        const int rows = (a.n_q_heads / H) * a.t_q;  // small: the launcher bounds the query
+        const char* q = static_cast<const char*>(a.q) + (((int64_t)li * H + h) * rows * d + slot * 8) * EB;
+        double acc[8];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const double kd = (double)cur[c][i];
-                    const double qv = qbar[(((2 * ((e0 >> 6) + c) + (i >> 1)) * 16 + sub) << 1) + (i & 1)];
-                    dot = fma(qv, kd, dot);
-                    nk2 = fma(kd, kd, nk2);
-                }
+        for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+        for (int r0 = part; r0 < rows; r0 += kRows * a.fold_slots) {
+            Raw8<QT> raw[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                zero_raw(raw[u]);
+                const int row = r0 + u * a.fold_slots;
+                if (row < rows) load_raw(q + (int64_t)row * d * EB, raw[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                float x[8];
+                widen(raw[u], x);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
             }
         }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) red[s * d + i * lpr + slot] = acc[i];  // position order: no bank conflicts
     }
-    dot = row16_sum_f64(dot);
-    nk2 = row16_sum_f64(nk2);
-    if (sub == 0 && t < a.n_groups) {
-        double s = dot;
-        if (a.sim == TOM_SIM_COSINE) s = dot / (fmax(nq, 1e-12) * fmax(sqrt(nk2), 1e-12));
-        a.scores[(int64_t)li * a.score_stride + t] = (float)s;
+    __syncthreads();
+    double sq = 0.0;
+    for (int e = tid; e < HD; e += kFoldThreads) {
+        const int hh = div_by(e, d, a.inv_head_dim), p = e - hh * d;  // position p of head hh
+        double sum = 0.0;
+        for (int w = 0; w < a.fold_slots; ++w) sum += red[(hh * a.fold_slots + w) * d + p];
+        const double qb = sum / (double)((a.n_q_heads / H) * a.t_q);
+        const int i8 = div_by(p, lpr, a.inv_lanes_per_row);
+        const int ch = hh * d + (p - i8 * lpr) * 8 + i8;
+        const int c = ch >> 6, sl = (ch >> 2) & 15, i = ch & 3;
+        qbar[(((2 * c + (i >> 1)) * 16 + sl) << 1) + (i & 1)] = qb;  // the order of score_mean_query_kernel
+        sq += qb * qb;
     }
+    sq = wave_sum_f64(sq);
+    if ((tid & 63) == 0) wsum[tid >> 6] = sq;
+    __syncthreads();
+    score_of_group(a, qbar, kx, load_keys, HD, sub, t, li, [&] {
+        double nq2 = 0.0;
+#pragma unroll
+        for (int w = 0; w < kFoldThreads / 64; ++w) nq2 += wsum[w];
+        return sqrt(nq2);
+    });
 }
 
 // ------------------------------------------------------------------ per-token GEMM
@@ -500,7 +591,7 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
 
 }  // namespace
 
-hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s) {
+static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s) {
     if (a.n_layers == 0) return hipSuccess;
     const dim3 grid(a.n_kv_heads, a.n_layers);
     switch (a.q_dtype) {
@@ -512,8 +603,34 @@ hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
-    if (a.n_layers == 0 || a.n_groups == 0) return hipSuccess;
+hipError_t launch_score_mean_query(const ScoreArgs& args, hipStream_t s) {
+    if (args.n_layers == 0 || args.n_groups == 0) return hipSuccess;
+    ScoreArgs a = args;
+    const int lpr = a.head_dim / 8;
+    a.fold_slots = (uint32_t)(kFoldThreads / lpr / a.n_kv_heads);
+    const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
+    const int64_t query = (int64_t)a.n_q_heads * a.t_q * a.head_dim;  // elements of a layer
+    // Folding inside the score kernel saves a launch (4 us of host time, as much on the device) and costs each
+    // workgroup 0.03 us per 1000 query elements (float64 conversions and sums), more once they
+    // share compute units: line at query elements x (workgroups + 64).  Whole question at 28 query heads of 128, fused / separate: 1 layer x 256 groups x 8 tokens 11.7 /
+    // 16.0 us, x 32 14.1 / 16.0; 28 x 256 x 8 14.6 / 16.4; on the line 1 x 1024 x 32 16.1 / 16.2
+    // and 8 x 256 x 32 15.6 / 15.8; beyond it 28 x 64 x 32 16.2 / 15.8, 1 x 3600 x 32 18.9 / 17.1.
+    constexpr int64_t kFusedWork = 12000000;
+    if (a.fold_slots > 0 && query <= kFusedWork / (blocks + 64)) {
+        a.inv_fold_slots = reciprocal_u32(a.fold_slots);
+        a.inv_lanes_per_row = reciprocal_u32((uint32_t)lpr);
+        a.inv_head_dim = reciprocal_u32((uint32_t)a.head_dim);
+        const dim3 grid((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16), a.n_layers), block(kFoldThreads);
+        const size_t lds = (size_t)((a.n_kv_heads * a.head_dim + 63) / 64 * 64) * sizeof(double);
+        switch (a.q_dtype) {
+            case TOM_F32: score_fold_query_kernel<In_f32><<<grid, block, lds, s>>>(a); break;
+            case TOM_BF16: score_fold_query_kernel<In_bf16><<<grid, block, lds, s>>>(a); break;
+            case TOM_F16: score_fold_query_kernel<In_f16><<<grid, block, lds, s>>>(a); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
+    if (hipError_t e = launch_query_fold(a, false, s)) return e;
     const int per_block = kBlock / 16;
     const dim3 grid((a.n_groups + per_block - 1) / per_block, a.n_layers);
     // q-bar, padded to whole 64-element chunks (the staged order permutes within a chunk)
@@ -524,6 +641,7 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
 
 hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.n_groups == 0) return hipSuccess;
+    if (hipError_t e = launch_query_fold(args, true, s)) return e;
     ScoreArgs a = args;
     const int64_t tiles16 = (a.n_groups + 15) / 16;
     const bool split = tiles16 * a.n_layers <= kSplitUnits;
