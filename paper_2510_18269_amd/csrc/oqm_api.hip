@@ -369,7 +369,9 @@ tom_status_t tom_oqm_topk(const float* scores, int64_t score_stride, int32_t n_r
 static tom_status_t assemble_impl(const tom_oqm_t* h, int32_t layer0, int32_t n_layers,
                                   const int32_t* idx, int32_t k, int32_t k_eff, int32_t prefix_rows,
                                   const void* sys_k, const void* sys_v, void* k_out, void* v_out,
-                                  void* hip_stream, bool launch, int32_t* all_idx = nullptr) {
+                                  void* hip_stream, bool launch, int32_t* all_idx = nullptr,
+                                  const float* scores = nullptr, int64_t score_stride = 0,
+                                  int32_t* sel_idx = nullptr) {
     if (!h) return fail(TOM_ERR_INVALID_ARG, "handle is NULL");
     if (!h->bound) return fail(TOM_ERR_NOT_BOUND, "tom_oqm_bind has not been called");
     if (tom_status_t st = check_layers(h, layer0, n_layers)) return st;
@@ -404,6 +406,9 @@ static tom_status_t assemble_impl(const tom_oqm_t* h, int32_t layer0, int32_t n_
     a.meta = h->meta;
     a.idx = idx;
     a.all_idx = all_idx;
+    a.scores = scores;
+    a.sel_idx = sel_idx;
+    a.score_stride = score_stride;
     a.sys_k = copy_prefix ? static_cast<const char*>(sys_k) : nullptr;
     a.sys_v = copy_prefix ? static_cast<const char*>(sys_v) : nullptr;
     a.k_out = k_out;
@@ -462,18 +467,18 @@ static tom_status_t retrieve_pass(const tom_oqm_t* h, int32_t layer0, int32_t n_
     if (tom_status_t st = score_impl(h, layer0, n_layers, q, q_dtype, t_q, scores, score_stride, nullptr,
                                      path, workspace, workspace_bytes, hip_stream, go))
         return st;
-    // Everything fits the budget: there is nothing to select, and the gather writes the indices 0 .. T-1
-    // itself (the top-k launch this saves takes 2 to 4 us).
-    const bool all = go && k_eff == T;
-    if (!all) {
-        if (tom_status_t st = topk_impl(scores, score_stride, n_layers, T, k, TOM_ORDER_INDEX_ASC, idx,
-                                        k_eff_host, hip_stream, go))
+    if (!go) {
+        if (tom_status_t st = topk_impl(scores, score_stride, n_layers, T, k, TOM_ORDER_INDEX_ASC, idx, k_eff_host,
+                                        hip_stream, false))
             return st;
     } else if (k_eff_host) {
         *k_eff_host = k_eff;
     }
-    return assemble_impl(h, layer0, n_layers, idx, k, k_eff < 0 ? 0 : k_eff, prefix_rows, sys_k, sys_v,
-                         k_out, v_out, hip_stream, go, all ? idx : nullptr);
+    // Everything fits the budget: there is nothing to select, and the gather writes the indices 0 .. T-1
+    // itself (the top-k launch this saves takes 2 to 4 us).  Otherwise its launcher has the groups selected.
+    const bool all = k_eff == T;
+    return assemble_impl(h, layer0, n_layers, idx, k, k_eff < 0 ? 0 : k_eff, prefix_rows, sys_k, sys_v, k_out, v_out,
+                         hip_stream, go, all ? idx : nullptr, all ? nullptr : scores, score_stride, idx);
 }
 
 tom_status_t tom_oqm_retrieve(const tom_oqm_t* h, int32_t layer0, int32_t n_layers, const void* q,

@@ -74,6 +74,9 @@ struct DequantArgs {
     const void* meta;
     const int32_t* idx;  // [n_layers][k]; unused when all_idx is given
     int32_t* all_idx;    // every stored group is taken in order, and these indices are written; or NULL
+    const float* scores; // the groups are still to be selected by these scores, and the indices written to sel_idx; or NULL
+    int32_t* sel_idx;
+    int64_t score_stride;
     const char* sys_k;   // source of the prefix rows [n_layers][H_k][prefix_rows][d], or NULL
     const char* sys_v;
     void* k_out;
@@ -114,7 +117,7 @@ struct ScoreArgs {
 // ---- launchers (each validates nothing: the API layer has done that) ------
 hipError_t launch_quantize_append(const QuantArgs& a, int in_dtype, hipStream_t s);
 hipError_t launch_quantize_append_tokens(const QuantArgs& a, int in_dtype, hipStream_t s);
-// Copies the prefix rows too where a.sys_k is given.
+// Copies the prefix rows too where a.sys_k is given, and selects the groups first where a.scores is.
 hipError_t launch_dequant_gather(const DequantArgs& a, int out_dtype, hipStream_t s);
 // The prefix rows alone.
 hipError_t launch_prefix_copy(const DequantArgs& a, const void* sys_k, const void* sys_v, int out_dtype,

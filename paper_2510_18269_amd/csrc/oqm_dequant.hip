@@ -24,6 +24,7 @@
 
 #include "oqm_common.h"
 #include "oqm_device.h"
+#include "oqm_select.h"
 
 namespace oqm {
 namespace {
@@ -35,6 +36,8 @@ __device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t 
     if (off < bytes) *reinterpret_cast<u32x4*>(dst + off) = *reinterpret_cast<const u32x4*>(src + off);
 }
 
+constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups
+
 // The 8-channel items of a tile (one 32-bit word of 4-bit codes each) are numbered row by row: item
 // row * (d/8) + slot.  Codes and output are linear in that number, and so are the pairs of the
 // head_dim axis (d/8 is a multiple of the gs/8 lanes of a quant-group), so a chunk is a linear stream and the
@@ -42,7 +45,9 @@ __device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t 
 // `step` = the largest multiple of d/8 below 256 apart, otherwise 256.
 // kUnroll: items per lane; all their loads are issued before the first is converted, and the host
 // cuts the tile into chunks that one trip covers.
-template <typename OUT, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB>
+// SELECT: waves of the workgroup that select its group from the layer's scores (256 scores each), or 0: the
+// index comes from memory.
+template <typename OUT, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB, int SELECT>
 __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArgs a) {
     constexpr int EB = elem_bytes<OUT>::value;
     constexpr uint32_t CW = BITS;          // bytes of packed codes per item
@@ -65,7 +70,23 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
         return;
     }
     typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;  // not written by this launch where it is read
-    const uint32_t t = a.all_idx ? r : ((scalar_ptr)(uintptr_t)a.idx)[(uint64_t)li * (uint32_t)a.k + r];
+    uint32_t t;
+    if constexpr (SELECT > 0) {
+        __shared__ uint32_t chosen;
+        __shared__ uint32_t slots[2][SELECT];
+        if (SELECT == kBlock / 64 || tid < 64 * SELECT) {
+            const int lane = (int)(tid & 63u), wave = SELECT == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(tid >> 6));
+            uint32_t key[kSelectKeys];
+            load_keys_of_row<kSelectKeys>(a.scores + (int64_t)li * a.score_stride, a.n_groups, wave, lane, key);
+            select_largest<SELECT, kSelectKeys>(key, a.k_eff, wave, lane, slots, [&](uint32_t rank, int i) {
+                if (rank == r) chosen = (uint32_t)i;  // one lane: ranks are distinct and r < k_eff
+            });
+        }
+        __syncthreads();
+        t = (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen);
+    } else {
+        t = a.all_idx ? r : ((scalar_ptr)(uintptr_t)a.idx)[(uint64_t)li * (uint32_t)a.k + r];
+    }
     if (t >= (uint32_t)a.n_groups) return;  // not a stored group: leave the rows alone
 
     const uint32_t begin = (blockIdx.x - r * a.chunks) * a.chunk_items;
@@ -110,8 +131,9 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
             store8(out + item * (8u * EB), OUT{}, x);
         }
     }
+    if (SELECT > 0 && blockIdx.y == 0 && begin == 0 && tid == 0) a.sel_idx[(int64_t)li * a.k + r] = (int32_t)t;
     // last, so that the index load above stays a scalar load
-    if (a.all_idx && blockIdx.y == 0 && begin == 0 && tid == 0) a.all_idx[(int64_t)li * a.k + r] = (int32_t)r;
+    if (SELECT == 0 && a.all_idx && blockIdx.y == 0 && begin == 0 && tid == 0) a.all_idx[(int64_t)li * a.k + r] = (int32_t)r;
 }
 
 // The prefix alone.  grid (chunks, H_k * n_layers, 2).
@@ -153,6 +175,28 @@ bool prefix_joins_gather(const DequantArgs& a) {
     return apart(a.sys_k, a.k_out) && apart(a.sys_k, a.v_out) && apart(a.sys_v, a.k_out) && apart(a.sys_v, a.v_out);
 }
 
+// Whether the workgroups of the gather select their groups themselves instead of reading the indices that a
+// top-k launch wrote.  The launch costs 2.5 to 4 us on the device; selecting delays each
+// workgroup by about 1 us with one wave (up to 256 scores) and 2 us with four, so it pays while the workgroups
+// run in about one round.  Whole one-call question at 4 heads, itself / with the launch: 256 scores, 896 workgroups 13.0 / 14.9 us,
+// 1792 15.2 / 17.4, 4000 16.3 / 17.3 or 16.6, 6000 21.1 / 20.4; 1024 scores, 64 workgroups 12.9 / 14.5, 896 24.8 / 25.6, 1280 14.5 / 14.9
+// (in a graph 14.2 / 14.1), 2560 20.5 / 17.5.
+constexpr int kSelectMaxGroups = kBlock * kSelectKeys;
+
+bool selects_itself(const DequantArgs& a, int64_t workgroups) {
+    if (a.n_groups > kSelectMaxGroups || workgroups > (a.n_groups <= 64 * kSelectKeys ? 2048 : 1024)) return false;
+    // the launch reads all scores while it writes: no output may share memory with them
+    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
+    const uint64_t out_bytes = (uint64_t)(heads * a.head_out_bytes);
+    const uintptr_t s = reinterpret_cast<uintptr_t>(a.scores);
+    const uint64_t score_bytes = 4u * ((uint64_t)(a.n_layers - 1) * (uint64_t)a.score_stride + (uint64_t)a.n_groups);
+    auto apart = [&](const void* out, uint64_t bytes) {
+        const uintptr_t o = reinterpret_cast<uintptr_t>(out);
+        return s + score_bytes <= o || o + bytes <= s;
+    };
+    return apart(a.k_out, out_bytes) && apart(a.v_out, out_bytes) && apart(a.sel_idx, 4u * (uint64_t)a.n_layers * (uint64_t)a.k);
+}
+
 template <typename OUT>
 hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.k_eff == 0) return hipSuccess;
@@ -178,6 +222,11 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     a.plane_tiles = (int64_t)a.capacity_groups * a.n_kv_heads;
     a.prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;
     a.head_out_bytes = a.prefix_bytes + (int64_t)a.k * a.group_tokens * a.head_dim * eb;
+    const bool select = a.scores && selects_itself(a, (int64_t)a.k_eff * a.chunks * 2 * a.n_kv_heads * a.n_layers);
+    if (a.scores && !select)
+        if (hipError_t e = launch_topk(a.scores, a.score_stride, a.n_layers, a.n_groups, a.k, a.k_eff, TOM_ORDER_INDEX_ASC,
+                                       a.sel_idx, s))
+            return e;
     uint32_t prefix_blocks = 0;
     if (a.sys_k && a.prefix_rows > 0) {
         if (prefix_joins_gather<OUT>(a)) {
@@ -190,8 +239,14 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     auto go = [&](auto unroll, auto bits, auto mb) {
         constexpr int U = decltype(unroll)::value, B = decltype(bits)::value;
         constexpr bool M = decltype(mb)::value;
-        if (tok) dequant_gather_kernel<OUT, U, true, B, M><<<grid, block, 0, s>>>(a);
-        else dequant_gather_kernel<OUT, U, false, B, M><<<grid, block, 0, s>>>(a);
+        auto with_select = [&](auto select) {
+            constexpr int S = decltype(select)::value;
+            if (tok) dequant_gather_kernel<OUT, U, true, B, M, S><<<grid, block, 0, s>>>(a);
+            else dequant_gather_kernel<OUT, U, false, B, M, S><<<grid, block, 0, s>>>(a);
+        };
+        if (!select) with_select(std::integral_constant<int, 0>{});
+        else if (a.n_groups <= 64 * kSelectKeys) with_select(std::integral_constant<int, 1>{});
+        else with_select(std::integral_constant<int, kBlock / 64>{});
     };
     auto with_meta = [&](auto unroll, auto bits) {
         if (a.meta_bf16) go(unroll, bits, std::true_type{});

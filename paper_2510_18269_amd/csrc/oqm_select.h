@@ -1,5 +1,5 @@
 // Selection of the k largest scores of a row held in registers: the device half shared by the
-// top-k kernel and by the one-workgroup retrieval front end.
+// top-k kernel and by the gather of a small retrieval.
 #pragma once
 
 #include "oqm_device.h"
@@ -19,15 +19,15 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t b) {
 }
 
 // WAVES waves hold the keys of one row, KEYS per lane: wave w, register c, lane l is entry
-// (w * KEYS + c) * 64 + l of the row (absent ones hold key 0; at least k_eff are present).  Writes the entries of
-// the k_eff largest keys to out[0 .. k_eff) in ascending entry order; of equal keys the lowest
-// entries are taken.  The k-th largest key is built bit by bit from the top: a bit stays set if at
+// (w * KEYS + c) * 64 + l of the row (absent ones hold key 0; at least k_eff are present).  Calls emit(rank, entry)
+// in the lane of each of the k_eff largest keys, ranks 0 .. k_eff - 1 in ascending entry order; of equal keys the
+// lowest entries are taken.  The k-th largest key is built bit by bit from the top: a bit stays set if at
 // least k keys reach the candidate, and the search ends early when exactly k do.  A count is
 // KEYS ballots and scalar population counts; with one wave there is no barrier and no LDS at all,
 // with several each count is one exchange through `slots` (two alternating sets of WAVES words).
-template <int WAVES, int KEYS>
+template <int WAVES, int KEYS, typename EMIT>
 __device__ __forceinline__ void select_largest(const uint32_t (&key)[KEYS], int k_eff, int wave, int lane,
-                                               int32_t* __restrict__ out, uint32_t (*slots)[WAVES]) {
+                                               uint32_t (*slots)[WAVES], EMIT emit) {
     int phase = 0;
     // sum over aligned sets of WAVES lanes (DPP), as a scalar
     auto lanes_sum = [](uint32_t v) -> uint32_t {
@@ -87,10 +87,24 @@ __device__ __forceinline__ void select_largest(const uint32_t (&key)[KEYS], int 
         const bool eq = key[c] == thr;
         const uint64_t bg = __ballot(gt), be = __ballot(eq);
         const uint32_t og = base_g + rank_in(bg), oe = base_e + rank_in(be);
-        if (gt) out[og + min(oe, need)] = i;
-        else if (eq && oe < need) out[og + oe] = i;
+        if (gt) emit(og + min(oe, need), i);
+        else if (eq && oe < need) emit(og + oe, i);
         base_g += (uint32_t)__popcll(bg);
         base_e += (uint32_t)__popcll(be);
+    }
+}
+
+// The keys of a row of n scores for select_largest.
+template <int KEYS>
+__device__ __forceinline__ void load_keys_of_row(const float* __restrict__ s, int n, int wave, int lane,
+                                                 uint32_t (&key)[KEYS]) {
+    float x[KEYS];
+#pragma unroll
+    for (int c = 0; c < KEYS; ++c) x[c] = s[(uint32_t)min((wave * KEYS + c) * 64 + lane, n - 1)];
+#pragma unroll
+    for (int c = 0; c < KEYS; ++c) {
+        asm volatile("" : "+v"(x[c]));  // all loads in flight before the first is used (the compiler would branch around each)
+        key[c] = (wave * KEYS + c) * 64 + lane < n ? orderable(x[c]) : 0u;
     }
 }
 

@@ -42,17 +42,9 @@ topk_ascending_kernel(const float* __restrict__ scores, const int64_t stride, co
         for (int i = threadIdx.x; i < n; i += 64 * WAVES) out[i] = i;
         return;
     }
-    const float* s = scores + (int64_t)blockIdx.x * stride;
-    float x[KEYS];
-#pragma unroll
-    for (int c = 0; c < KEYS; ++c) x[c] = s[(uint32_t)min((wave * KEYS + c) * 64 + lane, n - 1)];
     uint32_t key[KEYS];
-#pragma unroll
-    for (int c = 0; c < KEYS; ++c) {
-        asm volatile("" : "+v"(x[c]));  // all loads in flight before the first is used (the compiler would branch around each)
-        key[c] = (wave * KEYS + c) * 64 + lane < n ? orderable(x[c]) : 0u;
-    }
-    select_largest<WAVES, KEYS>(key, k_eff, wave, lane, out, slots);
+    load_keys_of_row<KEYS>(scores + (int64_t)blockIdx.x * stride, n, wave, lane, key);
+    select_largest<WAVES, KEYS>(key, k_eff, wave, lane, slots, [&](uint32_t rank, int i) { out[rank] = i; });
 }
 
 __global__ void __launch_bounds__(kTopkThreads)

@@ -1,0 +1,60 @@
+"""The one-call retrieval of a small store: the gather's workgroups select their groups themselves."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oqm():
+    from paper_2510_18269_amd import oqm as m      # raises if the library is not built
+    assert torch.cuda.is_available()
+    return m
+
+
+@pytest.mark.parametrize("T,k,L,G,dt,axis,prefix,where", [
+    (2, 1, 1, 16, "bf16", 0, 0, "apart"), (64, 63, 2, 5, "f16", 0, 0, "apart"), (65, 64, 3, 7, "f32", 1, 9, "apart"),
+    (255, 17, 1, 50, "bf16", 1, 0, "apart"), (256, 1, 2, 196, "bf16", 0, 3, "apart"), (256, 255, 1, 3, "f16", 0, 0, "apart"),
+    (257, 20, 1, 16, "bf16", 0, 0, "apart"), (1023, 41, 2, 16, "f32", 1, 2, "apart"),      # four waves select
+    (1024, 256, 1, 3, "f16", 0, 0, "apart"), (1024, 1, 1, 196, "bf16", 1, 0, "apart"),
+    (1024, 257, 1, 3, "bf16", 0, 0, "apart"), (256, 128, 4, 16, "f16", 0, 0, "apart"),     # the most workgroups with one wave (2048) and one group more than with four (1024)
+    (1025, 20, 1, 16, "bf16", 0, 0, "apart"), (255, 129, 4, 16, "bf16", 0, 5, "apart"),    # one score too many, one group too many
+    (100, 30, 2, 16, "bf16", 0, 0, "scores in k_out"), (100, 30, 2, 16, "bf16", 0, 0, "idx behind scores"),   # or shared memory (the second one only adjoins)
+])
+def test_retrieve_matches_separate_calls(oqm, T, k, L, G, dt, axis, prefix, where):
+    """Indices, scores and rows equal those of the separate calls bit for bit, with many equal scores."""
+    H, d, tq, stride = 2, 64, 3, T + 5
+    code, tdt = {"f32": (oqm.TOM_F32, torch.float32), "bf16": (oqm.TOM_BF16, torch.bfloat16), "f16": (oqm.TOM_F16, torch.float16)}[dt]
+    cfg = oqm.make_config(L, H, 4, d, G, 32, T, qaxis=axis, bits=4, in_dtype=code, out_dtype=code)
+    mem = oqm.Memory.allocate(cfg)
+    g = torch.Generator().manual_seed(T + k)
+    kinds = torch.randint(0, max(2, T // 3), (T,), generator=g)      # repeated frames: equal scores, lowest index first
+    kv = [torch.randn((int(kinds.max()) + 1, L, H, G, d), generator=g)[kinds].to(tdt).cuda() for _ in range(2)]
+    oqm.tom_oqm_quantize_append(mem.handle, 0, L, T, *kv)
+    q = torch.randn((L, 4, tq, d), generator=g).to(tdt).cuda()
+    ws = torch.empty(oqm.tom_oqm_score_workspace_bytes(mem.handle, L, tq), dtype=torch.uint8, device="cuda")
+    sys_kv = [torch.randn((L, H, prefix, d), generator=g).to(tdt).cuda() for _ in range(2)] if prefix else [None, None]
+    rows = prefix + k * G
+
+    def buffers():
+        return (torch.full((L, stride), -9.0, device="cuda"), torch.full((L, k), -7, dtype=torch.int32, device="cuda"),
+                *(torch.zeros((L, H, rows, d), dtype=tdt, device="cuda") for _ in range(2)))
+
+    s0, i0, k0, v0 = buffers()
+    oqm.tom_oqm_score_groups(mem.handle, 0, L, q, tq, s0, stride, None, oqm.TOM_SCORE_AUTO, ws)
+    oqm.tom_oqm_topk(s0, stride, L, T, k, i0)
+    oqm.tom_oqm_assemble_active(mem.handle, 0, L, i0, k, k, prefix, *sys_kv, k0, v0)
+    s1, i1, k1, v1 = buffers()
+    if where == "scores in k_out":
+        s1 = k1.view(-1).view(torch.float32)[:L * stride].view(L, stride)
+    elif where == "idx behind scores":
+        s1 = torch.full((L * stride + L * k,), -9.0, device="cuda")
+        i1 = s1[(L - 1) * stride + T - 3:].view(torch.int32)[3:3 + L * k].view(L, k)
+        s1 = s1[:L * stride].view(L, stride)
+    got = oqm.tom_oqm_retrieve(mem.handle, 0, L, q, tq, k, s1, stride, i1, k1, v1, ws, prefix_rows=prefix, sys_k=sys_kv[0], sys_v=sys_kv[1])
+    torch.cuda.synchronize()
+    assert got == k
+    assert torch.equal(i0, i1)
+    assert where == "scores in k_out" or torch.equal(s0[:, :T], s1[:, :T])
+    assert torch.equal(k0.view(torch.uint8), k1.view(torch.uint8)) and torch.equal(v0.view(torch.uint8), v1.view(torch.uint8))
+    mem.close()
