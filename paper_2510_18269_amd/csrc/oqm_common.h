@@ -110,8 +110,6 @@ struct ScoreArgs {
     // Filled in by the launcher of the per-token contraction: its unit decomposition.
     int32_t gemm_units, gemm_units_per_xcd, gemm_tiles_per_layer;
     uint32_t inv_gemm_tiles_per_layer;
-    // Filled in by the launcher of the fused fold and score: row slots per KV head and the reciprocals for oqm::div_by.
-    uint32_t fold_slots, inv_fold_slots, inv_lanes_per_row, inv_head_dim;
 };
 
 // ---- launchers (each validates nothing: the API layer has done that) ------

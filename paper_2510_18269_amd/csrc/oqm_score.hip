@@ -216,8 +216,14 @@ __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArg
 // The r * T_q rows of a KV head are contiguous in Q, so the mean over heads and tokens is one
 // sum over a run of rows: head h gets the same number of row slots (d/8 lanes each) of the
 // workgroup.  The key loads are in flight meanwhile.
+// Row slots per KV head and the reciprocals for div_by.  Not part of ScoreArgs: the other kernels' arguments then
+// stay within two 64-byte lines.
+struct FoldSplit {
+    uint32_t slots, inv_slots, inv_lanes_per_row, inv_head_dim;
+};
+
 template <typename QT>
-__global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const ScoreArgs a) {
+__global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const ScoreArgs a, const FoldSplit f) {
     constexpr int EB = elem_bytes<QT>::value;
     constexpr int kRows = 8;  // query rows per lane in flight
     extern __shared__ double qbar[];
@@ -241,20 +247,20 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
     load_keys(0);
 
     const int lpr = d >> 3;
-    const int s = div_by(tid, lpr, a.inv_lanes_per_row), slot = tid - s * lpr;
-    const int h = div_by(s, a.fold_slots, a.inv_fold_slots), part = s - h * a.fold_slots;
+    const int s = div_by(tid, lpr, f.inv_lanes_per_row), slot = tid - s * lpr;
+    const int h = div_by(s, f.slots, f.inv_slots), part = s - h * f.slots;
     if (h < H) {
         const int rows = (a.n_q_heads / H) * a.t_q;  // small: the launcher bounds the query
         const char* q = static_cast<const char*>(a.q) + (((int64_t)li * H + h) * rows * d + slot * 8) * EB;
         double acc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-        for (int r0 = part; r0 < rows; r0 += kRows * a.fold_slots) {
+        for (int r0 = part; r0 < rows; r0 += kRows * f.slots) {
             Raw8<QT> raw[kRows];
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 zero_raw(raw[u]);
-                const int row = r0 + u * a.fold_slots;
+                const int row = r0 + u * f.slots;
                 if (row < rows) load_raw(q + (int64_t)row * d * EB, raw[u]);
             }
 #pragma unroll
@@ -271,11 +277,11 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
     __syncthreads();
     double sq = 0.0;
     for (int e = tid; e < HD; e += kFoldThreads) {
-        const int hh = div_by(e, d, a.inv_head_dim), p = e - hh * d;  // position p of head hh
+        const int hh = div_by(e, d, f.inv_head_dim), p = e - hh * d;  // position p of head hh
         double sum = 0.0;
-        for (int w = 0; w < a.fold_slots; ++w) sum += red[(hh * a.fold_slots + w) * d + p];
+        for (int w = 0; w < f.slots; ++w) sum += red[(hh * f.slots + w) * d + p];
         const double qb = sum / (double)((a.n_q_heads / H) * a.t_q);
-        const int i8 = div_by(p, lpr, a.inv_lanes_per_row);
+        const int i8 = div_by(p, lpr, f.inv_lanes_per_row);
         const int ch = hh * d + (p - i8 * lpr) * 8 + i8;
         const int c = ch >> 6, sl = (ch >> 2) & 15, i = ch & 3;
         qbar[(((2 * c + (i >> 1)) * 16 + sl) << 1) + (i & 1)] = qb;  // the order of score_mean_query_kernel
@@ -603,11 +609,11 @@ static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_score_mean_query(const ScoreArgs& args, hipStream_t s) {
-    if (args.n_layers == 0 || args.n_groups == 0) return hipSuccess;
-    ScoreArgs a = args;
+hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
+    if (a.n_layers == 0 || a.n_groups == 0) return hipSuccess;
     const int lpr = a.head_dim / 8;
-    a.fold_slots = (uint32_t)(kFoldThreads / lpr / a.n_kv_heads);
+    FoldSplit f{};
+    f.slots = (uint32_t)(kFoldThreads / lpr / a.n_kv_heads);
     const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
     const int64_t query = (int64_t)a.n_q_heads * a.t_q * a.head_dim;  // elements of a layer
     // Folding inside the score kernel saves a launch (4 us of host time, as much on the device) and costs each
@@ -616,16 +622,16 @@ hipError_t launch_score_mean_query(const ScoreArgs& args, hipStream_t s) {
     // 16.0 us, x 32 14.1 / 16.0; 28 x 256 x 8 14.6 / 16.4; on the line 1 x 1024 x 32 16.1 / 16.2
     // and 8 x 256 x 32 15.6 / 15.8; beyond it 28 x 64 x 32 16.2 / 15.8, 1 x 3600 x 32 18.9 / 17.1.
     constexpr int64_t kFusedWork = 12000000;
-    if (a.fold_slots > 0 && query <= kFusedWork / (blocks + 64)) {
-        a.inv_fold_slots = reciprocal_u32(a.fold_slots);
-        a.inv_lanes_per_row = reciprocal_u32((uint32_t)lpr);
-        a.inv_head_dim = reciprocal_u32((uint32_t)a.head_dim);
+    if (f.slots > 0 && query <= kFusedWork / (blocks + 64)) {
+        f.inv_slots = reciprocal_u32(f.slots);
+        f.inv_lanes_per_row = reciprocal_u32((uint32_t)lpr);
+        f.inv_head_dim = reciprocal_u32((uint32_t)a.head_dim);
         const dim3 grid((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16), a.n_layers), block(kFoldThreads);
         const size_t lds = (size_t)((a.n_kv_heads * a.head_dim + 63) / 64 * 64) * sizeof(double);
         switch (a.q_dtype) {
-            case TOM_F32: score_fold_query_kernel<In_f32><<<grid, block, lds, s>>>(a); break;
-            case TOM_BF16: score_fold_query_kernel<In_bf16><<<grid, block, lds, s>>>(a); break;
-            case TOM_F16: score_fold_query_kernel<In_f16><<<grid, block, lds, s>>>(a); break;
+            case TOM_F32: score_fold_query_kernel<In_f32><<<grid, block, lds, s>>>(a, f); break;
+            case TOM_BF16: score_fold_query_kernel<In_bf16><<<grid, block, lds, s>>>(a, f); break;
+            case TOM_F16: score_fold_query_kernel<In_f16><<<grid, block, lds, s>>>(a, f); break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
