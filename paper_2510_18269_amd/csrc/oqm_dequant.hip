@@ -73,7 +73,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     uint32_t t;
     if constexpr (SELECT > 0) {
         __shared__ uint32_t chosen;
-        __shared__ uint32_t slots[2][SELECT];
+        __shared__ uint32_t slots[2][2 * SELECT];
         if (SELECT == kBlock / 64 || tid < 64 * SELECT) {
             const int lane = (int)(tid & 63u), wave = SELECT == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(tid >> 6));
             uint32_t key[kSelectKeys];

@@ -2,13 +2,15 @@
 // supplement keeps the selected indices in sorted, i.e. temporal, order).
 //
 // Ascending index order (what the retrieval uses) and rows of up to 4096 scores: the row is held
-// in registers and the threshold is found bit by bit with ballots (oqm_select.h).  The launch is
+// in registers and the threshold is found from the top bits down with ballots (oqm_select.h).  The launch is
 // bound by the latency of its serial steps (and by fetching its own code: unrolling 16 keys per
 // lane costs more than the barriers it saves), so rows of up to 256 scores take one wave without
 // any barrier, longer ones the fewest waves that keep a lane at 4 (8 above 1024) keys.  Kernel
 // time at 28 rows, this form against the radix select below: 256 scores 3.6 / 5.6 us, 1024
 // 6.0 / 6.3 us, 3600 8.4 / 10.6 us; one row: 2.5 / 4.6, 4.0 / 5.3, 5.7 / 9.6 us.  At 1024 scores
 // one wave with 16 keys takes 7.6 us; at 4096 four waves with 16 keys 9.7 us against 7.9 us.
+// Only where the k-th score occurs several times is the radix select faster (28 x 1024 scores, each five times over:
+// 6.0 us against 6.9), since it does not end early otherwise.
 //
 // Longer rows, and the best-first order: one workgroup of 1024 threads per row.  The k-th
 // largest score is found by a 4-pass, 8-bit most-significant-digit radix select over
@@ -35,7 +37,7 @@ template <int WAVES, int KEYS>
 __global__ void __launch_bounds__(64 * WAVES)
 topk_ascending_kernel(const float* __restrict__ scores, const int64_t stride, const int n, const int k,
                       const int k_eff, int32_t* __restrict__ idx) {
-    __shared__ uint32_t slots[2][WAVES];
+    __shared__ uint32_t slots[2][2 * WAVES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t* out = idx + (int64_t)blockIdx.x * k;
     if (k_eff == n) {  // everything is chosen
