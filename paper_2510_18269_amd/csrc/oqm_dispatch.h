@@ -1,0 +1,41 @@
+// The rules by which the host side chooses between forms of a kernel that give the same results:
+// plain functions of sizes and addresses, so that the CPU tests can ask them directly.
+#pragma once
+
+#include "oqm_common.h"
+
+namespace oqm {
+
+// Two byte ranges share no memory.
+inline bool apart(const void* a, uint64_t a_bytes, const void* b, uint64_t b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x + a_bytes <= y || y + b_bytes <= x;
+}
+
+// Bytes from the first to the last score of `n_layers` rows.
+inline uint64_t score_span(int64_t stride, int n_layers, int n_groups) {
+    return sizeof(float) * ((uint64_t)(n_layers - 1) * (uint64_t)stride + (uint64_t)n_groups);
+}
+
+// ---- mean-query score: the query is folded inside the score kernel -----------------------
+constexpr int kFoldThreads = 512;
+
+// Row slots per KV head of score_fold_query_kernel, or 0: the fold is a launch of its own.
+// Folding inside the score kernel saves a launch (4 us of host time, as much on the device) and costs each
+// workgroup 0.03 us per 1000 query elements (float64 conversions and sums), more once they
+// share compute units: line at query elements x (workgroups + 64).  Whole question at 28 query heads of 128, fused / separate: 1 layer x 256 groups x 8 tokens 11.7 /
+// 16.0 us, x 32 14.1 / 16.0; 28 x 256 x 8 14.6 / 16.4; on the line 1 x 1024 x 32 16.1 / 16.2
+// and 8 x 256 x 32 15.6 / 15.8; beyond it 28 x 64 x 32 16.2 / 15.8, 1 x 3600 x 32 18.9 / 17.1.
+// Scores that share memory with the query need the separate fold at any size: in one launch some
+// workgroups write scores while others still read the query.
+inline uint32_t fold_slots(const ScoreArgs& a) {
+    constexpr int64_t kFusedWork = 12000000;
+    const uint32_t slots = (uint32_t)(kFoldThreads / (a.head_dim / 8) / a.n_kv_heads);
+    const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
+    const int64_t query = (int64_t)a.n_q_heads * a.t_q * a.head_dim;  // elements of a layer
+    if (query > kFusedWork / (blocks + 64)) return 0;
+    const uint64_t query_bytes = (uint64_t)query * (uint64_t)a.n_layers * (a.q_dtype == TOM_F32 ? 4u : 2u);
+    return apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups)) ? slots : 0u;
+}
+
+}  // namespace oqm

@@ -16,6 +16,7 @@
 // reference up to the final rounding, and the selected indices with them.
 #include "oqm_common.h"
 #include "oqm_device.h"
+#include "oqm_dispatch.h"
 
 namespace oqm {
 namespace {
@@ -135,7 +136,6 @@ __device__ __forceinline__ double row16_sum_f64(double v) {
     return v;
 }
 
-constexpr int kFoldThreads = 512;
 constexpr int kScoreChunks = 8;  // 16-byte key loads per lane that are in flight together
 
 // Dot product and norm of one group's key (its first kScoreChunks pieces already in kx) against the
@@ -611,20 +611,11 @@ static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStr
 
 hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
     if (a.n_layers == 0 || a.n_groups == 0) return hipSuccess;
-    const int lpr = a.head_dim / 8;
     FoldSplit f{};
-    f.slots = (uint32_t)(kFoldThreads / lpr / a.n_kv_heads);
-    const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
-    const int64_t query = (int64_t)a.n_q_heads * a.t_q * a.head_dim;  // elements of a layer
-    // Folding inside the score kernel saves a launch (4 us of host time, as much on the device) and costs each
-    // workgroup 0.03 us per 1000 query elements (float64 conversions and sums), more once they
-    // share compute units: line at query elements x (workgroups + 64).  Whole question at 28 query heads of 128, fused / separate: 1 layer x 256 groups x 8 tokens 11.7 /
-    // 16.0 us, x 32 14.1 / 16.0; 28 x 256 x 8 14.6 / 16.4; on the line 1 x 1024 x 32 16.1 / 16.2
-    // and 8 x 256 x 32 15.6 / 15.8; beyond it 28 x 64 x 32 16.2 / 15.8, 1 x 3600 x 32 18.9 / 17.1.
-    constexpr int64_t kFusedWork = 12000000;
-    if (f.slots > 0 && query <= kFusedWork / (blocks + 64)) {
+    f.slots = fold_slots(a);
+    if (f.slots > 0) {
         f.inv_slots = reciprocal_u32(f.slots);
-        f.inv_lanes_per_row = reciprocal_u32((uint32_t)lpr);
+        f.inv_lanes_per_row = reciprocal_u32((uint32_t)a.head_dim / 8u);
         f.inv_head_dim = reciprocal_u32((uint32_t)a.head_dim);
         const dim3 grid((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16), a.n_layers), block(kFoldThreads);
         const size_t lds = (size_t)((a.n_kv_heads * a.head_dim + 63) / 64 * 64) * sizeof(double);

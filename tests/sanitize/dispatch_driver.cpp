@@ -1,0 +1,59 @@
+// Driver for the host-side rules of csrc/oqm_dispatch.h, built for the host with
+// -fsanitize=address,undefined by tests/test_sanitizers.py.  Both sides of every limit, and buffers that
+// overlap, adjoin or lie apart.  No device is touched: the addresses are fakes.  Exit status 0 = clean.
+#include <cstdio>
+
+#include "oqm_dispatch.h"
+
+using namespace oqm;
+
+static int failures = 0;
+#define CHECK(cond)                                                          \
+    do {                                                                     \
+        if (!(cond)) {                                                       \
+            std::fprintf(stderr, "line %d: %s does not hold\n", __LINE__, #cond); \
+            ++failures;                                                      \
+        }                                                                    \
+    } while (0)
+
+static char* at(uint64_t address) { return reinterpret_cast<char*>((uintptr_t)address); }
+
+static void fold() {
+    ScoreArgs a{};
+    a.n_kv_heads = 4, a.n_q_heads = 28, a.head_dim = 128, a.n_layers = 2, a.t_q = 8, a.n_groups = 100;
+    a.score_stride = 112, a.q_dtype = TOM_BF16;
+    const uint64_t q_bytes = 2ull * 28 * 8 * 128 * 2, s_bytes = (112 + 100) * 4;
+    a.q = at(1 << 20);
+    auto slots_with_scores_at = [&](uint64_t address) {
+        a.scores = reinterpret_cast<float*>(at(address));
+        return fold_slots(a);
+    };
+    const uint64_t q = 1 << 20;
+    CHECK(slots_with_scores_at(1 << 24) == 8);        // 512 threads, 16 lanes per row, 4 heads
+    CHECK(slots_with_scores_at(q + q_bytes) == 8);    // adjoining, behind
+    CHECK(slots_with_scores_at(q - s_bytes) == 8);    // and in front
+    CHECK(slots_with_scores_at(q) == 0);
+    CHECK(slots_with_scores_at(q + q_bytes - 4) == 0);
+    CHECK(slots_with_scores_at(q - s_bytes + 4) == 0);
+    CHECK(slots_with_scores_at(q + q_bytes / 2) == 0);
+    a.q_dtype = TOM_F32;                               // twice the bytes
+    CHECK(slots_with_scores_at(q + q_bytes) == 0);
+    CHECK(slots_with_scores_at(q + 2 * q_bytes) == 8);
+    // the line: 28 * 128 query elements a token, 8 workgroups a layer at 256 groups
+    a.scores = reinterpret_cast<float*>(at(1 << 28));
+    a.n_layers = 8, a.n_groups = 256, a.score_stride = 256, a.t_q = 26;
+    CHECK(fold_slots(a) == 8);
+    a.t_q = 27;
+    CHECK(fold_slots(a) == 0);
+    a.t_q = 1, a.head_dim = 256, a.n_kv_heads = a.n_q_heads = 16;
+    CHECK(fold_slots(a) == 1);
+    a.n_kv_heads = a.n_q_heads = 17;                   // no row slot left for the last head
+    CHECK(fold_slots(a) == 0);
+}
+
+int main() {
+    fold();
+    if (failures) { std::fprintf(stderr, "%d failures\n", failures); return 2; }
+    std::printf("dispatch driver: clean\n");
+    return 0;
+}

@@ -15,7 +15,7 @@ def oqm():
     return m
 
 
-def _check(oqm, L, H, r, d, T, tq, dt, cosine, seed):
+def _check(oqm, L, H, r, d, T, tq, dt, cosine, seed, scores_in_q=None):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     code = {"bf16": oqm.TOM_BF16, "f16": oqm.TOM_F16, "f32": oqm.TOM_F32}[dt]
     cfg = oqm.make_config(L, H, H * r, d, 1, 8, T, in_dtype=code, out_dtype=code,
@@ -27,10 +27,16 @@ def _check(oqm, L, H, r, d, T, tq, dt, cosine, seed):
         q = torch.randn((L, H * r, tq, d), generator=gen, device="cuda").to(TDT[dt])
         ws = torch.empty(oqm.tom_oqm_score_workspace_bytes(mem.handle, L, tq, oqm.TOM_SCORE_MEAN_QUERY, False),
                          dtype=torch.uint8, device="cuda")
-        scores = torch.full((L, T + 3), 7.0, device="cuda")
+        qb = q.double().view(L, H, r * tq, d).mean(2).reshape(L, 1, H * d).cpu()
+        if scores_in_q is None:
+            scores = torch.full((L, T + 3), 7.0, device="cuda")
+        else:
+            memory = q.view(-1).view(torch.float32)
+            first = round(scores_in_q * (memory.numel() - L * (T + 3))) // 4 * 4
+            scores = memory[first:first + L * (T + 3)].view(L, T + 3)
+            between = scores[:, T:].clone()
         oqm.tom_oqm_score_groups(mem.handle, 0, L, q, tq, scores, T + 3, None, oqm.TOM_SCORE_MEAN_QUERY, ws)
         keys = mem.keys.double().view(L, T, H * d).cpu()
-        qb = q.double().view(L, H, r * tq, d).mean(2).reshape(L, 1, H * d).cpu()
         want = (qb @ keys.transpose(1, 2))[:, 0]
         size = qb.norm(dim=-1) * keys.norm(dim=-1)
         # the mean's own terms are up to sqrt(r * T_q) larger than the mean: bound them by |q| / sqrt(r T_q) = 1
@@ -39,7 +45,7 @@ def _check(oqm, L, H, r, d, T, tq, dt, cosine, seed):
             want, slack = want / size.clamp_min(1e-24), slack / size.clamp_min(1e-24)
         got = scores[:, :T].double().cpu()
         assert ((got - want).abs() <= want.abs() * 2.0 ** -24 + slack).all()   # one rounding to float32
-        assert (scores[:, T:] == 7.0).all()
+        assert torch.equal(scores[:, T:], torch.full_like(scores[:, T:], 7.0) if scores_in_q is None else between)
     finally:
         mem.close()
 
@@ -59,3 +65,11 @@ def test_head_shapes(oqm, H, r, d):
 def test_both_sides_of_the_rule(oqm, L, T, tqs, dt):
     for tq in tqs:
         _check(oqm, L, 4, 7, 128, T, tq, dt, True, 1000 + tq)
+
+
+# scores written into the memory of the query: the query has to be consumed before the first of them
+@pytest.mark.parametrize("where", (0.0, 0.5, 1.0))
+@pytest.mark.parametrize("dt", ("bf16", "f32"))
+def test_scores_in_the_memory_of_the_query(oqm, dt, where):
+    for L, T, tq in ((1, 1000, 8), (2, 333, 16), (8, 256, 8)):
+        _check(oqm, L, 4, 7, 128, T, tq, dt, True, 2000 + tq, scores_in_q=where)
