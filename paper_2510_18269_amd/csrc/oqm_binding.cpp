@@ -18,7 +18,7 @@
 
 namespace {
 
-PyObject *g_raise, *g_argument_error, *g_is_initialized, *g_get_device, *g_get_raw_stream, *g_slow_stream;
+PyObject *g_raise, *g_argument_error, *g_void_p, *g_is_initialized, *g_get_device, *g_get_raw_stream, *g_slow_stream;
 PyObject *s_is_cuda, *s_data_ptr, *s_numel, *s_element_size, *s_stride, *s_cuda_stream;
 
 // What ctypes does with c_int32 / c_int64: any Python int, truncated; nothing else.
@@ -45,8 +45,9 @@ bool method_i64(PyObject* o, PyObject* name, int64_t& out) {
     return ok;
 }
 
-// None, a raw device pointer, or a tensor on the device.
-bool to_ptr(PyObject* o, void*& out) {
+// What ctypes does with c_void_p: None, an int, or (through the registered callable) one of its own pointer
+// objects.  A handle is never anything else: a tensor's address must not be taken for one.
+bool to_void_p(PyObject* o, void*& out) {
     int64_t v = 0;
     if (o == Py_None) {
         out = nullptr;
@@ -55,31 +56,51 @@ bool to_ptr(PyObject* o, void*& out) {
     if (PyLong_Check(o)) {
         if (!to_i64(o, v)) return false;
     } else {
-        PyObject* c = PyObject_GetAttr(o, s_is_cuda);
-        if (!c) return false;
-        const int on_device = PyObject_IsTrue(c);
-        Py_DECREF(c);
-        if (on_device < 0) return false;
-        if (!on_device) {
-            PyErr_SetString(PyExc_AssertionError, "device tensor expected");
-            return false;
-        }
-        if (!method_i64(o, s_data_ptr, v)) return false;
+        PyObject* r = PyObject_CallOneArg(g_void_p, o);
+        if (!r) return false;
+        const bool ok = to_i64(r, v);
+        Py_DECREF(r);
+        if (!ok) return false;
     }
     out = reinterpret_cast<void*>((uintptr_t)v);
     return true;
 }
+bool to_handle(PyObject* o, tom_oqm_t*& out) {
+    void* p;
+    if (!to_void_p(o, p)) return false;
+    out = static_cast<tom_oqm_t*>(p);
+    return true;
+}
+
+// None, a raw device pointer, or a tensor on the device.
+bool to_ptr(PyObject* o, void*& out) {
+    if (o == Py_None || PyLong_Check(o)) return to_void_p(o, out);
+    PyObject* c = PyObject_GetAttr(o, s_is_cuda);
+    if (!c) return false;
+    const int on_device = PyObject_IsTrue(c);
+    Py_DECREF(c);
+    if (on_device < 0) return false;
+    if (!on_device) {
+        PyErr_SetString(PyExc_AssertionError, "device tensor expected");
+        return false;
+    }
+    PyObject* r = PyObject_CallMethodNoArgs(o, s_data_ptr);
+    if (!r) return false;
+    const bool ok = to_void_p(r, out);
+    Py_DECREF(r);
+    return ok;
+}
 
 // None: the current stream of the current device; else a raw handle or an object with one.
 bool to_stream(PyObject* o, void*& out) {
-    int64_t v = 0;
+    if (PyLong_Check(o)) return to_void_p(o, out);
+    PyObject* r;
     if (o == Py_None) {
         PyObject* up = PyObject_CallNoArgs(g_is_initialized);
         if (!up) return false;
         const int ready = PyObject_IsTrue(up);
         Py_DECREF(up);
         if (ready < 0) return false;
-        PyObject* r;
         if (ready) {
             PyObject* dev = PyObject_CallNoArgs(g_get_device);
             if (!dev) return false;
@@ -88,21 +109,13 @@ bool to_stream(PyObject* o, void*& out) {
         } else {
             r = PyObject_CallNoArgs(g_slow_stream);  // initialises the device, or finds that there is none
         }
-        if (!r) return false;
-        const bool ok = to_i64(r, v);
-        Py_DECREF(r);
-        if (!ok) return false;
-    } else if (PyLong_Check(o)) {
-        if (!to_i64(o, v)) return false;
     } else {
-        PyObject* r = PyObject_GetAttr(o, s_cuda_stream);
-        if (!r) return false;
-        const bool ok = to_i64(r, v);
-        Py_DECREF(r);
-        if (!ok) return false;
+        r = PyObject_GetAttr(o, s_cuda_stream);
     }
-    out = reinterpret_cast<void*>((uintptr_t)v);
-    return true;
+    if (!r) return false;
+    const bool ok = to_void_p(r, out);
+    Py_DECREF(r);
+    return ok;
 }
 
 // Workspace tensor (or None): pointer and size in bytes.
@@ -175,25 +188,26 @@ bool to_strides(PyObject* o, PyObject* k, PyObject* v, int64_t (&out)[4]) {
 }
 
 PyObject* set_num_groups(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    void* h;
+    tom_oqm_t* h;
     int32_t groups;
-    if (!arity(n, 2) || !to_ptr(a[0], h) || !to_i32(a[1], groups)) return nullptr;
-    return finish_none(tom_oqm_set_num_groups(static_cast<tom_oqm_t*>(h), groups));
+    if (!arity(n, 2) || !to_handle(a[0], h) || !to_i32(a[1], groups)) return nullptr;
+    return finish_none(tom_oqm_set_num_groups(h, groups));
 }
 
 // h, layer0, n_layers, n_frames, k, v, k_for_summary, strides, commit, stream -> first group
 PyObject* quantize_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    void *h, *k, *v, *ks, *stream;
+    tom_oqm_t* h;
+    void *k, *v, *ks, *stream;
     int32_t layer0, n_layers, n_frames, first = -1;
     int64_t strides[4];
-    if (!arity(n, 10) || !to_strides(a[7], a[4], a[5], strides) || !to_ptr(a[0], h) || !to_i32(a[1], layer0) ||
+    if (!arity(n, 10) || !to_strides(a[7], a[4], a[5], strides) || !to_handle(a[0], h) || !to_i32(a[1], layer0) ||
         !to_i32(a[2], n_layers) || !to_i32(a[3], n_frames) || !to_ptr(a[4], k) || !to_ptr(a[5], v) || !to_ptr(a[6], ks))
         return nullptr;
     const int commit = PyObject_IsTrue(a[8]);
     if (commit < 0 || !to_stream(a[9], stream)) return nullptr;
     int st;
     Py_BEGIN_ALLOW_THREADS
-    st = tom_oqm_quantize_append(static_cast<tom_oqm_t*>(h), layer0, n_layers, n_frames, k, v, ks, strides, commit,
+    st = tom_oqm_quantize_append(h, layer0, n_layers, n_frames, k, v, ks, strides, commit,
                                  stream, &first);
     Py_END_ALLOW_THREADS
     return finish(st, PyLong_FromLong(first));
@@ -201,17 +215,18 @@ PyObject* quantize_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // h, layer0, n_layers, q, q_dtype, t_q, scores, score_stride, token_scores, path, workspace, stream
 PyObject* score_groups(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    void *h, *q, *scores, *tokens, *ws, *stream;
+    tom_oqm_t* h;
+    void *q, *scores, *tokens, *ws, *stream;
     int32_t layer0, n_layers, q_dtype, t_q, path;
     int64_t stride;
     size_t ws_bytes;
-    if (!arity(n, 12) || !to_ptr(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], q) ||
+    if (!arity(n, 12) || !to_handle(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], q) ||
         !to_i32(a[4], q_dtype) || !to_i32(a[5], t_q) || !to_ptr(a[6], scores) || !to_i64(a[7], stride) ||
         !to_ptr(a[8], tokens) || !to_i32(a[9], path) || !to_workspace(a[10], ws, ws_bytes) || !to_stream(a[11], stream))
         return nullptr;
     int st;
     Py_BEGIN_ALLOW_THREADS
-    st = tom_oqm_score_groups(static_cast<tom_oqm_t*>(h), layer0, n_layers, q, q_dtype, t_q,
+    st = tom_oqm_score_groups(h, layer0, n_layers, q, q_dtype, t_q,
                               static_cast<float*>(scores), stride, static_cast<float*>(tokens), path, ws, ws_bytes,
                               stream);
     Py_END_ALLOW_THREADS
@@ -237,14 +252,15 @@ PyObject* topk(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // h, layer0, n_layers, idx, k, k_eff, k_out, v_out, stream
 PyObject* dequant_gather(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    void *h, *idx, *ko, *vo, *stream;
+    tom_oqm_t* h;
+    void *idx, *ko, *vo, *stream;
     int32_t layer0, n_layers, k, k_eff;
-    if (!arity(n, 9) || !to_ptr(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], idx) ||
+    if (!arity(n, 9) || !to_handle(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], idx) ||
         !to_i32(a[4], k) || !to_i32(a[5], k_eff) || !to_ptr(a[6], ko) || !to_ptr(a[7], vo) || !to_stream(a[8], stream))
         return nullptr;
     int st;
     Py_BEGIN_ALLOW_THREADS
-    st = tom_oqm_dequant_gather(static_cast<tom_oqm_t*>(h), layer0, n_layers, static_cast<int32_t*>(idx), k, k_eff, ko,
+    st = tom_oqm_dequant_gather(h, layer0, n_layers, static_cast<int32_t*>(idx), k, k_eff, ko,
                                 vo, stream);
     Py_END_ALLOW_THREADS
     return finish_none(st);
@@ -252,15 +268,16 @@ PyObject* dequant_gather(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // h, layer0, n_layers, idx, k, k_eff, prefix_rows, sys_k, sys_v, k_out, v_out, stream
 PyObject* assemble_active(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    void *h, *idx, *sk, *sv, *ko, *vo, *stream;
+    tom_oqm_t* h;
+    void *idx, *sk, *sv, *ko, *vo, *stream;
     int32_t layer0, n_layers, k, k_eff, prefix;
-    if (!arity(n, 12) || !to_ptr(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], idx) ||
+    if (!arity(n, 12) || !to_handle(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], idx) ||
         !to_i32(a[4], k) || !to_i32(a[5], k_eff) || !to_i32(a[6], prefix) || !to_ptr(a[7], sk) || !to_ptr(a[8], sv) ||
         !to_ptr(a[9], ko) || !to_ptr(a[10], vo) || !to_stream(a[11], stream))
         return nullptr;
     int st;
     Py_BEGIN_ALLOW_THREADS
-    st = tom_oqm_assemble_active(static_cast<tom_oqm_t*>(h), layer0, n_layers, static_cast<int32_t*>(idx), k, k_eff,
+    st = tom_oqm_assemble_active(h, layer0, n_layers, static_cast<int32_t*>(idx), k, k_eff,
                                  prefix, sk, sv, ko, vo, stream);
     Py_END_ALLOW_THREADS
     return finish_none(st);
@@ -269,11 +286,12 @@ PyObject* assemble_active(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // h, layer0, n_layers, q, q_dtype, t_q, k, path, scores, score_stride, idx, prefix_rows, sys_k, sys_v, k_out, v_out,
 // [workspace,] stream -> k_eff; without a workspace the library's static scratch array is used
 PyObject* retrieve_with(PyObject* const* a, bool own_workspace) {
-    void *h, *q, *scores, *idx, *sk, *sv, *ko, *vo, *ws = nullptr, *stream;
+    tom_oqm_t* h;
+    void *q, *scores, *idx, *sk, *sv, *ko, *vo, *ws = nullptr, *stream;
     int32_t layer0, n_layers, q_dtype, t_q, k, path, prefix, k_eff = -1;
     int64_t stride;
     size_t ws_bytes = 0;
-    if (!to_ptr(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], q) ||
+    if (!to_handle(a[0], h) || !to_i32(a[1], layer0) || !to_i32(a[2], n_layers) || !to_ptr(a[3], q) ||
         !to_i32(a[4], q_dtype) || !to_i32(a[5], t_q) || !to_i32(a[6], k) || !to_i32(a[7], path) ||
         !to_ptr(a[8], scores) || !to_i64(a[9], stride) || !to_ptr(a[10], idx) || !to_i32(a[11], prefix) ||
         !to_ptr(a[12], sk) || !to_ptr(a[13], sv) || !to_ptr(a[14], ko) || !to_ptr(a[15], vo) ||
@@ -282,11 +300,11 @@ PyObject* retrieve_with(PyObject* const* a, bool own_workspace) {
     int st;
     Py_BEGIN_ALLOW_THREADS
     if (own_workspace)
-        st = tom_oqm_retrieve(static_cast<tom_oqm_t*>(h), layer0, n_layers, q, q_dtype, t_q, k, path,
+        st = tom_oqm_retrieve(h, layer0, n_layers, q, q_dtype, t_q, k, path,
                               static_cast<float*>(scores), stride, static_cast<int32_t*>(idx), prefix, sk, sv, ko, vo,
                               ws, ws_bytes, &k_eff, stream);
     else
-        st = tom_oqm_retrieve_noalloc(static_cast<tom_oqm_t*>(h), layer0, n_layers, q, q_dtype, t_q, k, path,
+        st = tom_oqm_retrieve_noalloc(h, layer0, n_layers, q, q_dtype, t_q, k, path,
                                       static_cast<float*>(scores), stride, static_cast<int32_t*>(idx), prefix, sk, sv,
                                       ko, vo, &k_eff, stream);
     Py_END_ALLOW_THREADS
@@ -301,10 +319,10 @@ PyObject* retrieve_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // The Python callables that the functions above need, in the order of the globals.
 PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (!arity(n, 6)) return nullptr;
-    PyObject** const slots[6] = {&g_raise, &g_argument_error, &g_is_initialized, &g_get_device, &g_get_raw_stream,
-                                 &g_slow_stream};
-    for (int i = 0; i < 6; ++i) {
+    if (!arity(n, 7)) return nullptr;
+    PyObject** const slots[7] = {&g_raise, &g_argument_error, &g_void_p, &g_is_initialized, &g_get_device,
+                                 &g_get_raw_stream, &g_slow_stream};
+    for (int i = 0; i < 7; ++i) {
         Py_INCREF(a[i]);
         Py_XSETREF(*slots[i], a[i]);
     }

@@ -124,6 +124,11 @@ def _raise(status: int) -> None:
     raise TomError(status, tom_last_error())
 
 
+def _void_p(o) -> int:
+    """The address in anything that ctypes takes for a c_void_p; ArgumentError otherwise."""
+    return C.cast(o, C.c_void_p).value or 0
+
+
 def _first_stream() -> int:
     """The current stream where the device has not been initialised yet."""
     # without a GPU only argument validation can run; it never reaches a launch
@@ -134,7 +139,8 @@ def _no_device(*_) -> int:
     raise RuntimeError("this build of PyTorch has no device support")
 
 
-_native.setup(_raise, C.ArgumentError, torch.cuda.is_initialized, getattr(torch._C, "_cuda_getDevice", _no_device),
+_native.setup(_raise, C.ArgumentError, _void_p, torch.cuda.is_initialized,
+              getattr(torch._C, "_cuda_getDevice", _no_device),
               getattr(torch._C, "_cuda_getCurrentRawStream", _no_device), _first_stream)
 
 

@@ -53,6 +53,41 @@ def test_integers_are_truncated_like_c_int32(store):
         oqm.tom_oqm_set_num_groups(None, 0)
 
 
+class AsParameter:
+    def __init__(self, value): self._as_parameter_ = value
+
+
+def test_handles_are_those_of_c_void_p(store):
+    """Of a NULL-able pointer argument ctypes takes an int, None and its own pointer objects; nothing that merely
+    has an address: a tensor's memory must never be taken for a handle."""
+    oqm, h = store
+    calls = (lambda x, **kw: oqm.tom_oqm_set_num_groups(x, 3),
+             lambda x, **kw: oqm.tom_oqm_quantize_append(x, 0, 2, 0, 0x1000, 0x1000, strides=(1, 1, 1, 64), **kw),
+             lambda x, **kw: oqm.tom_oqm_score_groups(x, 0, 0, 0x1000, 1, 0x1000, 8, q_dtype=oqm.TOM_F32, **kw),
+             lambda x, **kw: oqm.tom_oqm_dequant_gather(x, 0, 0, 0x1000, 1, 1, 0x1000, 0x1000, **kw),
+             lambda x, **kw: oqm.tom_oqm_assemble_active(x, 0, 0, 0x1000, 1, 1, 0, None, None, 0x1000, 0x1000, **kw),
+             lambda x, **kw: oqm.tom_oqm_retrieve(x, 0, 0, 0x1000, 1, 1, 0x1000, 8, 0x1000, 0x1000, 0x1000, None,
+                                                  q_dtype=oqm.TOM_F32, **kw),
+             lambda x, **kw: oqm.tom_oqm_retrieve_noalloc(x, 0, 0, 0x1000, 1, 1, 0x1000, 8, 0x1000, 0x1000, 0x1000,
+                                                          q_dtype=oqm.TOM_F32, **kw))
+    stand_in = FakeTensor()
+    stand_in.data_ptr = lambda: h      # were it read, it would be a valid handle
+    for call in calls:
+        for good in (h, C.c_void_p(h), C.cast(h, C.POINTER(C.c_char)), AsParameter(h), AsParameter(C.c_void_p(h))):
+            call(good)
+        for null in (None, C.c_void_p()):
+            with pytest.raises(oqm.TomError, match="handle is NULL"):
+                call(null)
+        for bad in (stand_in, torch.tensor(h), 1.0, C.c_int64(h), object(), AsParameter(stand_in)):
+            with pytest.raises(C.ArgumentError):
+                call(bad)
+    for call in calls[1:]:             # the same holds of the stream's address
+        for stream in (0, None, C.c_void_p(), AsParameter(0)):
+            call(h, stream=type("Stream", (), {"cuda_stream": stream}))
+        with pytest.raises(C.ArgumentError):
+            call(h, stream=type("Stream", (), {"cuda_stream": 1.0}))
+
+
 def test_strides_of_tensors_and_of_raw_pointers(store):
     oqm, h = store
     good = (2 * 2 * 4 * 64, 2 * 4 * 64, 4 * 64, 64, 1)
