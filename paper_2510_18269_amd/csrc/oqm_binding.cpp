@@ -18,21 +18,28 @@
 
 namespace {
 
-PyObject *g_raise, *g_argument_error, *g_void_p, *g_is_initialized, *g_get_device, *g_get_raw_stream, *g_slow_stream;
+PyObject *g_raise, *g_int32, *g_int64, *g_void_p, *g_is_initialized, *g_get_device, *g_get_raw_stream, *g_slow_stream;
 PyObject *s_is_cuda, *s_data_ptr, *s_numel, *s_element_size, *s_stride, *s_cuda_stream;
 
-// What ctypes does with c_int32 / c_int64: any Python int, truncated; nothing else.
-bool to_i64(PyObject* o, int64_t& out) {
-    if (!PyLong_Check(o)) {
-        PyErr_Format(g_argument_error, "int expected instead of %s instance", Py_TYPE(o)->tp_name);
-        return false;
+// What ctypes does with c_int32 / c_int64: a Python int is truncated; `slow`, a callable registered by oqm.py, makes
+// one of whatever else ctypes takes (__index__, its own integer objects) or raises its error.
+bool to_int(PyObject* o, PyObject* slow, int64_t& out) {
+    if (PyLong_Check(o)) {
+        out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
+        return true;
     }
-    out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
-    return true;
+    PyObject* r = PyObject_CallOneArg(slow, o);
+    if (!r) return false;
+    const bool ok = PyLong_Check(r);
+    if (ok) out = (int64_t)PyLong_AsUnsignedLongLongMask(r);
+    else PyErr_SetString(PyExc_SystemError, "the registered conversion did not return an int");
+    Py_DECREF(r);
+    return ok;
 }
+bool to_i64(PyObject* o, int64_t& out) { return to_int(o, g_int64, out); }
 bool to_i32(PyObject* o, int32_t& out) {
     int64_t v;
-    if (!to_i64(o, v)) return false;
+    if (!to_int(o, g_int32, v)) return false;
     out = (int32_t)(uint32_t)v;
     return true;
 }
@@ -49,19 +56,7 @@ bool method_i64(PyObject* o, PyObject* name, int64_t& out) {
 // objects.  A handle is never anything else: a tensor's address must not be taken for one.
 bool to_void_p(PyObject* o, void*& out) {
     int64_t v = 0;
-    if (o == Py_None) {
-        out = nullptr;
-        return true;
-    }
-    if (PyLong_Check(o)) {
-        if (!to_i64(o, v)) return false;
-    } else {
-        PyObject* r = PyObject_CallOneArg(g_void_p, o);
-        if (!r) return false;
-        const bool ok = to_i64(r, v);
-        Py_DECREF(r);
-        if (!ok) return false;
-    }
+    if (o != Py_None && !to_int(o, g_void_p, v)) return false;
     out = reinterpret_cast<void*>((uintptr_t)v);
     return true;
 }
@@ -154,11 +149,20 @@ PyObject* finish_none(int status) {
     return finish(status, Py_None);
 }
 
-// strides: four ints, or None for 5-d tensors k and v of equal strides with contiguous channels.
+// The strides of a tensor as a new tuple.
+PyObject* strides_of(PyObject* tensor) {
+    PyObject* s = PyObject_CallMethodNoArgs(tensor, s_stride);
+    if (!s || PyTuple_CheckExact(s)) return s;
+    PyObject* t = PySequence_Tuple(s);
+    Py_DECREF(s);
+    return t;
+}
+
+// strides: a tuple of four, or None for 5-d tensors k and v of equal strides with contiguous channels.
 bool to_strides(PyObject* o, PyObject* k, PyObject* v, int64_t (&out)[4]) {
     PyObject* t = o;
     if (o == Py_None) {
-        t = PyObject_CallMethodNoArgs(k, s_stride);
+        t = strides_of(k);
         if (!t) return false;
     } else {
         Py_INCREF(t);
@@ -168,7 +172,7 @@ bool to_strides(PyObject* o, PyObject* k, PyObject* v, int64_t (&out)[4]) {
         int64_t channel = 0;
         ok = to_i64(PyTuple_GET_ITEM(t, 4), channel) && channel == 1;
         if (ok) {
-            PyObject* vs = PyObject_CallMethodNoArgs(v, s_stride);
+            PyObject* vs = strides_of(v);
             const int same = vs ? PyObject_RichCompareBool(vs, t, Py_EQ) : -1;
             Py_XDECREF(vs);
             if (same == 0) PyErr_SetString(PyExc_AssertionError, "k and v must have the same strides");
@@ -319,10 +323,10 @@ PyObject* retrieve_noalloc(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // The Python callables that the functions above need, in the order of the globals.
 PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (!arity(n, 7)) return nullptr;
-    PyObject** const slots[7] = {&g_raise, &g_argument_error, &g_void_p, &g_is_initialized, &g_get_device,
-                                 &g_get_raw_stream, &g_slow_stream};
-    for (int i = 0; i < 7; ++i) {
+    if (!arity(n, 8)) return nullptr;
+    PyObject** const slots[8] = {&g_raise, &g_int32, &g_int64, &g_void_p, &g_is_initialized, &g_get_device, &g_get_raw_stream,
+                                 &g_slow_stream};
+    for (int i = 0; i < 8; ++i) {
         Py_INCREF(a[i]);
         Py_XSETREF(*slots[i], a[i]);
     }

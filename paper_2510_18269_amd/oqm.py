@@ -124,6 +124,20 @@ def _raise(status: int) -> None:
     raise TomError(status, tom_last_error())
 
 
+def _integer(ctype):
+    """Conversion of an argument that is not a Python int, as the ctypes prototype `ctype` would do it."""
+    def convert(o) -> int:
+        if isinstance(o, ctype):
+            return o.value
+        try:
+            return ctype(o).value
+        except Exception:
+            if not hasattr(o, "_as_parameter_"):
+                raise C.ArgumentError(f"int expected instead of {type(o).__name__} instance") from None
+        return convert(o._as_parameter_)
+    return convert
+
+
 def _void_p(o) -> int:
     """The address in anything that ctypes takes for a c_void_p; ArgumentError otherwise."""
     return C.cast(o, C.c_void_p).value or 0
@@ -139,7 +153,7 @@ def _no_device(*_) -> int:
     raise RuntimeError("this build of PyTorch has no device support")
 
 
-_native.setup(_raise, C.ArgumentError, _void_p, torch.cuda.is_initialized,
+_native.setup(_raise, _integer(C.c_int32), _integer(C.c_int64), _void_p, torch.cuda.is_initialized,
               getattr(torch._C, "_cuda_getDevice", _no_device),
               getattr(torch._C, "_cuda_getCurrentRawStream", _no_device), _first_stream)
 

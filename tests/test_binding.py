@@ -2,6 +2,7 @@
 prototypes of the same functions do.  No GPU: every call ends in the library's validation."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -57,6 +58,38 @@ class AsParameter:
     def __init__(self, value): self._as_parameter_ = value
 
 
+class Index:
+    def __init__(self, value): self.value = value
+    def __index__(self): return self.value
+
+
+def test_integers_of_other_types(store):
+    """Whatever has __index__, and the ctypes integer of the parameter's own type; no floats."""
+    oqm, h = store
+    kinds = (np.int32, np.int64, np.uint8, np.array, torch.tensor, Index, lambda v: torch.tensor([v]))
+    for kind in (*kinds, C.c_int32, lambda v: AsParameter(v), lambda v: AsParameter(C.c_int32(v))):
+        oqm.tom_oqm_set_num_groups(h, kind(5))
+        assert oqm.tom_oqm_num_groups(h) == 5
+        assert oqm.tom_oqm_topk(0, 8, 0, 8, kind(3), 0) == 3
+        assert oqm.tom_oqm_quantize_append(h, kind(0), kind(2), kind(0), 0x1000, 0x1000, strides=(1, 1, 1, 64)) == 5
+    for kind in (*kinds, C.c_int64):      # the 64-bit stride of the scores
+        with pytest.raises(oqm.TomError, match="score_stride < n_groups"):
+            oqm.tom_oqm_topk(0, kind(7), 0, 8, 3, 0)
+        assert oqm.tom_oqm_topk(0, kind(8), 0, 8, 3, 0) == 3
+    oqm.tom_oqm_set_num_groups(h, Index((1 << 32) + 2))
+    assert oqm.tom_oqm_num_groups(h) == 2
+    need = oqm.tom_oqm_score_workspace_bytes(h, 2, 1)
+    short = FakeTensor(numel=np.int64(need - 1))
+    with pytest.raises(oqm.TomError, match=f"{need} bytes needed, {need - 1} given"):
+        oqm.tom_oqm_score_groups(h, 0, np.int32(2), 0x1000, np.int64(1), 0x1000, 8, workspace=short, q_dtype=np.int8(0))
+    for bad in (np.float32(3), torch.tensor(3.0), C.c_int64(3), AsParameter(3.0), object()):
+        with pytest.raises(C.ArgumentError):
+            oqm.tom_oqm_topk(0, 8, 0, 8, bad, 0)
+    for bad in (3.0, np.float64(8), C.c_int32(8)):
+        with pytest.raises(C.ArgumentError):
+            oqm.tom_oqm_topk(0, bad, 0, 8, 3, 0)
+
+
 def test_handles_are_those_of_c_void_p(store):
     """Of a NULL-able pointer argument ctypes takes an int, None and its own pointer objects; nothing that merely
     has an address: a tensor's memory must never be taken for a handle."""
@@ -106,6 +139,8 @@ def test_strides_of_tensors_and_of_raw_pointers(store):
     with pytest.raises(IndexError):
         oqm.tom_oqm_quantize_append(h, 0, 2, 1, 0x1000, 0x1000, strides=(1, 2, 3, 4, 5))
     assert oqm.tom_oqm_quantize_append(h, 0, 2, 0, FakeTensor(good), FakeTensor(good)) == 0
+    as_list = [np.int64(s) for s in good]
+    assert oqm.tom_oqm_quantize_append(h, 0, 2, 0, FakeTensor(as_list), FakeTensor(good)) == 0
 
 
 def test_workspace_size_is_that_of_the_tensor(store):
