@@ -1,6 +1,9 @@
 """The native argument marshalling (csrc/oqm_binding.cpp) takes and refuses what the ctypes
 prototypes of the same functions do.  No GPU: every call ends in the library's validation."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -151,3 +154,19 @@ def test_workspace_size_is_that_of_the_tensor(store):
         oqm.tom_oqm_score_groups(h, 0, 2, 0x1000, 1, 0x1000, 8, workspace=FakeTensor(numel=need - 1), q_dtype=oqm.TOM_F32)
     with pytest.raises(oqm.TomError, match="0 given"):
         oqm.tom_oqm_score_groups(h, 0, 2, 0x1000, 1, 0x1000, 8, q_dtype=oqm.TOM_F32)
+
+
+def test_calls_reach_the_library_beside_the_binding(tmp_path):
+    """Another libtom_oqm.so on the loader's path is not the one that the handles come from."""
+    calls = ("set_num_groups", "quantize_append", "score_groups", "topk", "dequant_gather", "assemble_active", "retrieve",
+             "retrieve_noalloc")
+    (tmp_path / "other.c").write_text("".join(f"int tom_oqm_{c}() {{ return 42; }}\n" for c in calls))
+    subprocess.run(["gcc", "-w", "-shared", "-fPIC", str(tmp_path / "other.c"), "-o", str(tmp_path / "libtom_oqm.so")], check=True)
+    code = ("from paper_2510_18269_amd import oqm\n"
+            "h = oqm.tom_oqm_create(oqm.make_config(2, 2, 4, 64, 4, 32, 8))\n"
+            "oqm.tom_oqm_set_num_groups(h, 3)\n"
+            "print(oqm.tom_oqm_num_groups(h))")
+    path = os.pathsep.join([str(tmp_path), *filter(None, [os.environ.get("LD_LIBRARY_PATH")])])
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, LD_LIBRARY_PATH=path), capture_output=True, text=True,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.stdout.strip() == "3", r.stderr
