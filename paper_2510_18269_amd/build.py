@@ -12,7 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libtom_oqm.so")
 OBJ = os.path.join(HERE, "_build")
-BINDING = os.path.join(HERE, "_oqm_binding.so")
+# with the interpreter's tag: one of another version refuses the file instead of loading it
+BINDING = os.path.join(HERE, "_oqm_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 SELFCHECK = os.path.join(HERE, "selfcheck_division.bin")
 
 SOURCES = ["oqm_api.hip", "oqm_quantize.hip", "oqm_quantize_tokens.hip", "oqm_dequant.hip", "oqm_score.hip",

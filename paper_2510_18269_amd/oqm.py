@@ -96,7 +96,11 @@ def _load():
 
 lib = _load()
 
-from . import _oqm_binding as _native  # noqa: E402  (linked against the library that was just loaded)
+try:
+    from . import _oqm_binding as _native  # linked against the library that was just loaded
+except ImportError as e:
+    raise ImportError("_oqm_binding is missing for this Python: build it first (python -m paper_2510_18269_amd.build); "
+                      "there is no fallback implementation") from e
 
 _DTYPE_OF_TORCH = {torch.float32: TOM_F32, torch.bfloat16: TOM_BF16, torch.float16: TOM_F16}
 _TORCH_OF_DTYPE = {v: k for k, v in _DTYPE_OF_TORCH.items()}

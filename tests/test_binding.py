@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import subprocess
 import sys
+import sysconfig
 
 import numpy as np
 import pytest
@@ -170,3 +171,9 @@ def test_calls_reach_the_library_beside_the_binding(tmp_path):
     r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, LD_LIBRARY_PATH=path), capture_output=True, text=True,
                        cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     assert r.stdout.strip() == "3", r.stderr
+
+
+def test_binding_is_built_for_this_interpreter(store):
+    """CPython's headers fix the binding's layout: a file without the interpreter's tag would be loaded by any."""
+    oqm, _ = store
+    assert os.path.basename(oqm._native.__file__) == "_oqm_binding" + sysconfig.get_config_var("EXT_SUFFIX")
