@@ -73,12 +73,12 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     uint32_t t;
     if constexpr (SELECT > 0) {
         __shared__ uint32_t chosen;
-        __shared__ uint32_t slots[2][2 * SELECT];
+        __shared__ SelectScratch<SELECT> shared;
         if (SELECT == kBlock / 64 || tid < 64 * SELECT) {
             const int lane = (int)(tid & 63u), wave = SELECT == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(tid >> 6));
             uint32_t key[kSelectKeys];
             load_keys_of_row<kSelectKeys>(a.scores + (int64_t)li * a.score_stride, a.n_groups, wave, lane, key);
-            select_largest<SELECT, kSelectKeys>(key, a.k_eff, wave, lane, slots, [&](uint32_t rank, int i) {
+            select_largest<SELECT, kSelectKeys>(key, a.k_eff, wave, lane, &shared, [&](uint32_t rank, int i) {
                 if (rank == r) chosen = (uint32_t)i;  // one lane: ranks are distinct and r < k_eff
             });
         }

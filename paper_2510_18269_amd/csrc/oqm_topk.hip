@@ -5,12 +5,12 @@
 // in registers and the threshold is found from the top bits down with ballots (oqm_select.h).  The launch is
 // bound by the latency of its serial steps (and by fetching its own code: unrolling 16 keys per
 // lane costs more than the barriers it saves), so rows of up to 256 scores take one wave without
-// any barrier, longer ones the fewest waves that keep a lane at 4 (8 above 1024) keys.  Kernel
-// time at 28 rows, this form against the radix select below: 256 scores 3.6 / 5.6 us, 1024
-// 6.0 / 6.3 us, 3600 8.4 / 10.6 us; one row: 2.5 / 4.6, 4.0 / 5.3, 5.7 / 9.6 us.  At 1024 scores
-// one wave with 16 keys takes 7.6 us; at 4096 four waves with 16 keys 9.7 us against 7.9 us.
-// Only where the k-th score occurs several times is the radix select faster (28 x 1024 scores, each five times over:
-// 6.0 us against 6.9), since it does not end early otherwise.
+// any barrier, longer ones the fewest waves that keep a lane at 4 (8 above 2048) keys.  Time per launch in a graph at
+// 28 rows, this form against the radix select below: 200 scores 3.5 / 5.2 us, 1024 5.3 / 5.9,
+// 2048 6.5 / 7.5 (7.5 with 8 keys a lane), 3600 8.2 / 10.3; one row: 3.1 / 5.1, 5.1 / 5.8, 6.3 / 7.3,
+// 7.6 / 10.0 us.  At 1024 scores one wave with 16 keys is 1.6 us slower; at 4096 four waves with 16 keys 1.8 us.
+// Scores that repeat, up to all of them equal, take at most 5 % more than the radix select (777 scores with 60
+// of each 6.2 / 5.9 us), usually less (oqm_select.h).
 //
 // Longer rows, and the best-first order: one workgroup of 1024 threads per row.  The k-th
 // largest score is found by a 4-pass, 8-bit most-significant-digit radix select over
@@ -37,7 +37,7 @@ template <int WAVES, int KEYS>
 __global__ void __launch_bounds__(64 * WAVES)
 topk_ascending_kernel(const float* __restrict__ scores, const int64_t stride, const int n, const int k,
                       const int k_eff, int32_t* __restrict__ idx) {
-    __shared__ uint32_t slots[2][2 * WAVES];
+    __shared__ SelectScratch<WAVES> shared;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t* out = idx + (int64_t)blockIdx.x * k;
     if (k_eff == n) {  // everything is chosen
@@ -46,7 +46,7 @@ topk_ascending_kernel(const float* __restrict__ scores, const int64_t stride, co
     }
     uint32_t key[KEYS];
     load_keys_of_row<KEYS>(scores + (int64_t)blockIdx.x * stride, n, wave, lane, key);
-    select_largest<WAVES, KEYS>(key, k_eff, wave, lane, slots, [&](uint32_t rank, int i) { out[rank] = i; });
+    select_largest<WAVES, KEYS>(key, k_eff, wave, lane, &shared, [&](uint32_t rank, int i) { out[rank] = i; });
 }
 
 __global__ void __launch_bounds__(kTopkThreads)
@@ -211,6 +211,7 @@ hipError_t launch_topk(const float* scores, int64_t stride, int n_rows, int n_gr
         using std::integral_constant;
         if (n_groups <= 256) go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
         else if (n_groups <= 1024) go(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+        else if (n_groups <= 2048) go(integral_constant<int, 8>{}, integral_constant<int, 4>{});
         else go(integral_constant<int, 8>{}, integral_constant<int, 8>{});
         return hipGetLastError();
     }
