@@ -38,4 +38,24 @@ inline uint32_t fold_slots(const ScoreArgs& a) {
     return apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups)) ? slots : 0u;
 }
 
+// ---- per-token scores: the contraction is split over the waves of a workgroup -------------
+// Tiles of 16 query tokens per pass of score_token_split_kernel (1 to 4), or 0: the 64 x 64 form.
+// A whole question on the device (fold, this, top-k, gather of 4 groups) at 4 heads of 128, against the 64 x 64 form:
+// 1 layer x 256 groups x 32 tokens 18.1 / 28.0 us, x 64 tokens 25.8 / 39.3; 8 x 1024 (512 units)
+// x 32 25.3 / 31.0; but 28 x 400 (700 units) x 32 33.0 / 33.0, x 64 55.2 / 45.9: from three
+// units per compute unit on the query block is read too often.
+// The tokens are cut into equal passes.  A pass of four tiles takes 138 registers, so a compute unit
+// holds one workgroup (eight waves of three per SIMD): more than 256 units would then run in two rounds.  With
+// at most three tiles (112 registers, two workgroups) 512 units run in one.  Fold and scores at 448 to 512 units, equal
+// passes of three / passes of four / 64 x 64 form: one head of 64 x 65 tokens 14.5 / 18.0 / 15.8 us, x 1024
+// tokens 92 / 117 / 107; 4 heads of 128 x 65 tokens 36 / 45 / 46, x 1024 tokens 370 / 390 / 470.
+inline int split_tiles(const ScoreArgs& a) {
+    constexpr int64_t kSplitUnits = 512, kUnitsOfFourTiles = 256;
+    const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers;
+    if (units > kSplitUnits) return 0;
+    const int most = units > kUnitsOfFourTiles ? 3 : 4;
+    const int tiles = (a.t_q + 15) / 16, passes = (tiles + most - 1) / most;
+    return (tiles + passes - 1) / passes;
+}
+
 }  // namespace oqm

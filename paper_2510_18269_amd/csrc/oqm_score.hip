@@ -473,7 +473,7 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     }
 }
 
-// The same contraction for launches of at most kSplitUnits units of 16 groups, where the 64 x 64 form
+// The same contraction for launches of few units of 16 groups (split_tiles in oqm_dispatch.h), where the 64 x 64 form
 // leaves compute units idle and each of its few workgroups walks the whole contraction through
 // barriers (1.2 us per 32 channels).  Unit of work = (layer, 16
 // consecutive groups), all query tokens in passes of 16 * MT: the eight waves of a workgroup split the contraction,
@@ -481,11 +481,6 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
 // Operands go from memory straight into the MFMA registers: the order of a contraction is free,
 // so lane (fi, kk) takes channels 4 kk .. 4 kk + 3 of a block for its four MFMA steps and every load is 16 bytes
 // wide; kAhead blocks are requested before the first is used (four: no faster, one at a time: 3 to 8 us slower).
-// A whole question on the device (fold, this, top-k, gather of 4 groups) at 4 heads of 128, against the 64 x 64 form:
-// 1 layer x 256 groups x 32 tokens 18.1 / 28.0 us, x 64 tokens 25.8 / 39.3; 8 x 1024 (512 units)
-// x 32 25.3 / 31.0, x 64 40.1 / 42.9; but 28 x 400 (700 units) x 32 33.0 / 33.0, x 64 55.2 / 45.9: from three
-// units per compute unit on the query block is read too often.
-constexpr int kSplitUnits = 512;
 constexpr int kSplitWaves = 8, kSplitThreads = 64 * kSplitWaves, kAhead = 2;
 
 template <int MT>
@@ -640,9 +635,8 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.n_groups == 0) return hipSuccess;
     if (hipError_t e = launch_query_fold(args, true, s)) return e;
     ScoreArgs a = args;
-    const int64_t tiles16 = (a.n_groups + 15) / 16;
-    const bool split = tiles16 * a.n_layers <= kSplitUnits;
-    const int width = split ? 16 : kGemmN;
+    const int tiles = split_tiles(a);
+    const int width = tiles > 0 ? 16 : kGemmN;
     a.gemm_tiles_per_layer = (a.n_groups + width - 1) / width;
     a.inv_gemm_tiles_per_layer = reciprocal_u32((uint32_t)a.gemm_tiles_per_layer);
     const int64_t units = (int64_t)a.gemm_tiles_per_layer * a.n_layers;
@@ -650,11 +644,13 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     a.gemm_units = (int32_t)units;
     a.gemm_units_per_xcd = (int32_t)((units + 7) / 8);
     const dim3 grid(8u * (unsigned)a.gemm_units_per_xcd);
-    if (!split) score_token_gemm_kernel<<<grid, dim3(kBlock), 0, s>>>(a);
-    else if (a.t_q <= 16) score_token_split_kernel<1><<<grid, dim3(kSplitThreads), 0, s>>>(a);
-    else if (a.t_q <= 32) score_token_split_kernel<2><<<grid, dim3(kSplitThreads), 0, s>>>(a);
-    else if (a.t_q <= 48) score_token_split_kernel<3><<<grid, dim3(kSplitThreads), 0, s>>>(a);
-    else score_token_split_kernel<4><<<grid, dim3(kSplitThreads), 0, s>>>(a);
+    switch (tiles) {
+        case 0: score_token_gemm_kernel<<<grid, dim3(kBlock), 0, s>>>(a); break;
+        case 1: score_token_split_kernel<1><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
+        case 2: score_token_split_kernel<2><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
+        case 3: score_token_split_kernel<3><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
+        default: score_token_split_kernel<4><<<grid, dim3(kSplitThreads), 0, s>>>(a);
+    }
     return hipGetLastError();
 }
 }  // namespace oqm

@@ -51,8 +51,29 @@ static void fold() {
     CHECK(fold_slots(a) == 0);
 }
 
+static void split() {
+    ScoreArgs a{};
+    auto tiles = [&](int n_layers, int n_groups, int t_q) {
+        a.n_layers = n_layers, a.n_groups = n_groups, a.t_q = t_q;
+        return split_tiles(a);
+    };
+    for (int t_q = 1; t_q <= 1100; ++t_q)
+        for (int groups : {1, 256 * 16, 256 * 16 + 1, 512 * 16}) {
+            const int m = tiles(1, groups, t_q), all = (t_q + 15) / 16, most = groups > 256 * 16 ? 3 : 4;
+            const int passes = (all + m - 1) / m;
+            CHECK(m >= 1 && m <= most);
+            CHECK(passes == (all + most - 1) / most);   // no more passes than the widest would take
+            CHECK(m * passes - all < passes);           // and none with a whole idle tile more than it must have
+        }
+    CHECK(tiles(8, 1024, 64) == 2 && tiles(8, 1025, 64) == 0);   // 512 and 520 units
+    CHECK(tiles(512, 16, 1) == 1 && tiles(513, 16, 1) == 0);
+    CHECK(tiles(4, 1024, 64) == 4 && tiles(4, 1024, 65) == 3 && tiles(4, 1024, 1 << 20) == 4);
+    CHECK(tiles(65535, 0x7fffffff, 1) == 0);                     // far beyond, no overflow
+}
+
 int main() {
     fold();
+    split();
     if (failures) { std::fprintf(stderr, "%d failures\n", failures); return 2; }
     std::printf("dispatch driver: clean\n");
     return 0;

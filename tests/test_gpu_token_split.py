@@ -1,7 +1,7 @@
 """GPU: the per-token scores of small launches (the K-split form) against plain float64.
 
 A launch of at most 512 units of 16 groups splits the contraction over the waves of a workgroup, with
-1 to 4 tiles of 16 query tokens at a time; larger launches take the 64 x 64 form.  The cases sit on
+1 to 4 tiles of 16 query tokens at a time (1 to 3 above 256 units); larger launches take the 64 x 64 form.  The cases sit on
 both sides of every edge: token tiles, group tiles, contractions that end in half a block of 16
 channels or need several rounds of blocks, and the launch size itself."""
 import pytest
@@ -66,3 +66,10 @@ def test_contraction_lengths(oqm, H, d):
 @pytest.mark.parametrize("L,T", ((1, 8192), (1, 8193), (16, 512), (16, 513), (512, 16), (513, 16), (57, 129)))
 def test_launch_size_of_the_split_form(oqm, L, T):
     _check(oqm, L, 1, 1, 16, T, 3, True, L + T)
+
+
+# above 256 units: 3 tiles in one pass; 4 (two passes of 2), 5, 6 and 7 (2 x 3, 3 x 3) and 10 tiles (4 x 3) with idle ones
+@pytest.mark.parametrize("tq", (48, 49, 65, 96, 97, 145))
+def test_passes_above_256_units(oqm, tq):
+    for T in (4096, 4097):
+        _check(oqm, 1, 1, 1, 24, T, tq, T == 4096, tq + T)
