@@ -45,6 +45,21 @@ static void fold() {
     CHECK(fold_slots(a) == 8);
     a.t_q = 27;
     CHECK(fold_slots(a) == 0);
+    // one round of the chip: one workgroup per compute unit with a float32 query, two with a 16-bit one and short keys
+    a.t_q = 1, a.n_layers = 8;
+    for (int dtype : {TOM_F32, TOM_BF16, TOM_F16})
+        for (int heads : {1, 2}) {
+            a.q_dtype = dtype, a.n_kv_heads = a.n_q_heads = heads;
+            auto fused = [&](int groups) {
+                a.n_groups = groups, a.score_stride = groups;
+                return fold_slots(a) > 0;
+            };
+            CHECK(fused(256 * 32 / 8));
+            CHECK(fused(256 * 32 / 8 + 1) == (dtype != TOM_F32));
+            CHECK(fused(512 * 32 / 8) == (dtype != TOM_F32));
+            CHECK(fused(512 * 32 / 8 + 1) == (dtype != TOM_F32 && heads == 2));
+        }
+    a.n_layers = 1, a.n_groups = a.score_stride = 256, a.q_dtype = TOM_BF16;
     a.t_q = 1, a.head_dim = 256, a.n_kv_heads = a.n_q_heads = 16;
     CHECK(fold_slots(a) == 1);
     a.n_kv_heads = a.n_q_heads = 17;                   // no row slot left for the last head
