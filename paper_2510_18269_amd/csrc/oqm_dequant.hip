@@ -24,6 +24,7 @@
 
 #include "oqm_common.h"
 #include "oqm_device.h"
+#include "oqm_dispatch.h"
 #include "oqm_select.h"
 
 namespace oqm {
@@ -35,8 +36,6 @@ __device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t 
     const int64_t off = ((int64_t)block * kBlock + threadIdx.x) * 16;
     if (off < bytes) *reinterpret_cast<u32x4*>(dst + off) = *reinterpret_cast<const u32x4*>(src + off);
 }
-
-constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups
 
 // The 8-channel items of a tile (one 32-bit word of 4-bit codes each) are numbered row by row: item
 // row * (d/8) + slot.  Codes and output are linear in that number, and so are the pairs of the
@@ -157,46 +156,6 @@ hipError_t prefix_copy(const DequantArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Whether the prefix rows can be copied by blocks of the gather's own launch.  As a launch of its
-// own the copy costs 1.3 to 4.5 us for 14 rows (0.8 MB at 28 layers), inside the gather nothing
-// that can be measured.  Not where a grid dimension would pass 2^32 threads, nor where the source
-// overlaps the active buffer: the copy then has to come first.
-template <typename OUT>
-bool prefix_joins_gather(const DequantArgs& a) {
-    constexpr int64_t eb = elem_bytes<OUT>::value;
-    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
-    const int64_t prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;
-    const int64_t out_bytes = heads * ((int64_t)a.prefix_rows + (int64_t)a.k * a.group_tokens) * a.head_dim * eb;
-    if ((prefix_bytes / 16 + kBlock - 1) / kBlock + (int64_t)a.k_eff * a.chunks >= (1LL << 32) / kBlock) return false;
-    auto apart = [&](const void* sys, const void* out) {
-        const uintptr_t s = reinterpret_cast<uintptr_t>(sys), o = reinterpret_cast<uintptr_t>(out);
-        return s + (uintptr_t)(heads * prefix_bytes) <= o || o + (uintptr_t)out_bytes <= s;
-    };
-    return apart(a.sys_k, a.k_out) && apart(a.sys_k, a.v_out) && apart(a.sys_v, a.k_out) && apart(a.sys_v, a.v_out);
-}
-
-// Whether the workgroups of the gather select their groups themselves instead of reading the indices that a
-// top-k launch wrote.  The launch costs 2.5 to 4 us on the device; selecting delays each
-// workgroup by about 1 us with one wave (up to 256 scores) and 2 us with four, so it pays while the workgroups
-// run in about one round.  Whole one-call question at 4 heads, itself / with the launch: 256 scores, 896 workgroups 13.0 / 14.9 us,
-// 1792 15.2 / 17.4, 4000 16.3 / 17.3 or 16.6, 6000 21.1 / 20.4; 1024 scores, 64 workgroups 12.9 / 14.5, 896 24.8 / 25.6, 1280 14.5 / 14.9
-// (in a graph 14.2 / 14.1), 2560 20.5 / 17.5.
-constexpr int kSelectMaxGroups = kBlock * kSelectKeys;
-
-bool selects_itself(const DequantArgs& a, int64_t workgroups) {
-    if (a.n_groups > kSelectMaxGroups || workgroups > (a.n_groups <= 64 * kSelectKeys ? 2048 : 1024)) return false;
-    // the launch reads all scores while it writes: no output may share memory with them
-    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
-    const uint64_t out_bytes = (uint64_t)(heads * a.head_out_bytes);
-    const uintptr_t s = reinterpret_cast<uintptr_t>(a.scores);
-    const uint64_t score_bytes = 4u * ((uint64_t)(a.n_layers - 1) * (uint64_t)a.score_stride + (uint64_t)a.n_groups);
-    auto apart = [&](const void* out, uint64_t bytes) {
-        const uintptr_t o = reinterpret_cast<uintptr_t>(out);
-        return s + score_bytes <= o || o + bytes <= s;
-    };
-    return apart(a.k_out, out_bytes) && apart(a.v_out, out_bytes) && apart(a.sel_idx, 4u * (uint64_t)a.n_layers * (uint64_t)a.k);
-}
-
 template <typename OUT>
 hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.k_eff == 0) return hipSuccess;
@@ -222,14 +181,14 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     a.plane_tiles = (int64_t)a.capacity_groups * a.n_kv_heads;
     a.prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;
     a.head_out_bytes = a.prefix_bytes + (int64_t)a.k * a.group_tokens * a.head_dim * eb;
-    const bool select = a.scores && selects_itself(a, (int64_t)a.k_eff * a.chunks * 2 * a.n_kv_heads * a.n_layers);
+    const int select = a.scores ? select_waves(a) : 0;
     if (a.scores && !select)
         if (hipError_t e = launch_topk(a.scores, a.score_stride, a.n_layers, a.n_groups, a.k, a.k_eff, TOM_ORDER_INDEX_ASC,
                                        a.sel_idx, s))
             return e;
     uint32_t prefix_blocks = 0;
     if (a.sys_k && a.prefix_rows > 0) {
-        if (prefix_joins_gather<OUT>(a)) {
+        if (prefix_joins_gather(a)) {
             prefix_blocks = (uint32_t)((a.prefix_bytes / 16 + kBlock - 1) / kBlock);
         } else if (hipError_t e = prefix_copy<OUT>(a, s)) {
             return e;
@@ -245,7 +204,7 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
             else dequant_gather_kernel<OUT, U, false, B, M, S><<<grid, block, 0, s>>>(a);
         };
         if (!select) with_select(std::integral_constant<int, 0>{});
-        else if (a.n_groups <= 64 * kSelectKeys) with_select(std::integral_constant<int, 1>{});
+        else if (select == 1) with_select(std::integral_constant<int, 1>{});
         else with_select(std::integral_constant<int, kBlock / 64>{});
     };
     auto with_meta = [&](auto unroll, auto bits) {

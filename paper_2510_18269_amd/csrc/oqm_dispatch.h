@@ -65,4 +65,67 @@ inline int split_tiles(const ScoreArgs& a) {
     return (tiles + passes - 1) / passes;
 }
 
+// ---- token-axis store: tiles whose rows the waves hold -------------------------------------
+constexpr int kMostRows = 8, kMostRows16Bit = 13;  // rows a lane holds at most
+
+// Rows per lane where `waves` waves hold a tile; a wave covers 64 / lpr token rows of lpr lanes a pass.
+inline int rows_per_lane(int lpr, int group_tokens, int waves) {
+    const int passes = (group_tokens + 64 / lpr - 1) / (64 / lpr);
+    return (passes + waves - 1) / waves;
+}
+
+// Waves per tile, or 0: the general form (other head sizes, and where it is the better one).  Eight rows per
+// lane, at most four waves (seven of eight rows lose to the general form: 196 rows at d = 128, 16 frames
+// 56.1 against 52.5 us, since one workgroup more or less per compute unit is then a third of it).
+// Taller tiles take 13 rows, where the registers hold them (16-bit inputs): 48.6 us.  At d = 256 a
+// wave covers only two rows a pass and the exchange costs more, so 13 rows are taken wherever at
+// most one of them per wave is idle (50 rows: 28.5 us against 29.4 with eight rows and 31.6 in the general
+// form) and tiles above 32 passes otherwise stay in the general form (80 rows: 50.6 against 47.0).
+inline int row_waves(int lpr, int group_tokens, bool is_16_bit) {
+    if (lpr != 8 && lpr != 16 && lpr != 32) return 0;
+    const int passes = rows_per_lane(lpr, group_tokens, 1);
+    const int few = (passes + kMostRows16Bit - 1) / kMostRows16Bit;
+    if (lpr == 32 && is_16_bit && few <= 4 && few * kMostRows16Bit - passes <= few) return few;
+    if (passes <= 4 * kMostRows) return (passes + kMostRows - 1) / kMostRows;
+    return is_16_bit && lpr < 32 && few <= 4 ? 4 : 0;
+}
+
+// ---- gather: the prefix rows, and the selection ---------------------------------------------
+// Both ask about a launch whose sizes (chunks, prefix_bytes, head_out_bytes) are filled in.
+
+// Whether the prefix rows can be copied by blocks of the gather's own launch.  As a launch of its
+// own the copy costs 1.3 to 4.5 us for 14 rows (0.8 MB at 28 layers), inside the gather nothing
+// that can be measured.  Not where a grid dimension would pass 2^32 threads, nor where the source
+// overlaps the active buffer: the copy then has to come first.
+inline bool prefix_joins_gather(const DequantArgs& a) {
+    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
+    const uint64_t sys_bytes = (uint64_t)(heads * a.prefix_bytes), out_bytes = (uint64_t)(heads * a.head_out_bytes);
+    if ((a.prefix_bytes / 16 + kBlock - 1) / kBlock + (int64_t)a.k_eff * a.chunks >= (1LL << 32) / kBlock) return false;
+    for (const void* sys : {a.sys_k, a.sys_v})
+        for (const void* out : {a.k_out, a.v_out})
+            if (!apart(sys, sys_bytes, out, out_bytes)) return false;
+    return true;
+}
+
+constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups
+
+// Waves of each gather workgroup that select its group from the scores (256 scores each; one or all four), or
+// 0: the indices come from a top-k launch.  The launch costs 2.5 to 4 us on the device; selecting delays each
+// workgroup by about 1 us with one wave (up to 256 scores) and 2 us with four, so it pays while the workgroups
+// run in about one round.  Whole one-call question at 4 heads, itself / with the launch: 256 scores, 896 workgroups 13.0 / 14.9 us,
+// 1792 15.2 / 17.4, 4000 16.3 / 17.3 or 16.6, 6000 21.1 / 20.4; 1024 scores, 64 workgroups 12.9 / 14.5, 896 24.8 / 25.6, 1280 14.5 / 14.9
+// (in a graph 14.2 / 14.1), 2560 20.5 / 17.5.
+// The launch reads all scores while it writes: no output may share memory with them.
+inline int select_waves(const DequantArgs& a) {
+    const int waves = a.n_groups <= 64 * kSelectKeys ? 1 : kBlock / 64;
+    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
+    if (a.n_groups > kBlock * kSelectKeys || (int64_t)a.k_eff * a.chunks * 2 * heads > (waves == 1 ? 2048 : 1024)) return 0;
+    const uint64_t score_bytes = score_span(a.score_stride, a.n_layers, a.n_groups);
+    const uint64_t out_bytes = (uint64_t)(heads * a.head_out_bytes), idx_bytes = 4u * (uint64_t)a.n_layers * (uint64_t)a.k;
+    return apart(a.scores, score_bytes, a.k_out, out_bytes) && apart(a.scores, score_bytes, a.v_out, out_bytes) &&
+                   apart(a.scores, score_bytes, a.sel_idx, idx_bytes)
+               ? waves
+               : 0;
+}
+
 }  // namespace oqm

@@ -15,6 +15,7 @@
 
 #include "oqm_common.h"
 #include "oqm_device.h"
+#include "oqm_dispatch.h"
 
 namespace oqm {
 namespace {
@@ -320,23 +321,6 @@ __global__ void __launch_bounds__(256) quantize_append_rows_kernel(const QuantAr
     for (int j = 0; j < CH; ++j) key[c0 + j] = (float)(acc[j] / (double)G);
 }
 
-// Waves per tile for `passes` row passes of one wave; 0: the general form is the better one.  Eight rows per lane, at
-// most four waves (seven of eight rows lose to the general form: 196 rows at d = 128, 16 frames
-// 56.1 against 52.5 us, since one workgroup more or less per compute unit is then a third of it).
-// Taller tiles take 13 rows, where the registers hold them (16-bit inputs): 48.6 us.  At d = 256 a
-// wave covers only two rows a pass and the exchange costs more, so 13 rows are taken wherever at
-// most one of them per wave is idle (50 rows: 28.5 us against 29.4 with eight rows and 31.6 in the general
-// form) and tiles above 32 passes otherwise stay in the general form (80 rows: 50.6 against 47.0).
-constexpr int kMostRows = 8, kMostRows16Bit = 13;
-template <typename IN, int LPR>
-int row_waves(int passes) {
-    constexpr bool tall = sizeof(Raw8<IN>) <= 16;
-    const int few = (passes + kMostRows16Bit - 1) / kMostRows16Bit;
-    if (LPR == 32 && tall && few <= 4 && few * kMostRows16Bit - passes <= few) return few;
-    if (passes <= 4 * kMostRows) return (passes + kMostRows - 1) / kMostRows;
-    return tall && LPR < 32 && few <= 4 ? 4 : 0;
-}
-
 template <typename IN, int LPR, int HOLD>
 hipError_t launch_rows_h(const QuantArgs& a, int waves, hipStream_t s) {
     const dim3 grid(a.n_kv_heads, 2 * a.n_layers, a.n_frames), block(64 * waves);
@@ -353,8 +337,7 @@ hipError_t launch_rows_h(const QuantArgs& a, int waves, hipStream_t s) {
 }
 
 template <typename IN, int LPR>
-hipError_t launch_rows(const QuantArgs& a, int waves, int passes, hipStream_t s) {
-    const int rows = (passes + waves - 1) / waves;
+hipError_t launch_rows(const QuantArgs& a, int waves, int rows, hipStream_t s) {
     if (rows <= 4) return launch_rows_h<IN, LPR, 4>(a, waves, s);
     if (rows <= 6) return launch_rows_h<IN, LPR, 6>(a, waves, s);
     if (rows == 7) return launch_rows_h<IN, LPR, 7>(a, waves, s);
@@ -386,13 +369,11 @@ hipError_t launch_t(const QuantArgs& a, hipStream_t s) {
     if (a.n_frames == 0 || a.n_layers == 0) return hipSuccess;
     const int lpr = a.head_dim / 8;
     // a separate summary source is one more pass over another tensor: the general form is as fast there
-    if (a.ksum == a.k) {
-        const int passes = lpr <= 64 ? (a.group_tokens + 64 / lpr - 1) / (64 / lpr) : 0;
-        const int waves = lpr == 8 ? row_waves<IN, 8>(passes) : lpr == 16 ? row_waves<IN, 16>(passes)
-                        : lpr == 32 ? row_waves<IN, 32>(passes) : 0;
-        if (waves && lpr == 8) return launch_rows<IN, 8>(a, waves, passes, s);
-        if (waves && lpr == 16) return launch_rows<IN, 16>(a, waves, passes, s);
-        if (waves && lpr == 32) return launch_rows<IN, 32>(a, waves, passes, s);
+    if (const int waves = a.ksum == a.k ? row_waves(lpr, a.group_tokens, sizeof(Raw8<IN>) <= 16) : 0) {
+        const int rows = rows_per_lane(lpr, a.group_tokens, waves);
+        if (lpr == 8) return launch_rows<IN, 8>(a, waves, rows, s);
+        if (lpr == 16) return launch_rows<IN, 16>(a, waves, rows, s);
+        return launch_rows<IN, 32>(a, waves, rows, s);
     }
     const int rpp = kBlock / lpr;
     const int trips = (a.group_tokens + rpp - 1) / rpp;  // rows per lane

@@ -19,7 +19,6 @@ namespace oqm {
 STUB(launch_quantize_append, const QuantArgs&, int, hipStream_t)
 STUB(launch_dequant_gather, const DequantArgs&, int, hipStream_t)
 STUB(launch_prefix_copy, const DequantArgs&, const void*, const void*, int, hipStream_t)
-STUB(launch_query_fold, const ScoreArgs&, bool, hipStream_t)
 STUB(launch_score_mean_query, const ScoreArgs&, hipStream_t)
 STUB(launch_score_token_gemm, const ScoreArgs&, hipStream_t)
 STUB(launch_topk, const float*, int64_t, int, int, int, int, int, int32_t*, hipStream_t)

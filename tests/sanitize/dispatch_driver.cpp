@@ -2,6 +2,7 @@
 // -fsanitize=address,undefined by tests/test_sanitizers.py.  Both sides of every limit, and buffers that
 // overlap, adjoin or lie apart.  No device is touched: the addresses are fakes.  Exit status 0 = clean.
 #include <cstdio>
+#include <utility>
 
 #include "oqm_dispatch.h"
 
@@ -86,9 +87,87 @@ static void split() {
     CHECK(tiles(65535, 0x7fffffff, 1) == 0);                     // far beyond, no overflow
 }
 
+static void rows() {
+    // lanes per row, 16-bit input, rows of a tile -> waves (0: general form), rows per lane
+    const struct { int lpr; bool narrow; int tokens, waves, rows; } want[] = {
+        {16, true, 1, 1, 1},    {16, true, 32, 1, 8},   {16, true, 33, 2, 5},   {16, true, 50, 2, 7},   {16, true, 96, 3, 8},
+        {16, true, 97, 4, 7},   {16, true, 128, 4, 8},  {16, true, 129, 4, 9},  {16, true, 208, 4, 13}, {16, true, 209, 0, 0},
+        {16, false, 128, 4, 8}, {16, false, 129, 0, 0}, {8, true, 64, 1, 8},    {8, true, 65, 2, 5},    {8, true, 256, 4, 8},
+        {8, true, 416, 4, 13},  {8, true, 417, 0, 0},   {8, false, 257, 0, 0},  {32, true, 26, 1, 13},  {32, true, 24, 1, 12},
+        {32, true, 22, 2, 6},   {32, true, 50, 2, 13},  {32, true, 64, 4, 8},   {32, true, 65, 0, 0},   {32, true, 72, 3, 12},
+        {32, true, 104, 4, 13}, {32, true, 105, 0, 0},  {32, false, 26, 2, 7},  {32, false, 64, 4, 8},  {32, false, 65, 0, 0},
+        {12, true, 16, 0, 0},   {10, true, 50, 0, 0},   {1, true, 16, 0, 0},    {64, true, 16, 0, 0},   {512, false, 1, 0, 0},
+    };
+    for (const auto& w : want) {
+        const int waves = row_waves(w.lpr, w.tokens, w.narrow);
+        CHECK(waves == w.waves);
+        CHECK(!waves || rows_per_lane(w.lpr, w.tokens, waves) == w.rows);
+    }
+    for (int lpr : {8, 16, 32})
+        for (bool narrow : {false, true})
+            for (int tokens = 1; tokens < 3000; ++tokens) {
+                const int waves = row_waves(lpr, tokens, narrow);
+                CHECK(waves >= 0 && waves <= 4);
+                if (!waves) continue;
+                const int held = rows_per_lane(lpr, tokens, waves);
+                CHECK(held <= (narrow ? kMostRows16Bit : kMostRows));
+                CHECK(waves * held * (64 / lpr) >= tokens);   // every row has a lane
+            }
+}
+
+static void gather() {
+    DequantArgs a{};
+    a.n_kv_heads = 4, a.head_dim = 64, a.n_layers = 2, a.k = 10, a.k_eff = 10, a.n_groups = 200, a.chunks = 1;
+    a.score_stride = 208, a.prefix_bytes = 5 * 64 * 2, a.head_out_bytes = a.prefix_bytes + 10 * 16 * 64 * 2;
+    const uint64_t sys_bytes = 8 * a.prefix_bytes, out_bytes = 8 * a.head_out_bytes, s_bytes = (208 + 200) * 4;
+    const uint64_t k_out = 1 << 24, v_out = 1 << 25, idx = 1 << 20, far = 1 << 28, idx_bytes = 2 * 10 * 4;
+    a.k_out = at(k_out), a.v_out = at(v_out), a.sel_idx = reinterpret_cast<int32_t*>(at(idx));
+    auto scores_at = [&](uint64_t address) {
+        a.scores = reinterpret_cast<float*>(at(address));
+        return select_waves(a);
+    };
+    CHECK(scores_at(far) == 1);
+    for (const auto& [begin, bytes] : {std::pair<uint64_t, uint64_t>{k_out, out_bytes}, {v_out, out_bytes}, {idx, idx_bytes}}) {
+        CHECK(scores_at(begin + bytes) == 1);       // adjoining, behind
+        CHECK(scores_at(begin - s_bytes) == 1);     // and in front
+        CHECK(scores_at(begin + bytes - 4) == 0);
+        CHECK(scores_at(begin - s_bytes + 4) == 0);
+        CHECK(scores_at(begin) == 0);
+    }
+    a.scores = reinterpret_cast<float*>(at(far));
+    // one wave for up to 256 scores and 2048 workgroups, four for up to 1024 and 1024
+    auto waves = [&](int n_groups, int k, int chunks) {
+        a.n_groups = n_groups, a.k = a.k_eff = k, a.chunks = (uint32_t)chunks, a.n_layers = 1, a.n_kv_heads = 1;
+        return select_waves(a);
+    };
+    CHECK(waves(256, 255, 4) == 1 && waves(256, 128, 8) == 1 && waves(256, 129, 8) == 0);
+    CHECK(waves(257, 128, 4) == 4 && waves(257, 129, 4) == 0 && waves(1024, 512, 1) == 4 && waves(1024, 513, 1) == 0);
+    CHECK(waves(1025, 1, 1) == 0 && waves(1 << 30, 1, 1) == 0);
+
+    auto joins = [&](uint64_t sys_k, uint64_t sys_v) {
+        a.n_layers = 2, a.n_kv_heads = 4;
+        a.sys_k = at(sys_k), a.sys_v = at(sys_v);
+        return prefix_joins_gather(a);
+    };
+    CHECK(joins(far, far + sys_bytes) && joins(far, far));
+    for (uint64_t out : {k_out, v_out}) {
+        CHECK(joins(out + out_bytes, far) && joins(far, out - sys_bytes));
+        CHECK(!joins(out + out_bytes - 16, far) && !joins(far, out + out_bytes - 16));
+        CHECK(!joins(out - sys_bytes + 16, far) && !joins(far, out - sys_bytes + 16));
+        CHECK(!joins(out, far) && !joins(far, out));
+    }
+    a.chunks = 1, a.k = a.k_eff = (1 << 24) - 4;    // three blocks of prefix and 2^24 - 4 of the gather; 2^24 x 256 threads are too many
+    a.prefix_bytes = 3 * 256 * 16, a.head_out_bytes = 0;
+    CHECK(joins(far, far));
+    ++a.k_eff;
+    CHECK(!joins(far, far));
+}
+
 int main() {
     fold();
     split();
+    rows();
+    gather();
     if (failures) { std::fprintf(stderr, "%d failures\n", failures); return 2; }
     std::printf("dispatch driver: clean\n");
     return 0;
