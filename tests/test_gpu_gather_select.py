@@ -22,10 +22,26 @@ def oqm():
     (100, 30, 2, 16, "bf16", 0, 0, "scores in k_out"), (100, 30, 2, 16, "bf16", 0, 0, "idx behind scores"),   # or shared memory (the second one only adjoins)
 ])
 def test_retrieve_matches_separate_calls(oqm, T, k, L, G, dt, axis, prefix, where):
+    _check(oqm, T, k, L, G, dt, axis, prefix, where)
+
+
+@pytest.mark.parametrize("meta", ("f32", "bf16"))
+@pytest.mark.parametrize("bits", (4, 2))
+@pytest.mark.parametrize("dt", ("f32", "bf16", "f16"))
+def test_every_form_of_the_selecting_gather(oqm, dt, bits, meta):
+    """One and four selecting waves, one trip of four items a lane and chunks of three, both axes."""
+    for T in (200, 300):
+        for G in (16, 196):
+            for axis in (0, 1):
+                _check(oqm, T, 30, 1, G, dt, axis, 3, "apart", bits, meta)
+
+
+def _check(oqm, T, k, L, G, dt, axis, prefix, where, bits=4, meta="f32"):
     """Indices, scores and rows equal those of the separate calls bit for bit, with many equal scores."""
     H, d, tq, stride = 2, 64, 3, T + 5
     code, tdt = {"f32": (oqm.TOM_F32, torch.float32), "bf16": (oqm.TOM_BF16, torch.bfloat16), "f16": (oqm.TOM_F16, torch.float16)}[dt]
-    cfg = oqm.make_config(L, H, 4, d, G, 32, T, qaxis=axis, bits=4, in_dtype=code, out_dtype=code)
+    cfg = oqm.make_config(L, H, 4, d, G, 32, T, qaxis=axis, bits=bits, in_dtype=code, out_dtype=code,
+                          meta_dtype=oqm.TOM_BF16 if meta == "bf16" else oqm.TOM_F32)
     mem = oqm.Memory.allocate(cfg)
     g = torch.Generator().manual_seed(T + k)
     kinds = torch.randint(0, max(2, T // 3), (T,), generator=g)      # repeated frames: equal scores, lowest index first
