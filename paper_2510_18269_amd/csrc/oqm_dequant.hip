@@ -2,18 +2,19 @@
 // (paper Sec. 3.4, Eq. 11 and Eq. 13; supplement "Cache reconstruction for decoding").
 //
 // Grid (rank * chunks + chunk, then prefix blocks; K|V * H_k + head; layer): a workgroup of 256
-// threads owns up to three passes (48 token rows at head_dim 128) of one head tile of one
-// selected group; consecutive workgroups write consecutive row blocks of the active
-// buffer.  It reads the group index from device memory (the index array never visits
-// the host), streams its rows' packed codes and (scale, zero) pairs, and writes them
-// to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns one
+// threads owns one head tile of one selected group where four passes cover it (64 token rows at
+// head_dim 128), otherwise an equal share of it, at most three passes; consecutive workgroups
+// write consecutive row blocks of the active buffer.  It reads the group index from device memory
+// (the index array never visits the host), streams its rows' packed codes and (scale, zero) pairs,
+// and writes them to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns one
 // 32-bit word of codes (8 channels) into one 128-bit non-temporal store, so each store
 // instruction of a wave writes 1 KB of contiguous bf16.  HBM-bound: 0.5 + 8/gs bytes
 // read and 2 bytes written per element.
 //
-// Measured at 28 layers x 64 random groups x 196 x 128 (944 MB): 162 us = 5.83 TB/s, where an
-// arithmetic-free linear stream of the same byte mix reaches 6.1.  In-kernel clocks: a workgroup
-// lives 3.5 us (index 0.2, loads 1.5, stores 1.7), 1520 of 2048 slots are taken at any time.  One to
+// Measured at 28 layers x 64 random groups x 196 x 128 (944 MB): cards differ, the benchmark's kernel
+// trace averages 163 us (5.8 TB/s) on the fastest one seen and 169 (5.6) on another, where an
+// arithmetic-free linear stream of the same byte mix reaches 6.1 TB/s.  On the fast one, in-kernel
+// clocks: a workgroup lives 3.5 us (index 0.2, loads 1.5, stores 1.7), 1520 of 2048 slots are taken at any time.  One to
 // five passes per workgroup, 256 or 512 threads and a barrier between loads and stores
 // all stay within 1 %; seven passes 171, 1024 threads 165, three or five workgroups per compute unit
 // instead of eight 230 / 181, and a persistent loop that loads the next piece before it
