@@ -65,6 +65,28 @@ inline int split_tiles(const ScoreArgs& a) {
     return (tiles + passes - 1) / passes;
 }
 
+// ---- head_dim-axis store: who makes the summary keys ----------------------------------------
+constexpr int64_t kMostBlocks = (1LL << 32) / kBlock - 1;  // of a 1-D grid: it must stay below 2^32 threads
+
+// Whether K tiles are cut into chunks like V and the keys come from workgroups of their own (quantize_append_cut_kernel)
+// instead of the workgroups that walk the K tiles.  Always where the keys are averaged over another tensor.
+// Otherwise that reads K twice, which pays while the launch is bound by the longest chain of one workgroup: not where a walk is
+// one trip of four rows per lane, and up to 384 tiles, 256 with float32 input.  us per call, cut / walk, at 4 heads and 196 tokens:
+// d = 128 bf16 224 tiles 5.0 / 6.9, 320 6.2 / 7.2, 384 7.0 / 7.5, 448 7.7 / 7.7; float32 224 6.9 / 7.9, 320 9.2 / 8.9; d = 64
+// 320 4.6 / 4.7, 384 4.9 / 4.9, 448 5.3 / 5.2; d = 256 320 10.2 / 11.3; d = 80 224 4.5 / 5.5, 320 5.2 / 6.0; 50 tokens (one trip) x 8 frames 8.4 / 7.4.
+inline bool cut_append(const QuantArgs& a, bool is_16_bit) {
+    if (a.ksum != a.k) return true;
+    const int64_t tiles = 2LL * a.n_kv_heads * a.n_layers * a.n_frames;
+    return a.group_tokens > 4 * (kBlock / (a.head_dim / 8)) && tiles <= (is_16_bit ? 384 : 256);
+}
+
+// Workgroups per key there: one per 64 channels while each has a compute unit of its own, which halves the trips at d = 128
+// (one bf16 frame of 28 x 4 heads 5.0 against 5.4 us; two frames 8.2 against 7.8), otherwise one.
+inline int key_parts(const QuantArgs& a) {
+    const int64_t parts = a.head_dim / 64;
+    return a.head_dim % 64 == 0 && parts * a.n_kv_heads * a.n_layers * a.n_frames <= 256 ? (int)parts : 1;
+}
+
 // ---- token-axis store: tiles whose rows the waves hold -------------------------------------
 constexpr int kMostRows = 8, kMostRows16Bit = 13;  // rows a lane holds at most
 

@@ -1,7 +1,7 @@
 // Store step of Online Quantized Memory on gfx950: 4-bit (or 2-bit) quantization
 // of the frame-group tiles of K and V (paper Sec. 3.4, Eq. 8 and Eq. 9), code
 // packing, and the summary key (mean of the un-quantized keys over the G tokens
-// of the group) in the same pass over K.
+// of the group).
 //
 // Work decomposition.  A lane owns 8 consecutive channels of one token row: one
 // 128-bit load in, one 32-bit word of packed nibbles out, so every load and
@@ -10,25 +10,33 @@
 // all-reduced with DPP lane swaps; the first lane of the group stores its
 // (scale, zero) pair (8 bytes).
 //
-// A K tile (one (frame, layer, head) block of G x d keys) is walked by ONE
-// workgroup of 256 threads, a few token rows per trip, because the summary key
-// needs the column sums over all G rows and a reduction across workgroups costs
-// more than it saves (measured: float64 atomics or written-through partials plus an
-// arrival counter add 10 to 40 % to the kernel).  A V tile has no such coupling:
-// it is cut into equal chunks of at most one trip (7 x 28 rows at 196 x 128) and
-// every chunk is a workgroup of its own (two rows per lane in flight; one row per
-// lane is 40 % slower, three to five rows 5 % slower).  The 1-D grid holds all V chunks first, in the order the
-// tiles lie in memory, then all K tiles.  Measured on MI355X at 28 layers x 32
-// frames x 196 x 128 (474 MB per launch): whole tiles for K and V 100 us; V chunks
-// then K tiles 93 us; K tiles then V chunks 94 us; chunks and tiles interleaved in
-// blocks of 16 to 896 tiles 96 to 99 us (two address streams at once are slower
-// than one after the other); a role pattern with period 8 in the workgroup id
-// (e.g. one K tile after every 7 V chunks) puts all K tiles on one of the eight
-// XCDs, which take workgroups round-robin: 204 us.  Chunked workgroups stream
-// faster because the workgroups in flight then cover one dense, moving address
-// window instead of thousands of tiles at once; the same kernel with every tile
-// chunked and no summary key takes 86 us, an arithmetic-free linear stream of the
-// same byte mix 80 us.
+// A tile (one (frame, layer, K|V, head) block of G x d) is cut into equal chunks of at most
+// two rows per lane (7 x 28 rows at 196 x 128), and every chunk is a workgroup of 256 threads
+// (one row per lane is 40 % slower, three to five rows 5 % slower).  Chunked workgroups stream
+// faster than whole tiles because the workgroups in flight then cover one dense, moving
+// address window.  The summary key needs the column sums over all G rows, and a
+// reduction across workgroups costs more than it saves (float64 atomics or
+// written-through partials plus an arrival counter add 10 to 40 % to the kernel), so there are two forms:
+//
+//   quantize_append_kernel      V in chunks; a K tile is walked by one workgroup, four rows per lane
+//                               and trip, which sums its columns on the way.  Bound by HBM.  The
+//                               1-D grid holds V chunks, then all K tiles, then the last kTail V chunks: a
+//                               walk is long (4 trips at 196 x 128), so without chunks behind them the last
+//                               walks leave the chip half empty.  Medium launches thus start with the K tiles.
+//   quantize_append_cut_kernel  K in chunks as well, and the keys by workgroups of their own that read the
+//                               tensor to average.  For keys taken from another tensor (that one is read once
+//                               either way), and for launches so small that they are bound by the longest chain of
+//                               one workgroup and not by the K tiles that are read twice (cut_append in oqm_dispatch.h).
+//
+// Measured on MI355X, us per call at 28 layers x 4 heads x 196 x 128, bf16.  1 frame (224 tiles): cut 5.2, walk 6.9,
+// one workgroup of 1024 threads per tile 5.9.  Walk by frames, K tiles in front of the last kTail chunks / all V chunks
+// first / the same with two rows per lane and trip: 4 frames 10.8 / 13.2 / 13.9, 8 23.2 / 27 / 26.5, 16 46.4 / 48.0 / 49.0, 32 (474 MB)
+// 90.3 / 90.2 / 91.8 (5.25 TB/s; K cut too, with no key, 86; an arithmetic-free linear stream
+// of the byte mix 80).  kTail of 2048 / 3136 / 4096 / 6272 / 10000 at 8 frames: 25.9 / 24.2 / 23.1 / 22.7 / 22.9; at 32
+// 90.6 / 89.6 / 89.5 / 89.8 / 90.0.  At 32 frames 512 threads x 4 rows 91.6, 256 x 7 rows 94, a whole tile in
+// flight in 512 or 1024 threads 102 / 111; the sums themselves cost nothing; loads without a branch (rows past the end
+// read the last one again) 91.6 and 10.7 instead of 9.7 at 3 frames.  Keys from another tensor, one workgroup per K tile
+// before / cut: 1 frame 12.8 / 5.2, 8 39 / 34, 32 129.9 / 124 us.
 //
 // The kernel moves 2.64 B per element (bf16 in, gs 64).  At HBM speed that leaves
 // room for only about a dozen instructions per element on the plain fp32 vector
@@ -37,206 +45,326 @@
 //   float64 instructions per element of K for the summary key,
 // and the register footprint is kept small: measured, more resident waves help
 // this kernel more than deeper software prefetch does.
+#include <type_traits>
+
 #include "oqm_common.h"
 #include "oqm_device.h"
+#include "oqm_dispatch.h"
 
 namespace oqm {
 namespace {
 
-// Two forms of the kernel.
-// Streaming (more than kShallowTiles tiles): 256 threads, two token rows per lane and trip.  The
-// small register footprint keeps eight workgroups on a compute unit, and V tiles are cut into
-// one-trip chunks (see above).
-// Shallow (a launch of at most three tiles per compute unit, e.g. one frame of a live stream:
-// 224 tiles at 28 layers x 4 heads): such a launch is bound by the dependent memory round trips
-// and the serial arithmetic of the one workgroup that owns a tile, not by bandwidth, so a tile
-// gets 1024 threads with four rows per lane in flight (the whole 196 x 128 tile in one trip).
-// Measured kernel time, shallow against streaming form: 224 tiles 6.4 / 9.8 us (7.7 us with 256
-// threads and 13 rows per lane), 448 tiles 9.6 / 11.3 us, 672 tiles 13.6 / 15.2 us, 896 tiles
-// 17.1 / 17.5 us, 1344 tiles 23.6 / 21.6 us.
-constexpr int kUnrollStream = 2;
-constexpr int kUnrollShallow = 4;
-constexpr int kShallowThreads = 1024;
-constexpr int64_t kShallowTiles = 768;  // three per compute unit
+constexpr int kChunkRows = 2;  // rows per lane of a chunk
+constexpr int kWalkRows = 4;   // rows per lane and trip of a walk
+constexpr int kKeyRows = 4;     // rows per lane in flight where columns are summed (seven: 2 to 4 % slower above 400 tiles, 4 % faster at 224)
+constexpr int kTail = 6272;    // chunks behind the workgroups that walk a tile: three rounds of the chip
 
-// a.v_chunks: workgroups per V tile, a.v_rows_per_chunk token rows each (at most one trip of
-// kUnroll * rows-per-pass rows); 1 = whole tile.
-template <typename IN, int LPG, bool SEPARATE_SUMMARY, int BITS, bool MB, int kUnroll, int NT>
-__global__ void __launch_bounds__(NT) quantize_append_kernel(const QuantArgs a) {
-    constexpr int EB = elem_bytes<IN>::value;
-    constexpr uint32_t CW = BITS;  // bytes of packed codes per lane and row (8 channels)
-    const int H = a.n_kv_heads, d = a.head_dim, G = a.group_tokens;
+// What the kernels need of a QuantArgs, made on the host: offsets in bytes, and the constants their divisions and products take.
+struct AppendArgs {
+    const char *k, *v, *ksum;
+    uint64_t frame_bytes, layer_bytes, head_bytes;  // strides of the inputs
+    char *codes, *meta, *keys;                      // of the first layer and the first appended group
+    uint64_t plane_tiles, key_plane_bytes;          // tiles of a (layer, K|V), bytes of a layer's keys
+    uint32_t row_bytes, tile_code_bytes, tile_meta_bytes, key_bytes;
+    uint32_t heads, layers, items;                  // items: (frame, layer, head), head fastest, the order of a contiguous input
+    int32_t tokens, rows_per_pass, chunks, chunk_rows;
+    uint32_t lanes_per_row, inv_lanes_per_row, inv_heads, inv_layers, inv_chunks;
+    // quantize_append_cut_kernel only: workgroups per key, first block of this launch
+    uint32_t key_parts, inv_key_parts, first_block;
+};
 
-    const int lpr = a.lanes_per_row;  // d / 8
-    const int rpp = a.rows_per_pass;  // token rows per pass of the workgroup: 256 / lpr
-    const int step = kUnroll * rpp;   // token rows per trip
-    const int v_chunks = a.v_chunks;
+// Requests every argument of the address arithmetic in one go: the compiler would load them where they are
+// used, one round trip through the scalar cache after the other.
+__device__ __forceinline__ void request(const AppendArgs& a) {
+    asm volatile("" ::"s"(a.k), "s"(a.v), "s"(a.frame_bytes), "s"(a.layer_bytes), "s"(a.head_bytes), "s"(a.codes), "s"(a.meta),
+                 "s"(a.plane_tiles), "s"(a.row_bytes), "s"(a.tile_code_bytes), "s"(a.tile_meta_bytes), "s"(a.heads), "s"(a.layers),
+                 "s"(a.items), "s"(a.tokens), "s"(a.rows_per_pass), "s"(a.chunks), "s"(a.chunk_rows), "s"(a.lanes_per_row),
+                 "s"(a.inv_lanes_per_row), "s"(a.inv_heads), "s"(a.inv_layers), "s"(a.inv_chunks), "s"(a.keys), "s"(a.key_plane_bytes),
+                 "s"(a.key_bytes));
+}
 
-    // Workgroup id -> role.  [0, items * v_chunks): chunk (id % v_chunks) of the V tile of item
-    // id / v_chunks; after those: the K tile of item id - items * v_chunks.  Items run over
-    // (frame, layer, head), head fastest, which is the order of a contiguous input tensor.
-    const int items = a.n_frames * a.n_layers * H;
-    int item = blockIdx.x, kv = 1, row_begin = 0, row_end = G;
-    if (item >= items * v_chunks) {
-        kv = 0;
-        item -= items * v_chunks;
-    } else if (v_chunks > 1) {
-        const int tile_item = div_by(item, v_chunks, a.inv_v_chunks);
-        row_begin = (item - tile_item * v_chunks) * a.v_rows_per_chunk;
-        row_end = min(G, row_begin + a.v_rows_per_chunk);
-        item = tile_item;
+// Where a lane's rows lie within a tile whose rows go `rpp` to a pass of the workgroup.  32-bit byte offsets
+// (checked on the host) keep the address arithmetic per row to one add.
+template <typename IN, int LPG, int BITS>
+struct Lane {
+    uint32_t in, in_row, code, code_row;  // offset of the lane's first row, distance of two token rows
+    int meta, meta_row;                   // the same in (scale, zero) pairs
+    int row0, wave_row0, rpp, slot;       // first row of the lane and of its wave, rows per pass, place within the row
+    bool active, meta_writer;
+    __device__ __forceinline__ Lane(const AppendArgs& a, int tid) {
+        const int lpr = a.lanes_per_row;  // d / 8
+        rpp = a.rows_per_pass;
+        row0 = div_by(tid, lpr, a.inv_lanes_per_row);
+        slot = tid - row0 * lpr;
+        active = row0 < rpp;
+        wave_row0 = __builtin_amdgcn_readfirstlane(row0);
+        in_row = a.row_bytes;
+        in = (uint32_t)row0 * in_row + (uint32_t)slot * (8u * elem_bytes<IN>::value);
+        code_row = (uint32_t)(lpr * BITS);  // BITS bytes of codes per lane and row
+        code = (uint32_t)row0 * code_row + (uint32_t)(slot * BITS);
+        meta_row = (uint32_t)lpr / LPG;  // quant-groups per token row
+        meta = row0 * meta_row + (uint32_t)slot / LPG;
+        meta_writer = (slot & (LPG - 1)) == 0;
     }
-    const int fl = div_by(item, H, a.inv_heads);
-    const int h = item - fl * H;
-    const int f = div_by(fl, a.n_layers, a.inv_layers);
-    const int li = fl - f * a.n_layers;
-    const int l = a.layer0 + li;
-    const int64_t t = (int64_t)a.first_group + f;
+};
 
-    const int tid = threadIdx.x;
-    const int row0 = div_by(tid, lpr, a.inv_lanes_per_row);
-    const int slot = tid - row0 * lpr;
-    const bool active = row0 < rpp;
-    const int ng = lpr / LPG;       // quant-groups per token row
-    const int wave_row0 = __builtin_amdgcn_readfirstlane(row0);  // lowest row of this wave
-
-    // Tile bases are uniform per workgroup; per-lane offsets inside a tile fit 32 bits
-    // (checked on the host), which keeps the address arithmetic per row to one add.
-    const int64_t in_off = f * a.stride_frame + li * a.stride_layer + h * a.stride_head;
-    const char* src = static_cast<const char*>(kv ? a.v : a.k) + in_off * EB;
-    const int64_t tile = (((int64_t)l * 2 + kv) * a.capacity_groups + t) * H + h;
-    char* codes_t = reinterpret_cast<char*>(a.codes + tile * ((int64_t)G * d * BITS / 8));
-    typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
-    meta_pair* meta_t = reinterpret_cast<meta_pair*>(a.meta) + tile * ((int64_t)G * ng);
-    const uint32_t in_row_bytes = (uint32_t)a.stride_token * EB;
-    const uint32_t in_lane = (uint32_t)row0 * in_row_bytes + (uint32_t)slot * 8u * EB;
-    const uint32_t code_lane = ((uint32_t)row0 * lpr + slot) * CW;
-    const int meta_lane = row0 * ng + slot / LPG;
-    const bool meta_writer = (slot & (LPG - 1)) == 0;
-
-    __shared__ double shared_buf[NT * 8];  // 16 KB at 256 threads, key reduction
-
-    const bool do_sum = (kv == 0);
-    double acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-
-    auto fetch = [&](Raw8<IN> (&dst)[kUnroll], int r0) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int rb = r0 + u * rpp;
-            if (active && rb + row0 < row_end)
-                load_raw(src + (in_lane + (uint32_t)rb * in_row_bytes), dst[u]);
-        }
-    };
-    auto process = [&](const Raw8<IN> (&buf)[kUnroll], int r0) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int rb = r0 + u * rpp;
-            if (rb + wave_row0 >= row_end) break;  // nothing left for this wave (uniform)
-            const bool ok = active && rb + row0 < row_end;
-            float x[8];
-            widen(buf[u], x);  // lanes past the tile compute on stale rows; their results are dropped
-            // Eq. 9: m = min, s = (max - min) / 15 over the quant-group.  All lanes of a
-            // quant-group share one row, so a live lane only ever swaps with live lanes.
-            float mn = x[0], mx = x[0];
-#pragma unroll
-            for (int i = 1; i < 8; ++i) {
-                mn = fminf(mn, x[i]);
-                mx = fmaxf(mx, x[i]);
-            }
-            group_minmax<LPG>(mn, mx);
-            mn = mn + 0.0f;  // never store -0 as a zero point
-            float s = div_levels_exact<BITS>(__fsub_rn(mx, mn));
-            if (!(s >= 1.17549435e-38f)) s = 0.0f;  // flat or sub-normal range: all codes 0
-            meta_pair stored;
-            if constexpr (MB) stored = round_pair_bf16(s, mn);  // the codes follow the rounded pair
-            const float inv = s >= 1.17549435e-38f ? rcp_scale<BITS>(s) : 0.0f;
-            if constexpr (!MB) stored = f32x2{s, mn};
-            float tq[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                tq[i] = __builtin_fmaf(__fsub_rn(x[i], mn), inv, 8388608.0f);
-                if constexpr (MB) tq[i] = clamp_code<BITS>(tq[i]);  // m may lie above the minimum
-            }
-            if (ok) {
-                store_codes8<BITS>(codes_t + (code_lane + (uint32_t)rb * lpr * CW), tq);
-                if (meta_writer) meta_t[meta_lane + rb * ng] = stored;
-                if (!SEPARATE_SUMMARY && do_sum) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
-                }
-            }
-        }
-    };
-
-    Raw8<IN> buf[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) zero_raw(buf[u]);  // defined contents for rows never loaded
-    for (int r0 = row_begin; r0 < row_end; r0 += step) {
-        if (r0 + wave_row0 >= row_end) break;  // nothing left for this wave (uniform)
-        fetch(buf, r0);
-        process(buf, r0);
+struct Item {
+    uint32_t f, li, h;
+    __device__ __forceinline__ Item(const AppendArgs& a, uint32_t item) {
+        const uint32_t fl = div_by(item, a.heads, a.inv_heads);
+        h = item - fl * a.heads;
+        f = div_by(fl, a.layers, a.inv_layers);
+        li = fl - f * a.layers;
     }
+    __device__ __forceinline__ uint64_t input(const AppendArgs& a) const {
+        return f * a.frame_bytes + li * a.layer_bytes + h * a.head_bytes;
+    }
+    __device__ __forceinline__ float* key(const AppendArgs& a) const {
+        return reinterpret_cast<float*>(a.keys + li * a.key_plane_bytes + (uint64_t)(f * a.heads + h) * a.key_bytes);
+    }
+};
 
-    if (!do_sum) return;  // uniform per workgroup
-
-    if (SEPARATE_SUMMARY) {
-        // The keys to average come from another tensor (e.g. taken before the rotary
-        // embedding): one more pass, over that tensor only.
-        const char* ssrc = static_cast<const char*>(a.ksum) + in_off * EB;
-        for (int row = row0; active && row < G; row += rpp) {
-            float x[8];
-            load8(ssrc + ((int64_t)row * a.stride_token + slot * 8) * EB, IN{}, x);
+// Rows r0 + u * rpp of the lane, u < U, as far as they lie before row_end; zeros otherwise.
+template <int U, typename IN, typename LANE>
+__device__ __forceinline__ void fetch_rows(const char* src, const LANE& n, int r0, int row_end, Raw8<IN> (&buf)[U]) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
+    for (int u = 0; u < U; ++u) {
+        zero_raw(buf[u]);
+        const int rb = r0 + u * n.rpp;
+        if (n.active && rb + n.row0 < row_end) load_raw(src + (n.in + (uint32_t)rb * n.in_row), buf[u]);
+    }
+}
+
+// Where a tile is stored.
+template <bool MB>
+struct Stored {
+    char* codes;
+    typename MetaPair<MB>::type* meta;  // two float32, or two bfloat16 in one word
+    __device__ __forceinline__ Stored(const AppendArgs& a, const Item& t, uint32_t kv) {
+        const uint64_t tile = (t.li * 2u + kv) * a.plane_tiles + (t.f * a.heads + t.h);
+        codes = a.codes + tile * a.tile_code_bytes;
+        meta = reinterpret_cast<typename MetaPair<MB>::type*>(a.meta + tile * a.tile_meta_bytes);
+    }
+};
+
+// Quantizes and stores rows that fetch_rows has fetched; with SUM adds them to the lane's column sums.
+template <bool SUM, int BITS, bool MB, int LPG, int U, typename IN>
+__device__ __forceinline__ void quantize_rows(const Stored<MB>& to, const Raw8<IN> (&buf)[U], const Lane<IN, LPG, BITS>& n, int r0,
+                                              int row_end, double (&acc)[8]) {
+    typedef typename MetaPair<MB>::type meta_pair;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int rb = r0 + u * n.rpp;
+        if (rb + n.wave_row0 >= row_end) break;  // nothing left for this wave (uniform)
+        float x[8];
+        widen(buf[u], x);
+        // Eq. 9: m = min, s = (max - min) / 15 over the quant-group.  All lanes of a
+        // quant-group share one row, so a live lane only ever swaps with live lanes.
+        float mn = x[0], mx = x[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) {
+            mn = fminf(mn, x[i]);
+            mx = fmaxf(mx, x[i]);
+        }
+        group_minmax<LPG>(mn, mx);
+        mn = mn + 0.0f;  // never store -0 as a zero point
+        float s = div_levels_exact<BITS>(__fsub_rn(mx, mn));
+        if (!(s >= 1.17549435e-38f)) s = 0.0f;  // flat or sub-normal range: all codes 0
+        meta_pair stored;
+        if constexpr (MB) stored = round_pair_bf16(s, mn);  // the codes follow the rounded pair
+        const float inv = s >= 1.17549435e-38f ? rcp_scale<BITS>(s) : 0.0f;
+        if constexpr (!MB) stored = f32x2{s, mn};
+        float tq[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            tq[i] = __builtin_fmaf(__fsub_rn(x[i], mn), inv, 8388608.0f);
+            if constexpr (MB) tq[i] = clamp_code<BITS>(tq[i]);  // m may lie above the minimum
+        }
+        if (n.active && rb + n.row0 < row_end) {
+            store_codes8<BITS>(to.codes + (n.code + (uint32_t)rb * n.code_row), tq);
+            if (n.meta_writer) to.meta[n.meta + rb * n.meta_row] = stored;
+            if constexpr (SUM) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
+            }
         }
     }
+}
 
-    // Summary key: column sums over the rpp row slots of the workgroup, in float64.
-    if (active) {
+// Summary key from the column sums of the lanes: over the rows of a wave by lane swaps (64 / LPR rows of
+// LPR lanes each), over the waves in LDS.  One wave's rows hold `8 * LPR` channels, slot * 8 onwards in lane `slot`.
+template <int LPR>
+__device__ __forceinline__ void write_key_by_waves(double (&acc)[8], int slot, double* shared, float* key, int G) {
+    constexpr int CH = LPR / 8, D = 8 * LPR;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    reduce_rows<LPR>(acc, [](double p, double q) { return p + q; });
 #pragma unroll
-        for (int i = 0; i < 8; ++i) shared_buf[row0 * d + i * lpr + slot] = acc[i];
+    for (int j = 0; j < CH; ++j) shared[wave * D + slot * 8 + (lane / LPR) * CH + j] = acc[j];
+    __syncthreads();
+    if (threadIdx.x < D) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) sum += shared[w * D + threadIdx.x];
+        key[threadIdx.x] = (float)(sum / (double)G);
+    }
+}
+
+template <typename LANE>
+__device__ __forceinline__ void write_key(const AppendArgs& a, const LANE& n, double (&acc)[8], double* shared, float* key) {
+    const int lpr = a.lanes_per_row, d = lpr * 8, G = a.tokens;
+    if (lpr == 16) return write_key_by_waves<16>(acc, n.slot, shared, key, G);  // uniform, like the next two
+    if (lpr == 8) return write_key_by_waves<8>(acc, n.slot, shared, key, G);
+    if (lpr == 32) return write_key_by_waves<32>(acc, n.slot, shared, key, G);
+    if (n.active) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) shared[n.row0 * d + i * lpr + n.slot] = acc[i];
     }
     __syncthreads();
-    float* key = a.keys + (((int64_t)l * a.capacity_groups + t) * H + h) * d;
     // position q = i * lpr + slot holds channel slot * 8 + i: the lanes of a wave write
     // consecutive doubles (channel order would put them 64 bytes apart: 16-way bank conflicts)
-    for (int q = tid; q < d; q += NT) {
+    for (int q = threadIdx.x; q < d; q += kBlock) {
         double sum = 0.0;
-        for (int r = 0; r < rpp; ++r) sum += shared_buf[r * d + q];
+        for (int r = 0; r < n.rpp; ++r) sum += shared[r * d + q];
         key[(q % lpr) * 8 + q / lpr] = (float)(sum / (double)G);
     }
 }
 
 template <typename IN, int LPG, int BITS, bool MB>
-hipError_t launch_b(const QuantArgs& args, hipStream_t s) {
-    QuantArgs a = args;
-    const int64_t items = (int64_t)a.n_kv_heads * a.n_layers * a.n_frames;
-    const bool shallow = 2 * items <= kShallowTiles && a.ksum == a.k;
-    // V tiles: one workgroup per trip of the streaming form; whole tiles in the shallow form
-    const int rows_per_trip = kUnrollStream * (kBlock / (a.head_dim / 8));
-    const int v_chunks = shallow ? 1 : (a.group_tokens + rows_per_trip - 1) / rows_per_trip;
-    const int64_t blocks = items * (v_chunks + 1);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;  // the API layer has refused this already
-    a.v_chunks = v_chunks;
-    a.v_rows_per_chunk = (a.group_tokens + v_chunks - 1) / v_chunks;  // equal chunks, each within one trip
-    a.lanes_per_row = (uint32_t)a.head_dim / 8u;
-    const int threads = shallow ? kShallowThreads : kBlock;
-    a.rows_per_pass = (uint32_t)threads / a.lanes_per_row;
+__global__ void __launch_bounds__(kBlock) quantize_append_kernel(const AppendArgs a) {
+    __shared__ double shared[kBlock * 8];  // key reduction
+    request(a);
+    const int chunks = a.items * a.chunks, first_walk = max(0, chunks - kTail);
+    // One address computation for both roles: a short launch waits for every line of code it has not run before.
+    int id = blockIdx.x, row_begin = 0, row_end = a.tokens;
+    const bool walk = id >= first_walk && id < first_walk + (int)a.items;
+    if (walk) {
+        id -= first_walk;
+    } else {
+        if (id >= first_walk) id -= a.items;
+        const int item = div_by(id, a.chunks, a.inv_chunks);
+        row_begin = (id - item * a.chunks) * a.chunk_rows;
+        row_end = min(row_end, row_begin + a.chunk_rows);
+        id = item;
+    }
+    const Item t(a, id);
+    const Stored<MB> to(a, t, walk ? 0u : 1u);
+    const char* src = (walk ? a.k : a.v) + t.input(a);
+    const Lane<IN, LPG, BITS> n(a, threadIdx.x);
+    double acc[8];
+    if (!walk) {
+        Raw8<IN> buf[kChunkRows];
+        fetch_rows(src, n, row_begin, row_end, buf);
+        quantize_rows<false>(to, buf, n, row_begin, row_end, acc);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+    for (int r0 = 0; r0 + n.wave_row0 < a.tokens; r0 += kWalkRows * n.rpp) {
+        Raw8<IN> buf[kWalkRows];
+        fetch_rows(src, n, r0, a.tokens, buf);
+        quantize_rows<true>(to, buf, n, r0, a.tokens, acc);
+    }
+    write_key(a, n, acc, shared, t.key(a));
+}
+
+// Grid: chunks of all K tiles, then of all V tiles, and in front of the last kTail of them the workgroups that
+// make the keys, key_parts per K tile of 64 channels each, or one.
+template <typename IN, int LPG, int BITS, bool MB>
+__global__ void __launch_bounds__(kBlock) quantize_append_cut_kernel(const AppendArgs a) {
+    __shared__ double shared[kBlock * 8];  // key reduction
+    request(a);
+    const int chunks = 2 * a.items * a.chunks, key_blocks = a.items * a.key_parts, first_key = max(0, chunks - kTail);
+    int id = blockIdx.x + a.first_block;
+    Lane<IN, LPG, BITS> n(a, threadIdx.x);
+    if (id < first_key || id >= first_key + key_blocks) {
+        if (id >= first_key) id -= key_blocks;
+        const uint32_t tile = div_by(id, a.chunks, a.inv_chunks), kv = tile < a.items ? 0u : 1u;
+        const Item t(a, tile - kv * a.items);
+        const Stored<MB> to(a, t, kv);
+        const int row_begin = (id - (int)tile * a.chunks) * a.chunk_rows, row_end = min(a.tokens, row_begin + a.chunk_rows);
+        Raw8<IN> buf[kChunkRows];
+        double unused[8];
+        fetch_rows((kv ? a.v : a.k) + t.input(a), n, row_begin, row_end, buf);
+        quantize_rows<false>(to, buf, n, row_begin, row_end, unused);
+        return;
+    }
+    id -= first_key;
+    const uint32_t item = div_by(id, a.key_parts, a.inv_key_parts), part = id - item * a.key_parts;
+    const Item t(a, item);
+    const char* src = a.ksum + t.input(a);
+    if (a.key_parts > 1) {  // eight lanes per row
+        n.rpp = kBlock / 8;
+        n.row0 = threadIdx.x >> 3;
+        n.slot = threadIdx.x & 7;
+        n.active = true;
+        n.wave_row0 = __builtin_amdgcn_readfirstlane(n.row0);
+        n.in = (uint32_t)n.row0 * n.in_row + (part * 64 + n.slot * 8) * (uint32_t)elem_bytes<IN>::value;
+    }
+    double acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+    for (int r0 = 0; r0 + n.wave_row0 < a.tokens; r0 += kKeyRows * n.rpp) {
+        Raw8<IN> buf[kKeyRows];
+        fetch_rows(src, n, r0, a.tokens, buf);
+#pragma unroll
+        for (int u = 0; u < kKeyRows; ++u) {
+            float x[8];
+            widen(buf[u], x);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
+        }
+    }
+    if (a.key_parts > 1) write_key_by_waves<8>(acc, n.slot, shared, t.key(a) + part * 64, a.tokens);
+    else write_key(a, n, acc, shared, t.key(a));
+}
+
+template <typename IN, int LPG, int BITS, bool MB>
+hipError_t launch_b(const QuantArgs& q, hipStream_t s) {
+    constexpr uint32_t EB = elem_bytes<IN>::value;
+    const int64_t items = (int64_t)q.n_kv_heads * q.n_layers * q.n_frames;
+    AppendArgs a{};
+    a.k = static_cast<const char*>(q.k);
+    a.v = static_cast<const char*>(q.v);
+    a.ksum = static_cast<const char*>(q.ksum);
+    a.frame_bytes = (uint64_t)q.stride_frame * EB;
+    a.layer_bytes = (uint64_t)q.stride_layer * EB;
+    a.head_bytes = (uint64_t)q.stride_head * EB;
+    a.row_bytes = (uint32_t)q.stride_token * EB;
+    a.tokens = q.group_tokens;
+    a.lanes_per_row = (uint32_t)q.head_dim / 8u;
+    a.tile_code_bytes = (uint32_t)q.group_tokens * a.lanes_per_row * BITS;
+    a.tile_meta_bytes = (uint32_t)q.group_tokens * (a.lanes_per_row / LPG) * (uint32_t)sizeof(typename MetaPair<MB>::type);
+    a.key_bytes = (uint32_t)q.head_dim * sizeof(float);
+    a.plane_tiles = (uint64_t)q.capacity_groups * q.n_kv_heads;
+    a.key_plane_bytes = a.plane_tiles * a.key_bytes;
+    const uint64_t first = (uint64_t)q.first_group * q.n_kv_heads;  // tiles before the appended ones of a plane
+    a.codes = reinterpret_cast<char*>(q.codes) + (2u * q.layer0 * a.plane_tiles + first) * a.tile_code_bytes;
+    a.meta = static_cast<char*>(q.meta) + (2u * q.layer0 * a.plane_tiles + first) * a.tile_meta_bytes;
+    a.keys = reinterpret_cast<char*>(q.keys) + q.layer0 * a.key_plane_bytes + first * a.key_bytes;
+    a.heads = (uint32_t)q.n_kv_heads;
+    a.layers = (uint32_t)q.n_layers;
+    a.rows_per_pass = (int32_t)(kBlock / a.lanes_per_row);
+    a.chunks = (a.tokens + kChunkRows * a.rows_per_pass - 1) / (kChunkRows * a.rows_per_pass);
+    a.chunk_rows = (a.tokens + a.chunks - 1) / a.chunks;  // equal chunks
     a.inv_lanes_per_row = reciprocal_u32(a.lanes_per_row);
-    a.inv_heads = reciprocal_u32((uint32_t)a.n_kv_heads);
-    a.inv_layers = reciprocal_u32((uint32_t)a.n_layers);
-    a.inv_v_chunks = reciprocal_u32((uint32_t)v_chunks);
-    const dim3 grid((unsigned)blocks);
-    if (a.ksum != a.k)
-        quantize_append_kernel<IN, LPG, true, BITS, MB, kUnrollStream, kBlock><<<grid, dim3(kBlock), 0, s>>>(a);
-    else if (shallow)
-        quantize_append_kernel<IN, LPG, false, BITS, MB, kUnrollShallow, kShallowThreads>
-            <<<grid, dim3(kShallowThreads), 0, s>>>(a);
-    else
-        quantize_append_kernel<IN, LPG, false, BITS, MB, kUnrollStream, kBlock><<<grid, dim3(kBlock), 0, s>>>(a);
-    return hipGetLastError();
+    a.inv_heads = reciprocal_u32(a.heads);
+    a.inv_layers = reciprocal_u32(a.layers);
+    a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
+    if (items * (a.chunks + 1) > kMostBlocks) return hipErrorInvalidConfiguration;
+    a.items = (uint32_t)items;
+    if (!cut_append(q, sizeof(Raw8<IN>) <= 16)) {
+        quantize_append_kernel<IN, LPG, BITS, MB><<<dim3((unsigned)(items * (a.chunks + 1))), dim3(kBlock), 0, s>>>(a);
+        return hipGetLastError();
+    }
+    a.key_parts = (uint32_t)key_parts(q);
+    a.inv_key_parts = reciprocal_u32(a.key_parts);
+    const int64_t blocks = items * (2 * a.chunks + (int)a.key_parts);  // below 2^26: at most three times those above
+    for (int64_t b = 0; b < blocks; b += kMostBlocks) {  // one launch, except for millions of tiles
+        a.first_block = (uint32_t)b;
+        quantize_append_cut_kernel<IN, LPG, BITS, MB><<<dim3((unsigned)min(blocks - b, kMostBlocks)), dim3(kBlock), 0, s>>>(a);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 template <typename IN, int LPG>

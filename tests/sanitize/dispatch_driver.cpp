@@ -67,6 +67,44 @@ static void fold() {
     CHECK(fold_slots(a) == 0);
 }
 
+static void append() {
+    QuantArgs a{};
+    char k = 0, other = 0;
+    a.k = a.ksum = &k, a.n_kv_heads = 4, a.n_layers = 2, a.head_dim = 128, a.group_tokens = 196;
+    for (bool is_16_bit : {false, true}) {
+        a.n_frames = is_16_bit ? 24 : 16;             // 384 or 256 tiles of K and V
+        CHECK(cut_append(a, is_16_bit));
+        ++a.n_frames;
+        CHECK(!cut_append(a, is_16_bit));
+        a.ksum = &other;                              // keys of another tensor: at any size
+        CHECK(cut_append(a, is_16_bit));
+        a.ksum = &k;
+    }
+    a.n_frames = 1;
+    for (int d : {8, 64, 80, 128, 2048}) {            // a walk of one trip is no longer than a chunk
+        a.head_dim = d;
+        a.group_tokens = 4 * (256 / (d / 8));
+        CHECK(!cut_append(a, true));
+        ++a.group_tokens;
+        CHECK(cut_append(a, true));
+    }
+    a.n_frames = 16, a.head_dim = 128;                // 128 keys of two parts
+    CHECK(key_parts(a) == 2);
+    a.n_frames = 17;
+    CHECK(key_parts(a) == 1);
+    a.n_frames = 1;
+    for (int d : {8, 80, 96, 1032}) {
+        a.head_dim = d;
+        CHECK(key_parts(a) == 1);
+    }
+    a.head_dim = 192;
+    CHECK(key_parts(a) == 3);
+    a.head_dim = 2048;
+    CHECK(key_parts(a) == 32);
+    a.n_layers = 32767, a.n_kv_heads = 1023, a.n_frames = 65535;
+    CHECK(key_parts(a) == 1 && !cut_append(a, true));
+}
+
 static void split() {
     ScoreArgs a{};
     auto tiles = [&](int n_layers, int n_groups, int t_q) {
@@ -165,6 +203,7 @@ static void gather() {
 
 int main() {
     fold();
+    append();
     split();
     rows();
     gather();
