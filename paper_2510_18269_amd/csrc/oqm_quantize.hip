@@ -47,8 +47,7 @@
 // this kernel more than deeper software prefetch does.
 #include <type_traits>
 
-#include "oqm_common.h"
-#include "oqm_device.h"
+#include "oqm_append.h"
 #include "oqm_dispatch.h"
 
 namespace oqm {
@@ -58,30 +57,6 @@ constexpr int kChunkRows = 2;  // rows per lane of a chunk
 constexpr int kWalkRows = 4;   // rows per lane and trip of a walk
 constexpr int kKeyRows = 4;     // rows per lane in flight where columns are summed (seven: 2 to 4 % slower above 400 tiles, 4 % faster at 224)
 constexpr int kTail = 6272;    // chunks behind the workgroups that walk a tile: three rounds of the chip
-
-// What the kernels need of a QuantArgs, made on the host: offsets in bytes, and the constants their divisions and products take.
-struct AppendArgs {
-    const char *k, *v, *ksum;
-    uint64_t frame_bytes, layer_bytes, head_bytes;  // strides of the inputs
-    char *codes, *meta, *keys;                      // of the first layer and the first appended group
-    uint64_t plane_tiles, key_plane_bytes;          // tiles of a (layer, K|V), bytes of a layer's keys
-    uint32_t row_bytes, tile_code_bytes, tile_meta_bytes, key_bytes;
-    uint32_t heads, layers, items;                  // items: (frame, layer, head), head fastest, the order of a contiguous input
-    int32_t tokens, rows_per_pass, chunks, chunk_rows;
-    uint32_t lanes_per_row, inv_lanes_per_row, inv_heads, inv_layers, inv_chunks;
-    // quantize_append_cut_kernel only: workgroups per key, first block of this launch
-    uint32_t key_parts, inv_key_parts, first_block;
-};
-
-// Requests every argument of the address arithmetic in one go: the compiler would load them where they are
-// used, one round trip through the scalar cache after the other.
-__device__ __forceinline__ void request(const AppendArgs& a) {
-    asm volatile("" ::"s"(a.k), "s"(a.v), "s"(a.frame_bytes), "s"(a.layer_bytes), "s"(a.head_bytes), "s"(a.codes), "s"(a.meta),
-                 "s"(a.plane_tiles), "s"(a.row_bytes), "s"(a.tile_code_bytes), "s"(a.tile_meta_bytes), "s"(a.heads), "s"(a.layers),
-                 "s"(a.items), "s"(a.tokens), "s"(a.rows_per_pass), "s"(a.chunks), "s"(a.chunk_rows), "s"(a.lanes_per_row),
-                 "s"(a.inv_lanes_per_row), "s"(a.inv_heads), "s"(a.inv_layers), "s"(a.inv_chunks), "s"(a.keys), "s"(a.key_plane_bytes),
-                 "s"(a.key_bytes));
-}
 
 // Where a lane's rows lie within a tile whose rows go `rpp` to a pass of the workgroup.  32-bit byte offsets
 // (checked on the host) keep the address arithmetic per row to one add.
@@ -108,22 +83,6 @@ struct Lane {
     }
 };
 
-struct Item {
-    uint32_t f, li, h;
-    __device__ __forceinline__ Item(const AppendArgs& a, uint32_t item) {
-        const uint32_t fl = div_by(item, a.heads, a.inv_heads);
-        h = item - fl * a.heads;
-        f = div_by(fl, a.layers, a.inv_layers);
-        li = fl - f * a.layers;
-    }
-    __device__ __forceinline__ uint64_t input(const AppendArgs& a) const {
-        return f * a.frame_bytes + li * a.layer_bytes + h * a.head_bytes;
-    }
-    __device__ __forceinline__ float* key(const AppendArgs& a) const {
-        return reinterpret_cast<float*>(a.keys + li * a.key_plane_bytes + (uint64_t)(f * a.heads + h) * a.key_bytes);
-    }
-};
-
 // Rows r0 + u * rpp of the lane, u < U, as far as they lie before row_end; zeros otherwise.
 template <int U, typename IN, typename LANE>
 __device__ __forceinline__ void fetch_rows(const char* src, const LANE& n, int r0, int row_end, Raw8<IN> (&buf)[U]) {
@@ -134,18 +93,6 @@ __device__ __forceinline__ void fetch_rows(const char* src, const LANE& n, int r
         if (n.active && rb + n.row0 < row_end) load_raw(src + (n.in + (uint32_t)rb * n.in_row), buf[u]);
     }
 }
-
-// Where a tile is stored.
-template <bool MB>
-struct Stored {
-    char* codes;
-    typename MetaPair<MB>::type* meta;  // two float32, or two bfloat16 in one word
-    __device__ __forceinline__ Stored(const AppendArgs& a, const Item& t, uint32_t kv) {
-        const uint64_t tile = (t.li * 2u + kv) * a.plane_tiles + (t.f * a.heads + t.h);
-        codes = a.codes + tile * a.tile_code_bytes;
-        meta = reinterpret_cast<typename MetaPair<MB>::type*>(a.meta + tile * a.tile_meta_bytes);
-    }
-};
 
 // Quantizes and stores rows that fetch_rows has fetched; with SUM adds them to the lane's column sums.
 template <bool SUM, int BITS, bool MB, int LPG, int U, typename IN>
@@ -320,35 +267,11 @@ __global__ void __launch_bounds__(kBlock) quantize_append_cut_kernel(const Appen
 
 template <typename IN, int LPG, int BITS, bool MB>
 hipError_t launch_b(const QuantArgs& q, hipStream_t s) {
-    constexpr uint32_t EB = elem_bytes<IN>::value;
     const int64_t items = (int64_t)q.n_kv_heads * q.n_layers * q.n_frames;
-    AppendArgs a{};
-    a.k = static_cast<const char*>(q.k);
-    a.v = static_cast<const char*>(q.v);
-    a.ksum = static_cast<const char*>(q.ksum);
-    a.frame_bytes = (uint64_t)q.stride_frame * EB;
-    a.layer_bytes = (uint64_t)q.stride_layer * EB;
-    a.head_bytes = (uint64_t)q.stride_head * EB;
-    a.row_bytes = (uint32_t)q.stride_token * EB;
-    a.tokens = q.group_tokens;
-    a.lanes_per_row = (uint32_t)q.head_dim / 8u;
-    a.tile_code_bytes = (uint32_t)q.group_tokens * a.lanes_per_row * BITS;
-    a.tile_meta_bytes = (uint32_t)q.group_tokens * (a.lanes_per_row / LPG) * (uint32_t)sizeof(typename MetaPair<MB>::type);
-    a.key_bytes = (uint32_t)q.head_dim * sizeof(float);
-    a.plane_tiles = (uint64_t)q.capacity_groups * q.n_kv_heads;
-    a.key_plane_bytes = a.plane_tiles * a.key_bytes;
-    const uint64_t first = (uint64_t)q.first_group * q.n_kv_heads;  // tiles before the appended ones of a plane
-    a.codes = reinterpret_cast<char*>(q.codes) + (2u * q.layer0 * a.plane_tiles + first) * a.tile_code_bytes;
-    a.meta = static_cast<char*>(q.meta) + (2u * q.layer0 * a.plane_tiles + first) * a.tile_meta_bytes;
-    a.keys = reinterpret_cast<char*>(q.keys) + q.layer0 * a.key_plane_bytes + first * a.key_bytes;
-    a.heads = (uint32_t)q.n_kv_heads;
-    a.layers = (uint32_t)q.n_layers;
+    AppendArgs a = append_args(q, elem_bytes<IN>::value, (uint32_t)q.group_tokens * (uint32_t)(q.head_dim / q.qgroup));
     a.rows_per_pass = (int32_t)(kBlock / a.lanes_per_row);
     a.chunks = (a.tokens + kChunkRows * a.rows_per_pass - 1) / (kChunkRows * a.rows_per_pass);
     a.chunk_rows = (a.tokens + a.chunks - 1) / a.chunks;  // equal chunks
-    a.inv_lanes_per_row = reciprocal_u32(a.lanes_per_row);
-    a.inv_heads = reciprocal_u32(a.heads);
-    a.inv_layers = reciprocal_u32(a.layers);
     a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
     if (items * (a.chunks + 1) > kMostBlocks) return hipErrorInvalidConfiguration;
     a.items = (uint32_t)items;
@@ -358,13 +281,9 @@ hipError_t launch_b(const QuantArgs& q, hipStream_t s) {
     }
     a.key_parts = (uint32_t)key_parts(q);
     a.inv_key_parts = reciprocal_u32(a.key_parts);
-    const int64_t blocks = items * (2 * a.chunks + (int)a.key_parts);  // below 2^26: at most three times those above
-    for (int64_t b = 0; b < blocks; b += kMostBlocks) {  // one launch, except for millions of tiles
-        a.first_block = (uint32_t)b;
-        quantize_append_cut_kernel<IN, LPG, BITS, MB><<<dim3((unsigned)min(blocks - b, kMostBlocks)), dim3(kBlock), 0, s>>>(a);
-        if (hipError_t e = hipGetLastError()) return e;
-    }
-    return hipSuccess;
+    return launch_blocks(a, items * (2 * a.chunks + (int)a.key_parts), kBlock, [&](dim3 grid, dim3 block) {  // at most three times those above
+        quantize_append_cut_kernel<IN, LPG, BITS, MB><<<grid, block, 0, s>>>(a);
+    });
 }
 
 template <typename IN, int LPG>

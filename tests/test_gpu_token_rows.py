@@ -2,8 +2,8 @@
 
 The host takes head_dim 64, 128 and 256 to the form whose waves hold a tile in registers (8, 16 or
 32 lanes per token row; 8, 4 or 2 rows per wave and pass; rows per lane in templates of 4, 6, 7, 8 and, for
-16-bit inputs, 13; 1 to 4 waves); every other head_dim, a taller tile and a separate summary source to the general form
-(rows in registers up to 4 / 8 / 13 passes, read twice above).  Codes, scale / zero and
+16-bit inputs, 13; 1 to 4 waves); every other head_dim and a taller tile to the general form
+(rows in registers up to 4 / 8 / 13 passes, read twice above).  A separate summary source has workgroups of its own in both.  Codes, scale / zero and
 dequantized values are bit-exact against the oracle, summary keys within one float32 ulp."""
 import pytest
 import torch
@@ -43,8 +43,8 @@ def _run(oqm, d, G, dt, bits, meta, sep, seed, token_major=False):
 
 
 # rows per pass of one wave: 8, 4, 2; G as passes * rows (exact, one short, one over) at the
-# template edges 4 | 6 | 7 | 8 rows with one wave, then two to four, 13 rows and the general form.  Only tiles
-# without a summary source of their own are held by row waves; the same sizes with one run in the general form.
+# template edges 4 | 6 | 7 | 8 rows with one wave, then two to four, 13 rows and the general form, without and with a
+# summary source of its own.
 @pytest.mark.parametrize("dt", ("bf16", "f16", "f32"))
 @pytest.mark.parametrize("d", (64, 128, 256))
 def test_tiles_held_by_row_waves(oqm, d, dt):
