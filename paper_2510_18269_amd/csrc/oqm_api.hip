@@ -260,6 +260,7 @@ size_t tom_oqm_score_workspace_bytes(const tom_oqm_t* h, int32_t n_layers, int32
                                      int32_t path, int32_t want_token_scores) {
     if (!h || n_layers < 0 || n_layers > h->cfg.n_layers || t_q < 1 || t_q > kMaxQueryTokens) return 0;
     const size_t hd = (size_t)h->cfg.n_kv_heads * h->cfg.head_dim;
+    // q-bar, and a double per (layer, KV head) that no kernel uses: what callers allocate stays the same
     size_t doubles = (size_t)n_layers * hd + (size_t)n_layers * h->cfg.n_kv_heads;
     doubles = (doubles + 1) & ~(size_t)1;
     if (resolve_path(path, want_token_scores != 0) == TOM_SCORE_TOKEN_GEMM)
@@ -307,7 +308,6 @@ static tom_status_t score_impl(const tom_oqm_t* h, int32_t layer0, int32_t n_lay
     a.scores = scores;
     a.token_scores = token_scores;
     a.ws_qbar = static_cast<double*>(workspace);
-    a.ws_qnorm2 = a.ws_qbar + (size_t)n_layers * hd;
     size_t used = (size_t)n_layers * hd + (size_t)n_layers * c.n_kv_heads;
     used = (used + 1) & ~(size_t)1;
     a.ws_qtok = a.ws_qbar + used;

@@ -95,7 +95,6 @@ struct ScoreArgs {
     float* scores;      // [n_layers][score_stride]
     float* token_scores;
     double* ws_qbar;    // [n_layers][H_k*d]
-    double* ws_qnorm2;  // [n_layers][H_k] partial squared norms of q-bar
     double* ws_qtok;    // [n_layers][T_q][H_k*d] (TOKEN_GEMM only)
     int64_t score_stride;
     int32_t n_kv_heads, n_q_heads, head_dim, capacity_groups;

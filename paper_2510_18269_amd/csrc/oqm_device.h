@@ -150,13 +150,6 @@ __device__ __forceinline__ void spread_rows(float (&v)[8]) {
     }
 }
 
-// Sum of a double over all 64 lanes of the wave (result valid in every lane).
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // ---- loading 8 consecutive elements as float32 -----------------------------
 // p must be 16-byte aligned.  Widening bf16 / f16 to float32 is exact.
 __device__ __forceinline__ void load8(const void* p, In_bf16, float (&x)[8]) {

@@ -14,6 +14,8 @@
 // Everything accumulates in float64 (the CDNA vector and matrix pipes run it at
 // full rate), so the float32 scores handed to top-k agree with a float64
 // reference up to the final rounding, and the selected indices with them.
+#include <type_traits>
+
 #include "oqm_common.h"
 #include "oqm_device.h"
 #include "oqm_dispatch.h"
@@ -21,106 +23,14 @@
 namespace oqm {
 namespace {
 
-// ------------------------------------------------------------------ query fold
-// grid (H_k, n_layers); 256 threads = (256 / (d/8)) token lanes x (d/8) channel lanes.
-template <typename QT>
-__global__ void __launch_bounds__(kBlock) query_fold_kernel(const ScoreArgs a, const int want_tokens) {
-    constexpr int EB = elem_bytes<QT>::value;
-    const int h = blockIdx.x, li = blockIdx.y;
-    const int d = a.head_dim, H = a.n_kv_heads, Hq = a.n_q_heads, Tq = a.t_q;
-    const int r = Hq / H;
-    const int64_t HD = (int64_t)H * d;
-    const int lpr = d >> 3;
-    const int jn = kBlock / lpr;
-    const int tid = threadIdx.x;
-    const int jl = tid / lpr;
-    const int slot = tid - jl * lpr;
-    const bool active = jl < jn;
-    const char* q = static_cast<const char*>(a.q);
-
-    double acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-    const double inv_r = 1.0 / (double)r;
-    if (active) {
-        // Two tokens per trip; for GQA blocks of up to 8 heads all their loads are issued
-        // before the first is used (one memory round trip for T_q <= 2 * jn).
-        constexpr int kTok = 2, kHeads = 8;
-        for (int j0 = jl; j0 < Tq; j0 += kTok * jn) {
-            double qt[kTok][8];
-#pragma unroll
-            for (int u = 0; u < kTok; ++u)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) qt[u][i] = 0.0;
-            for (int g0 = 0; g0 < r; g0 += kHeads) {
-                Raw8<QT> raw[kTok][kHeads];
-#pragma unroll
-                for (int u = 0; u < kTok; ++u) {
-                    const int j = j0 + u * jn;
-#pragma unroll
-                    for (int g = 0; g < kHeads; ++g) {
-                        zero_raw(raw[u][g]);
-                        if (j < Tq && g0 + g < r) {
-                            const int64_t off =
-                                (((int64_t)li * Hq + (h * r + g0 + g)) * Tq + j) * d + slot * 8;
-                            load_raw(q + off * EB, raw[u][g]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kTok; ++u)
-#pragma unroll
-                    for (int g = 0; g < kHeads; ++g) {
-                        float x[8];
-                        widen(raw[u][g], x);  // heads past the block and tokens past T_q were zero-filled
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) qt[u][i] += (double)x[i];
-                    }
-            }
-#pragma unroll
-            for (int u = 0; u < kTok; ++u) {
-                const int j = j0 + u * jn;
-                if (j >= Tq) break;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    qt[u][i] = qt[u][i] * inv_r;
-                    acc[i] += qt[u][i];
-                }
-                if (want_tokens) {
-                    double* dst = a.ws_qtok + ((int64_t)li * Tq + j) * HD + (int64_t)h * d + slot * 8;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) dst[i] = qt[u][i];
-                }
-            }
-        }
-    }
-    __shared__ double red[kBlock * 8];
-    __shared__ double wsum[kBlock / 64];
-    if (active) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) red[jl * d + i * lpr + slot] = acc[i];  // position order: no bank conflicts
-    }
-    __syncthreads();
-    double sq = 0.0;
-    for (int p = tid; p < d; p += kBlock) {  // position p = i * lpr + slot holds channel slot * 8 + i
-        double sum = 0.0;
-        for (int j = 0; j < jn; ++j) sum += red[j * d + p];
-        const double qb = sum * (1.0 / (double)Tq);
-        const int c = (p % lpr) * 8 + p / lpr;
-        a.ws_qbar[(int64_t)li * HD + (int64_t)h * d + c] = qb;
-        sq += qb * qb;
-    }
-    sq = wave_sum_f64(sq);
-    if ((tid & 63) == 0) wsum[tid >> 6] = sq;
-    __syncthreads();
-    if (tid == 0) {
-        double tot = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) tot += wsum[w];
-        a.ws_qnorm2[(int64_t)li * H + h] = tot;  // this head's share of |q-bar|^2
-    }
+// Requests the arguments in one go: the compiler would load them where they are used, one round trip through the
+// scalar cache after the other.
+__device__ __forceinline__ void request(const ScoreArgs& a) {
+    asm volatile("" ::"s"(a.keys), "s"(a.q), "s"(a.scores), "s"(a.ws_qbar), "s"(a.ws_qtok), "s"(a.score_stride),
+                 "s"(a.n_kv_heads), "s"(a.n_q_heads), "s"(a.head_dim), "s"(a.capacity_groups), "s"(a.layer0), "s"(a.t_q),
+                 "s"(a.n_groups), "s"(a.sim));
 }
 
-// ------------------------------------------------------------------ mean-query GEMV
 // Sum of a double over an aligned set of 16 lanes (DPP swaps; valid in all 16 lanes).
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
@@ -135,31 +45,205 @@ __device__ __forceinline__ double row16_sum_f64(double v) {
     v += dpp_f64<0x140>(v);  // the other half of the 16
     return v;
 }
+// ... over all 64 lanes of a wave (valid in all of them).
+__device__ __forceinline__ double wave_sum_f64(double v) {
+    v = row16_sum_f64(v);
+    double w = v;
+    swap_lanes<16>(v, w);
+    v += w;
+    w = v;
+    swap_lanes<32>(v, w);
+    return v + w;
+}
 
+// A sum over the workgroup: every wave puts its share, the total can be read behind a barrier.
+__device__ __forceinline__ void put_wave_sum(double v, double* wsum) {
+    v = wave_sum_f64(v);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+}
+template <int WAVES>
+__device__ __forceinline__ double total_of(const double* wsum) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) v += wsum[w];
+    return v;
+}
+// |q-bar|^2 of a layer, from what query_fold_kernel has left: the shares of the waves.
+__device__ __forceinline__ void put_query_norm2(const ScoreArgs& a, int li, int HD, int threads, double* wsum) {
+    double sq = 0.0;
+    for (int e = threadIdx.x; e < HD; e += threads) {
+        const double qb = a.ws_qbar[(int64_t)li * HD + e];
+        sq = fma(qb, qb, sq);
+    }
+    put_wave_sum(sq, wsum);
+}
+
+// Column sums over the row slots of a wave where lpr = d/8 lanes per row divide it: one row of d sums per wave in `red`,
+// in channel order.  Every lane of the wave takes part.
+__host__ __device__ __forceinline__ bool rows_divide_a_wave(int lpr) { return lpr == 8 || lpr == 16 || lpr == 32; }
+__device__ __forceinline__ void join_rows_of_wave(double (&acc)[8], int lpr, int slot, double* red) {
+    const int lane = threadIdx.x & 63;
+    auto join = [&](auto lanes) {
+        constexpr int LPR = decltype(lanes)::value, CH = LPR / 8;
+        reduce_rows<LPR>(acc, [](double p, double q) { return p + q; });
+#pragma unroll
+        for (int j = 0; j < CH; ++j) red[(threadIdx.x >> 6) * (8 * LPR) + slot * 8 + (lane / LPR) * CH + j] = acc[j];
+    };
+    if (lpr == 16) join(std::integral_constant<int, 16>{});  // uniform
+    else if (lpr == 8) join(std::integral_constant<int, 8>{});
+    else join(std::integral_constant<int, 32>{});
+}
+
+// ------------------------------------------------------------------ query fold
+// grid (H_k * parts, n_layers); a workgroup owns d / parts channels of a KV head: kFoldThreads threads = row slots x lanes of 8
+// channels.  The r * T_q rows of a KV head are contiguous in Q: the mean alone is one sum over them.  TOKENS: every token's mean
+// over the r heads is wanted too, so a slot takes whole tokens.  Bound by latency and by what the few compute units that take part can
+// load, hence parts of 64 channels where those divide d.  28 layers x 28 heads of 128 in a graph of the whole question, 256 threads per head / 512 / 512
+// per part: 32 tokens 5.4 / 4.5 / 4.4 us, 64 7.5 / 5.7 / 5.0, 64 with every token kept 10.2 / 9.4 / 7.0.
+template <typename QT, bool TOKENS>
+__global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArgs a, const int parts) {
+    constexpr int EB = elem_bytes<QT>::value;
+    request(a);
+    const int h = blockIdx.x / parts, li = blockIdx.y;
+    const int H = a.n_kv_heads, Tq = a.t_q;
+    const int r = a.n_q_heads / H;
+    const int64_t HD = (int64_t)H * a.head_dim;
+    const int d = a.head_dim / parts, c0 = (blockIdx.x - h * parts) * d;  // channels of this workgroup
+    const int lpr = d >> 3;
+    const int jn = kFoldThreads / lpr;
+    const int tid = threadIdx.x;
+    const int jl = tid / lpr;
+    const int slot = tid - jl * lpr;
+    const bool active = jl < jn;
+    const uint32_t row_bytes = (uint32_t)a.head_dim * EB;
+    const char* q = static_cast<const char*>(a.q) + ((int64_t)li * H + h) * r * Tq * row_bytes + (c0 + slot * 8) * EB;
+
+    double acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.0;
+    constexpr int kRows = 8;  // rows of a lane in flight
+    if (!TOKENS) {
+        const int64_t rows = (int64_t)r * Tq;
+        const int trip = kRows * jn;
+        for (int64_t base = 0; base < rows; base += trip) {  // uniform
+            const char* src = q + base * row_bytes;
+            const int left = active ? (int)min(rows - base, (int64_t)trip) : 0;
+            Raw8<QT> raw[kRows];
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                zero_raw(raw[u]);
+                const int row = jl + u * jn;
+                if (row < left) load_raw(src + (uint32_t)row * row_bytes, raw[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) {
+                float x[8];
+                widen(raw[u], x);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
+            }
+        }
+    }
+    if (TOKENS && active) {
+        const double inv_r = 1.0 / (double)r;
+        for (int j = jl; j < Tq; j += jn) {
+            double qt[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) qt[i] = 0.0;
+            for (int g0 = 0; g0 < r; g0 += kRows) {
+                Raw8<QT> raw[kRows];
+#pragma unroll
+                for (int g = 0; g < kRows; ++g) {
+                    zero_raw(raw[g]);
+                    if (g0 + g < r) load_raw(q + ((uint64_t)(g0 + g) * Tq + j) * row_bytes, raw[g]);
+                }
+#pragma unroll
+                for (int g = 0; g < kRows; ++g) {
+                    float x[8];
+                    widen(raw[g], x);  // heads past the block were zero-filled
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) qt[i] += (double)x[i];
+                }
+            }
+            f64x2* dst = reinterpret_cast<f64x2*>(a.ws_qtok + ((int64_t)li * Tq + j) * HD + (int64_t)h * a.head_dim + c0 + slot * 8);
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) {
+                qt[i] = qt[i] * inv_r;
+                qt[i + 1] = qt[i + 1] * inv_r;
+                dst[i / 2] = f64x2{qt[i], qt[i + 1]};
+                acc[i] += qt[i];
+                acc[i + 1] += qt[i + 1];
+            }
+        }
+    }
+    const double share = 1.0 / (TOKENS ? (double)Tq : (double)r * (double)Tq);
+    __shared__ double red[kFoldThreads * 8];
+    const bool by_waves = rows_divide_a_wave(lpr);  // uniform
+    if (by_waves) {
+        join_rows_of_wave(acc, lpr, slot, red);
+    } else if (active) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) red[jl * d + i * lpr + slot] = acc[i];  // position order: no bank conflicts
+    }
+    __syncthreads();
+    for (int p = tid; p < d; p += kFoldThreads) {  // channel p, or position p = i * lpr + slot, which holds channel slot * 8 + i
+        const int n = by_waves ? kFoldThreads / 64 : jn;
+        double sum = 0.0;
+        for (int j = 0; j < n; ++j) sum += red[j * d + p];
+        a.ws_qbar[(int64_t)li * HD + (int64_t)h * a.head_dim + c0 + (by_waves ? p : (p % lpr) * 8 + p / lpr)] = sum * share;
+    }
+}
+
+// ------------------------------------------------------------------ mean-query GEMV
 constexpr int kScoreChunks = 8;  // 16-byte key loads per lane that are in flight together
 
-// Dot product and norm of one group's key (its first kScoreChunks pieces already in kx) against the
-// staged query, and the score.  16 lanes work on a group.
-template <typename LOAD, typename NORM>
-__device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double* qbar, f32x4 (&kx)[kScoreChunks],
-                                               LOAD load_keys, int HD, int sub, int t, int li, NORM query_norm) {
-    double dot = 0.0, nk2 = 0.0;
-    for (int e0 = 0; e0 < HD; e0 += kScoreChunks * 64) {
-        f32x4 cur[kScoreChunks];
+// q-bar in LDS: the 16 lanes of a frame-group read consecutive 16-byte pairs, so element e = 64c + 4s + i (chunk c, lane s, i < 4)
+// sits at ((2c + i/2) * 16 + s) * 2 + i%2 (in element order the lanes' pairs would be 32 bytes apart: bank conflicts on every read).
+__device__ __forceinline__ int staged_at(int e) {
+    const int c = e >> 6, sl = (e >> 2) & 15, i = e & 3;
+    return (((2 * c + (i >> 1)) * 16 + sl) << 1) + (i & 1);
+}
+
+// Key of one group, CH pieces of 64 channels at a time.  16 lanes work on a group: lane `sub` of them takes floats
+// [64c + 4 sub, 64c + 4 sub + 4) for c = 0, 1, ..., so every load instruction of the 16 lanes covers 256 contiguous bytes.
+// FULL: the key is a whole number of CH pieces.  Otherwise what lies past its end is zero here and in the staged q-bar.
+template <int CH, bool FULL>
+struct KeyPieces {
+    f32x4 x[CH];
+    __device__ __forceinline__ void load(const float* key, int e0, int HD, int sub) {
 #pragma unroll
-        for (int c = 0; c < kScoreChunks; ++c) cur[c] = kx[c];
-        if (e0 + kScoreChunks * 64 < HD) load_keys(e0 + kScoreChunks * 64);  // uniform
-#pragma unroll
-        for (int c = 0; c < kScoreChunks; ++c) {
+        for (int c = 0; c < CH; ++c) {
             const int e = e0 + c * 64 + sub * 4;
-            if (e < HD) {
+            if (FULL) {
+                x[c] = *reinterpret_cast<const f32x4*>(key + e);
+            } else {
+                x[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (e < HD) x[c] = *reinterpret_cast<const f32x4*>(key + e);
+            }
+        }
+    }
+};
+
+// Dot product and norm of one group's key (its first pieces already in `first`) against the staged query, and the score.
+// No branch around the products: the LDS reads of all pieces are then in flight together (with one, this function took 3000 of the 10000 cycles that
+// a workgroup of score_fold_query_kernel lives, now 1800; 1 layer x 256 groups x 16 tokens 7.7 -> 6.6 us).
+template <int CH, bool FULL>
+__device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double* qbar, const KeyPieces<CH, FULL>& first, const float* key,
+                                               int HD, int sub, int t, int li, double query_norm) {
+    double dot = 0.0, nk2 = 0.0;
+    KeyPieces<CH, FULL> next = first;
+    for (int e0 = 0; e0 < HD; e0 += CH * 64) {
+        const KeyPieces<CH, FULL> cur = next;
+        if (e0 + CH * 64 < HD) next.load(key, e0 + CH * 64, HD, sub);  // uniform
+        const f64x2* q = reinterpret_cast<const f64x2*>(qbar + e0) + sub;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const double kd = (double)cur[c][i];
-                    const double qv = qbar[(((2 * ((e0 >> 6) + c) + (i >> 1)) * 16 + sub) << 1) + (i & 1)];
-                    dot = fma(qv, kd, dot);
-                    nk2 = fma(kd, kd, nk2);
-                }
+        for (int c = 0; c < CH; ++c) {
+            const f64x2 q01 = q[2 * c * 16], q23 = q[(2 * c + 1) * 16];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const double kd = (double)cur.x[c][i];
+                dot = fma(i < 2 ? q01[i] : q23[i - 2], kd, dot);
+                nk2 = fma(kd, kd, nk2);
             }
         }
     }
@@ -167,52 +251,43 @@ __device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double*
     nk2 = row16_sum_f64(nk2);
     if (sub == 0 && t < a.n_groups) {
         double s = dot;
-        if (a.sim == TOM_SIM_COSINE) s = dot / (fmax(query_norm(), 1e-12) * fmax(sqrt(nk2), 1e-12));
+        if (a.sim == TOM_SIM_COSINE) s = dot / (fmax(query_norm, 1e-12) * fmax(sqrt(nk2), 1e-12));
         a.scores[(int64_t)li * a.score_stride + t] = (float)s;
     }
 }
 
-// grid (ceil(T / 16), n_layers); dynamic LDS: H_k*d doubles (q-bar).  16 lanes share one
-// frame-group: lane i of them takes floats [64c + 4i, 64c + 4i + 4) of the key for
-// c = 0, 1, ..., so every load instruction of the 16 lanes covers 256 contiguous bytes and a
-// 512-float key is fetched by one batch of 8 loads per lane.
+// grid (ceil(T / 16), n_layers); dynamic LDS: H_k*d doubles (q-bar), padded to whole CH * 64.
+template <int CH, bool FULL>
 __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArgs a) {
-    extern __shared__ double qbar[];
+    extern __shared__ __align__(16) double qbar[];
     const int li = blockIdx.y;
     const int HD = a.n_kv_heads * a.head_dim;
     const int tid = threadIdx.x, sub = tid & 15;
     const float* keys = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups) * HD;
     const int t = blockIdx.x * (kBlock / 16) + (tid >> 4);
     const int tc = min(t, a.n_groups - 1);  // the tail re-reads the last group
-    const float* key = keys + (int64_t)tc * HD + sub * 4;
+    const float* key = keys + (int64_t)tc * HD;
     // The first key loads do not depend on the query: issue them before q-bar is staged.
-    f32x4 kx[kScoreChunks];
-    auto load_keys = [&](int e0) {
-#pragma unroll
-        for (int c = 0; c < kScoreChunks; ++c) {
-            kx[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (e0 + c * 64 + sub * 4 < HD) kx[c] = *reinterpret_cast<const f32x4*>(key + e0 + c * 64);
-        }
-    };
-    load_keys(0);
+    KeyPieces<CH, FULL> first;
+    first.load(key, 0, HD, sub);
 
-    // q-bar is staged so that the 16 lanes of a frame-group read consecutive 16-byte pairs:
-    // element e = 64c + 4s + i (chunk c, lane s, i < 4) sits at ((2c + i/2) * 16 + s) * 2 + i%2
-    // (in element order the lanes' pairs would be 32 bytes apart: bank conflicts on every read)
-    for (int e = tid; e < HD; e += kBlock) {
-        const int c = e >> 6, sl = (e >> 2) & 15, i = e & 3;
-        qbar[(((2 * c + (i >> 1)) * 16 + sl) << 1) + (i & 1)] = a.ws_qbar[(int64_t)li * HD + e];
+    const int padded = FULL ? HD : (HD + CH * 64 - 1) / (CH * 64) * (CH * 64);
+    __shared__ double wsum[kBlock / 64];
+    double sq = 0.0;
+    for (int e = tid; e < padded; e += kBlock) {
+        const double qb = FULL || e < HD ? a.ws_qbar[(int64_t)li * HD + e] : 0.0;
+        qbar[staged_at(e)] = qb;
+        sq = fma(qb, qb, sq);
     }
-    double nq2 = 0.0;
-    for (int hh = 0; hh < a.n_kv_heads; ++hh) nq2 += a.ws_qnorm2[(int64_t)li * a.n_kv_heads + hh];
-    const double nq = sqrt(nq2);
+    put_wave_sum(sq, wsum);
     __syncthreads();
+    const double nq = sqrt(total_of<kBlock / 64>(wsum));
 
-    score_of_group(a, qbar, kx, load_keys, HD, sub, t, li, [&] { return nq; });
+    score_of_group(a, qbar, first, key, HD, sub, t, li, nq);
 }
 
 // Fold and score in one launch, for questions short enough that every workgroup can fold the query
-// of its layer by itself.  grid (ceil(T / 32), n_layers), 512 threads; dynamic LDS: H_k*d doubles.
+// of its layer by itself.  grid (ceil(T / 32), n_layers), 512 threads; dynamic LDS as above.
 // The r * T_q rows of a KV head are contiguous in Q, so the mean over heads and tokens is one
 // sum over a run of rows: head h gets the same number of row slots (d/8 lanes each) of the
 // workgroup.  The key loads are in flight meanwhile.
@@ -220,32 +295,28 @@ __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArg
 // stay within two 64-byte lines.
 struct FoldSplit {
     uint32_t slots, inv_slots, inv_lanes_per_row, inv_head_dim;
+    int32_t waves;  // of a head, where its slots are whole waves and rows divide a wave; or 0
 };
 
-template <typename QT>
+template <typename QT, int CH, bool FULL>
 __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const ScoreArgs a, const FoldSplit f) {
     constexpr int EB = elem_bytes<QT>::value;
     constexpr int kRows = 8;  // query rows per lane in flight
-    extern __shared__ double qbar[];
+    extern __shared__ __align__(16) double qbar[];
     __shared__ double red[kFoldThreads * 8];
     __shared__ double wsum[kFoldThreads / 64];
+    request(a);
     const int li = blockIdx.y;
     const int H = a.n_kv_heads, d = a.head_dim, HD = H * d;
     const int tid = threadIdx.x, sub = tid & 15;
     const float* keys = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups) * HD;
     const int t = blockIdx.x * (kFoldThreads / 16) + (tid >> 4);
     const int tc = min(t, a.n_groups - 1);  // the tail re-reads the last group
-    const float* key = keys + (int64_t)tc * HD + sub * 4;
-    f32x4 kx[kScoreChunks];
-    auto load_keys = [&](int e0) {
-#pragma unroll
-        for (int c = 0; c < kScoreChunks; ++c) {
-            kx[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (e0 + c * 64 + sub * 4 < HD) kx[c] = *reinterpret_cast<const f32x4*>(key + e0 + c * 64);
-        }
-    };
-    load_keys(0);
+    const float* key = keys + (int64_t)tc * HD;
+    KeyPieces<CH, FULL> first;
+    first.load(key, 0, HD, sub);
 
+    const double share = 1.0 / (double)((a.n_q_heads / H) * a.t_q);
     const int lpr = d >> 3;
     const int s = div_by(tid, lpr, f.inv_lanes_per_row), slot = tid - s * lpr;
     const int h = div_by(s, f.slots, f.inv_slots), part = s - h * f.slots;
@@ -271,31 +342,38 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
                 for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
             }
         }
+        if (f.waves > 0) {
+            join_rows_of_wave(acc, lpr, slot, red);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) red[s * d + i * lpr + slot] = acc[i];  // position order: no bank conflicts
+            for (int i = 0; i < 8; ++i) red[s * d + i * lpr + slot] = acc[i];  // position order: no bank conflicts
+        }
     }
     __syncthreads();
     double sq = 0.0;
-    for (int e = tid; e < HD; e += kFoldThreads) {
-        const int hh = div_by(e, d, f.inv_head_dim), p = e - hh * d;  // position p of head hh
+    const int padded = FULL ? HD : (HD + CH * 64 - 1) / (CH * 64) * (CH * 64);
+    for (int e = tid; e < padded; e += kFoldThreads) {
+        if (!FULL && e >= HD) {
+            qbar[staged_at(e)] = 0.0;
+            continue;
+        }
+        const int hh = div_by(e, d, f.inv_head_dim), p = e - hh * d;
+        int at = e;
         double sum = 0.0;
-        for (int w = 0; w < f.slots; ++w) sum += red[(hh * f.slots + w) * d + p];
-        const double qb = sum / (double)((a.n_q_heads / H) * a.t_q);
-        const int i8 = div_by(p, lpr, f.inv_lanes_per_row);
-        const int ch = hh * d + (p - i8 * lpr) * 8 + i8;
-        const int c = ch >> 6, sl = (ch >> 2) & 15, i = ch & 3;
-        qbar[(((2 * c + (i >> 1)) * 16 + sl) << 1) + (i & 1)] = qb;  // the order of score_mean_query_kernel
+        if (f.waves > 0) {  // channel p of head hh
+            for (int w = 0; w < f.waves; ++w) sum += red[(hh * f.waves + w) * d + p];
+        } else {  // position p
+            for (int w = 0; w < f.slots; ++w) sum += red[(hh * f.slots + w) * d + p];
+            const int i8 = div_by(p, lpr, f.inv_lanes_per_row);
+            at = hh * d + (p - i8 * lpr) * 8 + i8;
+        }
+        const double qb = sum * share;
+        qbar[staged_at(at)] = qb;
         sq += qb * qb;
     }
-    sq = wave_sum_f64(sq);
-    if ((tid & 63) == 0) wsum[tid >> 6] = sq;
+    put_wave_sum(sq, wsum);
     __syncthreads();
-    score_of_group(a, qbar, kx, load_keys, HD, sub, t, li, [&] {
-        double nq2 = 0.0;
-#pragma unroll
-        for (int w = 0; w < kFoldThreads / 64; ++w) nq2 += wsum[w];
-        return sqrt(nq2);
-    });
+    score_of_group(a, qbar, first, key, HD, sub, t, li, sqrt(total_of<kFoldThreads / 64>(wsum)));
 }
 
 // ------------------------------------------------------------------ per-token GEMM
@@ -446,6 +524,9 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     const float* keys = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups) * HD;
     const double* qtok = a.ws_qtok + (int64_t)li * Tq * HD;
 
+    __shared__ double wsum[kBlock / 64];
+    if (a.sim == TOM_SIM_COSINE) put_query_norm2(a, li, HD, kBlock, wsum);  // read behind the barriers of gemm_rows
+
     double colsum = 0.0, nk2 = 0.0;
     for (int m0 = 0; m0 < Tq; m0 += kGemmM) {
         const int mt = (min(kGemmM, Tq - m0) + 15) >> 4;
@@ -465,9 +546,7 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     if (kk == 0 && t < T) {
         double s = colsum / (double)Tq;
         if (a.sim == TOM_SIM_COSINE) {
-            double nq2 = 0.0;
-            for (int hh = 0; hh < a.n_kv_heads; ++hh) nq2 += a.ws_qnorm2[(int64_t)li * a.n_kv_heads + hh];
-            s = s / (fmax(sqrt(nq2), 1e-12) * fmax(sqrt(nk2), 1e-12));
+            s = s / (fmax(sqrt(total_of<kBlock / 64>(wsum)), 1e-12) * fmax(sqrt(nk2), 1e-12));
         }
         a.scores[(int64_t)li * a.score_stride + t] = (float)s;
     }
@@ -499,6 +578,9 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
     // groups past T and tokens past T_q repeat the last one and are dropped at the end
     const float* const key = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups + min(n0 + fi, T - 1)) * HD;
     const double* const qtok = a.ws_qtok + (int64_t)li * Tq * HD;
+
+    __shared__ double wsum[kSplitWaves];
+    if (a.sim == TOM_SIM_COSINE) put_query_norm2(a, li, HD, kSplitThreads, wsum);  // read behind barriers
 
     double csum = 0.0, nk2 = 0.0;
     for (int m0 = 0; m0 < Tq; m0 += 16 * MT) {
@@ -582,9 +664,7 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
         }
         s = s / (double)Tq;
         if (a.sim == TOM_SIM_COSINE) {
-            double nq2 = 0.0;
-            for (int hh = 0; hh < a.n_kv_heads; ++hh) nq2 += a.ws_qnorm2[(int64_t)li * a.n_kv_heads + hh];
-            s = s / (fmax(sqrt(nq2), 1e-12) * fmax(sqrt(n2), 1e-12));
+            s = s / (fmax(sqrt(total_of<kSplitWaves>(wsum)), 1e-12) * fmax(sqrt(n2), 1e-12));
         }
         a.scores[(int64_t)li * a.score_stride + n0 + tid] = (float)s;
     }
@@ -594,41 +674,62 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
 
 static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s) {
     if (a.n_layers == 0) return hipSuccess;
-    const dim3 grid(a.n_kv_heads, a.n_layers);
+    const int parts = a.head_dim % 64 == 0 ? a.head_dim / 64 : 1;
+    const dim3 grid(a.n_kv_heads * parts, a.n_layers), block(kFoldThreads);
+    auto go = [&](auto qt) {
+        typedef decltype(qt) QT;
+        if (want_tokens) query_fold_kernel<QT, true><<<grid, block, 0, s>>>(a, parts);
+        else query_fold_kernel<QT, false><<<grid, block, 0, s>>>(a, parts);
+        return hipGetLastError();
+    };
     switch (a.q_dtype) {
-        case TOM_F32: query_fold_kernel<In_f32><<<grid, dim3(kBlock), 0, s>>>(a, want_tokens); break;
-        case TOM_BF16: query_fold_kernel<In_bf16><<<grid, dim3(kBlock), 0, s>>>(a, want_tokens); break;
-        case TOM_F16: query_fold_kernel<In_f16><<<grid, dim3(kBlock), 0, s>>>(a, want_tokens); break;
+        case TOM_F32: return go(In_f32{});
+        case TOM_BF16: return go(In_bf16{});
+        case TOM_F16: return go(In_f16{});
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+}
+
+// Calls go with the pieces of 64 key channels that a lane loads together and whether the key is a whole number of them, as types.
+template <typename GO>
+static hipError_t with_pieces(int HD, GO go) {
+    auto with = [&](auto ch) {
+        constexpr int CH = decltype(ch)::value;
+        if (HD % (CH * 64) == 0) go(ch, std::true_type{}, (size_t)HD * sizeof(double));
+        else go(ch, std::false_type{}, (size_t)((HD + CH * 64 - 1) / (CH * 64) * (CH * 64)) * sizeof(double));
+        return hipGetLastError();
+    };
+    if (HD <= 128) return with(std::integral_constant<int, 2>{});
+    if (HD <= 256) return with(std::integral_constant<int, 4>{});
+    return with(std::integral_constant<int, kScoreChunks>{});
 }
 
 hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
     if (a.n_layers == 0 || a.n_groups == 0) return hipSuccess;
+    const int HD = a.n_kv_heads * a.head_dim;
     FoldSplit f{};
     f.slots = fold_slots(a);
     if (f.slots > 0) {
         f.inv_slots = reciprocal_u32(f.slots);
         f.inv_lanes_per_row = reciprocal_u32((uint32_t)a.head_dim / 8u);
         f.inv_head_dim = reciprocal_u32((uint32_t)a.head_dim);
+        const int lpr = a.head_dim / 8;
+        f.waves = rows_divide_a_wave(lpr) && f.slots * lpr % 64 == 0 ? f.slots * lpr / 64 : 0;
         const dim3 grid((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16), a.n_layers), block(kFoldThreads);
-        const size_t lds = (size_t)((a.n_kv_heads * a.head_dim + 63) / 64 * 64) * sizeof(double);
-        switch (a.q_dtype) {
-            case TOM_F32: score_fold_query_kernel<In_f32><<<grid, block, lds, s>>>(a, f); break;
-            case TOM_BF16: score_fold_query_kernel<In_bf16><<<grid, block, lds, s>>>(a, f); break;
-            case TOM_F16: score_fold_query_kernel<In_f16><<<grid, block, lds, s>>>(a, f); break;
-            default: return hipErrorInvalidValue;
-        }
-        return hipGetLastError();
+        return with_pieces(HD, [&](auto ch, auto full, size_t lds) {
+            constexpr int CH = decltype(ch)::value;
+            constexpr bool FULL = decltype(full)::value;
+            if (a.q_dtype == TOM_F32) score_fold_query_kernel<In_f32, CH, FULL><<<grid, block, lds, s>>>(a, f);
+            else if (a.q_dtype == TOM_BF16) score_fold_query_kernel<In_bf16, CH, FULL><<<grid, block, lds, s>>>(a, f);
+            else score_fold_query_kernel<In_f16, CH, FULL><<<grid, block, lds, s>>>(a, f);
+        });
     }
     if (hipError_t e = launch_query_fold(a, false, s)) return e;
     const int per_block = kBlock / 16;
     const dim3 grid((a.n_groups + per_block - 1) / per_block, a.n_layers);
-    // q-bar, padded to whole 64-element chunks (the staged order permutes within a chunk)
-    const size_t lds = (size_t)((a.n_kv_heads * a.head_dim + 63) / 64 * 64) * sizeof(double);
-    score_mean_query_kernel<<<grid, dim3(kBlock), lds, s>>>(a);
-    return hipGetLastError();
+    return with_pieces(HD, [&](auto ch, auto full, size_t lds) {
+        score_mean_query_kernel<decltype(ch)::value, decltype(full)::value><<<grid, dim3(kBlock), lds, s>>>(a);
+    });
 }
 
 hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
