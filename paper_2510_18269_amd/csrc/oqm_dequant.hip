@@ -38,19 +38,22 @@ __device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t 
     if (off < bytes) *reinterpret_cast<u32x4*>(dst + off) = *reinterpret_cast<const u32x4*>(src + off);
 }
 
-// The 8-channel items of a tile (one 32-bit word of 4-bit codes each) are numbered row by row: item
-// row * (d/8) + slot.  Codes and output are linear in that number, and so are the pairs of the
-// head_dim axis (d/8 is a multiple of the gs/8 lanes of a quant-group), so a chunk is a linear stream and the
+// The items of a tile (N channels: 16 bytes of output, so that a store of a wave writes 1 KB) are numbered row by row: item
+// row * (d/N) + slot.  Codes and output are linear in that number, and so are the pairs of the
+// head_dim axis (d/N is a multiple of the gs/N lanes of a quant-group), so a chunk is a linear stream and the
 // kernel divides by nothing.  On the token axis a lane has to keep its channels: its items are
-// `step` = the largest multiple of d/8 below 256 apart, otherwise 256.
+// `step` = the largest multiple of d/N below 256 apart, otherwise 256.
+// With float32 output, items of 8 channels are two stores of every other 16 bytes each: 28 layers x 20 groups x 4 x 196 x 128 (549 MB)
+// 177 us past the caches and 142 through them, items of 4 channels 98 (5.6 TB/s); token axis 185, 145 and 82. (8 channels stay where a
+// row of d/4 lanes does not fit the workgroup.)
 // kUnroll: items per lane; all their loads are issued before the first is converted, and the host
 // cuts the tile into chunks that one trip covers.
 // SELECT: waves of the workgroup that select its group from the layer's scores (256 scores each), or 0: the
 // index comes from memory.
-template <typename OUT, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB, int SELECT>
+template <typename OUT, int N, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB, int SELECT>
 __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArgs a) {
     constexpr int EB = elem_bytes<OUT>::value;
-    constexpr uint32_t CW = BITS;          // bytes of packed codes per item
+    constexpr uint32_t CW = BITS * N / 8;  // bytes of packed codes per item
     constexpr uint32_t CMASK = (1u << BITS) - 1u;
     typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
     const uint32_t tid = threadIdx.x;
@@ -94,14 +97,14 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     const uint64_t tile = (uint64_t)((a.layer0 + li) * 2u + kv) * a.plane_tiles + (uint64_t)t * (uint32_t)a.n_kv_heads + h;
     const char* const codes_t = reinterpret_cast<const char*>(a.codes) + tile * (a.tile_items * CW);
     const char* const meta_t = static_cast<const char*>(a.meta) + tile * a.tile_meta_bytes;
-    char* const out = head_out + a.prefix_bytes + (uint64_t)r * (a.tile_items * (8u * EB));
+    char* const out = head_out + a.prefix_bytes + (uint64_t)r * (a.tile_items * (N * EB));
     const uint32_t first = begin + tid;
     const bool active = !TOKEN_AXIS || tid < a.step;
-    f32x2 ch[8];  // token axis: the pairs of this lane's 8 channels, loaded once
+    f32x2 ch[N];  // token axis: the pairs of this lane's channels, loaded once
     if (TOKEN_AXIS) {
         const uint32_t slot = tid - div_by(tid, a.lanes_per_row, a.inv_lanes_per_row) * a.lanes_per_row;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) ch[i] = widen_pair(reinterpret_cast<const meta_pair*>(meta_t)[slot * 8u + i]);
+        for (int i = 0; i < N; ++i) ch[i] = widen_pair(reinterpret_cast<const meta_pair*>(meta_t)[slot * N + i]);
     }
 
     uint32_t w[kUnroll];
@@ -112,7 +115,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
         w[u] = 0u;
         sm[u] = meta_pair{};
         if (active && item < end) {
-            w[u] = load_codes8<BITS>(codes_t + item * CW);
+            w[u] = load_codes<BITS, N>(codes_t + item * CW);
             if (!TOKEN_AXIS)
                 sm[u] = *reinterpret_cast<const meta_pair*>(meta_t + (item >> a.lpg_shift) * (uint32_t)sizeof(meta_pair));
         }
@@ -121,14 +124,14 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     for (int u = 0; u < kUnroll; ++u) {
         const uint32_t item = first + u * a.step;
         if (active && item < end) {
-            float x[8];
+            float x[N];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < N; ++i) {
                 const float c = (float)((w[u] >> (BITS * i)) & CMASK);
                 const f32x2 p = TOKEN_AXIS ? ch[i] : widen_pair(sm[u]);
                 x[i] = __builtin_fmaf(c, p[0], p[1]);  // Eq. 11, rounded once to float32
             }
-            store8(out + item * (8u * EB), OUT{}, x);
+            store_items(out + item * (N * EB), OUT{}, x);
         }
     }
     if (SELECT > 0 && blockIdx.y == 0 && begin == 0 && tid == 0) a.sel_idx[(int64_t)li * a.k + r] = (int32_t)t;
@@ -157,13 +160,13 @@ hipError_t prefix_copy(const DequantArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename OUT>
+template <typename OUT, uint32_t N>
 hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.k_eff == 0) return hipSuccess;
     DequantArgs a = args;
     constexpr uint32_t eb = elem_bytes<OUT>::value;
     const bool tok = a.qaxis == TOM_QAXIS_TOKENS;
-    const uint32_t lpr = (uint32_t)a.head_dim / 8u, G = (uint32_t)a.group_tokens;
+    const uint32_t lpr = (uint32_t)a.head_dim / N, G = (uint32_t)a.group_tokens;
     a.lanes_per_row = lpr;
     a.inv_lanes_per_row = reciprocal_u32(lpr);
     a.step = tok ? kBlock / lpr * lpr : kBlock;
@@ -175,9 +178,10 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     while ((G + a.chunks - 1) / a.chunks * lpr > unroll * a.step) ++a.chunks;
     a.chunk_items = (G + a.chunks - 1) / a.chunks * lpr;
     a.inv_chunks = reciprocal_u32(a.chunks);
+    if (N < 8 && (int64_t)a.k_eff * a.chunks * kBlock >= 1LL << 31) return launch_t<OUT, 8>(args, s);  // fewer, longer workgroups
     if ((int64_t)a.k_eff * a.chunks > 0x7fffffffLL) return hipErrorInvalidValue;
     a.lpg_shift = 0;
-    while (!tok && (8 << a.lpg_shift) < a.qgroup) ++a.lpg_shift;  // qgroup is a power of two
+    while (!tok && ((int)N << a.lpg_shift) < a.qgroup) ++a.lpg_shift;  // qgroup is a power of two
     a.tile_meta_bytes = (tok ? (uint32_t)a.head_dim : G * (lpr >> a.lpg_shift)) * (a.meta_bf16 ? 4u : 8u);
     a.plane_tiles = (int64_t)a.capacity_groups * a.n_kv_heads;
     a.prefix_bytes = (int64_t)a.prefix_rows * a.head_dim * eb;
@@ -201,8 +205,8 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
         constexpr bool M = decltype(mb)::value;
         auto with_select = [&](auto select) {
             constexpr int S = decltype(select)::value;
-            if (tok) dequant_gather_kernel<OUT, U, true, B, M, S><<<grid, block, 0, s>>>(a);
-            else dequant_gather_kernel<OUT, U, false, B, M, S><<<grid, block, 0, s>>>(a);
+            if (tok) dequant_gather_kernel<OUT, N, U, true, B, M, S><<<grid, block, 0, s>>>(a);
+            else dequant_gather_kernel<OUT, N, U, false, B, M, S><<<grid, block, 0, s>>>(a);
         };
         if (!select) with_select(std::integral_constant<int, 0>{});
         else if (select == 1) with_select(std::integral_constant<int, 1>{});
@@ -234,9 +238,10 @@ hipError_t launch_prefix_copy(const DequantArgs& args, const void* sys_k, const 
 hipError_t launch_dequant_gather(const DequantArgs& a, int out_dtype, hipStream_t s) {
     if (a.k_eff == 0) return hipSuccess;
     switch (out_dtype) {
-        case TOM_F32: return launch_t<In_f32>(a, s);
-        case TOM_BF16: return launch_t<In_bf16>(a, s);
-        case TOM_F16: return launch_t<In_f16>(a, s);
+        // a lane keeps its channels on the token axis, and a row has to fit the workgroup
+        case TOM_F32: return a.head_dim / 4 <= kBlock ? launch_t<In_f32, 4>(a, s) : launch_t<In_f32, 8>(a, s);
+        case TOM_BF16: return launch_t<In_bf16, 8>(a, s);
+        case TOM_F16: return launch_t<In_f16, 8>(a, s);
         default: return hipErrorInvalidValue;
     }
 }

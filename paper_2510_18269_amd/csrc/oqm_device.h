@@ -289,10 +289,12 @@ __device__ __forceinline__ void store_codes8(char* p, const float (&t)[8]) {
     if constexpr (BITS == 4) *reinterpret_cast<uint32_t*>(p) = pack8(t);
     else *reinterpret_cast<uint16_t*>(p) = (uint16_t)pack8_2bit(t);
 }
-template <int BITS>
-__device__ __forceinline__ uint32_t load_codes8(const char* p) {
-    if constexpr (BITS == 4) return *reinterpret_cast<const uint32_t*>(p);
-    else return *reinterpret_cast<const uint16_t*>(p);
+// N codes (8, or 4) of BITS bits.
+template <int BITS, int N>
+__device__ __forceinline__ uint32_t load_codes(const char* p) {
+    if constexpr (BITS * N == 32) return *reinterpret_cast<const uint32_t*>(p);
+    else if constexpr (BITS * N == 16) return *reinterpret_cast<const uint16_t*>(p);
+    else return *reinterpret_cast<const uint8_t*>(p);
 }
 
 // 1 / s for a scale of BITS-bit codes.  With 15 steps s <= FLT_MAX / 15 < 2^126 and the
@@ -337,8 +339,8 @@ template <> struct elem_bytes<In_f32> { static constexpr int value = 4; };
 template <> struct elem_bytes<In_bf16> { static constexpr int value = 2; };
 template <> struct elem_bytes<In_f16> { static constexpr int value = 2; };
 
-// ---- storing 8 consecutive float32 values, narrowed round-to-nearest-even ---
-__device__ __forceinline__ void store8(void* p, In_bf16, const float (&x)[8]) {
+// ---- storing consecutive float32 values, narrowed round-to-nearest-even ---
+__device__ __forceinline__ void store_items(void* p, In_bf16, const float (&x)[8]) {
     u32x4 w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -348,7 +350,7 @@ __device__ __forceinline__ void store8(void* p, In_bf16, const float (&x)[8]) {
     __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
 }
 
-__device__ __forceinline__ void store8(void* p, In_f16, const float (&x)[8]) {
+__device__ __forceinline__ void store_items(void* p, In_f16, const float (&x)[8]) {
     f16x8 h;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -362,12 +364,14 @@ __device__ __forceinline__ void store8(void* p, In_f16, const float (&x)[8]) {
     __builtin_nontemporal_store(h, reinterpret_cast<f16x8*>(p));
 }
 
-__device__ __forceinline__ void store8(void* p, In_f32, const float (&x)[8]) {
+__device__ __forceinline__ void store_items(void* p, In_f32, const float (&x)[4]) {
+    __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, reinterpret_cast<f32x4*>(p));
+}
+// The lanes of a store write every other 16 bytes here, so it must be left to the caches to join the halves of a line.
+__device__ __forceinline__ void store_items(void* p, In_f32, const float (&x)[8]) {
     f32x4* o = reinterpret_cast<f32x4*>(p);
-    const f32x4 a = {x[0], x[1], x[2], x[3]};
-    const f32x4 b = {x[4], x[5], x[6], x[7]};
-    __builtin_nontemporal_store(a, o);
-    __builtin_nontemporal_store(b, o + 1);
+    o[0] = f32x4{x[0], x[1], x[2], x[3]};
+    o[1] = f32x4{x[4], x[5], x[6], x[7]};
 }
 
 }  // namespace oqm
