@@ -21,25 +21,28 @@ inline uint64_t score_span(int64_t stride, int n_layers, int n_groups) {
 constexpr int kFoldThreads = 512;
 
 // Row slots per KV head of score_fold_query_kernel, or 0: the fold is a launch of its own.
-// Folding inside the score kernel saves a launch (4 us of host time, as much on the device) and costs each
-// workgroup 0.03 us per 1000 query elements (float64 conversions and sums), more once they
-// share compute units: line at query elements x (workgroups + 64).  Whole question at 28 query heads of 128, fused / separate: 1 layer x 256 groups x 8 tokens 11.7 /
-// 16.0 us, x 32 14.1 / 16.0; 28 x 256 x 8 14.6 / 16.4; on the line 1 x 1024 x 32 16.1 / 16.2
-// and 8 x 256 x 32 15.6 / 15.8; beyond it 28 x 64 x 32 16.2 / 15.8, 1 x 3600 x 32 18.9 / 17.1.  (Calls from a
-// program; in a graph, where the launch costs less, fold and scores of 1 x 256 x 16 are 7.7 / 8.2 and x 32 9.8 / 8.7.)
+// Folding inside the score kernel saves a launch (about 4 us on the device) and costs every workgroup the serial sum over the rows
+// of a slot, 0.15 us a row, more once workgroups share compute units: line at rows x (workgroups + 160).  Whole question at k = 1, fused / separate:
+// 28 heads on 4 of 128, 2 workgroups x 24 tokens (21 rows) 10.5 / 11.5 us, 32 (28) 11.6 / 11.6, 48 13.9 / 11.3; 64 workgroups x 16 tokens 10.7 / 11.6, 24
+// 12.0 / 10.9; 56 heads on 8 of 80, 6 workgroups x 16 tokens (19 rows) 12.1 / 12.7, 24 (28) 13.2 / 12.4; 12 on 3 of 96, 325 workgroups x 24 tokens
+// (7 rows) 14.4 / 14.7, 32 (10) 16.4 / 14.6.  In several rounds of the chip it is the bytes of the query that count: 28 heads on 4 of 128, 896
+// workgroups x 1 token 20.0 / 20.1, x 4 21.1 / 20.2, 1764 x 1 32.0 / 32.3, x 2 32.6 / 32.2; 6 on 3 of 128, 2912 x 1 40.8 / 40.9, x 4 44.4 / 41.0.
 // A compute unit holds one workgroup with a float32 query (142 registers), two with a 16-bit one (109): a launch
 // of more runs the serial fold again in a second round.  Fold and scores in a graph, fused / separate: float32 4 heads of 128,
 // 256 workgroups x 1 token 6.9 / 9.2 us, 288 x 1 11.9 / 9.7, 896 x 1 23.3 / 16.9; one head of 64, 896 x 64 17.9 / 9.6.
 // 16-bit: one head of 64, 512 workgroups 6.7 / 8.4, 544 9.6 / 8.7, 896 x 64 tokens 13.2 / 9.7; where the keys are longer they hide it:
-// 4 heads of 128, 544 x 1 13.2 / 12.5, 768 x 1 14.5 / 16.0, 896 x 1 17.4 / 17.3.
+// 4 heads of 128, 768 x 1 14.5 / 16.0.
 // Scores that share memory with the query need the separate fold at any size: in one launch some
 // workgroups write scores while others still read the query.
 inline uint32_t fold_slots(const ScoreArgs& a) {
-    constexpr int64_t kFusedWork = 12000000;
+    constexpr int64_t kFusedRows = 3800, kFusedWork = 6500000;
     const uint32_t slots = (uint32_t)(kFoldThreads / (a.head_dim / 8) / a.n_kv_heads);
+    if (slots == 0) return 0;
     const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
-    const int64_t query = (int64_t)a.n_q_heads * a.t_q * a.head_dim;  // elements of a layer
-    if (query > kFusedWork / (blocks + 64)) return 0;
+    const int64_t rows = (int64_t)(a.n_q_heads / a.n_kv_heads) * a.t_q;
+    const int64_t query = rows * a.n_kv_heads * a.head_dim;  // elements of a layer
+    if ((rows + slots - 1) / slots > kFusedRows / (blocks + 160)) return 0;
+    if (blocks > 512 && query > kFusedWork / (blocks + 64)) return 0;
     if (a.q_dtype == TOM_F32 ? blocks > 256 : blocks > 512 && a.n_kv_heads * a.head_dim < 256) return 0;
     const uint64_t query_bytes = (uint64_t)query * (uint64_t)a.n_layers * (a.q_dtype == TOM_F32 ? 4u : 2u);
     return apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups)) ? slots : 0u;

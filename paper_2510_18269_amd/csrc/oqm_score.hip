@@ -45,20 +45,26 @@ __device__ __forceinline__ double row16_sum_f64(double v) {
     v += dpp_f64<0x140>(v);  // the other half of the 16
     return v;
 }
-// ... over all 64 lanes of a wave (valid in all of them).
-__device__ __forceinline__ double wave_sum_f64(double v) {
+// ... over aligned sets of 16, 32 or all 64 lanes of a wave (valid in all of them).
+template <int LANES>
+__device__ __forceinline__ double lanes_sum_f64(double v) {
     v = row16_sum_f64(v);
-    double w = v;
-    swap_lanes<16>(v, w);
-    v += w;
-    w = v;
-    swap_lanes<32>(v, w);
-    return v + w;
+    if constexpr (LANES >= 32) {
+        double w = v;
+        swap_lanes<16>(v, w);
+        v += w;
+    }
+    if constexpr (LANES >= 64) {
+        double w = v;
+        swap_lanes<32>(v, w);
+        v += w;
+    }
+    return v;
 }
 
 // A sum over the workgroup: every wave puts its share, the total can be read behind a barrier.
 __device__ __forceinline__ void put_wave_sum(double v, double* wsum) {
-    v = wave_sum_f64(v);
+    v = lanes_sum_f64<64>(v);
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
 }
 template <int WAVES>
@@ -197,24 +203,28 @@ __global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArg
 // ------------------------------------------------------------------ mean-query GEMV
 constexpr int kScoreChunks = 8;  // 16-byte key loads per lane that are in flight together
 
-// q-bar in LDS: the 16 lanes of a frame-group read consecutive 16-byte pairs, so element e = 64c + 4s + i (chunk c, lane s, i < 4)
-// sits at ((2c + i/2) * 16 + s) * 2 + i%2 (in element order the lanes' pairs would be 32 bytes apart: bank conflicts on every read).
+// q-bar in LDS: the W lanes of a frame-group read consecutive 16-byte pairs, so element e = 4W c + 4s + i (piece c, lane s, i < 4)
+// sits at ((2c + i/2) * W + s) * 2 + i%2 (in element order the lanes' pairs would be 32 bytes apart: bank conflicts on every read).
+template <int W>
 __device__ __forceinline__ int staged_at(int e) {
-    const int c = e >> 6, sl = (e >> 2) & 15, i = e & 3;
-    return (((2 * c + (i >> 1)) * 16 + sl) << 1) + (i & 1);
+    const int c = e / (4 * W), sl = (e >> 2) & (W - 1), i = e & 3;
+    return (((2 * c + (i >> 1)) * W + sl) << 1) + (i & 1);
 }
 
-// Key of one group, CH pieces of 64 channels at a time.  16 lanes work on a group: lane `sub` of them takes floats
-// [64c + 4 sub, 64c + 4 sub + 4) for c = 0, 1, ..., so every load instruction of the 16 lanes covers 256 contiguous bytes.
-// FULL: the key is a whole number of CH pieces.  Otherwise what lies past its end is zero here and in the staged q-bar.
-template <int CH, bool FULL>
+// Which lanes load: a key of whole trips of CH pieces; of one trip whose last piece is not whole; any other.  What lies past the
+// end of the key is zero in the registers and in the staged q-bar.
+enum Rest { kNoRest, kLastPiece, kAnyPiece };
+
+// Key of one group, CH pieces of 4W channels at a time.  W lanes work on a group: lane `sub` of them takes floats
+// [4W c + 4 sub, 4W c + 4 sub + 4) for c = 0, 1, ..., so every load instruction of the W lanes covers 16W contiguous bytes.
+template <int W, int CH, Rest REST>
 struct KeyPieces {
     f32x4 x[CH];
     __device__ __forceinline__ void load(const float* key, int e0, int HD, int sub) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int e = e0 + c * 64 + sub * 4;
-            if (FULL) {
+            const int e = e0 + c * (4 * W) + sub * 4;
+            if (REST == kNoRest || (REST == kLastPiece && c < CH - 1)) {
                 x[c] = *reinterpret_cast<const f32x4*>(key + e);
             } else {
                 x[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -227,18 +237,19 @@ struct KeyPieces {
 // Dot product and norm of one group's key (its first pieces already in `first`) against the staged query, and the score.
 // No branch around the products: the LDS reads of all pieces are then in flight together (with one, this function took 3000 of the 10000 cycles that
 // a workgroup of score_fold_query_kernel lives, now 1800; 1 layer x 256 groups x 16 tokens 7.7 -> 6.6 us).
-template <int CH, bool FULL>
-__device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double* qbar, const KeyPieces<CH, FULL>& first, const float* key,
+template <int W, int CH, Rest REST>
+__device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double* qbar, const KeyPieces<W, CH, REST>& first, const float* key,
                                                int HD, int sub, int t, int li, double query_norm) {
     double dot = 0.0, nk2 = 0.0;
-    KeyPieces<CH, FULL> next = first;
-    for (int e0 = 0; e0 < HD; e0 += CH * 64) {
-        const KeyPieces<CH, FULL> cur = next;
-        if (e0 + CH * 64 < HD) next.load(key, e0 + CH * 64, HD, sub);  // uniform
+    constexpr int trip = 4 * W * CH;
+    KeyPieces<W, CH, REST> next = first;
+    for (int e0 = 0; REST == kLastPiece ? e0 == 0 : e0 < HD; e0 += trip) {
+        const KeyPieces<W, CH, REST> cur = next;
+        if (REST != kLastPiece && e0 + trip < HD) next.load(key, e0 + trip, HD, sub);  // uniform
         const f64x2* q = reinterpret_cast<const f64x2*>(qbar + e0) + sub;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const f64x2 q01 = q[2 * c * 16], q23 = q[(2 * c + 1) * 16];
+            const f64x2 q01 = q[2 * c * W], q23 = q[(2 * c + 1) * W];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const double kd = (double)cur.x[c][i];
@@ -247,8 +258,8 @@ __device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double*
             }
         }
     }
-    dot = row16_sum_f64(dot);
-    nk2 = row16_sum_f64(nk2);
+    dot = lanes_sum_f64<W>(dot);
+    nk2 = lanes_sum_f64<W>(nk2);
     if (sub == 0 && t < a.n_groups) {
         double s = dot;
         if (a.sim == TOM_SIM_COSINE) s = dot / (fmax(query_norm, 1e-12) * fmax(sqrt(nk2), 1e-12));
@@ -256,27 +267,27 @@ __device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double*
     }
 }
 
-// grid (ceil(T / 16), n_layers); dynamic LDS: H_k*d doubles (q-bar), padded to whole CH * 64.
-template <int CH, bool FULL>
+// grid (ceil(T / (256 / W)), n_layers); dynamic LDS: H_k*d doubles (q-bar), padded to whole trips of CH pieces.
+template <int W, int CH, Rest REST>
 __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArgs a) {
     extern __shared__ __align__(16) double qbar[];
     const int li = blockIdx.y;
     const int HD = a.n_kv_heads * a.head_dim;
-    const int tid = threadIdx.x, sub = tid & 15;
+    const int tid = threadIdx.x, sub = tid & (W - 1);
     const float* keys = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups) * HD;
-    const int t = blockIdx.x * (kBlock / 16) + (tid >> 4);
+    const int t = blockIdx.x * (kBlock / W) + tid / W;
     const int tc = min(t, a.n_groups - 1);  // the tail re-reads the last group
     const float* key = keys + (int64_t)tc * HD;
     // The first key loads do not depend on the query: issue them before q-bar is staged.
-    KeyPieces<CH, FULL> first;
+    KeyPieces<W, CH, REST> first;
     first.load(key, 0, HD, sub);
 
-    const int padded = FULL ? HD : (HD + CH * 64 - 1) / (CH * 64) * (CH * 64);
+    const int padded = REST == kNoRest ? HD : REST == kLastPiece ? 4 * W * CH : (HD + 4 * W * CH - 1) / (4 * W * CH) * (4 * W * CH);
     __shared__ double wsum[kBlock / 64];
     double sq = 0.0;
     for (int e = tid; e < padded; e += kBlock) {
-        const double qb = FULL || e < HD ? a.ws_qbar[(int64_t)li * HD + e] : 0.0;
-        qbar[staged_at(e)] = qb;
+        const double qb = REST == kNoRest || e < HD ? a.ws_qbar[(int64_t)li * HD + e] : 0.0;
+        qbar[staged_at<W>(e)] = qb;
         sq = fma(qb, qb, sq);
     }
     put_wave_sum(sq, wsum);
@@ -298,7 +309,7 @@ struct FoldSplit {
     int32_t waves;  // of a head, where its slots are whole waves and rows divide a wave; or 0
 };
 
-template <typename QT, int CH, bool FULL>
+template <typename QT, int CH, Rest REST>
 __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const ScoreArgs a, const FoldSplit f) {
     constexpr int EB = elem_bytes<QT>::value;
     constexpr int kRows = 8;  // query rows per lane in flight
@@ -313,7 +324,7 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
     const int t = blockIdx.x * (kFoldThreads / 16) + (tid >> 4);
     const int tc = min(t, a.n_groups - 1);  // the tail re-reads the last group
     const float* key = keys + (int64_t)tc * HD;
-    KeyPieces<CH, FULL> first;
+    KeyPieces<16, CH, REST> first;
     first.load(key, 0, HD, sub);
 
     const double share = 1.0 / (double)((a.n_q_heads / H) * a.t_q);
@@ -351,10 +362,10 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
     }
     __syncthreads();
     double sq = 0.0;
-    const int padded = FULL ? HD : (HD + CH * 64 - 1) / (CH * 64) * (CH * 64);
+    const int padded = REST == kNoRest ? HD : REST == kLastPiece ? CH * 64 : (HD + CH * 64 - 1) / (CH * 64) * (CH * 64);
     for (int e = tid; e < padded; e += kFoldThreads) {
-        if (!FULL && e >= HD) {
-            qbar[staged_at(e)] = 0.0;
+        if (REST != kNoRest && e >= HD) {
+            qbar[staged_at<16>(e)] = 0.0;
             continue;
         }
         const int hh = div_by(e, d, f.inv_head_dim), p = e - hh * d;
@@ -368,7 +379,7 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
             at = hh * d + (p - i8 * lpr) * 8 + i8;
         }
         const double qb = sum * share;
-        qbar[staged_at(at)] = qb;
+        qbar[staged_at<16>(at)] = qb;
         sq += qb * qb;
     }
     put_wave_sum(sq, wsum);
@@ -690,18 +701,33 @@ static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStr
     }
 }
 
-// Calls go with the pieces of 64 key channels that a lane loads together and whether the key is a whole number of them, as types.
-template <typename GO>
+// Calls go with the pieces of 4 * W key channels that a lane loads together and what they leave, as types,
+// and the bytes of a staged q-bar: one trip of up to eight pieces, or the fewest equal trips if they leave nothing.  Exactly as many pieces as the key has
+// instead of two, four or eight: 28 layers x 1024 groups x 5 heads of 128 24.2 -> 21.1 us (whole question, k = 1), 3 of 96 18.5 -> 17.3.
+template <int W, typename GO>
 static hipError_t with_pieces(int HD, GO go) {
-    auto with = [&](auto ch) {
-        constexpr int CH = decltype(ch)::value;
-        if (HD % (CH * 64) == 0) go(ch, std::true_type{}, (size_t)HD * sizeof(double));
-        else go(ch, std::false_type{}, (size_t)((HD + CH * 64 - 1) / (CH * 64) * (CH * 64)) * sizeof(double));
+    const int pieces = (HD + 4 * W - 1) / (4 * W), trips = (pieces + kScoreChunks - 1) / kScoreChunks;
+    const bool whole = HD % (4 * W * trips) == 0;
+    auto with = [&](auto ch, auto rest) {
+        constexpr int trip = 4 * W * decltype(ch)::value;
+        go(ch, rest, (size_t)((HD + trip - 1) / trip * trip) * sizeof(double));
         return hipGetLastError();
     };
-    if (HD <= 128) return with(std::integral_constant<int, 2>{});
-    if (HD <= 256) return with(std::integral_constant<int, 4>{});
-    return with(std::integral_constant<int, kScoreChunks>{});
+    auto each = [&](auto ch) {
+        if (whole) return with(ch, std::integral_constant<Rest, kNoRest>{});
+        if (trips == 1) return with(ch, std::integral_constant<Rest, kLastPiece>{});
+        return with(std::integral_constant<int, kScoreChunks>{}, std::integral_constant<Rest, kAnyPiece>{});
+    };
+    switch ((pieces + trips - 1) / trips) {
+        case 1: return each(std::integral_constant<int, 1>{});
+        case 2: return each(std::integral_constant<int, 2>{});
+        case 3: return each(std::integral_constant<int, 3>{});
+        case 4: return each(std::integral_constant<int, 4>{});
+        case 5: return each(std::integral_constant<int, 5>{});
+        case 6: return each(std::integral_constant<int, 6>{});
+        case 7: return each(std::integral_constant<int, 7>{});
+        default: return each(std::integral_constant<int, 8>{});
+    }
 }
 
 hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
@@ -716,20 +742,25 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
         const int lpr = a.head_dim / 8;
         f.waves = rows_divide_a_wave(lpr) && f.slots * lpr % 64 == 0 ? f.slots * lpr / 64 : 0;
         const dim3 grid((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16), a.n_layers), block(kFoldThreads);
-        return with_pieces(HD, [&](auto ch, auto full, size_t lds) {
+        return with_pieces<16>(HD, [&](auto ch, auto rest, size_t lds) {
             constexpr int CH = decltype(ch)::value;
-            constexpr bool FULL = decltype(full)::value;
-            if (a.q_dtype == TOM_F32) score_fold_query_kernel<In_f32, CH, FULL><<<grid, block, lds, s>>>(a, f);
-            else if (a.q_dtype == TOM_BF16) score_fold_query_kernel<In_bf16, CH, FULL><<<grid, block, lds, s>>>(a, f);
-            else score_fold_query_kernel<In_f16, CH, FULL><<<grid, block, lds, s>>>(a, f);
+            constexpr Rest REST = decltype(rest)::value;
+            if (a.q_dtype == TOM_F32) score_fold_query_kernel<In_f32, CH, REST><<<grid, block, lds, s>>>(a, f);
+            else if (a.q_dtype == TOM_BF16) score_fold_query_kernel<In_bf16, CH, REST><<<grid, block, lds, s>>>(a, f);
+            else score_fold_query_kernel<In_f16, CH, REST><<<grid, block, lds, s>>>(a, f);
         });
     }
     if (hipError_t e = launch_query_fold(a, false, s)) return e;
-    const int per_block = kBlock / 16;
-    const dim3 grid((a.n_groups + per_block - 1) / per_block, a.n_layers);
-    return with_pieces(HD, [&](auto ch, auto full, size_t lds) {
-        score_mean_query_kernel<decltype(ch)::value, decltype(full)::value><<<grid, dim3(kBlock), lds, s>>>(a);
-    });
+    auto go = [&](auto lanes) {
+        constexpr int W = decltype(lanes)::value, per_block = kBlock / W;
+        const dim3 grid((a.n_groups + per_block - 1) / per_block, a.n_layers);
+        return with_pieces<W>(HD, [&](auto ch, auto rest, size_t lds) {
+            score_mean_query_kernel<W, decltype(ch)::value, decltype(rest)::value><<<grid, dim3(kBlock), lds, s>>>(a);
+        });
+    };
+    // long keys in one trip of 512-byte pieces: 28 x 1024 groups x 8 heads of 128 39.6 -> 35.9 us, 700 x 8 of 256 47.5 -> 45.1, but
+    // 1024 x 5 of 128 (two trips of five 256-byte pieces) 23.1 -> 25.4
+    return HD >= 1024 ? go(std::integral_constant<int, 32>{}) : go(std::integral_constant<int, 16>{});
 }
 
 hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {

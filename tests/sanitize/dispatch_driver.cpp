@@ -40,11 +40,15 @@ static void fold() {
     a.q_dtype = TOM_F32;                               // twice the bytes
     CHECK(slots_with_scores_at(q + q_bytes) == 0);
     CHECK(slots_with_scores_at(q + 2 * q_bytes) == 8);
-    // the line: 28 * 128 query elements a token, 8 workgroups a layer at 256 groups
+    // the line: seven rows a token in eight slots, 8 workgroups a layer at 256 groups
     a.scores = reinterpret_cast<float*>(at(1 << 28));
-    a.n_layers = 8, a.n_groups = 256, a.score_stride = 256, a.t_q = 26;
+    a.n_layers = 8, a.n_groups = 256, a.score_stride = 256, a.t_q = 18;
     CHECK(fold_slots(a) == 8);
-    a.t_q = 27;
+    a.t_q = 19;
+    CHECK(fold_slots(a) == 0);
+    a.n_layers = 28, a.n_groups = a.score_stride = 1024, a.t_q = 1, a.q_dtype = TOM_BF16;  // several rounds of the chip
+    CHECK(fold_slots(a) == 8);
+    a.t_q = 2;
     CHECK(fold_slots(a) == 0);
     // one round of the chip: one workgroup per compute unit with a float32 query, two with a 16-bit one and short keys
     a.t_q = 1, a.n_layers = 8;

@@ -17,14 +17,16 @@ def oqm():
     return m
 
 
-# H_k * d = 8 .. 128 (two pieces), .. 256 (four), above (eight; 512, 1024: whole; 520, 1280: with a rest)
-@pytest.mark.parametrize("H,d", ((1, 8), (1, 64), (1, 72), (2, 64), (1, 136), (3, 64), (2, 128), (2, 136), (3, 96), (5, 64),
-                                 (4, 128), (65, 8), (8, 128), (5, 256)))
+# one to eight pieces of 64 channels, whole and with a rest; above 512 channels equal trips (640, 768, 896), eight pieces and a rest
+# (520, 704), and from 1024 on pieces of 128 channels: 1024, 1152 (two trips and a rest), 1280, 2048, 2056
+@pytest.mark.parametrize("H,d", ((1, 8), (1, 64), (1, 72), (2, 64), (1, 136), (3, 64), (1, 200), (2, 128), (2, 136), (3, 96), (5, 64),
+                                 (3, 112), (3, 128), (7, 56), (7, 64), (4, 120), (4, 128), (65, 8), (5, 128), (11, 64), (6, 128), (7, 128),
+                                 (8, 128), (9, 128), (5, 256), (8, 256), (257, 8)))
 def test_pieces_of_the_key(oqm, H, d):
     for i, (L, T, tq) in enumerate(((2, 17, 3), (1, 70, 40))):
         check_mean(oqm, L, H, 2, d, T, tq, ("bf16", "f32")[i], True, H * d + i)
-    # long questions: past 12e6 query elements x (workgroups + 64), so fold and scores are launches of their own
-    tq = 12000000 // 64 // (2 * H * d) + 1
+    # long questions, more rows than the rule allows a slot: fold and scores are launches of their own
+    tq = 12 * max(1, 4096 // (H * d)) + 1
     check_mean(oqm, 1, H, 2, d, 33, tq, "f16", H % 2 == 0, H * d + 7)
 
 
