@@ -2,21 +2,21 @@
 // (paper Sec. 3.4, Eq. 11 and Eq. 13; supplement "Cache reconstruction for decoding").
 //
 // Grid (rank * chunks + chunk, then prefix blocks; K|V * H_k + head; layer): a workgroup of 256
-// threads owns one head tile of one selected group where four passes cover it (64 token rows at
-// head_dim 128), otherwise an equal share of it, at most three passes; consecutive workgroups
+// threads owns one head tile of one selected group where few passes cover it, otherwise an equal share of
+// it (launch_t); consecutive workgroups
 // write consecutive row blocks of the active buffer.  It reads the group index from device memory
 // (the index array never visits the host), streams its rows' packed codes and (scale, zero) pairs,
-// and writes them to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns one
-// 32-bit word of codes (8 channels) into one 128-bit non-temporal store, so each store
-// instruction of a wave writes 1 KB of contiguous bf16.  HBM-bound: 0.5 + 8/gs bytes
+// and writes them to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns the codes of
+// 16 bytes of output (8 channels, 4 in float32) into one 128-bit non-temporal store, so each store
+// instruction of a wave writes 1 KB of contiguous memory.  HBM-bound: 0.5 + 8/gs bytes
 // read and 2 bytes written per element.
 //
 // Measured at 28 layers x 64 random groups x 196 x 128 (944 MB): cards differ, the benchmark's kernel
 // trace averages 163 us (5.8 TB/s) on the fastest one seen and 169 (5.6) on another, where an
-// arithmetic-free linear stream of the same byte mix reaches 6.1 TB/s.  On the fast one, in-kernel
-// clocks: a workgroup lives 3.5 us (index 0.2, loads 1.5, stores 1.7), 1520 of 2048 slots are taken at any time.  One to
+// arithmetic-free linear stream of the same byte mix reaches 6.1 TB/s.  Before the stores stopped waiting for each other (below) a
+// workgroup lived 3.5 us (index 0.2, loads 1.5, stores 1.7) and 1520 of 2048 slots were taken at any time; one to
 // five passes per workgroup, 256 or 512 threads and a barrier between loads and stores
-// all stay within 1 %; seven passes 171, 1024 threads 165, three or five workgroups per compute unit
+// all stayed within 1 %; seven passes 171, 1024 threads 165, three or five workgroups per compute unit
 // instead of eight 230 / 181, and a persistent loop that loads the next piece before it
 // stores the current one 187 us: the memory system prefers workgroups whose reads and writes
 // are separate bursts.  All heads' K before all heads' V (162 us) is 1 % faster than K and V of a
@@ -120,6 +120,10 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
                 sm[u] = *reinterpret_cast<const meta_pair*>(meta_t + (item >> a.lpg_shift) * (uint32_t)sizeof(meta_pair));
         }
     }
+    // One wait for all loads.  Without it each item waits for its own, which after the first store is a wait for
+    // that store as well: 28 layers x 64 groups x 196 x 128 163.5 -> 162 us, 73 tokens x 13 groups 3 % less; but the token axis, with more items a lane,
+    // and float32 output are 2 to 5 % slower with it.
+    if constexpr (!TOKEN_AXIS && EB == 2) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0) alone
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const uint32_t item = first + u * a.step;
@@ -172,11 +176,17 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     a.step = tok ? kBlock / lpr * lpr : kBlock;
     a.tile_items = G * lpr;  // G * d * 4 < 2^31 is checked by the API layer
     const uint32_t passes = (a.tile_items + a.step - 1) / a.step;
-    // up to four passes: one workgroup per tile; more: equal chunks (whole rows) of at most three passes
-    const uint32_t unroll = passes <= 4 ? 4 : 3;
-    a.chunks = passes <= 4 ? 1 : (passes + 2) / 3;
-    while ((G + a.chunks - 1) / a.chunks * lpr > unroll * a.step) ++a.chunks;
+    // Up to `whole` passes one workgroup takes the tile, above that equal chunks (whole rows) of at most `most`.  On the token axis every
+    // lane first loads the pairs of its channels, 64 bytes at 16-bit output against 16 stored per pass, so it takes more passes.  28 layers, us per question (200
+    // stored groups, 10 to 60 selected), chunks of at most 3 / 4 / 5 / 7 passes: head_dim axis bf16 109.0 / 110.6 / 111.8 / 113.0, float32 105 / 101.7 / 112 / 112;
+    // token axis bf16 13 passes 115 / 115 / 107 / 110, 5 passes 85 / 85 / 70 / 70, 7 passes 107 / 92 / 92 / 87.6, 8 passes 114 / 106 / 106 /
+    // 106 (all in one 112), float32 88.7 / 97 / 100 / 100.
+    const uint32_t whole = tok && eb == 2 ? 7 : 4, most = eb == 2 ? (tok ? 5 : 3) : (tok ? 3 : 4);
+    const uint32_t fit = passes <= whole ? whole : most;
+    a.chunks = passes <= whole ? 1 : (passes + most - 1) / most;
+    while ((G + a.chunks - 1) / a.chunks * lpr > fit * a.step) ++a.chunks;
     a.chunk_items = (G + a.chunks - 1) / a.chunks * lpr;
+    const uint32_t unroll = (a.chunk_items + a.step - 1) / a.step;  // at most fit
     a.inv_chunks = reciprocal_u32(a.chunks);
     if (N < 8 && (int64_t)a.k_eff * a.chunks * kBlock >= 1LL << 31) return launch_t<OUT, 8>(args, s);  // fewer, longer workgroups
     if ((int64_t)a.k_eff * a.chunks > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -200,28 +210,30 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
         }
     }
     const dim3 grid((uint32_t)a.k_eff * a.chunks + prefix_blocks, 2 * a.n_kv_heads, a.n_layers), block(kBlock);
-    auto go = [&](auto unroll, auto bits, auto mb) {
+    auto go = [&](auto unroll, auto tokens, auto bits, auto mb) {
         constexpr int U = decltype(unroll)::value, B = decltype(bits)::value;
-        constexpr bool M = decltype(mb)::value;
-        auto with_select = [&](auto select) {
-            constexpr int S = decltype(select)::value;
-            if (tok) dequant_gather_kernel<OUT, N, U, true, B, M, S><<<grid, block, 0, s>>>(a);
-            else dequant_gather_kernel<OUT, N, U, false, B, M, S><<<grid, block, 0, s>>>(a);
-        };
-        if (!select) with_select(std::integral_constant<int, 0>{});
-        else if (select == 1) with_select(std::integral_constant<int, 1>{});
-        else with_select(std::integral_constant<int, kBlock / 64>{});
+        constexpr bool K = decltype(tokens)::value, M = decltype(mb)::value;
+        if (!select) dequant_gather_kernel<OUT, N, U, K, B, M, 0><<<grid, block, 0, s>>>(a);
+        else if (select == 1) dequant_gather_kernel<OUT, N, U, K, B, M, 1><<<grid, block, 0, s>>>(a);
+        else dequant_gather_kernel<OUT, N, U, K, B, M, kBlock / 64><<<grid, block, 0, s>>>(a);
     };
-    auto with_meta = [&](auto unroll, auto bits) {
-        if (a.meta_bf16) go(unroll, bits, std::true_type{});
-        else go(unroll, bits, std::false_type{});
+    auto with_storage = [&](auto unroll, auto tokens) {
+        if (a.bits == 2 && a.meta_bf16) go(unroll, tokens, std::integral_constant<int, 2>{}, std::true_type{});
+        else if (a.bits == 2) go(unroll, tokens, std::integral_constant<int, 2>{}, std::false_type{});
+        else if (a.meta_bf16) go(unroll, tokens, std::integral_constant<int, 4>{}, std::true_type{});
+        else go(unroll, tokens, std::integral_constant<int, 4>{}, std::false_type{});
     };
-    auto with_bits = [&](auto unroll) {
-        if (a.bits == 2) with_meta(unroll, std::integral_constant<int, 2>{});
-        else with_meta(unroll, std::integral_constant<int, 4>{});
-    };
-    if (unroll == 4) with_bits(std::integral_constant<int, 4>{});
-    else with_bits(std::integral_constant<int, 3>{});
+    if (!tok) {
+        if (unroll <= 3) with_storage(std::integral_constant<int, 3>{}, std::false_type{});
+        else with_storage(std::integral_constant<int, 4>{}, std::false_type{});
+    } else {
+        if (unroll <= 3) with_storage(std::integral_constant<int, 3>{}, std::true_type{});
+        else if (unroll == 4) with_storage(std::integral_constant<int, 4>{}, std::true_type{});
+        else if constexpr (eb == 2) {
+            if (unroll == 5) with_storage(std::integral_constant<int, 5>{}, std::true_type{});
+            else with_storage(std::integral_constant<int, 7>{}, std::true_type{});
+        }
+    }
     return hipGetLastError();
 }
 
