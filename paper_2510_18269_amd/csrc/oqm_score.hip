@@ -62,6 +62,16 @@ __device__ __forceinline__ double lanes_sum_f64(double v) {
     return v;
 }
 
+// Sum of the four lanes of a wave that are equal modulo 16 (valid in all of them).
+__device__ __forceinline__ double rows16_sum_f64(double v) {
+    double w = v;
+    swap_lanes<16>(v, w);
+    v += w;
+    w = v;
+    swap_lanes<32>(v, w);
+    return v + w;
+}
+
 // A sum over the workgroup: every wave puts its share, the total can be read behind a barrier.
 __device__ __forceinline__ void put_wave_sum(double v, double* wsum) {
     v = lanes_sum_f64<64>(v);
@@ -74,15 +84,27 @@ __device__ __forceinline__ double total_of(const double* wsum) {
     for (int w = 0; w < WAVES; ++w) v += wsum[w];
     return v;
 }
-// |q-bar|^2 of a layer, from what query_fold_kernel has left: the shares of the waves.
-__device__ __forceinline__ void put_query_norm2(const ScoreArgs& a, int li, int HD, int threads, double* wsum) {
-    double sq = 0.0;
-    for (int e = threadIdx.x; e < HD; e += threads) {
-        const double qb = a.ws_qbar[(int64_t)li * HD + e];
-        sq = fma(qb, qb, sq);
+// |q-bar|^2 of a layer, from what query_fold_kernel has left: the first elements are requested where this is made, and
+// put() behind the work that their latency shall not hold up (summed in front of it, 2000 of the 10800 cycles of a split workgroup with one tile of
+// tokens: 28 layers x 100 groups x 10 tokens 13.8 -> 13.3 us, 17 x 167 x 10 at 5 heads of 256 18.3 -> 17.5, 28 x 1024 x 64 62.9 -> 62.3, with the sums over
+// lanes by swaps).
+template <int THREADS>
+struct QueryNorm2 {
+    const double* qbar;
+    int HD;
+    double first;
+    __device__ __forceinline__ QueryNorm2(const ScoreArgs& a, int li, int HD_) : qbar(a.ws_qbar + (int64_t)li * HD_), HD(HD_) {
+        first = qbar[min((int)threadIdx.x, HD - 1)];
     }
-    put_wave_sum(sq, wsum);
-}
+    __device__ __forceinline__ void put(double* wsum) const {
+        double sq = (int)threadIdx.x < HD ? first * first : 0.0;
+        for (int e = threadIdx.x + THREADS; e < HD; e += THREADS) {
+            const double qb = qbar[e];
+            sq = fma(qb, qb, sq);
+        }
+        put_wave_sum(sq, wsum);
+    }
+};
 
 // Column sums over the row slots of a wave where lpr = d/8 lanes per row divide it: one row of d sums per wave in `red`,
 // in channel order.  Every lane of the wave takes part.
@@ -536,7 +558,7 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     const double* qtok = a.ws_qtok + (int64_t)li * Tq * HD;
 
     __shared__ double wsum[kBlock / 64];
-    if (a.sim == TOM_SIM_COSINE) put_query_norm2(a, li, HD, kBlock, wsum);  // read behind the barriers of gemm_rows
+    const QueryNorm2<kBlock> norm(a, li, HD);
 
     double colsum = 0.0, nk2 = 0.0;
     for (int m0 = 0; m0 < Tq; m0 += kGemmM) {
@@ -548,11 +570,11 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
             default: gemm_rows<4>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
         }
     }
+    norm.put(wsum);
     // lanes fi, 16 + fi, 32 + fi, 48 + fi hold the partial sums of group n0 + 16*wave + fi
-    colsum += __shfl_xor(colsum, 16, 64);
-    colsum += __shfl_xor(colsum, 32, 64);
-    nk2 += __shfl_xor(nk2, 16, 64);
-    nk2 += __shfl_xor(nk2, 32, 64);
+    colsum = rows16_sum_f64(colsum);
+    nk2 = rows16_sum_f64(nk2);
+    __syncthreads();
     const int t = n0 + wave * 16 + fi;
     if (kk == 0 && t < T) {
         double s = colsum / (double)Tq;
@@ -577,6 +599,8 @@ template <int MT>
 __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const ScoreArgs a) {
     __shared__ double red[kSplitWaves][2 * 256];  // two 16 x 16 tiles of every wave
     __shared__ double col[2][kSplitWaves][16];
+    __shared__ double wsum[kSplitWaves];
+    request(a);
     const int unit = (int)(blockIdx.x & 7u) * a.gemm_units_per_xcd + (int)(blockIdx.x >> 3);
     if (unit >= a.gemm_units) return;  // uniform per workgroup
     const int li = div_by(unit, a.gemm_tiles_per_layer, a.inv_gemm_tiles_per_layer);
@@ -589,9 +613,7 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
     // groups past T and tokens past T_q repeat the last one and are dropped at the end
     const float* const key = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups + min(n0 + fi, T - 1)) * HD;
     const double* const qtok = a.ws_qtok + (int64_t)li * Tq * HD;
-
-    __shared__ double wsum[kSplitWaves];
-    if (a.sim == TOM_SIM_COSINE) put_query_norm2(a, li, HD, kSplitThreads, wsum);  // read behind barriers
+    const QueryNorm2<kSplitThreads> norm(a, li, HD);
 
     double csum = 0.0, nk2 = 0.0;
     for (int m0 = 0; m0 < Tq; m0 += 16 * MT) {
@@ -637,6 +659,7 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
                 }
             }
         }
+        if (m0 == 0) norm.put(wsum);  // read behind the barriers below
         // add up the waves, two tiles at a time: thread (u, e) owns element e = v * 64 + lane of tile m + u
 #pragma unroll
         for (int m = 0; m < MT; m += 2) {
@@ -657,11 +680,10 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
             }
         }
     }
+    const double nq = sqrt(total_of<kSplitWaves>(wsum));
     // lanes fi, 16 + fi, 32 + fi, 48 + fi hold parts of group n0 + fi
-    csum += __shfl_xor(csum, 16, 64);
-    csum += __shfl_xor(csum, 32, 64);
-    nk2 += __shfl_xor(nk2, 16, 64);
-    nk2 += __shfl_xor(nk2, 32, 64);
+    csum = rows16_sum_f64(csum);
+    nk2 = rows16_sum_f64(nk2);
     if (kk == 0) {
         col[0][wave][fi] = csum;
         col[1][wave][fi] = nk2;
@@ -669,14 +691,13 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
     __syncthreads();
     if (tid < 16 && n0 + tid < T) {
         double s = 0.0, n2 = 0.0;
+#pragma unroll
         for (int w = 0; w < kSplitWaves; ++w) {
             s += col[0][w][tid];
             n2 += col[1][w][tid];
         }
         s = s / (double)Tq;
-        if (a.sim == TOM_SIM_COSINE) {
-            s = s / (fmax(sqrt(total_of<kSplitWaves>(wsum)), 1e-12) * fmax(sqrt(n2), 1e-12));
-        }
+        if (a.sim == TOM_SIM_COSINE) s = s / (fmax(nq, 1e-12) * fmax(sqrt(n2), 1e-12));
         a.scores[(int64_t)li * a.score_stride + n0 + tid] = (float)s;
     }
 }
