@@ -135,16 +135,15 @@ inline bool prefix_joins_gather(const DequantArgs& a) {
 constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups
 
 // Waves of each gather workgroup that select its group from the scores (256 scores each; one or all four), or
-// 0: the indices come from a top-k launch.  The launch costs 2.5 to 4 us on the device; selecting delays each
-// workgroup by about 1 us with one wave (up to 256 scores) and 2 us with four, so it pays while the workgroups
-// run in about one round.  Whole one-call question at 4 heads, itself / with the launch: 256 scores, 896 workgroups 13.0 / 14.9 us,
-// 1792 15.2 / 17.4, 4000 16.3 / 17.3 or 16.6, 6000 21.1 / 20.4; 1024 scores, 64 workgroups 12.9 / 14.5, 896 24.8 / 25.6, 1280 14.5 / 14.9
-// (in a graph 14.2 / 14.1), 2560 20.5 / 17.5.
+// 0: the indices come from a top-k launch.  The launch costs 2.5 to 4 us on the device; selecting delays every
+// round of workgroups by the 1 to 2 us of the selection.  Whole one-call question with one query token at 4 heads, with the launch / itself: 256 scores, 40
+// workgroups 11.6 / 8.7 us, 1280 11.9 / 10.8, 2560 14.7 / 14.4, 5376 24.4 / 23.1, 7168 29.0 / 27.4, 8960 26.7 / 26.2, 14336 51.5 / 56.9; 500 scores, 640 11.5 /
+// 10.8, 1920 13.9 / 14.0, 2240 20.5 / 19.9, 2560 15.3 / 16.0; 1024 scores, 640 13.8 / 10.7, 1920 14.2 / 14.0, 2400 15.0 / 15.3, 5120 20.6 / 22.7.
 // The launch reads all scores while it writes: no output may share memory with them.
 inline int select_waves(const DequantArgs& a) {
     const int waves = a.n_groups <= 64 * kSelectKeys ? 1 : kBlock / 64;
     const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
-    if (a.n_groups > kBlock * kSelectKeys || (int64_t)a.k_eff * a.chunks * 2 * heads > (waves == 1 ? 2048 : 1024)) return 0;
+    if (a.n_groups > kBlock * kSelectKeys || (int64_t)a.k_eff * a.chunks * 2 * heads > (waves == 1 ? 8192 : 2048)) return 0;
     const uint64_t score_bytes = score_span(a.score_stride, a.n_layers, a.n_groups);
     const uint64_t out_bytes = (uint64_t)(heads * a.head_out_bytes), idx_bytes = 4u * (uint64_t)a.n_layers * (uint64_t)a.k;
     return apart(a.scores, score_bytes, a.k_out, out_bytes) && apart(a.scores, score_bytes, a.v_out, out_bytes) &&

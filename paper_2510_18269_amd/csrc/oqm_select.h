@@ -2,6 +2,8 @@
 // top-k kernel and by the gather of a small retrieval.
 #pragma once
 
+#include <type_traits>
+
 #include "oqm_device.h"
 
 namespace oqm {
@@ -18,33 +20,52 @@ __device__ __forceinline__ uint32_t rank_in(uint64_t b) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
 }
 
-constexpr uint32_t kSelectList = 16;  // keys that are ranked in less time than two more steps take
+// Inclusive sum over the lanes of a wave up to this one.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    auto step = [&](auto ctrl, auto rows) {
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});  // row_shr:1, 2, 4, 8
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});  // row_bcast:15 into rows 1 and 3
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});  // row_bcast:31 into rows 2 and 3
+    return v;
+}
 
-// Memory that the waves of select_largest share (one wave uses none).
+constexpr int kHistCopies = 4;        // words per bin: lanes that add to one bin take turns
+constexpr uint32_t kSelectList = 16;  // keys that are ranked in less time than another digit takes
+
+// Memory that the waves of select_largest share.
 template <int WAVES>
-struct SelectScratch {
-    uint32_t slots[2][2 * WAVES];
+struct alignas(16) SelectScratch {
+    uint32_t hist[2][256 * kHistCopies];
     uint32_t list[kSelectList];
+    uint32_t slots[2][2 * WAVES];
+    uint32_t listed;
 };
 
 // WAVES waves hold the keys of one row, KEYS per lane: wave w, register c, lane l is entry
 // (w * KEYS + c) * 64 + l of the row (absent ones hold key 0; more than k_eff are present).  Calls emit(rank, entry)
 // in the lane of each of the k_eff largest keys, ranks 0 .. k_eff - 1 in ascending entry order; of equal keys the
-// lowest entries are taken.  The k-th largest key is built from the top: the largest extension of it that at
-// least k keys reach is taken, and the search ends early when exactly k do.  A count is
-// KEYS ballots and scalar population counts.  One wave settles a bit at a time, with no barrier and no
-// LDS at all.  Several exchange their counts through `slots` (two alternating sets of two words a wave), which
-// is most of a step (0.28 us), so a step of theirs settles two bits with three counts; once the range that holds
-// the k-th key is down to 16 keys these are listed and every wave ranks the list by itself.  Scores that occur
-// several times (a camera that does not move) never let the search end with exactly k, and 16 steps are slower
-// than the radix select of oqm_topk.hip: they end on the list, or, if more than 16 are equal, by the comparison of a
-// range that a step inside the mantissa has not divided with one of its keys.  28 rows of 1024 scores, this / without
-// list and comparison / radix select: all different 5.3 / 5.2 / 5.9 us, each five times over 5.6 / 6.7 / 5.9, all
-// equal 4.8 / 6.5 / 8.6.  Listing at 64 keys: 5.5 / 5.6 / 4.9, and 7.2 instead of 6.2 us at 777 scores with 60 of each.
+// lowest entries are taken.
+// The k-th largest key is found from the top, eight bits at a time: the keys that share its upper digits are counted by their next one
+// in LDS, and every wave scans the 256 counts by itself, so a digit costs a barrier or none.  The search ends early when a range
+// is chosen whole, when it is down to 16 keys (these are listed, and every wave ranks the list by itself), or when a digit has not divided it and all
+// its keys are equal (a camera that does not move).  Bound by the latency of its serial steps: two digits and the list at random scores.  Lanes that
+// add to one word take their turns, hence four words a bin.  28 rows in a graph, this / two bits a barrier by ballots: 200
+// scores 2.9 / 3.0 us, 1024 3.7 / 5.0, 2000 3.9 / 6.1, 3600 5.6 / 7.4; 1024 equal ones 3.6 / 4.7, 4096 6.2 / 7.0 (one word a bin 10.8), each of 1024 five
+// times 3.8 / 5.3, 777 with 60 of each 4.1 / 5.5.  One word a bin and a test of each register for lanes that all share a bin: 3.9 at 1024, 6.4 at 3600.
 template <int WAVES, int KEYS, typename EMIT>
 __device__ __forceinline__ void select_largest(const uint32_t (&key)[KEYS], int k_eff, int wave, int lane,
                                                SelectScratch<WAVES>* shared, EMIT emit) {
-    int phase = 0;
+    // what the waves have written is read by all; one wave's LDS operations are in order anyway
+    auto sync = [] {
+        if constexpr (WAVES > 1) __syncthreads();
+        else __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    };
     // sum over aligned sets of WAVES lanes (DPP), as a scalar
     auto lanes_sum = [](uint32_t v) -> uint32_t {
         if constexpr (WAVES >= 2) v += dpp_u32<0xB1>(v);
@@ -53,120 +74,107 @@ __device__ __forceinline__ void select_largest(const uint32_t (&key)[KEYS], int 
         if constexpr (WAVES >= 16) v += dpp_u32<0x140>(v);
         return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
     };
+    int phase = 0;
     // two words of every wave, in lane w of each aligned set of WAVES lanes
     auto exchange = [&](uint32_t& x, uint32_t& y) {
-        if (lane == 0) {
-            shared->slots[phase][2 * wave] = x;
-            shared->slots[phase][2 * wave + 1] = y;
+        if constexpr (WAVES > 1) {
+            if (lane == 0) {
+                shared->slots[phase][2 * wave] = x;
+                shared->slots[phase][2 * wave + 1] = y;
+            }
+            __syncthreads();
+            x = shared->slots[phase][2 * (lane & (WAVES - 1))];
+            y = shared->slots[phase][2 * (lane & (WAVES - 1)) + 1];
+            phase ^= 1;
         }
-        __syncthreads();
-        x = shared->slots[phase][2 * (lane & (WAVES - 1))];
-        y = shared->slots[phase][2 * (lane & (WAVES - 1)) + 1];
-        phase ^= 1;
     };
-    // keys of this wave that reach `cand`
-    auto reach = [&](uint32_t cand) -> uint32_t {
-        uint32_t mine = 0;
-#pragma unroll
-        for (int c = 0; c < KEYS; ++c) mine += (uint32_t)__popcll(__ballot(key[c] >= cand));
-        return mine;
+    auto clear = [&](int digit, int n) {
+        u32x4* const h = reinterpret_cast<u32x4*>(shared->hist[digit & 1]);
+        for (int i = wave * 64 + lane; i < n * 64 * kHistCopies; i += 64 * WAVES) h[i] = u32x4{0u, 0u, 0u, 0u};
     };
-    uint32_t thr = 0;   // the k-th largest key; only keys above it once `exact`
-    bool exact = false, counted = false;
-    uint32_t gt_all = 0, base_g = 0, base_e = 0;   // keys above thr: in all waves; in the waves before this one, and keys equal to it there
-    if constexpr (WAVES == 1) {
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)(thr | 1u << bit));
-            const uint32_t cnt = reach(cand);
-            if (cnt >= (uint32_t)k_eff) thr = cand;
-            if (cnt == (uint32_t)k_eff) {
-                exact = true;
-                break;
-            }
-        }
-    } else {
-        const bool earlier = (lane & (WAVES - 1)) < wave;
-        uint32_t lo = 64 * KEYS * WAVES, hi = 0;  // keys from thr on; keys above the range [thr, thr + 2^bit)
-        uint32_t lo_w = 64 * KEYS, hi_w = 0;      // lane w: of these those of wave w
-        uint32_t unequal = 0;                     // size of the last range that did not hold one value only
-        for (int bit = 30; bit >= 0; bit -= 2) {
-            const uint32_t one = 1u << bit, before = lo - hi;
-            const uint32_t c1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(thr | one)), c2 = c1 + one, c3 = c2 + one;
-            uint32_t w12 = reach(c1) | reach(c2) << 16, w3 = reach(c3);  // at most 4096 each
-            exchange(w12, w3);
-            const uint32_t n12 = lanes_sum(w12), n1 = n12 & 0xffffu, n2 = n12 >> 16, n3 = lanes_sum(w3);
-            const uint32_t w1 = w12 & 0xffffu, w2 = w12 >> 16;
-            if (n3 >= (uint32_t)k_eff) {
-                thr = c3, lo = n3, lo_w = w3;
-            } else if (n2 >= (uint32_t)k_eff) {
-                thr = c2, lo = n2, lo_w = w2, hi = n3, hi_w = w3;
-            } else if (n1 >= (uint32_t)k_eff) {
-                thr = c1, lo = n1, lo_w = w1, hi = n2, hi_w = w2;
-            } else {
-                hi = n1, hi_w = w1;
-            }
-            if (lo == (uint32_t)k_eff) {
-                exact = true;
-                break;
-            }
-            const uint32_t range = lo - hi;
-            if (bit > 0 && range <= kSelectList) {  // uniform, like all that follows from the exchanged counts
-                const uint32_t first = lanes_sum(earlier ? lo_w - hi_w : 0u);  // this wave's place in the list
-                uint32_t at = first;
-#pragma unroll
-                for (int c = 0; c < KEYS; ++c) {
-                    const bool in = key[c] - thr < one;
-                    const uint64_t b = __ballot(in);
-                    if (in) shared->list[at + rank_in(b)] = key[c];
-                    at += (uint32_t)__popcll(b);
-                }
-                __syncthreads();
-                const uint32_t x = (uint32_t)lane < range ? shared->list[lane] : 0u;
-                uint32_t above = 0;  // listed keys above this lane's
-                for (uint32_t j = 0; j < range; j += 8) {  // padded with zeros, which are above none
-#pragma unroll
-                    for (uint32_t u = 0; u < 8; ++u) above += (uint32_t)__builtin_amdgcn_readlane((int)x, (int)(j + u)) > x;
-                }
-                const uint32_t want = (uint32_t)k_eff - hi;
-                // The k-th key: of all with fewer than `want` above them the one with the most, want - 1 unless it occurs
-                // again.  Lanes past the list have at least `want` keys above them.
-                uint64_t eq = __ballot(above == want - 1);
-                if (!eq) {
-                    uint32_t most = 0;
-                    for (uint64_t rest = __ballot(above < want); rest; rest = __ballot(above > most && above < want))
-                        most = (uint32_t)__builtin_amdgcn_readlane((int)above, __builtin_ctzll(rest));
-                    eq = __ballot(above == most);
-                }
-                thr = (uint32_t)__builtin_amdgcn_readlane((int)x, __builtin_ctzll(eq));
-                const uint64_t gt = __ballot(x > thr), front = (1ull << first) - 1;
-                gt_all = hi + (uint32_t)__popcll(gt);
-                base_g = lanes_sum(earlier ? hi_w : 0u) + (uint32_t)__popcll(gt & front);
-                base_e = (uint32_t)__popcll(eq & front);
-                counted = true;
-                break;
-            }
-            if (bit > 0 && bit < 22 && range == before && range != unequal) {  // uniform, like the counts
-                uint32_t first = 0, same = 1;  // a key of this wave in the range (0: none), and whether all are it
-#pragma unroll
-                for (int c = 0; c < KEYS; ++c) {
-                    const uint64_t in = __ballot(key[c] - thr < one);
-                    if (in && !first) first = (uint32_t)__builtin_amdgcn_readlane((int)key[c], __builtin_ctzll(in));
-                    if (__ballot(key[c] == first) & in ^ in) same = 0;
-                }
-                exchange(first, same);
-                const uint64_t some = __ballot(first != 0);  // the range holds a present key: some wave has one
-                const uint32_t value = (uint32_t)__builtin_amdgcn_readlane((int)first, __builtin_ctzll(some));
-                if (!__ballot(same == 0 || (first != 0 && first != value))) {
-                    thr = value;
-                    break;
-                }
-                unequal = range;
-            }
-        }
-    }
-    if (exact) thr -= 1u;   // "above thr" is now exactly the chosen set (cand >= 1)
+    clear(0, 2);
+    if (wave == 0 && lane == 0) shared->listed = 0u;
+    sync();
 
-    if (!counted) {
+    uint32_t thr = 0;   // the k-th largest key; only keys above it once `exact`
+    uint32_t hi = 0;    // keys above the range that is looked at
+    uint32_t before = 64 * KEYS * WAVES, unequal = 0;  // keys in it; the last size that did not hold one value only
+    bool exact = false;
+    for (int digit = 0; digit < 4; ++digit) {
+        const int shift = 24 - 8 * digit;
+        uint32_t* const hist = shared->hist[digit & 1];
+        if (digit >= 2) {  // rarely
+            clear(digit, 1);
+            sync();
+        }
+#pragma unroll
+        for (int c = 0; c < KEYS; ++c)
+            if (digit == 0 || (key[c] ^ thr) >> (shift + 8) == 0)
+                atomicAdd(&hist[((key[c] >> shift) & 255u) * kHistCopies + (lane & (kHistCopies - 1))], 1u);
+        sync();
+        // lane l owns the bins 252 - 4 l .. 255 - 4 l, so that the scan runs from the largest digit down
+        uint32_t n[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const u32x4 w = reinterpret_cast<const u32x4*>(hist)[252 - 4 * lane + b];
+            n[b] = w[0] + w[1] + w[2] + w[3];
+        }
+        const uint32_t want = (uint32_t)k_eff - hi;
+        const uint32_t incl = wave_scan(n[0] + n[1] + n[2] + n[3]);
+        const uint32_t c3 = incl - n[0] - n[1] - n[2], c2 = c3 + n[2], c1 = c2 + n[1];  // keys down to bin 3, 2, 1 of the four
+        const uint32_t excl = c3 - n[3];
+        uint32_t bin = 255u - 4u * (uint32_t)lane, above = excl, range = n[3];
+        if (want > c3) bin -= 1u, above = c3, range = n[2];
+        if (want > c2) bin -= 1u, above = c2, range = n[1];
+        if (want > c1) bin -= 1u, above = c1, range = n[0];
+        const int at = __builtin_ctzll(__ballot(excl < want && want <= incl));  // exactly one lane
+        thr |= (uint32_t)__builtin_amdgcn_readlane((int)bin, at) << shift;
+        hi += (uint32_t)__builtin_amdgcn_readlane((int)above, at);
+        range = (uint32_t)__builtin_amdgcn_readlane((int)range, at);
+        if (hi + range == (uint32_t)k_eff) {
+            exact = true;
+            break;
+        }
+        if (shift == 0) break;
+        if (range <= kSelectList) {
+#pragma unroll
+            for (int c = 0; c < KEYS; ++c)
+                if ((key[c] ^ thr) >> shift == 0) shared->list[atomicAdd(&shared->listed, 1u)] = key[c];
+            sync();
+            const uint32_t left = (uint32_t)k_eff - hi;
+            const uint32_t x = shared->list[min((uint32_t)lane, range - 1u)];
+            uint32_t greater = 0, reach = 0;  // listed keys above this lane's, and at least it
+            for (uint32_t j = 0; j < range; ++j) {
+                const uint32_t y = (uint32_t)__builtin_amdgcn_readlane((int)x, (int)j);
+                greater += y > x;
+                reach += y >= x;
+            }
+            thr = (uint32_t)__builtin_amdgcn_readlane((int)x, __builtin_ctzll(__ballot(greater < left && reach >= left)));
+            break;
+        }
+        if (digit > 0 && range == before && range != unequal) {  // uniform, like the counts
+            uint32_t first = 0, same = 1;  // a key of this wave in the range (0: none), and whether all are it
+#pragma unroll
+            for (int c = 0; c < KEYS; ++c) {
+                const uint64_t in = __ballot((key[c] ^ thr) >> shift == 0);
+                if (in && !first) first = (uint32_t)__builtin_amdgcn_readlane((int)key[c], __builtin_ctzll(in));
+                if (__ballot(key[c] == first) & in ^ in) same = 0;
+            }
+            exchange(first, same);
+            const uint64_t some = __ballot(first != 0);  // the range holds a present key: some wave has one
+            const uint32_t value = (uint32_t)__builtin_amdgcn_readlane((int)first, __builtin_ctzll(some));
+            if (!__ballot(same == 0 || (first != 0 && first != value))) {
+                thr = value;
+                break;
+            }
+            unequal = range;
+        }
+        before = range;
+    }
+    if (exact) thr -= 1u;   // "above thr" is now exactly the chosen set (thr >= 1: a present key reaches it)
+
+    uint32_t gt_all = 0, base_g = 0, base_e = 0;  // keys above thr: in all waves, in the waves before this one; keys equal to it there
+    {
         uint32_t g = 0, e = 0;
 #pragma unroll
         for (int c = 0; c < KEYS; ++c) {

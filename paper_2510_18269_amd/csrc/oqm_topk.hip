@@ -2,15 +2,11 @@
 // supplement keeps the selected indices in sorted, i.e. temporal, order).
 //
 // Ascending index order (what the retrieval uses) and rows of up to 4096 scores: the row is held
-// in registers and the threshold is found from the top bits down with ballots (oqm_select.h).  The launch is
-// bound by the latency of its serial steps (and by fetching its own code: unrolling 16 keys per
-// lane costs more than the barriers it saves), so rows of up to 256 scores take one wave without
+// in registers and the threshold is found from the top digits down with counts in LDS (oqm_select.h).  The launch is
+// bound by the latency of its serial steps and by fetching its own code, so rows of up to 256 scores take one wave without
 // any barrier, longer ones the fewest waves that keep a lane at 4 (8 above 2048) keys.  Time per launch in a graph at
-// 28 rows, this form against the radix select below: 200 scores 3.5 / 5.2 us, 1024 5.3 / 5.9,
-// 2048 6.5 / 7.5 (7.5 with 8 keys a lane), 3600 8.2 / 10.3; one row: 3.1 / 5.1, 5.1 / 5.8, 6.3 / 7.3,
-// 7.6 / 10.0 us.  At 1024 scores one wave with 16 keys is 1.6 us slower; at 4096 four waves with 16 keys 1.8 us.
-// Scores that repeat, up to all of them equal, take at most 5 % more than the radix select (777 scores with 60
-// of each 6.2 / 5.9 us), usually less (oqm_select.h).
+// 28 rows, this form against the radix select below: 200 scores 2.9 / 5.2 us, 1024 3.7 / 5.9,
+// 2000 3.9 / 7.5, 3600 5.6 / 10.3; scores that repeat, up to all of them equal, take at most 15 % more (oqm_select.h).
 //
 // Longer rows, and the best-first order: one workgroup of 1024 threads per row.  The k-th
 // largest score is found by a 4-pass, 8-bit most-significant-digit radix select over

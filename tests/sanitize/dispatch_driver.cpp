@@ -177,13 +177,13 @@ static void gather() {
         CHECK(scores_at(begin) == 0);
     }
     a.scores = reinterpret_cast<float*>(at(far));
-    // one wave for up to 256 scores and 2048 workgroups, four for up to 1024 and 1024
+    // one wave for up to 256 scores and 8192 workgroups, four for up to 1024 and 2048
     auto waves = [&](int n_groups, int k, int chunks) {
         a.n_groups = n_groups, a.k = a.k_eff = k, a.chunks = (uint32_t)chunks, a.n_layers = 1, a.n_kv_heads = 1;
         return select_waves(a);
     };
-    CHECK(waves(256, 255, 4) == 1 && waves(256, 128, 8) == 1 && waves(256, 129, 8) == 0);
-    CHECK(waves(257, 128, 4) == 4 && waves(257, 129, 4) == 0 && waves(1024, 512, 1) == 4 && waves(1024, 513, 1) == 0);
+    CHECK(waves(256, 255, 4) == 1 && waves(256, 128, 32) == 1 && waves(256, 129, 32) == 0);
+    CHECK(waves(257, 128, 8) == 4 && waves(257, 129, 8) == 0 && waves(1024, 512, 2) == 4 && waves(1024, 513, 2) == 0);
     CHECK(waves(1025, 1, 1) == 0 && waves(1 << 30, 1, 1) == 0);
 
     auto joins = [&](uint64_t sys_k, uint64_t sys_v) {

@@ -17,8 +17,10 @@ def oqm():
     (255, 17, 1, 50, "bf16", 1, 0, "apart"), (256, 1, 2, 196, "bf16", 0, 3, "apart"), (256, 255, 1, 3, "f16", 0, 0, "apart"),
     (257, 20, 1, 16, "bf16", 0, 0, "apart"), (1023, 41, 2, 16, "f32", 1, 2, "apart"),      # four waves select
     (1024, 256, 1, 3, "f16", 0, 0, "apart"), (1024, 1, 1, 196, "bf16", 1, 0, "apart"),
-    (1024, 257, 1, 3, "bf16", 0, 0, "apart"), (256, 128, 4, 16, "f16", 0, 0, "apart"),     # the most workgroups with one wave (2048) and one group more than with four (1024)
-    (1025, 20, 1, 16, "bf16", 0, 0, "apart"), (255, 129, 4, 16, "bf16", 0, 5, "apart"),    # one score too many, one group too many
+    (1024, 257, 1, 3, "bf16", 0, 0, "apart"), (256, 128, 4, 16, "f16", 0, 0, "apart"),
+    (1025, 20, 1, 16, "bf16", 0, 0, "apart"), (255, 129, 4, 16, "bf16", 0, 5, "apart"),    # one score too many; several rounds of workgroups
+    (256, 128, 16, 16, "bf16", 0, 0, "apart"), (256, 129, 16, 16, "f16", 0, 3, "apart"),   # the most workgroups with one wave (8192), and one group more
+    (1000, 128, 4, 16, "bf16", 0, 0, "apart"), (1000, 129, 4, 16, "f16", 1, 0, "apart"),   # the same with four (2048)
     (100, 30, 2, 16, "bf16", 0, 0, "scores in k_out"), (100, 30, 2, 16, "bf16", 0, 0, "idx behind scores"),   # or shared memory (the second one only adjoins)
 ])
 def test_retrieve_matches_separate_calls(oqm, T, k, L, G, dt, axis, prefix, where):

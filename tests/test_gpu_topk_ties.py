@@ -1,7 +1,7 @@
 """GPU: top-k in index order over rows in which scores repeat, against a stable sort.
 
-Rows of more than 256 scores are searched by several waves, which list the range of the k-th score once it holds
-at most 16 of them, and compare a larger one that the steps no longer divide with one of its scores.  The rows
+The search counts eight bits at a time, lists the range of the k-th score once it holds
+at most 16 of them, and compares a larger one that a digit has not divided with one of its scores.  The rows
 sit on both sides of these: runs of 15 to 18 and of 65 equal scores, neighbours that differ in the last bits, one value
 only, few values, both zeros and infinities, and sizes at the edges of the wave forms."""
 import pytest
