@@ -49,7 +49,9 @@ __device__ __forceinline__ void copy_prefix(const char* src, char* dst, int64_t 
 // kUnroll: items per lane; all their loads are issued before the first is converted, and the host
 // cuts the tile into chunks that one trip covers.
 // SELECT: waves of the workgroup that select its group from the layer's scores (256 scores each), or 0: the
-// index comes from memory.
+// index comes from memory; kPastCaches: the same, and the codes are read past the caches (gather_past_caches in oqm_dispatch.h).
+constexpr int kPastCaches = -1;
+
 template <typename OUT, int N, int kUnroll, bool TOKEN_AXIS, int BITS, bool MB, int SELECT>
 __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArgs a) {
     constexpr int EB = elem_bytes<OUT>::value;
@@ -115,7 +117,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
         w[u] = 0u;
         sm[u] = meta_pair{};
         if (active && item < end) {
-            w[u] = load_codes<BITS, N>(codes_t + item * CW);
+            w[u] = load_codes<BITS, N, SELECT == kPastCaches>(codes_t + item * CW);
             if (!TOKEN_AXIS)
                 sm[u] = *reinterpret_cast<const meta_pair*>(meta_t + (item >> a.lpg_shift) * (uint32_t)sizeof(meta_pair));
         }
@@ -140,7 +142,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     }
     if (SELECT > 0 && blockIdx.y == 0 && begin == 0 && tid == 0) a.sel_idx[(int64_t)li * a.k + r] = (int32_t)t;
     // last, so that the index load above stays a scalar load
-    if (SELECT == 0 && a.all_idx && blockIdx.y == 0 && begin == 0 && tid == 0) a.all_idx[(int64_t)li * a.k + r] = (int32_t)r;
+    if (SELECT <= 0 && a.all_idx && blockIdx.y == 0 && begin == 0 && tid == 0) a.all_idx[(int64_t)li * a.k + r] = (int32_t)r;
 }
 
 // The prefix alone.  grid (chunks, H_k * n_layers, 2).
@@ -213,6 +215,9 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     auto go = [&](auto unroll, auto tokens, auto bits, auto mb) {
         constexpr int U = decltype(unroll)::value, B = decltype(bits)::value;
         constexpr bool K = decltype(tokens)::value, M = decltype(mb)::value;
+        if constexpr (!K && B == 4 && eb == 2) {
+            if (!select && gather_past_caches(a)) return dequant_gather_kernel<OUT, N, U, K, B, M, kPastCaches><<<grid, block, 0, s>>>(a);
+        }
         if (!select) dequant_gather_kernel<OUT, N, U, K, B, M, 0><<<grid, block, 0, s>>>(a);
         else if (select == 1) dequant_gather_kernel<OUT, N, U, K, B, M, 1><<<grid, block, 0, s>>>(a);
         else dequant_gather_kernel<OUT, N, U, K, B, M, kBlock / 64><<<grid, block, 0, s>>>(a);

@@ -289,12 +289,17 @@ __device__ __forceinline__ void store_codes8(char* p, const float (&t)[8]) {
     if constexpr (BITS == 4) *reinterpret_cast<uint32_t*>(p) = pack8(t);
     else *reinterpret_cast<uint16_t*>(p) = (uint16_t)pack8_2bit(t);
 }
-// N codes (8, or 4) of BITS bits.
-template <int BITS, int N>
+// N codes (8, or 4) of BITS bits.  PAST_CACHES: they are not worth a place in the caches.
+template <int BITS, int N, bool PAST_CACHES>
 __device__ __forceinline__ uint32_t load_codes(const char* p) {
-    if constexpr (BITS * N == 32) return *reinterpret_cast<const uint32_t*>(p);
-    else if constexpr (BITS * N == 16) return *reinterpret_cast<const uint16_t*>(p);
-    else return *reinterpret_cast<const uint8_t*>(p);
+    auto load = [&](auto type) -> uint32_t {
+        const auto* q = reinterpret_cast<const decltype(type)*>(p);
+        if constexpr (PAST_CACHES) return __builtin_nontemporal_load(q);
+        else return *q;
+    };
+    if constexpr (BITS * N == 32) return load(uint32_t{});
+    else if constexpr (BITS * N == 16) return load(uint16_t{});
+    else return load(uint8_t{});
 }
 
 // 1 / s for a scale of BITS-bit codes.  With 15 steps s <= FLT_MAX / 15 < 2^126 and the

@@ -17,6 +17,14 @@ inline uint64_t score_span(int64_t stride, int n_layers, int n_groups) {
     return sizeof(float) * ((uint64_t)(n_layers - 1) * (uint64_t)stride + (uint64_t)n_groups);
 }
 
+// ---- mean-query score: keys past the caches --------------------------------------------------
+// Where the keys of a call are a good part of the last-level cache (256 MB) they only push out what else is there.  Whole question at one selected
+// group, three stores in turn, through / past the caches: 28 layers x 1500 groups x 512 channels (86 MB) 26.2 / 26.4 us, 2200 (126 MB) 35.3 / 33.3, 3000 (172 MB)
+// 42.8 / 39.7; 1000 (57 MB) 19.2 / 20.5, 200 12.8 / 13.3.
+inline bool keys_past_caches(const ScoreArgs& a) {
+    return (int64_t)a.n_layers * a.n_groups * a.n_kv_heads * a.head_dim * (int64_t)sizeof(float) >= 100000000;
+}
+
 // ---- mean-query score: the query is folded inside the score kernel -----------------------
 constexpr int kFoldThreads = 512;
 
@@ -130,6 +138,14 @@ inline bool prefix_joins_gather(const DequantArgs& a) {
         for (const void* out : {a.k_out, a.v_out})
             if (!apart(sys, sys_bytes, out, out_bytes)) return false;
     return true;
+}
+
+// Whether the codes are read past the caches: where a call reads and writes more than the last-level cache (256 MB) keeps, whatever it
+// leaves there is gone before the next question.  Asked for 4-bit codes on the head_dim axis with 16-bit output alone: the narrower loads of float32
+// output were 7 % slower past the caches, the token axis 2 %.  Question of the benchmark's streams, through / past: 64 groups of 1024 (944 MB) 184 / 181 us, 64 of 3600
+// 211 / 205; 28 layers x 32 of 600 groups (472 MB) 98 / 94; but 16 (236 MB) that the question before read too 51 / 58, 24 (354 MB) 76 / 76.5.
+inline bool gather_past_caches(const DequantArgs& a) {
+    return (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff * a.tile_items * 20 >= 360000000;  // 4 bytes of codes become 16
 }
 
 constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups

@@ -242,15 +242,21 @@ enum Rest { kNoRest, kLastPiece, kAnyPiece };
 template <int W, int CH, Rest REST>
 struct KeyPieces {
     f32x4 x[CH];
+    template <bool PAST_CACHES = false>
     __device__ __forceinline__ void load(const float* key, int e0, int HD, int sub) {
+        auto piece = [](const float* p) {
+            const f32x4* q = reinterpret_cast<const f32x4*>(p);
+            if constexpr (PAST_CACHES) return __builtin_nontemporal_load(q);
+            else return *q;
+        };
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int e = e0 + c * (4 * W) + sub * 4;
             if (REST == kNoRest || (REST == kLastPiece && c < CH - 1)) {
-                x[c] = *reinterpret_cast<const f32x4*>(key + e);
+                x[c] = piece(key + e);
             } else {
                 x[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                if (e < HD) x[c] = *reinterpret_cast<const f32x4*>(key + e);
+                if (e < HD) x[c] = piece(key + e);
             }
         }
     }
@@ -259,7 +265,7 @@ struct KeyPieces {
 // Dot product and norm of one group's key (its first pieces already in `first`) against the staged query, and the score.
 // No branch around the products: the LDS reads of all pieces are then in flight together (with one, this function took 3000 of the 10000 cycles that
 // a workgroup of score_fold_query_kernel lives, now 1800; 1 layer x 256 groups x 16 tokens 7.7 -> 6.6 us).
-template <int W, int CH, Rest REST>
+template <bool PAST_CACHES, int W, int CH, Rest REST>
 __device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double* qbar, const KeyPieces<W, CH, REST>& first, const float* key,
                                                int HD, int sub, int t, int li, double query_norm) {
     double dot = 0.0, nk2 = 0.0;
@@ -267,7 +273,7 @@ __device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double*
     KeyPieces<W, CH, REST> next = first;
     for (int e0 = 0; REST == kLastPiece ? e0 == 0 : e0 < HD; e0 += trip) {
         const KeyPieces<W, CH, REST> cur = next;
-        if (REST != kLastPiece && e0 + trip < HD) next.load(key, e0 + trip, HD, sub);  // uniform
+        if (REST != kLastPiece && e0 + trip < HD) next.template load<PAST_CACHES>(key, e0 + trip, HD, sub);  // uniform
         const f64x2* q = reinterpret_cast<const f64x2*>(qbar + e0) + sub;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -290,7 +296,7 @@ __device__ __forceinline__ void score_of_group(const ScoreArgs& a, const double*
 }
 
 // grid (ceil(T / (256 / W)), n_layers); dynamic LDS: H_k*d doubles (q-bar), padded to whole trips of CH pieces.
-template <int W, int CH, Rest REST>
+template <int W, int CH, Rest REST, bool PAST_CACHES>
 __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArgs a) {
     extern __shared__ __align__(16) double qbar[];
     const int li = blockIdx.y;
@@ -302,7 +308,7 @@ __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArg
     const float* key = keys + (int64_t)tc * HD;
     // The first key loads do not depend on the query: issue them before q-bar is staged.
     KeyPieces<W, CH, REST> first;
-    first.load(key, 0, HD, sub);
+    first.template load<PAST_CACHES>(key, 0, HD, sub);
 
     const int padded = REST == kNoRest ? HD : REST == kLastPiece ? 4 * W * CH : (HD + 4 * W * CH - 1) / (4 * W * CH) * (4 * W * CH);
     __shared__ double wsum[kBlock / 64];
@@ -316,7 +322,7 @@ __global__ void __launch_bounds__(kBlock) score_mean_query_kernel(const ScoreArg
     __syncthreads();
     const double nq = sqrt(total_of<kBlock / 64>(wsum));
 
-    score_of_group(a, qbar, first, key, HD, sub, t, li, nq);
+    score_of_group<PAST_CACHES>(a, qbar, first, key, HD, sub, t, li, nq);
 }
 
 // Fold and score in one launch, for questions short enough that every workgroup can fold the query
@@ -406,7 +412,7 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
     }
     put_wave_sum(sq, wsum);
     __syncthreads();
-    score_of_group(a, qbar, first, key, HD, sub, t, li, sqrt(total_of<kFoldThreads / 64>(wsum)));
+    score_of_group<false>(a, qbar, first, key, HD, sub, t, li, sqrt(total_of<kFoldThreads / 64>(wsum)));
 }
 
 // ------------------------------------------------------------------ per-token GEMM
@@ -776,7 +782,10 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
         constexpr int W = decltype(lanes)::value, per_block = kBlock / W;
         const dim3 grid((a.n_groups + per_block - 1) / per_block, a.n_layers);
         return with_pieces<W>(HD, [&](auto ch, auto rest, size_t lds) {
-            score_mean_query_kernel<W, decltype(ch)::value, decltype(rest)::value><<<grid, dim3(kBlock), lds, s>>>(a);
+            constexpr int CH = decltype(ch)::value;
+            constexpr Rest REST = decltype(rest)::value;
+            if (keys_past_caches(a)) score_mean_query_kernel<W, CH, REST, true><<<grid, dim3(kBlock), lds, s>>>(a);
+            else score_mean_query_kernel<W, CH, REST, false><<<grid, dim3(kBlock), lds, s>>>(a);
         });
     };
     // long keys in one trip of 512-byte pieces: 28 x 1024 groups x 8 heads of 128 39.6 -> 35.9 us, 700 x 8 of 256 47.5 -> 45.1, but
