@@ -463,8 +463,8 @@ __device__ __forceinline__ void mma_chunk(const double* __restrict__ As, const f
 
 // One block of up to 64 query rows: the chunk loop with the row-tile count fixed at compile
 // time, so the accumulators stay in place across the whole contraction.
-template <int MT>
-__device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][kGemmM * kLdA], float (&Bs)[2][kGemmN * kLdB],
+template <int MT, int SIZE>
+__device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SIZE], float (&Bs)[2][kGemmN * kLdB],
                                           const double* qtok, const float* keys, int m0, int n0, int li,
                                           double& colsum, double& nk2) {
     const int HD = a.n_kv_heads * a.head_dim;
@@ -548,9 +548,13 @@ __device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][kG
     }
 }
 
+// MOST: row tiles of a pass.  With one or two the whole question is one pass, and with registers and LDS for them alone six or four
+// workgroups share a compute unit instead of three: 28 layers x 2200 groups x 2 heads of 128 x 16 tokens 29.3 -> 26.5 us (whole question, k = 1), 32 tokens
+// 37.9 -> 35.3, 2000 x 1 head of 64 x 16 18.5 -> 16.6; up to one round of the chip 1 to 2 %.  Three tiles gain nothing.
+template <int MOST>
 __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArgs a) {
     // two LDS stages: chunk c is multiplied while chunk c+1 travels global -> registers -> LDS
-    __shared__ double As[2][kGemmM * kLdA];
+    __shared__ double As[2][MOST * 16 * kLdA];
     __shared__ float Bs[2][kGemmN * kLdB];
     const int unit = (int)(blockIdx.x & 7u) * a.gemm_units_per_xcd + (int)(blockIdx.x >> 3);
     if (unit >= a.gemm_units) return;  // uniform per workgroup
@@ -567,13 +571,17 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     const QueryNorm2<kBlock> norm(a, li, HD);
 
     double colsum = 0.0, nk2 = 0.0;
-    for (int m0 = 0; m0 < Tq; m0 += kGemmM) {
-        const int mt = (min(kGemmM, Tq - m0) + 15) >> 4;
-        switch (mt) {  // uniform
-            case 1: gemm_rows<1>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
-            case 2: gemm_rows<2>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
-            case 3: gemm_rows<3>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
-            default: gemm_rows<4>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+    if constexpr (MOST <= 2) {
+        gemm_rows<MOST>(a, As, Bs, qtok, keys, 0, n0, li, colsum, nk2);
+    } else {
+        for (int m0 = 0; m0 < Tq; m0 += kGemmM) {
+            const int mt = (min(kGemmM, Tq - m0) + 15) >> 4;
+            switch (mt) {  // uniform
+                case 1: gemm_rows<1>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+                case 2: gemm_rows<2>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+                case 3: gemm_rows<3>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+                default: gemm_rows<4>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+            }
         }
     }
     norm.put(wsum);
@@ -807,7 +815,11 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     a.gemm_units_per_xcd = (int32_t)((units + 7) / 8);
     const dim3 grid(8u * (unsigned)a.gemm_units_per_xcd);
     switch (tiles) {
-        case 0: score_token_gemm_kernel<<<grid, dim3(kBlock), 0, s>>>(a); break;
+        case 0:
+            if (a.t_q <= 16) score_token_gemm_kernel<1><<<grid, dim3(kBlock), 0, s>>>(a);
+            else if (a.t_q <= 32) score_token_gemm_kernel<2><<<grid, dim3(kBlock), 0, s>>>(a);
+            else score_token_gemm_kernel<4><<<grid, dim3(kBlock), 0, s>>>(a);
+            break;
         case 1: score_token_split_kernel<1><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
         case 2: score_token_split_kernel<2><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
         case 3: score_token_split_kernel<3><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
