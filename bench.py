@@ -375,6 +375,9 @@ class Leg:
                     "frac_by_committed_kernel_trace": round(b / (traced * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4) if traced else None}
 
         tok = self.tok
+        # the form that the library takes at this size (a few tiles: K cut into chunks like V)
+        append_kernel = ("quantize_append_rows_kernel" if tok else
+                         "quantize_append_cut_kernel" if 2 * L * w.n_kv_heads * fpa <= 384 else "quantize_append_kernel")
         r = {
             "workload": f"{w.name}: {L} layers, {w.n_kv_heads} KV heads ({w.n_q_heads} query heads), "
                         f"head_dim {w.head_dim}, {w.dtype} K/V, {T} frames x {w.group_tokens} tokens stored, "
@@ -399,8 +402,7 @@ class Leg:
             "retrieval_ms_per_query": round(ms_retrieve_call, 4),
             "retrieval_ms_per_query_separate_calls": round(ms_score + ms_topk + ms_gather, 4),
             "roofline": roof("dequant_gather_kernel", b_gat, ms_gather, probes.get("gather")),
-            "roofline_append": roof("quantize_append_tokens_kernel" if tok else "quantize_append_kernel", b_app,
-                                    ms_append, probes.get("append")),
+            "roofline_append": roof(append_kernel, b_app, ms_append, probes.get("append")),
         }
         if self.path == self.oqm.TOM_SCORE_TOKEN_GEMM:
             # the per-token contraction runs on the float64 matrix cores: 2 * T_q * H_k*d flop per group
