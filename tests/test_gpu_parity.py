@@ -84,12 +84,12 @@ def test_shapes_dtypes_and_ragged_tails(oqm, G, d, gs, dt, H_k, H_q):
     (47, 256, 128, 2, 97),    # 8 rows per pass: 16-row V chunks, 6 passes -> 2 gather chunks of 24
     (31, 1032, 8, 1, 193)])   # 129 lanes per row: one row per pass, 31 passes
 def test_chunk_boundaries_of_the_store_and_gather_kernels(oqm, G, d, gs, H_k, frames):
-    """The streaming form of the append cuts V tiles into one-trip chunks and the gather cuts
+    """The append cuts V tiles into one-trip chunks (in launches of few tiles K tiles as well) and the gather cuts
     tiles of more than four row passes into equal chunks: shapes that put chunk ends next to
-    tile ends, on launches of more than 768 tiles (the streaming form) and three frames at a time."""
+    tile ends, on launches of more than 768 tiles (K tiles are walked) and three frames at a time."""
     w = synth_kv.Workload("X", 2, H_k, 2 * H_k, d, G, frames, gs, 5, 5, "bf16", "cosine", 4400 + G + d,
                           "layer_std", frames)
-    assert 2 * 2 * H_k * frames > 768          # K and V tiles of 2 layers: the streaming form
+    assert 2 * 2 * H_k * frames > 768          # K and V tiles of 2 layers: K tiles are walked
     r = _stream_and_check(oqm, w, frames)
     assert r["k_eff"] == 5 and r["loose_rows"] == 0
     r = _stream_and_check(oqm, w, 3, bits=2, meta="bf16")
@@ -164,9 +164,9 @@ def test_bf16_metadata(oqm, qaxis, bits, G, d, gs, dt, H_k, H_q):
     (4, "f32", "bf16", 50, 128, 64, 4, 49), (2, "f32", "f16", 13, 96, 8, 3, 65),
     (4, "bf16", "f32", 33, 256, 128, 2, 97), (2, "bf16", "bf16", 196, 128, 64, 4, 49)])
 def test_append_launches_above_and_below_three_tiles_per_cu(oqm, bits, meta, dt, G, d, gs, H_k, frames):
-    """The head_dim-axis append has two forms of one kernel: 1024 threads per tile with four rows
-    per lane in flight for launches of at most 768 tiles, above that 256 threads, two rows per
-    trip and V tiles cut into chunks.  Most cases in this file are small launches; here one
+    """The head_dim-axis append has two forms: K and V tiles cut into chunks for launches of few tiles
+    (at most 384 at 16-bit input, 256 at float32), above that workgroups that walk a K tile each
+    beside chunks of V.  Most cases in this file are small launches; here one
     call stores more than 768 tiles, then the same stream goes in frame by frame, and both must
     match the oracle."""
     w = synth_kv.Workload("X", 2, H_k, 2 * H_k, d, G, frames, gs, 5, 6, dt, "cosine", 2100 + G + d + bits,
