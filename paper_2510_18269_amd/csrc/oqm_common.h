@@ -27,6 +27,19 @@ tom_status_t fail(tom_status_t st, const char* fmt, ...);
 
 constexpr int kBlock = 256;  // threads per workgroup of the streaming kernels (4 waves)
 
+// Launches a kernel.  The triple-chevron form takes its launch shape through a stack of the runtime, two more calls into it,
+// which cost the host 0.2 to 0.3 us of 3.9 (four calls on a store of 0.7 MB, bound by the host, 15.4 -> 14.7 us).  Errors are left
+// for hipGetLastError, as there.
+template <typename T>
+struct As {
+    typedef T type;
+};
+template <typename... P>
+inline void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t s, typename As<P>::type... args) {
+    void* list[] = {&args...};
+    (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, list, lds, s);
+}
+
 // ---- element offsets of the storage arrays -------------------------------
 struct Layout {
     int64_t tile_code_bytes;  // G * d * bits / 8

@@ -161,7 +161,7 @@ hipError_t prefix_copy(const DequantArgs& a, hipStream_t s) {
     if (prefix_bytes == 0 || a.n_layers == 0) return hipSuccess;
     const int64_t chunks = (prefix_bytes / 16 + kBlock - 1) / kBlock;
     if (chunks > 0x7fffffffLL || (int64_t)a.n_kv_heads * a.n_layers > 65535) return hipErrorInvalidValue;
-    prefix_copy_kernel<<<dim3((unsigned)chunks, a.n_kv_heads * a.n_layers, 2), dim3(kBlock), 0, s>>>(a, head_bytes,
+    launch(prefix_copy_kernel, dim3((unsigned)chunks, a.n_kv_heads * a.n_layers, 2), dim3(kBlock), 0, s, a, head_bytes,
                                                                                                      prefix_bytes);
     return hipGetLastError();
 }
@@ -216,11 +216,11 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
         constexpr int U = decltype(unroll)::value, B = decltype(bits)::value;
         constexpr bool K = decltype(tokens)::value, M = decltype(mb)::value;
         if constexpr (!K && B == 4 && eb == 2) {
-            if (!select && gather_past_caches(a)) return dequant_gather_kernel<OUT, N, U, K, B, M, kPastCaches><<<grid, block, 0, s>>>(a);
+            if (!select && gather_past_caches(a)) return launch(dequant_gather_kernel<OUT, N, U, K, B, M, kPastCaches>, grid, block, 0, s, a);
         }
-        if (!select) dequant_gather_kernel<OUT, N, U, K, B, M, 0><<<grid, block, 0, s>>>(a);
-        else if (select == 1) dequant_gather_kernel<OUT, N, U, K, B, M, 1><<<grid, block, 0, s>>>(a);
-        else dequant_gather_kernel<OUT, N, U, K, B, M, kBlock / 64><<<grid, block, 0, s>>>(a);
+        if (!select) launch(dequant_gather_kernel<OUT, N, U, K, B, M, 0>, grid, block, 0, s, a);
+        else if (select == 1) launch(dequant_gather_kernel<OUT, N, U, K, B, M, 1>, grid, block, 0, s, a);
+        else launch(dequant_gather_kernel<OUT, N, U, K, B, M, kBlock / 64>, grid, block, 0, s, a);
     };
     auto with_storage = [&](auto unroll, auto tokens) {
         if (a.bits == 2 && a.meta_bf16) go(unroll, tokens, std::integral_constant<int, 2>{}, std::true_type{});

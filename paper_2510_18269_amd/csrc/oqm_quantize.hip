@@ -276,13 +276,13 @@ hipError_t launch_b(const QuantArgs& q, hipStream_t s) {
     if (items * (a.chunks + 1) > kMostBlocks) return hipErrorInvalidConfiguration;
     a.items = (uint32_t)items;
     if (!cut_append(q, sizeof(Raw8<IN>) <= 16)) {
-        quantize_append_kernel<IN, LPG, BITS, MB><<<dim3((unsigned)(items * (a.chunks + 1))), dim3(kBlock), 0, s>>>(a);
+        launch(quantize_append_kernel<IN, LPG, BITS, MB>, dim3((unsigned)(items * (a.chunks + 1))), dim3(kBlock), 0, s, a);
         return hipGetLastError();
     }
     a.key_parts = (uint32_t)key_parts(q);
     a.inv_key_parts = reciprocal_u32(a.key_parts);
     return launch_blocks(a, items * (2 * a.chunks + (int)a.key_parts), kBlock, [&](dim3 grid, dim3 block) {  // at most three times those above
-        quantize_append_cut_kernel<IN, LPG, BITS, MB><<<grid, block, 0, s>>>(a);
+        launch(quantize_append_cut_kernel<IN, LPG, BITS, MB>, grid, block, 0, s, a);
     });
 }
 

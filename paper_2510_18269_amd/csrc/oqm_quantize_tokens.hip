@@ -374,7 +374,7 @@ hipError_t launch_rows_h(const QuantArgs& q, int waves, hipStream_t s) {
         constexpr int B = decltype(bits)::value;
         constexpr bool M = decltype(mb)::value, S = decltype(sep)::value;
         return launch_blocks(a, (S ? 3 : 2) * set_items(a, q), 64 * waves, [&](dim3 grid, dim3 block) {
-            quantize_append_rows_kernel<IN, LPR, HOLD, B, M, S><<<grid, block, lds, s>>>(a, waves);
+            launch(quantize_append_rows_kernel<IN, LPR, HOLD, B, M, S>, grid, block, lds, s, a, waves);
         });
     };
     return with_options(q, go);
@@ -400,7 +400,7 @@ hipError_t launch_h(const QuantArgs& q, hipStream_t s) {
         constexpr int B = decltype(bits)::value;
         constexpr bool M = decltype(mb)::value, S = decltype(sep)::value;
         return launch_blocks(a, (S ? 3 : 2) * set_items(a, q), kBlock, [&](dim3 grid, dim3 block) {
-            quantize_append_tokens_kernel<IN, S, HOLD, B, M><<<grid, block, lds, s>>>(a);
+            launch(quantize_append_tokens_kernel<IN, S, HOLD, B, M>, grid, block, lds, s, a);
         });
     };
     return with_options(q, go);

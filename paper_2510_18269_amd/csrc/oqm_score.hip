@@ -724,8 +724,8 @@ static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStr
     const dim3 grid(a.n_kv_heads * parts, a.n_layers), block(kFoldThreads);
     auto go = [&](auto qt) {
         typedef decltype(qt) QT;
-        if (want_tokens) query_fold_kernel<QT, true><<<grid, block, 0, s>>>(a, parts);
-        else query_fold_kernel<QT, false><<<grid, block, 0, s>>>(a, parts);
+        if (want_tokens) launch(query_fold_kernel<QT, true>, grid, block, 0, s, a, parts);
+        else launch(query_fold_kernel<QT, false>, grid, block, 0, s, a, parts);
         return hipGetLastError();
     };
     switch (a.q_dtype) {
@@ -780,9 +780,9 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
         return with_pieces<16>(HD, [&](auto ch, auto rest, size_t lds) {
             constexpr int CH = decltype(ch)::value;
             constexpr Rest REST = decltype(rest)::value;
-            if (a.q_dtype == TOM_F32) score_fold_query_kernel<In_f32, CH, REST><<<grid, block, lds, s>>>(a, f);
-            else if (a.q_dtype == TOM_BF16) score_fold_query_kernel<In_bf16, CH, REST><<<grid, block, lds, s>>>(a, f);
-            else score_fold_query_kernel<In_f16, CH, REST><<<grid, block, lds, s>>>(a, f);
+            if (a.q_dtype == TOM_F32) launch(score_fold_query_kernel<In_f32, CH, REST>, grid, block, lds, s, a, f);
+            else if (a.q_dtype == TOM_BF16) launch(score_fold_query_kernel<In_bf16, CH, REST>, grid, block, lds, s, a, f);
+            else launch(score_fold_query_kernel<In_f16, CH, REST>, grid, block, lds, s, a, f);
         });
     }
     if (hipError_t e = launch_query_fold(a, false, s)) return e;
@@ -792,8 +792,8 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
         return with_pieces<W>(HD, [&](auto ch, auto rest, size_t lds) {
             constexpr int CH = decltype(ch)::value;
             constexpr Rest REST = decltype(rest)::value;
-            if (keys_past_caches(a)) score_mean_query_kernel<W, CH, REST, true><<<grid, dim3(kBlock), lds, s>>>(a);
-            else score_mean_query_kernel<W, CH, REST, false><<<grid, dim3(kBlock), lds, s>>>(a);
+            if (keys_past_caches(a)) launch(score_mean_query_kernel<W, CH, REST, true>, grid, dim3(kBlock), lds, s, a);
+            else launch(score_mean_query_kernel<W, CH, REST, false>, grid, dim3(kBlock), lds, s, a);
         });
     };
     // long keys in one trip of 512-byte pieces: 28 x 1024 groups x 8 heads of 128 39.6 -> 35.9 us, 700 x 8 of 256 47.5 -> 45.1, but
@@ -816,14 +816,14 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     const dim3 grid(8u * (unsigned)a.gemm_units_per_xcd);
     switch (tiles) {
         case 0:
-            if (a.t_q <= 16) score_token_gemm_kernel<1><<<grid, dim3(kBlock), 0, s>>>(a);
-            else if (a.t_q <= 32) score_token_gemm_kernel<2><<<grid, dim3(kBlock), 0, s>>>(a);
-            else score_token_gemm_kernel<4><<<grid, dim3(kBlock), 0, s>>>(a);
+            if (a.t_q <= 16) launch(score_token_gemm_kernel<1>, grid, dim3(kBlock), 0, s, a);
+            else if (a.t_q <= 32) launch(score_token_gemm_kernel<2>, grid, dim3(kBlock), 0, s, a);
+            else launch(score_token_gemm_kernel<4>, grid, dim3(kBlock), 0, s, a);
             break;
-        case 1: score_token_split_kernel<1><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
-        case 2: score_token_split_kernel<2><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
-        case 3: score_token_split_kernel<3><<<grid, dim3(kSplitThreads), 0, s>>>(a); break;
-        default: score_token_split_kernel<4><<<grid, dim3(kSplitThreads), 0, s>>>(a);
+        case 1: launch(score_token_split_kernel<1>, grid, dim3(kSplitThreads), 0, s, a); break;
+        case 2: launch(score_token_split_kernel<2>, grid, dim3(kSplitThreads), 0, s, a); break;
+        case 3: launch(score_token_split_kernel<3>, grid, dim3(kSplitThreads), 0, s, a); break;
+        default: launch(score_token_split_kernel<4>, grid, dim3(kSplitThreads), 0, s, a);
     }
     return hipGetLastError();
 }

@@ -202,7 +202,7 @@ hipError_t launch_topk(const float* scores, int64_t stride, int n_rows, int n_gr
     if (order == TOM_ORDER_INDEX_ASC && n_groups <= kTopkMaxInRegisters) {
         auto go = [&](auto waves, auto keys) {
             constexpr int W = decltype(waves)::value, C = decltype(keys)::value;
-            topk_ascending_kernel<W, C><<<dim3(n_rows), dim3(64 * W), 0, s>>>(scores, stride, n_groups, k, k_eff, idx);
+            launch(topk_ascending_kernel<W, C>, dim3(n_rows), dim3(64 * W), 0, s, scores, stride, n_groups, k, k_eff, idx);
         };
         using std::integral_constant;
         if (n_groups <= 256) go(integral_constant<int, 1>{}, integral_constant<int, 4>{});
@@ -211,7 +211,7 @@ hipError_t launch_topk(const float* scores, int64_t stride, int n_rows, int n_gr
         else go(integral_constant<int, 8>{}, integral_constant<int, 8>{});
         return hipGetLastError();
     }
-    topk_kernel<<<dim3(n_rows), dim3(kTopkThreads), 0, s>>>(scores, stride, n_groups, k, k_eff,
+    launch(topk_kernel, dim3(n_rows), dim3(kTopkThreads), 0, s, scores, stride, n_groups, k, k_eff,
                                                             order, idx);
     return hipGetLastError();
 }
