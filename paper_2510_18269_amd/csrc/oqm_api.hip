@@ -208,8 +208,8 @@ tom_status_t tom_oqm_quantize_append(tom_oqm_t* h, int32_t layer0, int32_t n_lay
         return fail(TOM_ERR_INVALID_ARG, "k, v and k_for_summary must be 16-byte aligned");
     if (n_frames > 65535 || 2 * n_layers > 65535)
         return fail(TOM_ERR_UNSUPPORTED, "at most 65535 frames and 32767 layers per call");
-    // the head_dim-axis kernel takes up to G + 1 workgroups per (frame, layer, head) in a 1-D grid
-    // (n_frames <= 65535 and n_layers * n_kv_heads < 2^25, so the first product fits 64 bits)
+    // the store kernels number their workgroups in 32 bits: up to G + 2 per (frame, layer, head) on the head_dim axis, three on
+    // the other (n_frames <= 65535 and n_layers * n_kv_heads < 2^25, so the first product fits 64 bits)
     if ((int64_t)n_frames * n_layers * c.n_kv_heads > 0x7fffffffLL / ((int64_t)c.group_tokens + 1))
         return fail(TOM_ERR_UNSUPPORTED, "n_frames * n_layers * n_kv_heads * (group_tokens + 1) exceeds 2^31 - 1: "
                                          "append fewer frames per call");

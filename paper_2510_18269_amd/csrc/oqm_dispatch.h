@@ -77,8 +77,6 @@ inline int split_tiles(const ScoreArgs& a) {
 }
 
 // ---- head_dim-axis store: who makes the summary keys ----------------------------------------
-constexpr int64_t kMostBlocks = (1LL << 32) / kBlock - 1;  // of a 1-D grid, which stays below 2^32 threads
-
 // Whether K tiles are cut into chunks like V and the keys come from workgroups of their own (quantize_append_cut_kernel)
 // instead of the workgroups that walk the K tiles.  Always where the keys are averaged over another tensor.
 // Otherwise that reads K twice, which pays while the launch is bound by the longest chain of one workgroup: not where a walk is
