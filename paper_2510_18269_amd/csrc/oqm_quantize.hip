@@ -56,7 +56,7 @@ namespace {
 constexpr int kChunkRows = 2;  // rows per lane of a chunk
 constexpr int kWalkRows = 4;   // rows per lane and trip of a walk
 constexpr int kKeyRows = 4;     // rows per lane in flight where columns are summed (seven: 2 to 4 % slower above 400 tiles, 4 % faster at 224)
-constexpr uint32_t kTail = 6272;  // chunks behind the workgroups that walk a tile: three rounds of the chip
+constexpr int kTail = 6272;    // chunks behind the workgroups that walk a tile: three rounds of the chip
 
 // Where a lane's rows lie within a tile whose rows go `rpp` to a pass of the workgroup.  32-bit byte offsets
 // (checked on the host) keep the address arithmetic per row to one add.
@@ -180,17 +180,16 @@ template <typename IN, int LPG, int BITS, bool MB>
 __global__ void __launch_bounds__(kBlock) quantize_append_kernel(const AppendArgs a) {
     __shared__ double shared[kBlock * 8];  // key reduction
     request(a);
-    const uint32_t chunks = a.items * (uint32_t)a.chunks, first_walk = chunks - min(chunks, kTail);
+    const int chunks = a.items * a.chunks, first_walk = max(0, chunks - kTail);
     // One address computation for both roles: a short launch waits for every line of code it has not run before.
-    uint32_t id = blockIdx.x + a.first_block;
-    int row_begin = 0, row_end = a.tokens;
-    const bool walk = id >= first_walk && id < first_walk + a.items;
+    int id = blockIdx.x, row_begin = 0, row_end = a.tokens;
+    const bool walk = id >= first_walk && id < first_walk + (int)a.items;
     if (walk) {
         id -= first_walk;
     } else {
         if (id >= first_walk) id -= a.items;
-        const uint32_t item = div_by(id, a.chunks, a.inv_chunks);
-        row_begin = (int)(id - item * a.chunks) * a.chunk_rows;
+        const int item = div_by(id, a.chunks, a.inv_chunks);
+        row_begin = (id - item * a.chunks) * a.chunk_rows;
         row_end = min(row_end, row_begin + a.chunk_rows);
         id = item;
     }
@@ -221,15 +220,15 @@ template <typename IN, int LPG, int BITS, bool MB>
 __global__ void __launch_bounds__(kBlock) quantize_append_cut_kernel(const AppendArgs a) {
     __shared__ double shared[kBlock * 8];  // key reduction
     request(a);
-    const uint32_t chunks = 2u * a.items * (uint32_t)a.chunks, key_blocks = a.items * a.key_parts, first_key = chunks - min(chunks, kTail);
-    uint32_t id = blockIdx.x + a.first_block;
+    const uint32_t key_blocks = a.items * a.key_parts, first_key = (uint32_t)max(0, (int)(2u * a.items * (uint32_t)a.chunks) - kTail);
+    int id = (int)(blockIdx.x + a.first_block);  // compared as unsigned, but a signed quotient stays in the scalar unit
     Lane<IN, LPG, BITS> n(a, threadIdx.x);
-    if (id < first_key || id >= first_key + key_blocks) {
-        if (id >= first_key) id -= key_blocks;
+    if ((uint32_t)id < first_key || (uint32_t)id >= first_key + key_blocks) {
+        if ((uint32_t)id >= first_key) id -= (int)key_blocks;
         const uint32_t tile = div_by(id, a.chunks, a.inv_chunks), kv = tile < a.items ? 0u : 1u;
         const Item t(a, tile - kv * a.items);
         const Stored<MB> to(a, t, kv);
-        const int row_begin = (int)(id - tile * a.chunks) * a.chunk_rows, row_end = min(a.tokens, row_begin + a.chunk_rows);
+        const int row_begin = (id - (int)tile * a.chunks) * a.chunk_rows, row_end = min(a.tokens, row_begin + a.chunk_rows);
         Raw8<IN> buf[kChunkRows];
         double unused[8];
         fetch_rows((kv ? a.v : a.k) + t.input(a), n, row_begin, row_end, buf);
@@ -275,12 +274,14 @@ hipError_t launch_b(const QuantArgs& q, hipStream_t s) {
     a.chunk_rows = (a.tokens + a.chunks - 1) / a.chunks;  // equal chunks
     a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
     a.items = (uint32_t)items;
-    // A chunk has two rows at least and the API layer keeps items * (tokens + 1) below 2^31: the ids of both forms fit 32 bits.
-    if (!cut_append(q, sizeof(Raw8<IN>) <= 16)) {
-        return launch_blocks(a, items * (a.chunks + 1), kBlock, [&](dim3 grid, dim3 block) {
-            launch(quantize_append_kernel<IN, LPG, BITS, MB>, grid, block, 0, s, a);
-        });
+    // One grid.  (The place of this launch within a split one would cost the small launches 1 to 2 %: another argument in front of all
+    // addresses.  More workgroups than a grid takes are cut instead.)
+    if (!cut_append(q, sizeof(Raw8<IN>) <= 16) && items * (a.chunks + 1) < (1LL << 32) / kBlock) {
+        launch(quantize_append_kernel<IN, LPG, BITS, MB>, dim3((unsigned)(items * (a.chunks + 1))), dim3(kBlock), 0, s, a);
+        return hipGetLastError();
     }
+    // A chunk has two rows at least and the API layer keeps items * (tokens + 1) below 2^31: 2 * items * chunks fits a signed integer,
+    // the ids an unsigned one.
     a.key_parts = (uint32_t)key_parts(q);
     a.inv_key_parts = reciprocal_u32(a.key_parts);
     return launch_blocks(a, items * (2 * a.chunks + (int)a.key_parts), kBlock, [&](dim3 grid, dim3 block) {
