@@ -77,23 +77,45 @@ inline int split_tiles(const ScoreArgs& a) {
 }
 
 // ---- head_dim-axis store: who makes the summary keys ----------------------------------------
-// Whether K tiles are cut into chunks like V and the keys come from workgroups of their own (quantize_append_cut_kernel)
-// instead of the workgroups that walk the K tiles.  Always where the keys are averaged over another tensor.
-// Otherwise that reads K twice, which pays while the launch is bound by the longest chain of one workgroup: not where a walk is
-// one trip of four rows per lane, and up to 384 tiles, 256 with float32 input.  us per call, cut / walk, at 4 heads and 196 tokens:
-// d = 128 bf16 224 tiles 5.0 / 6.9, 320 6.2 / 7.2, 384 7.0 / 7.5, 448 7.7 / 7.7; float32 224 6.9 / 7.9, 320 9.2 / 8.9; d = 64
-// 320 4.6 / 4.7, 384 4.9 / 4.9, 448 5.3 / 5.2; d = 256 320 10.2 / 11.3; d = 80 224 4.5 / 5.5, 320 5.2 / 6.0; 50 tokens (one trip) x 8 frames 8.4 / 7.4.
-inline bool cut_append(const QuantArgs& a, bool is_16_bit) {
-    if (a.ksum != a.k) return true;
-    const int64_t tiles = 2LL * a.n_kv_heads * a.n_layers * a.n_frames;
-    return a.group_tokens > 4 * (kBlock / (a.head_dim / 8)) && tiles <= (is_16_bit ? 384 : 256);
-}
+constexpr int kTallBlock = 1024;  // threads of a workgroup that walks a tall tile
+constexpr int64_t kLowTile = 64 << 10, kTallTile = 128 << 10, kTallTile16Bit = 96 << 10;  // bytes of the input
 
-// Workgroups per key there: one per 64 channels while each has a compute unit of its own, which halves the trips at d = 128
+inline int64_t append_items(const QuantArgs& a) { return (int64_t)a.n_kv_heads * a.n_layers * a.n_frames; }  // K tiles
+inline int64_t tile_bytes(const QuantArgs& a, bool is_16_bit) { return (int64_t)a.group_tokens * a.head_dim * (is_16_bit ? 2 : 4); }
+
+// Workgroups per key of the cut form: one per 64 channels while each has a compute unit of its own, which halves the trips at d = 128
 // (one bf16 frame of 28 x 4 heads 5.0 against 5.4 us; two frames 8.2 against 7.8), otherwise one.
 inline int key_parts(const QuantArgs& a) {
     const int64_t parts = a.head_dim / 64;
-    return a.head_dim % 64 == 0 && parts * a.n_kv_heads * a.n_layers * a.n_frames <= 256 ? (int)parts : 1;
+    return a.head_dim % 64 == 0 && parts * append_items(a) <= 256 ? (int)parts : 1;
+}
+
+// Whether K tiles are cut into chunks like V and the keys come from workgroups of their own (quantize_append_cut_kernel)
+// instead of the workgroups that walk the K tiles.  Always where the keys are averaged over another tensor.
+// Otherwise that reads K twice, which pays while the launch is bound by the longest chain of one workgroup: not where a walk is
+// one trip of four rows per lane, and up to 384 tiles, 256 with float32 input.  us per call in a graph, cut / walk, at 4 heads:
+// 196 x 128 bf16 224 tiles 4.5 / 6.0, 336 5.7 / 6.4, 448 6.9 / 6.9; 256 x 64 float32 224 4.1 / 4.8, 336 5.8 / 5.5; 50 tokens (one trip) x 8 frames 8.4 / 7.4.
+// Of tiles above 64 KB as far as reading K again costs less than the shorter chains gain.  With keys in parts that is by the trips of a walk:
+// cut / 1024 threads at 500 x 128 bf16 10 MB of K 6.2 / 8.2, 14 8.8 / 8.5, 21 12.7 / 11.4; 1000 x 128 20 MB 12.5 / 13.9, 29 16.4 / 15.3; 2000 x 128 29 MB 19.0 /
+// 22.9, 41 25.0 / 24.1; float32 196 x 128 11.2 MB 5.1 / 5.2, 12.8 6.5 / 5.4; 500 x 128 14 MB 7.8 / 8.4, 20 11.0 / 10.0.  A key in one part walks its tile too:
+// 196 x 256 bf16 8.0 MB 6.6 / 6.9, 11.2 7.5 / 7.3; 1000 x 64 10 MB 8.1 / 8.1; 400 x 96 9.8 MB 6.8 / 7.1; float32 400 x 64 6.6 MB 4.7 / 4.9, 9.8 5.5 / 5.2.
+inline bool cut_append(const QuantArgs& a, bool is_16_bit) {
+    if (a.ksum != a.k) return true;
+    const int64_t items = append_items(a), tile = tile_bytes(a, is_16_bit);
+    if (a.group_tokens <= 4 * (kBlock / (a.head_dim / 8)) || 2 * items > (is_16_bit ? 384 : 256)) return false;
+    if (tile <= kLowTile) return true;
+    const int64_t trips = (int64_t)a.group_tokens * a.head_dim / (4 * 8 * kBlock);
+    return items * tile <= (key_parts(a) > 1 ? 9000000 + 800000 * trips : (int64_t)(is_16_bit ? 10 : 8) << 20);
+}
+
+// Threads of the workgroups that walk K tiles otherwise.  With 1024 the chain of a tall tile is a quarter as long, but the last of a few
+// trips is often nearly empty.  Above 128 KB of input, 96 KB at 16 bits, and above 64 KB up to 384 tiles.  us per call in a graph, 1024 / 256 threads: 500 x 128 bf16
+// (125 KB) 224 tiles 8.5 / 12.7, 448 14.2 / 15.8, 1344 34.7 / 39.4, 7168 223 / 232; 196 x 256 bf16 (98 KB) 448 12.1 / 13.1, 672 16.3 / 17.2, 896 20.1 / 19.7, 7168 177 / 181;
+// 330 x 128 bf16 (82 KB) 384 9.3 / 10.2, 512 12.4 / 12.3; 196 x 128 bf16 (49 KB) 448 7.2 / 7.0, 896 12.4 / 11.2.  float32 196 x 128 (98 KB) 384 8.6 / 9.2, 512
+// 11.6 / 11.2, 896 18.2 / 16.8; 256 x 128 (128 KB) 336 9.3 / 9.3, 1792 43.3 / 40.1; 500 x 128 448 20.6 / 21.6, 3584 203 / 212.
+inline int walk_threads(const QuantArgs& a, bool is_16_bit) {
+    const int64_t tile = tile_bytes(a, is_16_bit);
+    return tile > (is_16_bit ? kTallTile16Bit : kTallTile) || (tile > kLowTile && 2 * append_items(a) <= 384) ? kTallBlock : kBlock;
 }
 
 // ---- token-axis store: tiles whose rows the waves hold -------------------------------------

@@ -23,6 +23,8 @@
 //                               1-D grid holds V chunks, then all K tiles, then the last kTail V chunks: a
 //                               walk is long (4 trips at 196 x 128), so without chunks behind them the last
 //                               walks leave the chip half empty.  Medium launches thus start with the K tiles.
+//                               Tall tiles take workgroups of 1024 threads, which walk four times the rows a trip
+//                               (walk_threads in oqm_dispatch.h).
 //   quantize_append_cut_kernel  K in chunks as well, and the keys by workgroups of their own that read the
 //                               tensor to average.  For keys taken from another tensor (that one is read once
 //                               either way), and for launches so small that they are bound by the longest chain of
@@ -36,7 +38,9 @@
 // 90.6 / 89.6 / 89.5 / 89.8 / 90.0.  At 32 frames 512 threads x 4 rows 91.6, 256 x 7 rows 94, a whole tile in
 // flight in 512 or 1024 threads 102 / 111; the sums themselves cost nothing; loads without a branch (rows past the end
 // read the last one again) 91.6 and 10.7 instead of 9.7 at 3 frames.  Keys from another tensor, one workgroup per K tile
-// before / cut: 1 frame 12.8 / 5.2, 8 39 / 34, 32 129.9 / 124 us.
+// before / cut: 1 frame 12.8 / 5.2, 8 39 / 34, 32 129.9 / 124 us.  Tall tiles, 28 layers x 4 heads, in a graph, 1024 threads / 256 / cut: 2000 x 128,
+// 2 frames 47.4 / 88.3 / 68.7, 6 174 / 225 / 249; 500 x 128, 3 frames 19.6 / 20.7 / 24.3, 32 223 / 232 / 313; 196 x 256 float32, 1 frame
+// 9.5 / 12.7 / 12.6.  Chunks of four rows a lane instead of two: 0 to 6 % slower.
 //
 // The kernel moves 2.64 B per element (bf16 in, gs 64).  At HBM speed that leaves
 // room for only about a dozen instructions per element on the plain fp32 vector
@@ -140,7 +144,7 @@ __device__ __forceinline__ void quantize_rows(const Stored<MB>& to, const Raw8<I
 
 // Summary key from the column sums of the lanes: over the rows of a wave by lane swaps (64 / LPR rows of
 // LPR lanes each), over the waves in LDS.  One wave's rows hold `8 * LPR` channels, slot * 8 onwards in lane `slot`.
-template <int LPR>
+template <int NT, int LPR>
 __device__ __forceinline__ void write_key_by_waves(double (&acc)[8], int slot, double* shared, float* key, int G) {
     constexpr int CH = LPR / 8, D = 8 * LPR;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -151,17 +155,17 @@ __device__ __forceinline__ void write_key_by_waves(double (&acc)[8], int slot, d
     if (threadIdx.x < D) {
         double sum = 0.0;
 #pragma unroll
-        for (int w = 0; w < kBlock / 64; ++w) sum += shared[w * D + threadIdx.x];
+        for (int w = 0; w < NT / 64; ++w) sum += shared[w * D + threadIdx.x];
         key[threadIdx.x] = (float)(sum / (double)G);
     }
 }
 
-template <typename LANE>
+template <int NT, typename LANE>
 __device__ __forceinline__ void write_key(const AppendArgs& a, const LANE& n, double (&acc)[8], double* shared, float* key) {
     const int lpr = a.lanes_per_row, d = lpr * 8, G = a.tokens;
-    if (lpr == 16) return write_key_by_waves<16>(acc, n.slot, shared, key, G);  // uniform, like the next two
-    if (lpr == 8) return write_key_by_waves<8>(acc, n.slot, shared, key, G);
-    if (lpr == 32) return write_key_by_waves<32>(acc, n.slot, shared, key, G);
+    if (lpr == 16) return write_key_by_waves<NT, 16>(acc, n.slot, shared, key, G);  // uniform, like the next two
+    if (lpr == 8) return write_key_by_waves<NT, 8>(acc, n.slot, shared, key, G);
+    if (lpr == 32) return write_key_by_waves<NT, 32>(acc, n.slot, shared, key, G);
     if (n.active) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) shared[n.row0 * d + i * lpr + n.slot] = acc[i];
@@ -169,16 +173,16 @@ __device__ __forceinline__ void write_key(const AppendArgs& a, const LANE& n, do
     __syncthreads();
     // position q = i * lpr + slot holds channel slot * 8 + i: the lanes of a wave write
     // consecutive doubles (channel order would put them 64 bytes apart: 16-way bank conflicts)
-    for (int q = threadIdx.x; q < d; q += kBlock) {
+    for (int q = threadIdx.x; q < d; q += NT) {
         double sum = 0.0;
         for (int r = 0; r < n.rpp; ++r) sum += shared[r * d + q];
         key[(q % lpr) * 8 + q / lpr] = (float)(sum / (double)G);
     }
 }
 
-template <typename IN, int LPG, int BITS, bool MB>
-__global__ void __launch_bounds__(kBlock) quantize_append_kernel(const AppendArgs a) {
-    __shared__ double shared[kBlock * 8];  // key reduction
+template <typename IN, int LPG, int BITS, bool MB, int NT>
+__global__ void __launch_bounds__(NT) quantize_append_kernel(const AppendArgs a) {
+    __shared__ double shared[NT * 8];  // key reduction
     request(a);
     const int chunks = a.items * a.chunks, first_walk = max(0, chunks - kTail);
     // One address computation for both roles: a short launch waits for every line of code it has not run before.
@@ -211,7 +215,7 @@ __global__ void __launch_bounds__(kBlock) quantize_append_kernel(const AppendArg
         fetch_rows(src, n, r0, a.tokens, buf);
         quantize_rows<true>(to, buf, n, r0, a.tokens, acc);
     }
-    write_key(a, n, acc, shared, t.key(a));
+    write_key<NT>(a, n, acc, shared, t.key(a));
 }
 
 // Grid: chunks of all K tiles, then of all V tiles, and in front of the last kTail of them the workgroups that
@@ -261,25 +265,35 @@ __global__ void __launch_bounds__(kBlock) quantize_append_cut_kernel(const Appen
             for (int i = 0; i < 8; ++i) acc[i] += (double)x[i];
         }
     }
-    if (a.key_parts > 1) write_key_by_waves<8>(acc, n.slot, shared, t.key(a) + part * 64, a.tokens);
-    else write_key(a, n, acc, shared, t.key(a));
+    if (a.key_parts > 1) write_key_by_waves<kBlock, 8>(acc, n.slot, shared, t.key(a) + part * 64, a.tokens);
+    else write_key<kBlock>(a, n, acc, shared, t.key(a));
 }
 
 template <typename IN, int LPG, int BITS, bool MB>
 hipError_t launch_b(const QuantArgs& q, hipStream_t s) {
     const int64_t items = (int64_t)q.n_kv_heads * q.n_layers * q.n_frames;
     AppendArgs a = append_args(q, elem_bytes<IN>::value, (uint32_t)q.group_tokens * (uint32_t)(q.head_dim / q.qgroup));
-    a.rows_per_pass = (int32_t)(kBlock / a.lanes_per_row);
-    a.chunks = (a.tokens + kChunkRows * a.rows_per_pass - 1) / (kChunkRows * a.rows_per_pass);
-    a.chunk_rows = (a.tokens + a.chunks - 1) / a.chunks;  // equal chunks
-    a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
+    constexpr bool is_16_bit = sizeof(Raw8<IN>) <= 16;
+    auto set_chunks = [&](int threads) {
+        a.rows_per_pass = (int32_t)((uint32_t)threads / a.lanes_per_row);
+        a.chunks = (a.tokens + kChunkRows * a.rows_per_pass - 1) / (kChunkRows * a.rows_per_pass);
+        a.chunk_rows = (a.tokens + a.chunks - 1) / a.chunks;  // equal chunks
+        a.inv_chunks = reciprocal_u32((uint32_t)a.chunks);
+    };
     a.items = (uint32_t)items;
-    // One grid.  (The place of this launch within a split one would cost the small launches 1 to 2 %: another argument in front of all
-    // addresses.  More workgroups than a grid takes are cut instead.)
-    if (!cut_append(q, sizeof(Raw8<IN>) <= 16) && items * (a.chunks + 1) < (1LL << 32) / kBlock) {
-        launch(quantize_append_kernel<IN, LPG, BITS, MB>, dim3((unsigned)(items * (a.chunks + 1))), dim3(kBlock), 0, s, a);
-        return hipGetLastError();
+    if (!cut_append(q, is_16_bit)) {
+        const int threads = walk_threads(q, is_16_bit);
+        set_chunks(threads);
+        // One grid.  (The place of this launch within a split one would cost the small launches 1 to 2 %: another argument in front of all
+        // addresses.  More workgroups than a grid takes are cut instead.)
+        if (items * (a.chunks + 1) < (1LL << 32) / threads) {
+            const dim3 grid((unsigned)(items * (a.chunks + 1))), block(threads);
+            if (threads == kBlock) launch(quantize_append_kernel<IN, LPG, BITS, MB, kBlock>, grid, block, 0, s, a);
+            else launch(quantize_append_kernel<IN, LPG, BITS, MB, kTallBlock>, grid, block, 0, s, a);
+            return hipGetLastError();
+        }
     }
+    set_chunks(kBlock);
     // A chunk has two rows at least and the API layer keeps items * (tokens + 1) below 2^31: 2 * items * chunks fits a signed integer,
     // the ids an unsigned one.
     a.key_parts = (uint32_t)key_parts(q);

@@ -76,7 +76,8 @@ static void append() {
     char k = 0, other = 0;
     a.k = a.ksum = &k, a.n_kv_heads = 4, a.n_layers = 2, a.head_dim = 128, a.group_tokens = 196;
     for (bool is_16_bit : {false, true}) {
-        a.n_frames = is_16_bit ? 24 : 16;             // 384 or 256 tiles of K and V
+        a.n_frames = is_16_bit ? 24 : 16;             // 384 or 256 tiles of K and V, of at most 64 KB
+        a.group_tokens = is_16_bit ? 196 : 128;
         CHECK(cut_append(a, is_16_bit));
         ++a.n_frames;
         CHECK(!cut_append(a, is_16_bit));
@@ -107,6 +108,20 @@ static void append() {
     CHECK(key_parts(a) == 32);
     a.n_layers = 32767, a.n_kv_heads = 1023, a.n_frames = 65535;
     CHECK(key_parts(a) == 1 && !cut_append(a, true));
+    // taller tiles: cut by the bytes of K, walked by 1024 threads above 64 KB or 128 KB
+    auto form = [&](int d, int G, int items, bool is_16_bit) {
+        a.head_dim = d, a.group_tokens = G, a.n_kv_heads = 1, a.n_layers = items, a.n_frames = 1;
+        return cut_append(a, is_16_bit) ? 0 : walk_threads(a, is_16_bit);
+    };
+    CHECK(form(128, 256, 192, true) == 0 && form(128, 256, 193, true) == 256);           // 64 KB
+    CHECK(form(128, 257, 128, true) == 0 && form(128, 257, 192, true) == 1024 && form(128, 257, 193, true) == 256);
+    CHECK(form(128, 384, 193, true) == 256 && form(128, 385, 193, true) == 1024);        // 96 KB, above 384 tiles
+    CHECK(form(128, 385, 1 << 20, true) == 1024 && form(128, 256, 1 << 20, false) == 256 && form(128, 257, 1 << 20, false) == 1024);
+    CHECK(form(128, 500, 111, true) == 0 && form(128, 500, 115, true) == 1024);          // two parts a key: 14.6 MB at 7 trips
+    CHECK(form(128, 2000, 66, true) == 0 && form(128, 2000, 68, true) == 1024);          // 33.8 MB at 31
+    CHECK(form(64, 1000, 81, true) == 0 && form(64, 1000, 82, true) == 1024);            // one part: 10 MiB
+    CHECK(form(64, 400, 81, false) == 0 && form(64, 400, 82, false) == 1024);            // 8 MiB with float32 input
+    CHECK(form(512, 196, 32, true) == 0 && form(512, 196, 33, true) == 0 && form(512, 196, 53, true) == 1024);
 }
 
 static void split() {

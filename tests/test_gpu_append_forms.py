@@ -3,7 +3,7 @@
 A K tile is walked by one workgroup in trips of four rows per lane, or it is cut into chunks of two
 rows per lane and its key made by workgroups of their own: for keys taken from another tensor, and
 for small launches of tiles taller than one trip.  The keys' column sums are joined by lane swaps at 8, 16 and 32 lanes per row
-and through LDS otherwise, in one part per 64 channels while the launch is small.  The workgroups that walk or
+and through LDS otherwise, in one part per 64 channels while the launch is small.  Tall tiles are walked by 1024 threads.  The workgroups that walk or
 make keys stand in front of the last 6272 chunks, so larger launches have chunks on both sides.  Codes, scale / zero and dequantized
 values are bit-exact against the oracle, summary keys within one float32 ulp."""
 import pytest
@@ -66,3 +66,20 @@ def test_both_sides_of_the_rule(oqm, dt, frames):
 def test_chunks_on_both_sides_of_the_long_workgroups(oqm, frames, heads, G):
     for sep in (False, True):
         _run(oqm, d=128, G=G, frames=frames, heads=heads, sep=sep, gs=32, seed=frames + G)
+
+
+# tiles just above 64 KB, 162 of K: walked by 1024 threads, two passes a chunk and four a trip.  G around both, with a rest that leaves waves idle
+@pytest.mark.parametrize("dt", ("bf16", "f32"))
+@pytest.mark.parametrize("d", (8, 24, 64, 96, 128, 192, 256, 512, 2048))
+def test_tall_tiles(oqm, d, dt):
+    rpp = 1024 // (d // 8)
+    low = 65536 // (d * (2 if dt == "bf16" else 4))
+    base = (low // (4 * rpp) + 1) * 4 * rpp
+    for i, G in enumerate((base, base + 1) if dt == "bf16" else (base - 1 if base - 1 > low else base + 2 * rpp, base + 2 * rpp + 1)):
+        _run(oqm, d=d, G=G, frames=81, heads=2, dt=dt, bits=(4, 2)[i], meta=("f32", "bf16")[i], token_major=i == 1, seed=d + i)
+
+
+# above 96 KB at any number of tiles; fewer of them are cut
+@pytest.mark.parametrize("frames,G", [(20, 390), (100, 390), (400, 520)])
+def test_tiles_above_96_kb(oqm, frames, G):
+    _run(oqm, d=128, G=G, frames=frames, heads=2, gs=64, seed=frames)
