@@ -21,8 +21,9 @@ inline uint64_t score_span(int64_t stride, int n_layers, int n_groups) {
 // Where the keys of a call are a good part of the last-level cache (256 MB) they only push out what else is there.  Whole question at one selected
 // group, three stores in turn, through / past the caches: 28 layers x 1500 groups x 512 channels (86 MB) 26.2 / 26.4 us, 2200 (126 MB) 35.3 / 33.3, 3000 (172 MB)
 // 42.8 / 39.7; 1000 (57 MB) 19.2 / 20.5, 200 12.8 / 13.3.
+constexpr int64_t kKeysPastCaches = 100000000;
 inline bool keys_past_caches(const ScoreArgs& a) {
-    return (int64_t)a.n_layers * a.n_groups * a.n_kv_heads * a.head_dim * (int64_t)sizeof(float) >= 100000000;
+    return (int64_t)a.n_layers * a.n_groups * a.n_kv_heads * a.head_dim * (int64_t)sizeof(float) >= kKeysPastCaches;
 }
 
 // ---- mean-query score: the query is folded inside the score kernel -----------------------
@@ -160,12 +161,17 @@ inline bool prefix_joins_gather(const DequantArgs& a) {
     return true;
 }
 
-// Whether the codes are read past the caches: where a call reads and writes more than the last-level cache (256 MB) keeps, whatever it
-// leaves there is gone before the next question.  Asked for 4-bit codes on the head_dim axis with 16-bit output alone: the narrower loads of float32
-// output were 7 % slower past the caches, the token axis 2 %.  Question of the benchmark's streams, through / past: 64 groups of 1024 (944 MB) 184 / 181 us, 64 of 3600
-// 211 / 205; 28 layers x 32 of 600 groups (472 MB) 98 / 94; but 16 (236 MB) that the question before read too 51 / 58, 24 (354 MB) 76 / 76.5.
+// Whether the codes are read past the caches: where what a question reads, its codes, pairs and keys, is more than the last-level cache (256 MB) keeps
+// for the next one.  (The output is written past the caches anyway, keys of kKeysPastCaches and more are read past them.)  Asked for 4-bit codes on the
+// head_dim axis with 16-bit output alone: the narrower loads of float32 output were 7 % slower past the caches, the token axis 2 %.
+// Below the line a repeated question loses its hits, above it the lines that are brought in only evict each other.  28 layers x 4 heads x 196 x 128, us per question,
+// through / past, the same question again: 40 of 200 groups (140 MB and 11 MB of keys) 94 / 106, 56 (197) 133 / 144, 58 (204) 152 / 147, 64 (225) 183 / 162; 40 of
+// 1024 (59 MB of keys) 102 / 119, 48 (169) 151 / 138; 56 of 3593 (keys past the caches) 170 / 181, 60 (211) 199 / 191.  Three stores in turn: 40 of 200 109 / 106, 56 147 / 143,
+// 64 165 / 161.  All groups of a store are one range without holes, which the cache keeps further: 72 of 72 (253) 148 / 172, 80 of 80 (281) 197 / 190.
 inline bool gather_past_caches(const DequantArgs& a) {
-    return (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff * a.tile_items * 20 >= 360000000;  // 4 bytes of codes become 16
+    const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
+    const int64_t read = heads * 2 * a.k_eff * ((int64_t)a.tile_items * 4 + a.tile_meta_bytes), keys = heads * a.n_groups * a.head_dim * (int64_t)sizeof(float);
+    return read + (keys < kKeysPastCaches ? keys : 0) > (a.k_eff == a.n_groups ? 265000000 : 210000000);
 }
 
 constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups

@@ -201,6 +201,16 @@ static void gather() {
     CHECK(waves(257, 128, 8) == 4 && waves(257, 129, 8) == 0 && waves(1024, 512, 2) == 4 && waves(1024, 513, 2) == 0);
     CHECK(waves(1025, 1, 1) == 0 && waves(1 << 30, 1, 1) == 0);
 
+    // codes, pairs and keys of the question against what the last-level cache keeps; keys of 100 MB and more are not kept
+    auto past = [&](int k_eff, int n_groups, int n_layers = 28) {
+        DequantArgs q{};
+        q.n_layers = n_layers, q.n_kv_heads = 4, q.head_dim = 128, q.k = q.k_eff = k_eff, q.n_groups = n_groups;
+        q.tile_items = 196 * 16, q.tile_meta_bytes = 196 * 2 * 8;
+        return gather_past_caches(q);
+    };
+    CHECK(!past(56, 200) && past(58, 200) && !past(40, 1024) && past(48, 1024) && !past(59, 3600) && past(60, 3600));
+    CHECK(!past(64, 64) && past(64, 65 + 135) && !past(72, 72) && past(80, 80) && !past(64, 1024, 7) && past(256, 1024, 7));
+
     auto joins = [&](uint64_t sys_k, uint64_t sys_v) {
         a.n_layers = 2, a.n_kv_heads = 4;
         a.sys_k = at(sys_k), a.sys_v = at(sys_v);

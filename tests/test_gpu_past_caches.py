@@ -1,4 +1,4 @@
-"""GPU: calls that read past the caches (gathers of 360 MB and more, keys of 100 MB and more) against the same work in
+"""GPU: calls that read past the caches (gathers that read more than 210 MB, keys of 100 MB and more) against the same work in
 calls below those sizes: every bit equal."""
 import pytest
 import torch
@@ -20,7 +20,7 @@ def oqm():
 def test_large_gather(oqm, dt, meta, G):
     L, H, d, T = 8, 4, 128, 64
     code, tdt = {"bf16": (oqm.TOM_BF16, torch.bfloat16), "f16": (oqm.TOM_F16, torch.float16)}[dt]
-    k = 360_000_000 // (2 * L * H * G * d // 8 * 20) + 1
+    k = 210_000_000 // (2 * L * H * G * (d // 2 + d // 64 * (4 if meta == "bf16" else 8))) + 1
     cfg = oqm.make_config(L, H, H, d, G, 64, T, in_dtype=code, out_dtype=code,
                           meta_dtype=oqm.TOM_BF16 if meta == "bf16" else oqm.TOM_F32)
     mem = oqm.Memory.allocate(cfg)
