@@ -179,11 +179,14 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     a.tile_items = G * lpr;  // G * d * 4 < 2^31 is checked by the API layer
     const uint32_t passes = (a.tile_items + a.step - 1) / a.step;
     // Up to `whole` passes one workgroup takes the tile, above that equal chunks (whole rows) of at most `most`.  On the token axis every
-    // lane first loads the pairs of its channels, 64 bytes at 16-bit output against 16 stored per pass, so it takes more passes.  28 layers, us per question (200
-    // stored groups, 10 to 60 selected), chunks of at most 3 / 4 / 5 / 7 passes: head_dim axis bf16 109.0 / 110.6 / 111.8 / 113.0, float32 105 / 101.7 / 112 / 112;
-    // token axis bf16 13 passes 115 / 115 / 107 / 110, 5 passes 85 / 85 / 70 / 70, 7 passes 107 / 92 / 92 / 87.6, 8 passes 114 / 106 / 106 /
-    // 106 (all in one 112), float32 88.7 / 97 / 100 / 100.
-    const uint32_t whole = tok && eb == 2 ? 7 : 4, most = eb == 2 ? (tok ? 5 : 3) : (tok ? 3 : 4);
+    // lane first loads the pairs of its channels, 64 bytes at 16-bit output against 16 stored per pass, so it takes more passes, but for
+    // launches that leave most compute units without a tile.  28 layers, us per question (200 stored groups, 10 to 60 selected), chunks of at most 3 / 4 / 5
+    // passes: head_dim axis bf16 109.0 / 110.6 / 111.8, float32 105 / 101.7 / 112; token axis float32 88.7 / 97 / 100.  Token axis bf16, 64 of 200 groups,
+    // chunks of at most 3 / 4 / 5 passes and the tile whole, three stores in turn: 80 x 128 (5 passes) 85 / 85 / 74, 100 x 128 (7) 109 / 93 / 93 / 94, 112 x 128 (7) 113 / 101 /
+    // 101 / 105, 196 x 128 (13) 182 / 172 / 161; the same question again: 58 / 58 / 62, 72 / 68 / 68 / 77, 75 / 80 / 80 / 88, 163 / 143 / 148; 32 groups 35 / 35 / 34, 43 / 39 / 39 / 42,
+    // 45 / 44 / 44 / 46, 65 / 66 / 71.  One group of one layer, 8 tiles: 9.0 / 9.0 / 9.5, 9.0 / 9.3 / 9.3 / 9.9, 9.1 / 9.3 / 9.3 / 9.9, 9.0 / 9.3 / 9.5; 64 tiles 0.1 to 0.4 apart, 256 level.
+    const bool many = tok && eb == 2 && (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff > 128;
+    const uint32_t whole = many ? 5 : 4, most = eb == 2 ? (many ? 5 : 3) : (tok ? 3 : 4);
     const uint32_t fit = passes <= whole ? whole : most;
     a.chunks = passes <= whole ? 1 : (passes + most - 1) / most;
     while ((G + a.chunks - 1) / a.chunks * lpr > fit * a.step) ++a.chunks;
@@ -234,10 +237,7 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     } else {
         if (unroll <= 3) with_storage(std::integral_constant<int, 3>{}, std::true_type{});
         else if (unroll == 4) with_storage(std::integral_constant<int, 4>{}, std::true_type{});
-        else if constexpr (eb == 2) {
-            if (unroll == 5) with_storage(std::integral_constant<int, 5>{}, std::true_type{});
-            else with_storage(std::integral_constant<int, 7>{}, std::true_type{});
-        }
+        else if constexpr (eb == 2) with_storage(std::integral_constant<int, 5>{}, std::true_type{});
     }
     return hipGetLastError();
 }
