@@ -185,8 +185,11 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     // chunks of at most 3 / 4 / 5 passes and the tile whole, three stores in turn: 80 x 128 (5 passes) 85 / 85 / 74, 100 x 128 (7) 109 / 93 / 93 / 94, 112 x 128 (7) 113 / 101 /
     // 101 / 105, 196 x 128 (13) 182 / 172 / 161; the same question again: 58 / 58 / 62, 72 / 68 / 68 / 77, 75 / 80 / 80 / 88, 163 / 143 / 148; 32 groups 35 / 35 / 34, 43 / 39 / 39 / 42,
     // 45 / 44 / 44 / 46, 65 / 66 / 71.  One group of one layer, 8 tiles: 9.0 / 9.0 / 9.5, 9.0 / 9.3 / 9.3 / 9.9, 9.1 / 9.3 / 9.3 / 9.9, 9.0 / 9.3 / 9.5; 64 tiles 0.1 to 0.4 apart, 256 level.
-    const bool many = tok && eb == 2 && (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff > 128;
-    const uint32_t whole = many ? 5 : 4, most = eb == 2 ? (many ? 5 : 3) : (tok ? 3 : 4);
+    // Six and seven passes in two workgroups / whole, while a round of the chip (2048) holds the whole tiles: 96 x 128 (6 passes) 5 groups (1120 tiles) 15.4 / 13.9, 8 (1792) 17.3 / 16.9,
+    // 10 (2240) 20.5 / 20.5, 16 26.0 / 25.4, 64 65 / 74; 150 x 80 10 20.6 / 22.0; 100 x 128 (7) 6 17.7 / 16.4, 8 19.2 / 18.5; of 700 groups 8 25.3 / 23.7, 10 27.3 / 28.1, 32 45 / 48.
+    const int64_t tiles = (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff;
+    const bool many = tok && eb == 2 && tiles > 128;
+    const uint32_t whole = many ? (tiles <= 2048 ? 7 : 5) : 4, most = eb == 2 ? (many ? 5 : 3) : (tok ? 3 : 4);
     const uint32_t fit = passes <= whole ? whole : most;
     a.chunks = passes <= whole ? 1 : (passes + most - 1) / most;
     while ((G + a.chunks - 1) / a.chunks * lpr > fit * a.step) ++a.chunks;
@@ -237,7 +240,10 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     } else {
         if (unroll <= 3) with_storage(std::integral_constant<int, 3>{}, std::true_type{});
         else if (unroll == 4) with_storage(std::integral_constant<int, 4>{}, std::true_type{});
-        else if constexpr (eb == 2) with_storage(std::integral_constant<int, 5>{}, std::true_type{});
+        else if constexpr (eb == 2) {
+            if (unroll == 5) with_storage(std::integral_constant<int, 5>{}, std::true_type{});
+            else with_storage(std::integral_constant<int, 7>{}, std::true_type{});
+        }
     }
     return hipGetLastError();
 }
