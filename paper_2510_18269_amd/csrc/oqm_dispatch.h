@@ -145,7 +145,7 @@ inline int row_waves(int lpr, int group_tokens, bool is_16_bit) {
 }
 
 // ---- gather: the prefix rows, and the selection ---------------------------------------------
-// Both ask about a launch whose sizes (chunks, prefix_bytes, head_out_bytes) are filled in.
+// All ask about a launch whose sizes (from chunks to head_out_bytes) are filled in.
 
 // Whether the prefix rows can be copied by blocks of the gather's own launch.  As a launch of its
 // own the copy costs 1.3 to 4.5 us for 14 rows (0.8 MB at 28 layers), inside the gather nothing
@@ -177,15 +177,21 @@ inline bool gather_past_caches(const DequantArgs& a) {
 constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups
 
 // Waves of each gather workgroup that select its group from the scores (256 scores each; one or all four), or
-// 0: the indices come from a top-k launch.  The launch costs 2.5 to 4 us on the device; selecting delays every
-// round of workgroups by the 1 to 2 us of the selection.  Whole one-call question with one query token at 4 heads, with the launch / itself: 256 scores, 40
-// workgroups 11.6 / 8.7 us, 1280 11.9 / 10.8, 2560 14.7 / 14.4, 5376 24.4 / 23.1, 7168 29.0 / 27.4, 8960 26.7 / 26.2, 14336 51.5 / 56.9; 500 scores, 640 11.5 /
-// 10.8, 1920 13.9 / 14.0, 2240 20.5 / 19.9, 2560 15.3 / 16.0; 1024 scores, 640 13.8 / 10.7, 1920 14.2 / 14.0, 2400 15.0 / 15.3, 5120 20.6 / 22.7.
+// 0: the indices come from a top-k launch.  The launch costs 2.5 to 4 us; selecting delays every round of 2048 workgroups by the 1 to 2 us of
+// the selection, which workgroups of four passes hide behind each other's loads and stores, shorter ones do not.  Question with one query token at 28 layers x 4 heads,
+// the gather's own selection over the launch, 50 and 256 scores, one and three stores in turn: 16 tokens x 128 (one pass) 16 groups (3584 workgroups) 0.96 to 1.04,
+// 20 (4480) 1.01 to 1.10, 32 (7168) 1.16 to 1.23; 50 x 64 (two) 18 1.02 to 1.05, 20 1.07 to 1.11; 50 x 128 (four) 18 0.91 to 0.97, 32 0.95 to 1.01, 36 (8064) 0.97 to 1.02; token axis 50 x 128
+// (four) 18 0.94 to 0.97, 20 0.99 to 1.03, 32 1.06 to 1.09, 80 x 128 (five) 24 0.93 to 0.98, 32 0.95 to 0.98; float32 32 x 128 (four) 32 0.93, token axis 0.92; 16 x 128 (two) 18 0.99 to 1.01, 24 1.03 to 1.07; 196 x 128 (three, five workgroups a tile) 3 (3360) 0.96,
+// 5 (5600) 1.00, 6 (6720) 1.03.  Four waves, 300 to 1000 scores: 16 x 128 4 (896) 0.98 to 0.99, 5 (1120) 1.00 to 1.01, 9 (2016) 1.03 to 1.09; 50 x 64 5 0.98 to 1.04, 6 1.00 to 1.06, 9 1.04 to 1.11; 196 x 128 1 (1120) 0.98; 50 x 128 9 0.97 to 1.00, token axis 0.95 to 1.01.
 // The launch reads all scores while it writes: no output may share memory with them.
 inline int select_waves(const DequantArgs& a) {
     const int waves = a.n_groups <= 64 * kSelectKeys ? 1 : kBlock / 64;
     const int64_t heads = (int64_t)a.n_layers * a.n_kv_heads;
-    if (a.n_groups > kBlock * kSelectKeys || (int64_t)a.k_eff * a.chunks * 2 * heads > (waves == 1 ? 8192 : 2048)) return 0;
+    auto passes_above = [&](uint32_t n) { return a.chunk_items > n * a.step; };
+    const bool many_pairs = a.qaxis == TOM_QAXIS_TOKENS && a.lanes_per_row * 8 == (uint32_t)a.head_dim;  // a lane loads 8 pairs first: a pass more
+    const int most = waves > 1 ? (passes_above(3) ? 2048 : 1152)
+                               : passes_above(many_pairs ? 4 : 3) ? 8192 : passes_above(2) && !many_pairs ? 5632 : 4096;
+    if (a.n_groups > kBlock * kSelectKeys || (int64_t)a.k_eff * a.chunks * 2 * heads > most) return 0;
     const uint64_t score_bytes = score_span(a.score_stride, a.n_layers, a.n_groups);
     const uint64_t out_bytes = (uint64_t)(heads * a.head_out_bytes), idx_bytes = 4u * (uint64_t)a.n_layers * (uint64_t)a.k;
     return apart(a.scores, score_bytes, a.k_out, out_bytes) && apart(a.scores, score_bytes, a.v_out, out_bytes) &&

@@ -192,14 +192,24 @@ static void gather() {
         CHECK(scores_at(begin) == 0);
     }
     a.scores = reinterpret_cast<float*>(at(far));
-    // one wave for up to 256 scores and 8192 workgroups, four for up to 1024 and 2048
-    auto waves = [&](int n_groups, int k, int chunks) {
+    // one wave for up to 256 scores and 4096 workgroups, 5632 of three passes, 8192 of four (five where every lane loads the pairs of 8 channels); four
+    // for up to 1024 scores and 1152 workgroups, 2048 of four passes
+    auto waves = [&](int n_groups, int k, int chunks, int passes = 1) {
         a.n_groups = n_groups, a.k = a.k_eff = k, a.chunks = (uint32_t)chunks, a.n_layers = 1, a.n_kv_heads = 1;
+        a.step = 256, a.chunk_items = (uint32_t)passes * 256 - 255;
         return select_waves(a);
     };
-    CHECK(waves(256, 255, 4) == 1 && waves(256, 128, 32) == 1 && waves(256, 129, 32) == 0);
-    CHECK(waves(257, 128, 8) == 4 && waves(257, 129, 8) == 0 && waves(1024, 512, 2) == 4 && waves(1024, 513, 2) == 0);
-    CHECK(waves(1025, 1, 1) == 0 && waves(1 << 30, 1, 1) == 0);
+    for (int axis : {TOM_QAXIS_HEAD_DIM, TOM_QAXIS_TOKENS})
+        for (int channels : {4, 8})
+            for (int passes : {1, 2, 3, 4, 5}) {
+                a.qaxis = axis, a.lanes_per_row = 64 / (uint32_t)channels;
+                const bool pairs = axis == TOM_QAXIS_TOKENS && channels == 8;
+                const int one = passes > (pairs ? 4 : 3) ? 64 : passes == 3 && !pairs ? 44 : 32, four = passes > 3 ? 16 : 9;
+                CHECK(waves(256, 64, one, passes) == 1 && waves(256, 65, one, passes) == 0);
+                CHECK(waves(257, 64, four, passes) == 4 && waves(257, 65, four, passes) == 0);
+                CHECK(waves(1024, 64, four, passes) == 4 && waves(1024, 65, four, passes) == 0);
+            }
+    CHECK(waves(256, 255, 4) == 1 && waves(1025, 1, 1) == 0 && waves(1 << 30, 1, 1) == 0);
 
     // codes, pairs and keys of the question against what the last-level cache keeps; keys of 100 MB and more are not kept
     auto past = [&](int k_eff, int n_groups, int n_layers = 28) {

@@ -19,8 +19,11 @@ def oqm():
     (1024, 256, 1, 3, "f16", 0, 0, "apart"), (1024, 1, 1, 196, "bf16", 1, 0, "apart"),
     (1024, 257, 1, 3, "bf16", 0, 0, "apart"), (256, 128, 4, 16, "f16", 0, 0, "apart"),
     (1025, 20, 1, 16, "bf16", 0, 0, "apart"), (255, 129, 4, 16, "bf16", 0, 5, "apart"),    # one score too many; several rounds of workgroups
-    (256, 128, 16, 16, "bf16", 0, 0, "apart"), (256, 129, 16, 16, "f16", 0, 3, "apart"),   # the most workgroups with one wave (8192), and one group more
-    (1000, 128, 4, 16, "bf16", 0, 0, "apart"), (1000, 129, 4, 16, "f16", 1, 0, "apart"),   # the same with four (2048)
+    (256, 128, 8, 16, "bf16", 0, 0, "apart"), (256, 129, 8, 16, "f16", 0, 3, "apart"),     # the most workgroups with one wave (4096), and one group more
+    (256, 128, 16, 100, "bf16", 0, 0, "apart"), (256, 129, 16, 50, "f32", 1, 3, "apart"),  # the same where they make four passes (8192)
+    (256, 128, 11, 70, "f16", 0, 0, "apart"), (256, 129, 11, 70, "bf16", 0, 0, "apart"),   # three passes (5632)
+    (1000, 144, 2, 16, "bf16", 0, 0, "apart"), (1000, 145, 2, 16, "f16", 1, 0, "apart"),   # the same with four waves (1152, and 2048)
+    (1000, 128, 4, 100, "f16", 1, 0, "apart"), (1000, 129, 4, 100, "bf16", 0, 0, "apart"),
     (100, 30, 2, 16, "bf16", 0, 0, "scores in k_out"), (100, 30, 2, 16, "bf16", 0, 0, "idx behind scores"),   # or shared memory (the second one only adjoins)
 ])
 def test_retrieve_matches_separate_calls(oqm, T, k, L, G, dt, axis, prefix, where):
