@@ -34,16 +34,20 @@ def test_retrieve_matches_separate_calls(oqm, T, k, L, G, dt, axis, prefix, wher
 @pytest.mark.parametrize("bits", (4, 2))
 @pytest.mark.parametrize("dt", ("f32", "bf16", "f16"))
 def test_every_form_of_the_selecting_gather(oqm, dt, bits, meta):
-    """One and four selecting waves, one trip of four items a lane and chunks of three, both axes."""
+    """One and four selecting waves on both axes with three and four items a lane, and with five and seven where the token axis has 16-bit
+    output (132 tiles).  Passes of a whole tile of 64 channels: one, two, four, five and seven at 16 bits; one, four and above,
+    in chunks of three (token axis) or four, in float32.  Float32 items of eight channels, two to seven passes, above head_dim 1024."""
     for T in (200, 300):
-        for G in (16, 196):
+        for G in (16, 60, 100, 150, 196):
             for axis in (0, 1):
-                _check(oqm, T, 30, 1, G, dt, axis, 3, "apart", bits, meta)
+                _check(oqm, T, 33, 1, G, dt, axis, 3, "apart", bits, meta)
+        for G, axis in ((2, 0), (2, 1), (4, 1), (7, 0)) if dt == "f32" else ():
+            _check(oqm, T, 33, 1, G, dt, axis, 3, "apart", bits, meta, d=1088)
 
 
-def _check(oqm, T, k, L, G, dt, axis, prefix, where, bits=4, meta="f32"):
+def _check(oqm, T, k, L, G, dt, axis, prefix, where, bits=4, meta="f32", d=64):
     """Indices, scores and rows equal those of the separate calls bit for bit, with many equal scores."""
-    H, d, tq, stride = 2, 64, 3, T + 5
+    H, tq, stride = 2, 3, T + 5
     code, tdt = {"f32": (oqm.TOM_F32, torch.float32), "bf16": (oqm.TOM_BF16, torch.bfloat16), "f16": (oqm.TOM_F16, torch.float16)}[dt]
     cfg = oqm.make_config(L, H, 4, d, G, 32, T, qaxis=axis, bits=bits, in_dtype=code, out_dtype=code,
                           meta_dtype=oqm.TOM_BF16 if meta == "bf16" else oqm.TOM_F32)
