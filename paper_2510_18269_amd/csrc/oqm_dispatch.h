@@ -57,6 +57,18 @@ inline uint32_t fold_slots(const ScoreArgs& a) {
     return apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups)) ? slots : 0u;
 }
 
+// ---- query fold of its own -------------------------------------------------------------------
+// Workgroups per KV head of query_fold_kernel: one per 64 channels where those divide the head and the launch stays within one round of the chip (two
+// workgroups a compute unit), or where a row slot of a whole head would fold more than three tokens one after the other; otherwise one.  Fold and scores of 28 layers
+// x 64 groups in a graph, parts / one: 5 heads of 256 (560 workgroups), per-token scores of 1 query token 13.9 / 12.0 us, 33 30.1 / 28.2, mean query of 33 11.0 / 8.5; 8 of
+// 256 (896) 1 17.6 / 15.2, 33 39.1 / 37.0, 64 54.6 / 56.3, mean of 64 14.8 / 10.3; 4 of 512 (896) 10 21.0 / 19.7, 64 54.8 / 57.8, mean of 64 14.8 / 12.1; 4 of 256 (448) 10 13.2 /
+// 13.5, 64 34.1 / 35.2, mean of 64 10.0 / 12.1.
+inline int fold_parts(const ScoreArgs& a, bool want_tokens) {
+    const int64_t parts = a.head_dim / 64;
+    if (a.head_dim % 64 != 0) return 1;
+    return parts * a.n_kv_heads * a.n_layers <= 512 || (want_tokens && a.t_q > 3 * (kFoldThreads / (a.head_dim / 8))) ? (int)parts : 1;
+}
+
 // ---- per-token scores: the contraction is split over the waves of a workgroup -------------
 // Tiles of 16 query tokens per pass of score_token_split_kernel (1 to 4), or 0: the 64 x 64 form.
 // A whole question on the device (fold, this, top-k, gather of 4 groups) at 4 heads of 128, against the 64 x 64 form:

@@ -126,7 +126,7 @@ __device__ __forceinline__ void join_rows_of_wave(double (&acc)[8], int lpr, int
 // grid (H_k * parts, n_layers); a workgroup owns d / parts channels of a KV head: kFoldThreads threads = row slots x lanes of 8
 // channels.  The r * T_q rows of a KV head are contiguous in Q: the mean alone is one sum over them.  TOKENS: every token's mean
 // over the r heads is wanted too, so a slot takes whole tokens.  Bound by latency and by what the few compute units that take part can
-// load, hence parts of 64 channels where those divide d.  28 layers x 28 heads of 128 in a graph of the whole question, 256 threads per head / 512 / 512
+// load, hence parts of 64 channels in small launches (fold_parts in oqm_dispatch.h).  28 layers x 28 heads of 128 in a graph of the whole question, 256 threads per head / 512 / 512
 // per part: 32 tokens 5.4 / 4.5 / 4.4 us, 64 7.5 / 5.7 / 5.0, 64 with every token kept 10.2 / 9.4 / 7.0.
 template <typename QT, bool TOKENS>
 __global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArgs a, const int parts) {
@@ -720,7 +720,7 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
 
 static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s) {
     if (a.n_layers == 0) return hipSuccess;
-    const int parts = a.head_dim % 64 == 0 ? a.head_dim / 64 : 1;
+    const int parts = fold_parts(a, want_tokens);
     const dim3 grid(a.n_kv_heads * parts, a.n_layers), block(kFoldThreads);
     auto go = [&](auto qt) {
         typedef decltype(qt) QT;

@@ -69,6 +69,14 @@ static void fold() {
     CHECK(fold_slots(a) == 1);
     a.n_kv_heads = a.n_q_heads = 17;                   // no row slot left for the last head
     CHECK(fold_slots(a) == 0);
+    auto parts = [&](int heads, int d, int layers, int t_q = 1, bool want_tokens = false) {
+        a.n_kv_heads = heads, a.head_dim = d, a.n_layers = layers, a.t_q = t_q;
+        return fold_parts(a, want_tokens);
+    };
+    // of 64 channels while 512 workgroups hold them, and above three tokens a slot
+    CHECK(parts(4, 256, 32) == 4 && parts(4, 256, 33) == 1 && parts(1, 2048, 16) == 32 && parts(1, 2048, 17) == 1);
+    CHECK(parts(4, 256, 33, 48, true) == 1 && parts(4, 256, 33, 49, true) == 4 && parts(4, 256, 33, 49) == 1 && parts(4, 128, 65, 97, true) == 2);
+    CHECK(parts(4, 64, 65535) == 1 && parts(1, 96, 1) == 1 && parts(1, 8, 1, 1 << 20, true) == 1 && parts(1, 2048, 1 << 20, 7, true) == 32);
 }
 
 static void append() {

@@ -35,5 +35,6 @@ def test_pieces_of_the_key(oqm, H, d):
 def test_rows_of_the_fold(oqm, d):
     for r, tq in ((1, 63), (1, 64), (1, 65), (7, 9), (8, 64), (9, 57)):
         check_tokens(oqm, 2, 3, r, d, 21, tq, True, d + r * tq)
+        check_tokens(oqm, 171, 3, r, d, 5, tq, True, d + r * tq + 1)     # 513 heads: whole, in 8, 16, 24 and 32 lanes a row
     check_mean(oqm, 600, 3, 8, d, 19, 64, "bf16", True, d)    # 64 + 600 workgroups: separate, one row more than a trip's
     check_mean(oqm, 600, 3, 8, d, 19, 65, "bf16", True, d + 1)
