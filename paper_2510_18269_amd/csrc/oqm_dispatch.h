@@ -31,10 +31,10 @@ constexpr int kFoldThreads = 512;
 
 // Row slots per KV head of score_fold_query_kernel, or 0: the fold is a launch of its own.
 // Folding inside the score kernel saves a launch (about 4 us on the device) and costs every workgroup the serial sum over the rows
-// of a slot, 0.15 us a row, more once workgroups share compute units: line at rows x (workgroups + 160).  Whole question at k = 1, fused / separate:
+// of a slot, 0.15 us a row, more once workgroups share compute units: line at rows x (workgroups + 168).  Whole question at k = 1, fused / separate:
 // 28 heads on 4 of 128, 2 workgroups x 24 tokens (21 rows) 10.5 / 11.5 us, 32 (28) 11.6 / 11.6, 48 13.9 / 11.3; 64 workgroups x 16 tokens 10.7 / 11.6, 24
 // 12.0 / 10.9; 56 heads on 8 of 80, 6 workgroups x 16 tokens (19 rows) 12.1 / 12.7, 24 (28) 13.2 / 12.4; 12 on 3 of 96, 325 workgroups x 24 tokens
-// (7 rows) 14.4 / 14.7, 32 (10) 16.4 / 14.6.  In several rounds of the chip it is the bytes of the query that count: 28 heads on 4 of 128, 896
+// (7 rows) 14.4 / 14.7, 32 (10) 16.4 / 14.6; 224 workgroups x 32 tokens (10 rows) 10.0 / 11.6, 28 on 4 of 128 224 x 11 tokens (10 rows) 11.3 / 11.3, 12 (11) 12.1 / 11.3.  In several rounds of the chip it is the bytes of the query that count: 28 heads on 4 of 128, 896
 // workgroups x 1 token 20.0 / 20.1, x 4 21.1 / 20.2, 1764 x 1 32.0 / 32.3, x 2 32.6 / 32.2; 6 on 3 of 128, 2912 x 1 40.8 / 40.9, x 4 44.4 / 41.0.
 // A compute unit holds one workgroup with a float32 query (142 registers), two with a 16-bit one (109): a launch
 // of more runs the serial fold again in a second round.  Fold and scores in a graph, fused / separate: float32 4 heads of 128,
@@ -44,13 +44,13 @@ constexpr int kFoldThreads = 512;
 // Scores that share memory with the query need the separate fold at any size: in one launch some
 // workgroups write scores while others still read the query.
 inline uint32_t fold_slots(const ScoreArgs& a) {
-    constexpr int64_t kFusedRows = 3800, kFusedWork = 6500000;
+    constexpr int64_t kFusedRows = 3930, kFusedWork = 6500000;
     const uint32_t slots = (uint32_t)(kFoldThreads / (a.head_dim / 8) / a.n_kv_heads);
     if (slots == 0) return 0;
     const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
     const int64_t rows = (int64_t)(a.n_q_heads / a.n_kv_heads) * a.t_q;
     const int64_t query = rows * a.n_kv_heads * a.head_dim;  // elements of a layer
-    if ((rows + slots - 1) / slots > kFusedRows / (blocks + 160)) return 0;
+    if ((rows + slots - 1) / slots > kFusedRows / (blocks + 168)) return 0;
     if (blocks > 512 && query > kFusedWork / (blocks + 64)) return 0;
     if (a.q_dtype == TOM_F32 ? blocks > 256 : blocks > 512 && a.n_kv_heads * a.head_dim < 256) return 0;
     const uint64_t query_bytes = (uint64_t)query * (uint64_t)a.n_layers * (a.q_dtype == TOM_F32 ? 4u : 2u);

@@ -46,7 +46,11 @@ static void fold() {
     CHECK(fold_slots(a) == 8);
     a.t_q = 19;
     CHECK(fold_slots(a) == 0);
-    a.n_layers = 28, a.n_groups = a.score_stride = 1024, a.t_q = 1, a.q_dtype = TOM_BF16;  // several rounds of the chip
+    a.n_layers = 28, a.t_q = 11;                       // ten rows, 224 workgroups
+    CHECK(fold_slots(a) == 8);
+    a.t_q = 12;
+    CHECK(fold_slots(a) == 0);
+    a.n_groups = a.score_stride = 1024, a.t_q = 1, a.q_dtype = TOM_BF16;  // several rounds of the chip
     CHECK(fold_slots(a) == 8);
     a.t_q = 2;
     CHECK(fold_slots(a) == 0);
