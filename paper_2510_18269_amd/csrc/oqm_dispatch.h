@@ -36,9 +36,10 @@ constexpr int kFoldThreads = 512;
 // 12.0 / 10.9; 56 heads on 8 of 80, 6 workgroups x 16 tokens (19 rows) 12.1 / 12.7, 24 (28) 13.2 / 12.4; 12 on 3 of 96, 325 workgroups x 24 tokens
 // (7 rows) 14.4 / 14.7, 32 (10) 16.4 / 14.6; 224 workgroups x 32 tokens (10 rows) 10.0 / 11.6, 28 on 4 of 128 224 x 11 tokens (10 rows) 11.3 / 11.3, 12 (11) 12.1 / 11.3.  In several rounds of the chip it is the bytes of the query that count: 28 heads on 4 of 128, 896
 // workgroups x 1 token 20.0 / 20.1, x 4 21.1 / 20.2, 1764 x 1 32.0 / 32.3, x 2 32.6 / 32.2; 6 on 3 of 128, 2912 x 1 40.8 / 40.9, x 4 44.4 / 41.0.
-// A compute unit holds one workgroup with a float32 query (142 registers), two with a 16-bit one (109): a launch
-// of more runs the serial fold again in a second round.  Fold and scores in a graph, fused / separate: float32 4 heads of 128,
-// 256 workgroups x 1 token 6.9 / 9.2 us, 288 x 1 11.9 / 9.7, 896 x 1 23.3 / 16.9; one head of 64, 896 x 64 17.9 / 9.6.
+// A compute unit holds two workgroups of up to 128 registers: 16-bit queries at any key (77 to 110), float32 ones at keys of up to five pieces of 64
+// channels (110 to 128; six to eight 130 to 140).  A launch of more runs the serial fold again in a second round.  Fold and scores in a graph, fused / separate:
+// float32, 270 / 448 / 512 workgroups x 1 token, one head of 64 4.7 / 6.4 us, 4.8 / 6.8, 4.8 / 6.7; 5 heads of 64 6.0 / 7.3, 6.2 / 8.0, 6.2 / 8.0, x 16 tokens 6.7 / 7.3,
+// 6.9 / 7.9, 6.9 / 8.0; 3 of 128 (six pieces) x 4 7.8 / 7.5, 7.9 / 8.2, 8.0 / 8.3; 4 of 128 x 1 8.4 / 7.9, 8.5 / 8.7, 8.6 / 9.0, x 16 9.6 / 7.9, 12.1 / 8.9, 11.8 / 9.8, 256 x 1 6.9 / 9.2; one head of 64, 896 x 64 17.9 / 9.6.
 // 16-bit: one head of 64, 512 workgroups 6.7 / 8.4, 544 9.6 / 8.7, 896 x 64 tokens 13.2 / 9.7; where the keys are longer they hide it:
 // 4 heads of 128, 768 x 1 14.5 / 16.0.
 // Scores that share memory with the query need the separate fold at any size: in one launch some
@@ -52,7 +53,8 @@ inline uint32_t fold_slots(const ScoreArgs& a) {
     const int64_t query = rows * a.n_kv_heads * a.head_dim;  // elements of a layer
     if ((rows + slots - 1) / slots > kFusedRows / (blocks + 168)) return 0;
     if (blocks > 512 && query > kFusedWork / (blocks + 64)) return 0;
-    if (a.q_dtype == TOM_F32 ? blocks > 256 : blocks > 512 && a.n_kv_heads * a.head_dim < 256) return 0;
+    const int channels = a.n_kv_heads * a.head_dim;
+    if (a.q_dtype == TOM_F32 ? blocks > (channels <= 5 * 64 ? 512 : 256) : blocks > 512 && channels < 256) return 0;
     const uint64_t query_bytes = (uint64_t)query * (uint64_t)a.n_layers * (a.q_dtype == TOM_F32 ? 4u : 2u);
     return apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups)) ? slots : 0u;
 }

@@ -54,20 +54,26 @@ static void fold() {
     CHECK(fold_slots(a) == 8);
     a.t_q = 2;
     CHECK(fold_slots(a) == 0);
-    // one round of the chip: one workgroup per compute unit with a float32 query, two with a 16-bit one and short keys
+    // one round of the chip: two workgroups per compute unit, one with a float32 query and a key of more than five pieces; longer keys hide the second
+    // round of a 16-bit query
     a.t_q = 1, a.n_layers = 8;
     for (int dtype : {TOM_F32, TOM_BF16, TOM_F16})
-        for (int heads : {1, 2}) {
+        for (int heads : {1, 2, 3}) {
             a.q_dtype = dtype, a.n_kv_heads = a.n_q_heads = heads;
             auto fused = [&](int groups) {
                 a.n_groups = groups, a.score_stride = groups;
                 return fold_slots(a) > 0;
             };
             CHECK(fused(256 * 32 / 8));
-            CHECK(fused(256 * 32 / 8 + 1) == (dtype != TOM_F32));
-            CHECK(fused(512 * 32 / 8) == (dtype != TOM_F32));
-            CHECK(fused(512 * 32 / 8 + 1) == (dtype != TOM_F32 && heads == 2));
+            CHECK(fused(256 * 32 / 8 + 1) == (dtype != TOM_F32 || heads < 3));
+            CHECK(fused(512 * 32 / 8) == (dtype != TOM_F32 || heads < 3));
+            CHECK(fused(512 * 32 / 8 + 1) == (dtype != TOM_F32 && heads > 1));
         }
+    a.q_dtype = TOM_F32, a.n_groups = a.score_stride = 512 * 32 / 8;
+    a.head_dim = 64, a.n_kv_heads = a.n_q_heads = 5;   // five pieces
+    CHECK(fold_slots(a) > 0);
+    a.head_dim = 328, a.n_kv_heads = a.n_q_heads = 1;  // and a rest
+    CHECK(fold_slots(a) == 0);
     a.n_layers = 1, a.n_groups = a.score_stride = 256, a.q_dtype = TOM_BF16;
     a.t_q = 1, a.head_dim = 256, a.n_kv_heads = a.n_q_heads = 16;
     CHECK(fold_slots(a) == 1);

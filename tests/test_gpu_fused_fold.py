@@ -68,6 +68,13 @@ def test_both_sides_of_the_rule(oqm, L, T, tqs, dt):
         _check(oqm, L, 4, 7, 128, T, tq, dt, True, 1000 + tq)
 
 
+# float32: two workgroups a compute unit (512) at keys of five pieces, one (256) above
+@pytest.mark.parametrize("H,d", ((5, 64), (4, 80), (1, 328), (3, 128)))
+def test_float32_rounds(oqm, H, d):
+    for L, T in ((8, 1024), (8, 1025), (16, 1024), (16, 1025)):
+        _check(oqm, L, H, 2, d, T, 2, "f32", L == 8, 3000 + d + T)
+
+
 # scores written into the memory of the query: the query has to be consumed before the first of them
 @pytest.mark.parametrize("where", (0.0, 0.5, 1.0))
 @pytest.mark.parametrize("dt", ("bf16", "f32"))
