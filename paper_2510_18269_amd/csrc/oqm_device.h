@@ -150,35 +150,7 @@ __device__ __forceinline__ void spread_rows(float (&v)[8]) {
     }
 }
 
-// ---- loading 8 consecutive elements as float32 -----------------------------
-// p must be 16-byte aligned.  Widening bf16 / f16 to float32 is exact.
-__device__ __forceinline__ void load8(const void* p, In_bf16, float (&x)[8]) {
-    const u32x4 w = *reinterpret_cast<const u32x4*>(p);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        x[2 * i] = __uint_as_float(w[i] << 16);
-        x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-}
-
-__device__ __forceinline__ void load8(const void* p, In_f16, float (&x)[8]) {
-    const f16x8 h = *reinterpret_cast<const f16x8*>(p);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = (float)h[i];
-}
-
-__device__ __forceinline__ void load8(const void* p, In_f32, float (&x)[8]) {
-    const f32x4 a = reinterpret_cast<const f32x4*>(p)[0];
-    const f32x4 b = reinterpret_cast<const f32x4*>(p)[1];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        x[i] = a[i];
-        x[4 + i] = b[i];
-    }
-}
-
-
-// ---- raw (not yet widened) 8-element loads, for software-pipelined loops ----
+// ---- raw (not yet widened) 8-element loads: p must be 16-byte aligned; widening bf16 / f16 to float32 is exact ----
 template <typename T> struct Raw8;
 template <> struct Raw8<In_bf16> { u32x4 a; };
 template <> struct Raw8<In_f16> { f16x8 a; };

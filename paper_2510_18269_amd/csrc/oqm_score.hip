@@ -748,16 +748,25 @@ static hipError_t with_pieces(int HD, GO go) {
         go(ch, rest, (size_t)((HD + trip - 1) / trip * trip) * sizeof(double));
         return hipGetLastError();
     };
+    // 32 lanes take keys of at least eight pieces: eight whole ones, or several trips of five to eight
+    constexpr bool long_keys = W == 32;
     auto each = [&](auto ch) {
         if (whole) return with(ch, std::integral_constant<Rest, kNoRest>{});
-        if (trips == 1) return with(ch, std::integral_constant<Rest, kLastPiece>{});
+        if constexpr (!long_keys) {
+            if (trips == 1) return with(ch, std::integral_constant<Rest, kLastPiece>{});
+        }
         return with(std::integral_constant<int, kScoreChunks>{}, std::integral_constant<Rest, kAnyPiece>{});
     };
-    switch ((pieces + trips - 1) / trips) {
-        case 1: return each(std::integral_constant<int, 1>{});
-        case 2: return each(std::integral_constant<int, 2>{});
-        case 3: return each(std::integral_constant<int, 3>{});
-        case 4: return each(std::integral_constant<int, 4>{});
+    const int per_trip = (pieces + trips - 1) / trips;
+    if constexpr (!long_keys) {
+        switch (per_trip) {
+            case 1: return each(std::integral_constant<int, 1>{});
+            case 2: return each(std::integral_constant<int, 2>{});
+            case 3: return each(std::integral_constant<int, 3>{});
+            case 4: return each(std::integral_constant<int, 4>{});
+        }
+    }
+    switch (per_trip) {
         case 5: return each(std::integral_constant<int, 5>{});
         case 6: return each(std::integral_constant<int, 6>{});
         case 7: return each(std::integral_constant<int, 7>{});
