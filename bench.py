@@ -55,6 +55,17 @@ def bytes_topk(w, T, k_eff):
 
 
 # ------------------------------------------------------------------ committed counter summaries
+def traced_append_kernel(workload):
+    """The append kernel in the committed kernel trace of `bench.py --workload <workload>`: the library
+    chooses among several by rules of its own.  None if there is no trace."""
+    try:
+        with open(os.path.join(ROOT, "profiles", f"kernel_trace_bench_{workload.lower()}.txt")) as f:
+            names = [l.split("<")[0].split()[0] for l in f if l.startswith("quantize_append")]
+    except OSError:
+        return None
+    return names[0] if names else None
+
+
 def kernel_sources_hash():
     """SHA-256 over the kernels' sources (every .hip / .h under csrc/ except the benchmark-only
     probe and the division self-check), in name order: ties a committed counter summary to the
@@ -375,9 +386,7 @@ class Leg:
                     "frac_by_committed_kernel_trace": round(b / (traced * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4) if traced else None}
 
         tok = self.tok
-        # the form that the library takes at this size (a few tiles: K cut into chunks like V)
-        append_kernel = ("quantize_append_rows_kernel" if tok else
-                         "quantize_append_cut_kernel" if 2 * L * w.n_kv_heads * fpa <= 384 else "quantize_append_kernel")
+        append_kernel = (traced_append_kernel(w.name) if default_variant else None) or "quantize_append"
         r = {
             "workload": f"{w.name}: {L} layers, {w.n_kv_heads} KV heads ({w.n_q_heads} query heads), "
                         f"head_dim {w.head_dim}, {w.dtype} K/V, {T} frames x {w.group_tokens} tokens stored, "
