@@ -18,9 +18,12 @@ inline uint64_t score_span(int64_t stride, int n_layers, int n_groups) {
 }
 
 // ---- mean-query score: keys past the caches --------------------------------------------------
-// Where the keys of a call are a good part of the last-level cache (256 MB) they only push out what else is there.  Whole question at one selected
-// group, three stores in turn, through / past the caches: 28 layers x 1500 groups x 512 channels (86 MB) 26.2 / 26.4 us, 2200 (126 MB) 35.3 / 33.3, 3000 (172 MB)
-// 42.8 / 39.7; 1000 (57 MB) 19.2 / 20.5, 200 12.8 / 13.3.
+// From 100 MB up the keys of a call are a good part of the last-level cache (256 MB), and read through it they push out the codes of the next gather.  Past the caches they are
+// read again from memory for the next question about the same store, which costs less than it looks, since 100 MB of keys do not survive a
+// question whole either.  28 layers x 512 channels, us, through / past, one store asked in a row and three in turn.  Scores alone: 100 MB 20.8 / 20.2, 23.2 / 21.9; 126 24.7 / 24.0, 27.1 / 25.6;
+// 172 30.5 / 30.3, 34.5 / 32.1; 206 34.9 / 35.2, 40.1 / 37.0; 300 51.1 / 48.5, 55.0 / 50.7.  Whole question at 4 selected groups: 100 33.6 / 34.2, 40.7 / 34.8; 126 38.9 / 39.4, 46.1 / 39.9; 172
+// 44.6 / 46.0, 53.7 / 46.5; 206 50.6 / 50.6, 58.8 / 51.1; at 1 172 39.0 / 39.6, 44.7 / 41.1; at 16 126 61.8 / 60.7, 75.1 / 64.9; 172 79.6 / 67.1, 82.4 / 72.3; at 64 172 198 / 192, 203 / 195.  The most lost:
+// 8 heads of 128, 172 MB, 4 groups 44.4 / 46.5 (in turn 51.7 / 46.3).  Smaller ones in turn: 57 MB 14.9 / 15.8 (scores alone), 86 19.9 / 20.5.
 constexpr int64_t kKeysPastCaches = 100000000;
 inline bool keys_past_caches(const ScoreArgs& a) {
     return (int64_t)a.n_layers * a.n_groups * a.n_kv_heads * a.head_dim * (int64_t)sizeof(float) >= kKeysPastCaches;
@@ -77,9 +80,9 @@ inline int fold_parts(const ScoreArgs& a, bool want_tokens) {
 // 1 layer x 256 groups x 32 tokens 18.1 / 28.0 us, x 64 tokens 25.8 / 39.3; 8 x 1024 (512 units)
 // x 32 25.3 / 31.0; but 28 x 400 (700 units) x 32 33.0 / 33.0, x 64 55.2 / 45.9: from three
 // units per compute unit on the query block is read too often.
-// The tokens are cut into equal passes.  A pass of four tiles takes 138 registers, so a compute unit
+// The tokens are cut into equal passes.  A pass of four tiles takes 144 registers, so a compute unit
 // holds one workgroup (eight waves of three per SIMD): more than 256 units would then run in two rounds.  With
-// at most three tiles (112 registers, two workgroups) 512 units run in one.  Fold and scores at 448 to 512 units, equal
+// at most three tiles (118 registers, two workgroups) 512 units run in one.  Fold and scores at 448 to 512 units, equal
 // passes of three / passes of four / 64 x 64 form: one head of 64 x 65 tokens 14.5 / 18.0 / 15.8 us, x 1024
 // tokens 92 / 117 / 107; 4 heads of 128 x 65 tokens 36 / 45 / 46, x 1024 tokens 370 / 390 / 470.
 inline int split_tiles(const ScoreArgs& a) {

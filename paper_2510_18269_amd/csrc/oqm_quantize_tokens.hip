@@ -225,8 +225,7 @@ __global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const Ap
 // Grid: those, then all K tiles, then all V tiles, so that one dense stream of addresses is read at a time and the
 // longer workgroups start first.  Measured, us: 28 layers x 4 heads x 50 x 128 (two waves of seven rows), K and V of a layer in turn with the sums in front
 // of the exchange / in turn / V first / K first: 8 FP16 frames 9.2 / 9.3 / 8.8 / 8.6, 32 bf16 frames (124 MB) 25.6 / 25.9 / 25.3 / 24.3 (5.1
-// TB/s), 16 13.5 / 13.2 / 12.9 / 12.0; 196 tokens x 4 frames 15.2 / 14.0 / 13.3 / 12.9.  112 registers became 74 on the way, which by
-// itself gains nothing; forcing fewer spills and loses.  At 32 frames one wave of 13 rows takes
+// TB/s), 16 13.5 / 13.2 / 12.9 / 12.0; 196 tokens x 4 frames 15.2 / 14.0 / 13.3 / 12.9.  It takes 88 registers, five waves per SIMD; forcing fewer spills and loses.  At 32 frames one wave of 13 rows takes
 // 29.1 us, three waves of five 28.4, four of four 29.8, skipping the dead rows by a branch per row
 // 27.5 (no v_min3 across rows), where this form took 25.9; the 256-thread form below 30.1.
 template <typename IN, int LPR, int HOLD, int BITS, bool MB, bool SEP>

@@ -106,7 +106,7 @@ struct QueryNorm2 {
     }
 };
 
-// Column sums over the row slots of a wave where lpr = d/8 lanes per row divide it: one row of d sums per wave in `red`,
+// Column sums over the row slots of a wave where lpr (d/8) lanes per row divide it: one row of d sums per wave in `red`,
 // in channel order.  Every lane of the wave takes part.
 __host__ __device__ __forceinline__ bool rows_divide_a_wave(int lpr) { return lpr == 8 || lpr == 16 || lpr == 32; }
 __device__ __forceinline__ void join_rows_of_wave(double (&acc)[8], int lpr, int slot, double* red) {

@@ -58,6 +58,8 @@ struct alignas(16) SelectScratch {
 // add to one word take their turns, hence four words a bin.  28 rows in a graph, this / two bits a barrier by ballots: 200
 // scores 2.9 / 3.0 us, 1024 3.7 / 5.0, 2000 3.9 / 6.1, 3600 5.6 / 7.4; 1024 equal ones 3.6 / 4.7, 4096 6.2 / 7.0 (one word a bin 10.8), each of 1024 five
 // times 3.8 / 5.3, 777 with 60 of each 4.1 / 5.5.  One word a bin and a test of each register for lanes that all share a bin: 3.9 at 1024, 6.4 at 3600.
+// Ballots end sooner where a few high scores stand apart, and start without clearing counts: one row, the first 1 to 4 of 300 to 777 scores 3.0 to 3.6 / 2.7 to
+// 3.1, of up to 256 2.5 to 3.0 / 2.2 to 3.0; the first 16 or 64 of 300 to 777 3.4 / 4.4 to 5.0.
 template <int WAVES, int KEYS, typename EMIT>
 __device__ __forceinline__ void select_largest(const uint32_t (&key)[KEYS], int k_eff, int wave, int lane,
                                                SelectScratch<WAVES>* shared, EMIT emit) {
