@@ -40,7 +40,10 @@ constexpr int kFoldThreads = 512;
 // (7 rows) 14.4 / 14.7, 32 (10) 16.4 / 14.6; 224 workgroups x 32 tokens (10 rows) 10.0 / 11.6, 28 on 4 of 128 224 x 11 tokens (10 rows) 11.3 / 11.3, 12 (11) 12.1 / 11.3.  In several rounds of the chip it is the bytes of the query that count: 28 heads on 4 of 128, 896
 // workgroups x 1 token 20.0 / 20.1, x 4 21.1 / 20.2, 1764 x 1 32.0 / 32.3, x 2 32.6 / 32.2; 6 on 3 of 128, 2912 x 1 40.8 / 40.9, x 4 44.4 / 41.0.
 // A compute unit holds two workgroups of up to 128 registers: 16-bit queries at any key (77 to 110), float32 ones at keys of up to five pieces of 64
-// channels (110 to 128; six to eight 130 to 140).  A launch of more runs the serial fold again in a second round.  Fold and scores in a graph, fused / separate:
+// channels (110 to 128; six to eight 130 to 140).  A launch of more runs the serial fold again in a second round.  Every workgroup of a layer reads its question, so an XCD
+// reads that of every layer with eight workgroups or more, besides an eighth of the keys: a float32 question that the L2 (4 MiB) cannot hold so keeps the limits of one
+// workgroup a compute unit, and rows x (workgroups + 160).  28 layers, MB of question and keys an XCD, us fused / separate: 4 heads of 64, 280 workgroups 3.9 6.8 / 7.0, 4.4 7.7 / 7.0, 4.8 10.1 / 7.0; 448 4.1
+// 6.9 / 7.4, 4.6 8.0 / 7.4; 5 of 64 448 4.4 7.9 / 8.0, 4.9 9.3 / 8.1; 3 of 96 448 4.2 7.5 / 8.3, 4.8 9.2 / 8.3; 224 x 10 rows 4 of 64 5.5 10.0 / 6.7, 14 layers x 16 (3.2) 5.9 / 6.7, 4 of 128 (4.1) 8.2 / 7.6.  Fold and scores in a graph, fused / separate:
 // float32, 270 / 448 / 512 workgroups x 1 token, one head of 64 4.7 / 6.4 us, 4.8 / 6.8, 4.8 / 6.7; 5 heads of 64 6.0 / 7.3, 6.2 / 8.0, 6.2 / 8.0, x 16 tokens 6.7 / 7.3,
 // 6.9 / 7.9, 6.9 / 8.0; 3 of 128 (six pieces) x 4 7.8 / 7.5, 7.9 / 8.2, 8.0 / 8.3; 4 of 128 x 1 8.4 / 7.9, 8.5 / 8.7, 8.6 / 9.0, x 16 9.6 / 7.9, 12.1 / 8.9, 11.8 / 9.8, 256 x 1 6.9 / 9.2; one head of 64, 896 x 64 17.9 / 9.6.
 // 16-bit: one head of 64, 512 workgroups 6.7 / 8.4, 544 9.6 / 8.7, 896 x 64 tokens 13.2 / 9.7; where the keys are longer they hide it:
@@ -48,17 +51,23 @@ constexpr int kFoldThreads = 512;
 // Scores that share memory with the query need the separate fold at any size: in one launch some
 // workgroups write scores while others still read the query.
 inline uint32_t fold_slots(const ScoreArgs& a) {
-    constexpr int64_t kFusedRows = 3930, kFusedWork = 6500000;
+    constexpr int64_t kFusedRows = 3930, kFusedRowsPastL2 = 3800, kFusedWork = 6500000, kL2 = 4 << 20, kXcds = 8;
     const uint32_t slots = (uint32_t)(kFoldThreads / (a.head_dim / 8) / a.n_kv_heads);
     if (slots == 0) return 0;
-    const int64_t blocks = (int64_t)((a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16)) * a.n_layers;
+    const int64_t layer_blocks = (a.n_groups + kFoldThreads / 16 - 1) / (kFoldThreads / 16), blocks = layer_blocks * a.n_layers;
     const int64_t rows = (int64_t)(a.n_q_heads / a.n_kv_heads) * a.t_q;
     const int64_t query = rows * a.n_kv_heads * a.head_dim;  // elements of a layer
-    if ((rows + slots - 1) / slots > kFusedRows / (blocks + 168)) return 0;
-    if (blocks > 512 && query > kFusedWork / (blocks + 64)) return 0;
     const int channels = a.n_kv_heads * a.head_dim;
-    if (a.q_dtype == TOM_F32 ? blocks > (channels <= 5 * 64 ? 512 : 256) : blocks > 512 && channels < 256) return 0;
-    const uint64_t query_bytes = (uint64_t)query * (uint64_t)a.n_layers * (a.q_dtype == TOM_F32 ? 4u : 2u);
+    const bool is_f32 = a.q_dtype == TOM_F32;
+    bool one = false;  // float32: one workgroup a compute unit
+    if (is_f32) {
+        const int64_t readers = layer_blocks < kXcds ? layer_blocks : kXcds;
+        one = channels > 5 * 64 || query * readers + (int64_t)a.n_groups * channels > kL2 / 4 * kXcds / a.n_layers;
+    }
+    if ((rows + slots - 1) / slots > (one ? kFusedRowsPastL2 / (blocks + 160) : kFusedRows / (blocks + 168))) return 0;
+    if (blocks > 512 && query > kFusedWork / (blocks + 64)) return 0;
+    if (is_f32 ? blocks > (one ? 256 : 512) : blocks > 512 && channels < 256) return 0;
+    const uint64_t query_bytes = (uint64_t)query * (uint64_t)a.n_layers * (is_f32 ? 4u : 2u);
     return apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups)) ? slots : 0u;
 }
 

@@ -46,10 +46,24 @@ static void fold() {
     CHECK(fold_slots(a) == 8);
     a.t_q = 19;
     CHECK(fold_slots(a) == 0);
-    a.n_layers = 28, a.t_q = 11;                       // ten rows, 224 workgroups
-    CHECK(fold_slots(a) == 8);
-    a.t_q = 12;
-    CHECK(fold_slots(a) == 0);
+    a.n_layers = 28;                                   // 224 workgroups: ten rows, nine with a float32 question on keys of more than five pieces
+    for (int dtype : {TOM_F32, TOM_BF16, TOM_F16}) {
+        a.q_dtype = dtype;
+        a.t_q = dtype == TOM_F32 ? 10 : 11;
+        CHECK(fold_slots(a) == 8);
+        ++a.t_q;
+        CHECK(fold_slots(a) == 0);
+    }
+    // float32 on keys of four pieces: question and keys an XCD reads, 1.8 MB of keys and 115 KB a token or 0.9 MB and 57 KB
+    a.q_dtype = TOM_F32, a.head_dim = 64, a.n_q_heads = 16;
+    auto past_l2 = [&](int layers, int groups, int t_q) {
+        a.n_layers = layers, a.n_groups = a.score_stride = groups, a.t_q = t_q;
+        return fold_slots(a) == 0;
+    };
+    CHECK(!past_l2(28, 512, 20) && past_l2(28, 512, 21) && !past_l2(28, 480, 21));
+    CHECK(!past_l2(28, 256, 36) && past_l2(28, 256, 37) && !past_l2(14, 512, 40) && past_l2(14, 512, 41));
+    CHECK(!past_l2(56, 256, 10) && past_l2(56, 256, 11) && !past_l2(112, 128, 10) && past_l2(112, 128, 11) && past_l2(1 << 30, 1, 1));
+    a.q_dtype = TOM_BF16, a.n_q_heads = 28, a.head_dim = 128, a.n_layers = 28;
     a.n_groups = a.score_stride = 1024, a.t_q = 1, a.q_dtype = TOM_BF16;  // several rounds of the chip
     CHECK(fold_slots(a) == 8);
     a.t_q = 2;

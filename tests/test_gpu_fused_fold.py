@@ -59,9 +59,9 @@ def test_head_shapes(oqm, H, r, d):
         _check(oqm, 2, H, r, d, T, tq, ("bf16", "f16", "f32")[i % 3], i % 2 == 0, 10 * d + i)
 
 
-# 7 T_q rows in 8 slots, times (blocks + 168), against the rule's 3930, and 28 x 128 x T_q x (blocks + 64) against its 6.5e6: last
-# fused and first separate question lengths
-@pytest.mark.parametrize("L,T,tqs", ((1, 64, (26, 27)), (1, 256, (25, 26)), (8, 256, (18, 19)), (28, 256, (11, 12)), (28, 1024, (1, 2))))
+# 7 T_q rows in 8 slots, times (blocks + 168), against the rule's 3930 (float32 at this key: + 160, 3800), and 28 x 128 x T_q x (blocks + 64)
+# against its 6.5e6: last fused and first separate question lengths
+@pytest.mark.parametrize("L,T,tqs", ((1, 64, (26, 27)), (1, 256, (25, 26)), (8, 256, (18, 19)), (28, 256, (10, 11, 12)), (28, 1024, (1, 2))))
 @pytest.mark.parametrize("dt", ("bf16", "f32"))
 def test_both_sides_of_the_rule(oqm, L, T, tqs, dt):
     for tq in tqs:
@@ -73,6 +73,13 @@ def test_both_sides_of_the_rule(oqm, L, T, tqs, dt):
 def test_float32_rounds(oqm, H, d):
     for L, T in ((8, 1024), (8, 1025), (16, 1024), (16, 1025)):
         _check(oqm, L, H, 2, d, T, 2, "f32", L == 8, 3000 + d + T)
+
+
+# float32 questions that an L2 holds beside an eighth of the keys, and of a token more
+@pytest.mark.parametrize("L,T,tqs", ((28, 512, (20, 21)), (28, 256, (36, 37)), (14, 512, (40, 41)), (112, 128, (10, 11))))
+def test_float32_past_l2(oqm, L, T, tqs):
+    for tq in tqs:
+        _check(oqm, L, 4, 4, 64, T, tq, "f32", True, 4000 + L + tq)
 
 
 # scores written into the memory of the query: the query has to be consumed before the first of them
