@@ -145,6 +145,175 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
     if (SELECT <= 0 && a.all_idx && blockIdx.y == 0 && begin == 0 && tid == 0) a.all_idx[(int64_t)li * a.k + r] = (int32_t)r;
 }
 
+// ------------------------------------------------------------------ the gather by pieces of its output
+// Large launches of the head_dim axis (gather_by_pieces in oqm_dispatch.h).  What bounds them is the order in which memory is written: plain
+// 16-byte stores of 755 MB take 112 us where every workgroup writes the next 4 KB, 124 where it writes 16 KB, 153 with 64 KB and 180 from
+// a persistent grid.  Tiles and their chunks are not multiples of 4 KB, so here the rows of a head are cut into aligned pieces of 4 KB whatever tile they belong to, and
+// a workgroup takes kPieces of them, eight pieces apart: workgroups go round-robin over the eight XCDs, so that the ones in flight write one dense window of which each
+// XCD has every eighth piece.  Two pieces hide the loads; with one a wave lives too short for them, three or four open the window.
+// A wave's 64 items lie in at most two tiles.  Buffer instructions drop what lies outside of the rows, so nothing branches.
+// 28 layers x 4 heads x 196 x 128 x 64 groups (944 MB), codes and pairs of random bits, one store, us: chunks 158, one piece 185, two 156.2, three 157, four 158.6; an arithmetic-free
+// kernel of the same order with nothing but this shape's constants 153.4 (two adjacent pieces 157; runs of 16 workgroups per XCD 155; 512 threads 156, 1024 172; index loads per lane 174).
+// 128 groups (quant-groups of 32, 2.0 GB) 337 -> 325; 37 x 256, 700 MB of output 162 -> 152; 61 x 96 168 -> 162.
+constexpr int kPieces = 2;
+constexpr uint32_t kXcds = 8;
+
+// What the kernel needs of a DequantArgs, made on the host.
+struct PieceArgs {
+    const char *codes, *meta;  // of the first layer asked for
+    const int32_t* idx;        // or, where every stored group is taken in order, where these indices go
+    char *k_out, *v_out;       // behind the prefix rows of the first head
+    uint64_t code_plane, meta_plane, head_out_bytes;        // bytes of a (layer, K|V); of a head's active buffer
+    uint32_t code_tile, meta_tile, code_group, meta_group;  // bytes of a tile, of the tiles of a group
+    uint32_t tile_items, inv_tile_items, k_eff, n_groups;
+    uint32_t k, heads, blocks, pair_shift;
+    const char *sys_k, *sys_v;
+    uint64_t prefix_bytes;
+};
+
+constexpr int kNonTemporal = 2;  // cache policy of the buffer builtins
+
+template <int BYTES, bool PAST>
+__device__ __forceinline__ uint32_t buffer_codes(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    constexpr int aux = PAST ? kNonTemporal : 0;
+    if constexpr (BYTES == 4) return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, aux);
+    else if constexpr (BYTES == 2) return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, aux);
+    else return (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, (int)off, 0, aux);
+}
+__device__ __forceinline__ void buffer_pair(__amdgpu_buffer_rsrc_t r, uint32_t off, f32x2& p) {
+    p = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void buffer_pair(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t& p) {
+    p = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0);
+}
+// Memory from `base` on, raw: byte offsets, and what lies past `bytes` is read as zero and not written.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)bytes, 0x00020000);
+}
+
+// grid (a multiple of 8 workgroups for the pieces, then prefix blocks; K heads, then V heads; layer).  ALL: every stored group is taken in order, and
+// these indices are written.
+template <typename OUT, int N, int BITS, bool MB, bool PAST_CACHES, bool ALL>
+__global__ void __launch_bounds__(kBlock) dequant_gather_pieces_kernel(const PieceArgs a) {
+    constexpr uint32_t CW = BITS * N / 8;  // bytes of packed codes per item
+    constexpr uint32_t CMASK = (1u << BITS) - 1u;
+    constexpr uint32_t kItemBytes = 16, kApart = kXcds * kBlock;  // items between a workgroup's pieces
+    typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
+    // everything the addresses need is requested at once, not behind the index
+    asm volatile("" ::"s"(a.codes), "s"(a.meta), "s"(a.idx), "s"(a.k_out), "s"(a.v_out), "s"(a.code_plane), "s"(a.meta_plane), "s"(a.head_out_bytes),
+                 "s"(a.code_tile), "s"(a.meta_tile), "s"(a.code_group), "s"(a.meta_group), "s"(a.tile_items), "s"(a.inv_tile_items), "s"(a.k_eff), "s"(a.n_groups),
+                 "s"(a.k), "s"(a.heads), "s"(a.blocks), "s"(a.pair_shift));
+    const uint32_t kv = blockIdx.y >= a.heads ? 1u : 0u, h = blockIdx.y - kv * a.heads, li = blockIdx.z, head = li * a.heads + h;
+    char* const out0 = kv ? a.v_out : a.k_out;
+    if (blockIdx.x >= a.blocks) {  // uniform: one of the prefix blocks that end the x dimension
+        copy_prefix((kv ? a.sys_v : a.sys_k) + head * a.prefix_bytes, out0 + head * a.head_out_bytes - a.prefix_bytes, (int64_t)a.prefix_bytes,
+                    blockIdx.x - a.blocks);
+        return;
+    }
+    const uint32_t lane = threadIdx.x & 63u, ti = a.tile_items, last = a.k_eff - 1u;
+    // items between the start of the first piece and the rows
+    const uint32_t lead = (((uint32_t)(uintptr_t)out0 + head * (uint32_t)a.head_out_bytes) & (kBlock * kItemBytes - 1u)) / kItemBytes;
+    // first item of the wave, of the first piece; below zero in front of the rows
+    const uint32_t first = ((blockIdx.x & ~(kXcds - 1u)) * kPieces + (blockIdx.x & (kXcds - 1u))) * kBlock +
+                           ((uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63u) - lead;
+    typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;  // not written by this launch where it is read
+    typedef const __attribute__((address_space(4))) char* scalar_bytes;
+    const scalar_bytes idx = (scalar_bytes)(uintptr_t)a.idx;
+    uint32_t r[kPieces], t[kPieces][2];  // rank of the wave's first tile; groups of it and of the next
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+        r[p] = min(div_by((uint32_t)max((int)(first + p * kApart), 0), ti, a.inv_tile_items), last);
+        const uint32_t next = min(r[p] + 1u, last);
+        t[p][0] = ALL ? r[p] : *(scalar_ptr)(idx + (li * a.k + r[p]) * 4u);
+        t[p][1] = ALL ? next : *(scalar_ptr)(idx + (li * a.k + next) * 4u);
+    }
+    const uint32_t plane = li * 2u + kv;
+    const __amdgpu_buffer_rsrc_t codes = buffer(a.codes + plane * a.code_plane + h * a.code_tile, (uint32_t)a.code_plane - h * a.code_tile);
+    const __amdgpu_buffer_rsrc_t pairs = buffer(a.meta + plane * a.meta_plane + h * a.meta_tile, (uint32_t)a.meta_plane - h * a.meta_tile);
+    const __amdgpu_buffer_rsrc_t rows = buffer(out0 + head * a.head_out_bytes, a.k_eff * ti * kItemBytes);
+    uint32_t w[kPieces], to[kPieces];
+    meta_pair sm[kPieces];
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+        const uint32_t item = first + p * kApart + lane, at = item - r[p] * ti;
+        const bool second = (int)at >= (int)ti;
+        // offsets of the tile that item 0 of the wave's first tile would have
+        const uint32_t c0 = t[p][0] * a.code_group, c1 = t[p][1] * a.code_group - a.code_tile;
+        const uint32_t m0 = t[p][0] * a.meta_group, m1 = t[p][1] * a.meta_group - a.meta_tile;
+        w[p] = buffer_codes<CW, PAST_CACHES>(codes, (second ? c1 : c0) + at * CW);
+        buffer_pair(pairs, (second ? m1 : m0) + (at >> a.pair_shift) * (uint32_t)sizeof(meta_pair), sm[p]);
+        // not a stored group: leave the rows alone
+        to[p] = (second ? t[p][1] : t[p][0]) < a.n_groups ? item * kItemBytes : 0xffffffffu;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0) alone: one wait for all loads, so that no store is waited for
+#pragma unroll
+    for (int p = 0; p < kPieces; ++p) {
+        float x[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float c = (float)((w[p] >> (BITS * i)) & CMASK);
+            const f32x2 pair = widen_pair(sm[p]);
+            x[i] = __builtin_fmaf(c, pair[0], pair[1]);  // Eq. 11, rounded once to float32
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(pack_items(OUT{}, x), rows, (int)to[p], 0, kNonTemporal);
+    }
+    if (ALL && blockIdx.y == 0) {
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p) {
+            const uint32_t item = first + p * kApart + lane, at = item - r[p] * ti, rank = r[p] + (at == ti ? 1u : 0u);
+            if ((int)item >= 0 && (at == 0u || at == ti) && rank <= last) const_cast<int32_t*>(a.idx)[(uint64_t)li * a.k + rank] = (int32_t)rank;
+        }
+    }
+}
+
+template <typename OUT, int N>
+hipError_t launch_pieces(const DequantArgs& a, uint32_t prefix_blocks, hipStream_t s) {
+    PieceArgs f{};
+    f.code_tile = a.tile_items * (uint32_t)(N * a.bits / 8);
+    f.meta_tile = a.tile_meta_bytes;
+    f.code_plane = (uint64_t)a.plane_tiles * f.code_tile;
+    f.meta_plane = (uint64_t)a.plane_tiles * f.meta_tile;
+    f.code_group = f.code_tile * (uint32_t)a.n_kv_heads;
+    f.meta_group = f.meta_tile * (uint32_t)a.n_kv_heads;
+    f.codes = reinterpret_cast<const char*>(a.codes) + 2u * (uint64_t)a.layer0 * f.code_plane;
+    f.meta = static_cast<const char*>(a.meta) + 2u * (uint64_t)a.layer0 * f.meta_plane;
+    f.idx = a.all_idx ? a.all_idx : a.idx;
+    f.k_out = static_cast<char*>(a.k_out) + a.prefix_bytes;
+    f.v_out = static_cast<char*>(a.v_out) + a.prefix_bytes;
+    f.head_out_bytes = (uint64_t)a.head_out_bytes;
+    f.tile_items = a.tile_items;
+    f.inv_tile_items = reciprocal_u32(a.tile_items);
+    f.k_eff = (uint32_t)a.k_eff;
+    f.n_groups = (uint32_t)a.n_groups;
+    f.k = (uint32_t)a.k;
+    f.heads = (uint32_t)a.n_kv_heads;
+    f.pair_shift = a.lpg_shift;
+    f.sys_k = a.sys_k;
+    f.sys_v = a.sys_v;
+    f.prefix_bytes = (uint64_t)a.prefix_bytes;
+    const uint32_t pieces = (uint32_t)a.k_eff * a.tile_items / kBlock + 2;  // the first and the last one may be parts
+    f.blocks = (pieces + kXcds * kPieces - 1) / (kXcds * kPieces) * kXcds;
+    const dim3 grid(f.blocks + (prefix_blocks + kXcds - 1) / kXcds * kXcds, 2 * f.heads, a.n_layers);
+    auto go = [&](auto bits, auto mb, auto past) {
+        constexpr int B = decltype(bits)::value;
+        constexpr bool M = decltype(mb)::value, C = decltype(past)::value;
+        if (a.all_idx) launch(dequant_gather_pieces_kernel<OUT, N, B, M, C, true>, grid, dim3(kBlock), 0, s, f);
+        else launch(dequant_gather_pieces_kernel<OUT, N, B, M, C, false>, grid, dim3(kBlock), 0, s, f);
+        return hipGetLastError();
+    };
+    using std::integral_constant;
+    if constexpr (N == 8) {
+        auto four = [&](auto mb) {
+            return gather_past_caches(a) ? go(integral_constant<int, 4>{}, mb, std::true_type{}) : go(integral_constant<int, 4>{}, mb, std::false_type{});
+        };
+        if (a.bits == 4) return a.meta_bf16 ? four(std::true_type{}) : four(std::false_type{});
+        return go(integral_constant<int, 2>{}, std::false_type{}, std::false_type{});
+    } else {
+        return a.meta_bf16 ? go(integral_constant<int, 2>{}, std::true_type{}, std::false_type{})
+                           : go(integral_constant<int, 2>{}, std::false_type{}, std::false_type{});
+    }
+}
+
 // The prefix alone.  grid (chunks, H_k * n_layers, 2).
 __global__ void __launch_bounds__(kBlock) prefix_copy_kernel(const DequantArgs a, const int64_t head_bytes,
                                                              const int64_t prefix_bytes) {
@@ -216,6 +385,9 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
         } else if (hipError_t e = prefix_copy<OUT>(a, s)) {
             return e;
         }
+    }
+    if constexpr (N * eb == 16) {
+        if (!select && gather_by_pieces(a, eb == 2, prefix_blocks)) return launch_pieces<OUT, N>(a, prefix_blocks, s);
     }
     const dim3 grid((uint32_t)a.k_eff * a.chunks + prefix_blocks, 2 * a.n_kv_heads, a.n_layers), block(kBlock);
     auto go = [&](auto unroll, auto tokens, auto bits, auto mb) {

@@ -317,17 +317,17 @@ template <> struct elem_bytes<In_bf16> { static constexpr int value = 2; };
 template <> struct elem_bytes<In_f16> { static constexpr int value = 2; };
 
 // ---- storing consecutive float32 values, narrowed round-to-nearest-even ---
-__device__ __forceinline__ void store_items(void* p, In_bf16, const float (&x)[8]) {
+__device__ __forceinline__ u32x4 pack_items(In_bf16, const float (&x)[8]) {
     u32x4 w;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const f32x2 v = {x[2 * i], x[2 * i + 1]};
         w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // v_cvt_pk_bf16_f32
     }
-    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+    return w;
 }
 
-__device__ __forceinline__ void store_items(void* p, In_f16, const float (&x)[8]) {
+__device__ __forceinline__ u32x4 pack_items(In_f16, const float (&x)[8]) {
     f16x8 h;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -338,11 +338,14 @@ __device__ __forceinline__ void store_items(void* p, In_f16, const float (&x)[8]
         asm volatile("" : "+v"(v));
         h[i] = (_Float16)v;  // v_cvt_f16_f32, ties to even
     }
-    __builtin_nontemporal_store(h, reinterpret_cast<f16x8*>(p));
+    return __builtin_bit_cast(u32x4, h);
 }
 
-__device__ __forceinline__ void store_items(void* p, In_f32, const float (&x)[4]) {
-    __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, reinterpret_cast<f32x4*>(p));
+__device__ __forceinline__ u32x4 pack_items(In_f32, const float (&x)[4]) { return __builtin_bit_cast(u32x4, f32x4{x[0], x[1], x[2], x[3]}); }
+
+template <typename OUT, int N>
+__device__ __forceinline__ void store_items(void* p, OUT out, const float (&x)[N]) {
+    __builtin_nontemporal_store(pack_items(out, x), reinterpret_cast<u32x4*>(p));
 }
 // The lanes of a store write every other 16 bytes here, so it must be left to the caches to join the halves of a line.
 __device__ __forceinline__ void store_items(void* p, In_f32, const float (&x)[8]) {

@@ -200,6 +200,23 @@ inline bool gather_past_caches(const DequantArgs& a) {
     return read + (keys < kKeysPastCaches ? keys : 0) > (a.k_eff == a.n_groups ? 265000000 : 210000000);
 }
 
+// Whether the gather goes by aligned pieces of its output instead of by tiles (dequant_gather_pieces_kernel).  Large launches on the head_dim axis alone: the pieces are
+// written in a better order, but a wave of them has a longer way to its first load, which smaller launches do not hide.  28 layers, 600 groups and more stored, us, by tiles / by pieces, three stores
+// in turn (the same question again): 4 heads of 196 x 128 bf16, 200 MB of output 47.7 / 49.8 (38.6 / 38.7), 300 70.0 / 69.8 (58.3 / 57.7), 450 106.2 / 105.7 (89.3 / 87.9), 700 156.3 / 154.2; 50 x 128 200 49.7 / 50.4
+// (40.1 / 40.5), 450 104.5 / 102.6 (89.6 / 87.2), 700 155.2 / 151.4; 61 x 96 450 108.7 / 104.9 (93.3 / 91.8), 700 167.8 / 162.4; 37 x 256 450 105.4 / 102.7, 700 162.3 / 152.2.  2-bit codes, 196 x 128 450 104.8 / 104.8 (80.4 / 79.6),
+// 61 x 96 112.0 / 107.4 (84.6 / 83.7), but with bfloat16 pairs 50 x 128 92.7 / 98.9.  float32 output of 2-bit codes: 196 x 128 400 71.7 / 61.2 (69.6 / 61.1), 700 138 / 110 with bfloat16 pairs, 149 / 152 (130 / 109) with float32
+// ones, 1400 265 / 282 (263 / 217); of 4-bit codes 700 151 / 158.
+// The pieces take 32-bit offsets, and a wave at most two tiles.
+inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t prefix_blocks) {
+    const int64_t items = (int64_t)a.k_eff * a.tile_items, heads = 2 * (int64_t)a.n_layers * a.n_kv_heads, out = heads * items * 16;
+    if (a.qaxis == TOM_QAXIS_TOKENS || a.tile_items < 64) return false;
+    if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
+    constexpr int64_t kMost = 1LL << 31;
+    const int64_t code_tile = (int64_t)a.tile_items * (is_16_bit ? 8 : 4) * a.bits / 8;
+    return items < kMost / 16 && a.plane_tiles * code_tile < kMost && a.plane_tiles * a.tile_meta_bytes < kMost && (int64_t)a.n_layers * a.k < kMost / 4 &&
+           prefix_blocks < 1u << 23;
+}
+
 constexpr int kSelectKeys = 4;  // scores per lane where the gather selects its groups
 
 // Waves of each gather workgroup that select its group from the scores (256 scores each; one or all four), or

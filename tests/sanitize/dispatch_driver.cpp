@@ -253,6 +253,24 @@ static void gather() {
     CHECK(!past(56, 200) && past(58, 200) && !past(40, 1024) && past(48, 1024) && !past(59, 3600) && past(60, 3600));
     CHECK(!past(64, 64) && past(64, 65 + 135) && !past(72, 72) && past(80, 80) && !past(64, 1024, 7) && past(256, 1024, 7));
 
+    // 400 MB of 16-bit output; with float32 output 2-bit codes between 300 MB and 1 GB
+    auto pieces = [&](int64_t k_eff, bool is_16_bit, int bits, bool meta_bf16 = false, int tokens = 196, int capacity = 1024, int k = 0, uint32_t prefix_blocks = 0) {
+        DequantArgs q{};
+        q.n_layers = 28, q.n_kv_heads = 4, q.head_dim = 128, q.k_eff = (int32_t)k_eff, q.k = k ? k : (int32_t)k_eff, q.bits = bits, q.meta_bf16 = meta_bf16;
+        q.tile_items = (uint32_t)tokens * (is_16_bit ? 16u : 32u), q.tile_meta_bytes = (uint32_t)tokens * 2 * 8, q.plane_tiles = (int64_t)capacity * 4;
+        q.qaxis = TOM_QAXIS_HEAD_DIM;
+        const bool yes = gather_by_pieces(q, is_16_bit, prefix_blocks);
+        q.qaxis = TOM_QAXIS_TOKENS;
+        CHECK(!gather_by_pieces(q, is_16_bit, prefix_blocks));
+        return yes;
+    };
+    CHECK(!pieces(35, true, 4) && pieces(36, true, 4) && pieces(36, true, 4, true) && pieces(36, true, 2) && !pieces(36, true, 2, true));
+    CHECK(!pieces(13, false, 2) && pieces(14, false, 2) && pieces(44, false, 2, true) && !pieces(45, false, 2) && !pieces(20, false, 4));
+    CHECK(pieces(3000, true, 4, false, 4) && !pieces(3000, true, 4, false, 3));         // 64 items: a wave meets two tiles at most
+    CHECK(pieces(36, true, 4, false, 196, 42000) && !pieces(36, true, 4, false, 196, 43000));   // codes of a (layer, K|V) against 2^31 bytes
+    CHECK(!pieces(42800, true, 4) && pieces(42700, true, 4));                           // rows of a head
+    CHECK(!pieces(36, true, 4, false, 196, 1024, 1 << 25) && !pieces(36, true, 4, false, 196, 1024, 0, 1u << 23));
+
     auto joins = [&](uint64_t sys_k, uint64_t sys_v) {
         a.n_layers = 2, a.n_kv_heads = 4;
         a.sys_k = at(sys_k), a.sys_v = at(sys_v);

@@ -1,0 +1,122 @@
+"""The gather by 4 KB pieces of its output (large launches of the head_dim axis) against the gather by tiles, bit for bit.
+
+Tiles of 1 to 12 pieces that are and are not whole waves, whole pieces or aligned, prefix rows that move the rows off a
+piece's start, indices that name no stored group (their rows are left alone), repeated indices, and the one-call form that takes
+every group in order and writes the indices.  The launches by tiles are small ones of the same groups, which the oracle covers
+elsewhere; a launch above the line of the rule is large, hence the repeated groups."""
+import pytest
+import torch
+
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+LINE = {"f32": 300_000_000, "bf16": 400_000_000, "f16": 400_000_000}
+
+
+@pytest.fixture(scope="module")
+def oqm():
+    from paper_2510_18269_amd import oqm as m      # raises if the library is not built
+    assert torch.cuda.is_available()
+    return m
+
+
+def filled(oqm, L, heads, d, G, gs, T, out, bits, meta, seed):
+    code, dt = H.DT[out]
+    cfg = oqm.make_config(L, heads, heads, d, G, gs, T, bits=bits, in_dtype=code, out_dtype=code,
+                          meta_dtype=oqm.TOM_BF16 if meta == "bf16" else oqm.TOM_F32)
+    mem = oqm.Memory.allocate(cfg)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    k, v = (torch.randn((T, L, heads, G, d), generator=gen, device="cuda").to(dt) for _ in range(2))
+    oqm.tom_oqm_quantize_append(mem.handle, 0, L, T, k, v)
+    return mem, dt
+
+
+def by_tiles(oqm, mem, dt, L, heads, d, G, T):
+    """Every group once: [L][heads][T][G][d] of K and V, a few groups to a launch."""
+    parts = [[], []]
+    step = max(1, 100_000_000 // (L * heads * G * d * 2 * dt.itemsize))
+    for t in range(0, T, step):
+        n = min(step, T - t)
+        idx = torch.arange(t, t + n, dtype=torch.int32, device="cuda").repeat(L, 1)
+        out = [torch.zeros((L, heads, n * G, d), dtype=dt, device="cuda") for _ in range(2)]
+        oqm.tom_oqm_dequant_gather(mem.handle, 0, L, idx, n, n, *out)
+        for p, o in zip(parts, out):
+            p.append(o.view(L, heads, n, G, d))
+    return [torch.cat(p, 2) for p in parts]
+
+
+def raw(t):
+    return t.view(torch.int16 if t.element_size() == 2 else torch.int32)
+
+
+@pytest.mark.parametrize("G, d, gs, L, heads, prefix", (
+    (4, 128, 8, 2, 2, 0),        # 64 items: one wave's
+    (3, 176, 16, 3, 1, 0),       # 66
+    (5, 104, 8, 1, 2, 1),        # 65
+    (16, 128, 32, 2, 1, 0),      # one piece
+    (50, 128, 64, 2, 3, 14),
+    (61, 96, 32, 3, 1, 5),
+    (196, 128, 64, 2, 1, 0),
+    (37, 256, 128, 1, 2, 0),
+    (13, 8, 8, 1, 2, 0),         # 13 items: stays with the tiles
+))
+@pytest.mark.parametrize("out, bits, meta", (("bf16", 4, "f32"), ("f16", 4, "bf16"), ("bf16", 2, "f32"), ("f32", 2, "f32"), ("f32", 2, "bf16")))
+def test_pieces_against_tiles(oqm, G, d, gs, L, heads, prefix, out, bits, meta):
+    T = 7
+    mem, dt = filled(oqm, L, heads, d, G, gs, T, out, bits, meta, G * d)
+    try:
+        want = by_tiles(oqm, mem, dt, L, heads, d, G, T)
+        group = 2 * L * heads * G * d * dt.itemsize
+        k = LINE[out] // group + 3
+        gen = torch.Generator(device="cuda").manual_seed(G)
+        idx = torch.randint(-1, T + 1, (L, k), generator=gen, device="cuda", dtype=torch.int32)
+        idx[:, -1], idx[:, 0] = T - 1, 0
+        rows = prefix + k * G
+        got = [torch.full((L, heads, rows, d), -3.0, dtype=dt, device="cuda") for _ in range(2)]
+        if prefix:
+            sys = [torch.randn((L, heads, prefix, d), generator=gen, device="cuda").to(dt) for _ in range(2)]
+            oqm.tom_oqm_assemble_active(mem.handle, 0, L, idx, k, k, prefix, *sys, *got)
+            for g, s in zip(got, sys):
+                assert torch.equal(raw(g[:, :, :prefix].contiguous()), raw(s))
+        else:
+            oqm.tom_oqm_dequant_gather(mem.handle, 0, L, idx, k, k, *got)
+        stored = (idx >= 0) & (idx < T)
+        assert not bool(stored.all())
+        for g, w in zip(got, want):
+            for li in range(L):
+                body = g[li, :, prefix:].view(heads, k, G, d)
+                expect = w[li][:, idx[li].clamp(0, T - 1).long()]
+                expect[:, ~stored[li]] = -3.0
+                assert torch.equal(raw(body.contiguous()), raw(expect))
+    finally:
+        mem.close()
+
+
+@pytest.mark.parametrize("G, d, gs, prefix, out, bits, meta", ((50, 128, 64, 0, "bf16", 4, "f32"), (61, 96, 32, 7, "f16", 4, "bf16"),
+                                                              (33, 72, 8, 0, "bf16", 2, "f32"), (20, 128, 32, 3, "f32", 2, "f32")))
+def test_every_group_in_order(oqm, G, d, gs, prefix, out, bits, meta):
+    L, heads = 2, 2
+    T = LINE[out] // (2 * L * heads * G * d * (4 if out == "f32" else 2)) + 2
+    mem, dt = filled(oqm, L, heads, d, G, gs, T, out, bits, meta, G + d)
+    try:
+        want = by_tiles(oqm, mem, dt, L, heads, d, G, T)
+        k, t_q = T + 3, 2                       # rows of the three absent groups are left alone
+        gen = torch.Generator(device="cuda").manual_seed(G)
+        q = torch.randn((L, heads, t_q, d), generator=gen, device="cuda").to(dt)
+        sys = [torch.randn((L, heads, max(prefix, 1), d), generator=gen, device="cuda").to(dt) for _ in range(2)] if prefix else [None, None]
+        ws = torch.empty(oqm.tom_oqm_score_workspace_bytes(mem.handle, L, t_q, oqm.TOM_SCORE_MEAN_QUERY, False), dtype=torch.uint8, device="cuda")
+        scores = torch.zeros((L, T), dtype=torch.float32, device="cuda")
+        idx = torch.full((L, k), -5, dtype=torch.int32, device="cuda")
+        got = [torch.full((L, heads, prefix + k * G, d), -3.0, dtype=dt, device="cuda") for _ in range(2)]
+        oqm.tom_oqm_retrieve(mem.handle, 0, L, q, t_q, k, scores, T, idx, *got, ws, path=oqm.TOM_SCORE_MEAN_QUERY,
+                             prefix_rows=prefix, sys_k=sys[0], sys_v=sys[1])
+        assert torch.equal(idx[:, :T], torch.arange(T, dtype=torch.int32, device="cuda").repeat(L, 1))
+        for g, w, s in zip(got, want, sys):
+            body = g[:, :, prefix:].reshape(L, heads, k, G, d)
+            assert torch.equal(raw(body[:, :, :T].contiguous()), raw(w))
+            assert bool((body[:, :, T:] == -3.0).all())
+            if prefix:
+                assert torch.equal(raw(g[:, :, :prefix].contiguous()), raw(s))
+    finally:
+        mem.close()
