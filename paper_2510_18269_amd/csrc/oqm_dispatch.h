@@ -103,6 +103,32 @@ inline int split_tiles(const ScoreArgs& a) {
     return (tiles + passes - 1) / passes;
 }
 
+// Tiles of 16 query tokens per pass of score_token_fold_kernel (1 to 4), or 0: the fold is a launch of its own, and split_tiles decides about the contraction.
+// What a workgroup has to convert (query heads per KV head x tokens of all passes x channels, twice that in float32) against the launch that is saved.  Whole question of bf16 at 4 groups, launch of its own / inside.
+// Up to 256 (layer, 16-group) units, one workgroup a compute unit: 16 heads on 4 of 128 x 64 tokens (131 K) 24.7 / 19.5 us, 32 on 8 of 256 x 64 (524 K) 62.0 / 51.5; more than four heads, loaded in turns: 28 on 4 of 128 x 16 (57 K)
+// 13.0 / 11.9, 32 (115 K) 15.1 / 15.4, 64 21.7 / 25.4; float32 16 (115 K) 13.7 / 16.1.  257 to 512, two workgroups of at most two tiles a compute unit, three of up to two heads: 16 on 4 of 128 x 32 (66 K) 22.2 / 19.6, 64 (131 K) 34.1 / 31.2, but
+// three tiles in two passes of two 26.6 / 30.3; 8 on 4 45 tokens in one pass of three 26.5 / 23.0; 28 on 4 x 16 (57 K) 17.0 / 16.5, 24 20.3 / 24.0; 14 on 2 of 128 x 32 (57 K) 17.4 / 16.7.  Above, short questions of up to two heads on keys that are not the shortest: 4 on 4 of 128
+// x 32, 588 units 27.9 / 21.9, 1064 35.5 / 30.0, 1792 35.9 / 38.7; 2 on 2 of 96, 900 20.7 / 19.1; 2 on 1 of 64, 1064 14.4 / 15.6.  A few tokens on long keys read less folded: 1 token, 32 on 8 of 256 21.3 / 24.1, 16 on 8 of 128 (504 units) 22.3 / 23.3, 10 on 5 of 256 17.4 / 17.0.
+// Scores that share memory with the query need the separate fold, as above.
+inline int fold_tiles(const ScoreArgs& a) {
+    const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers, channels = (int64_t)a.n_kv_heads * a.head_dim;
+    const bool is_f32 = a.q_dtype == TOM_F32, few = units <= 256, most_units = units <= 512;
+    const int r = a.n_q_heads / a.n_kv_heads, heads = is_f32 ? 2 * r : r;
+    if (units > 1100 || channels > 3072) return 0;  // q-bar sums: at most 24 KB of LDS
+    if (!most_units && (heads > 2 || a.t_q > 32 || channels < 192)) return 0;
+    if (a.t_q < 8 && heads * channels > (few ? 4000 : 2000)) return 0;
+    const int most = few ? 4 : heads <= 2 && most_units ? 3 : 2;
+    const int tiles = (a.t_q + 15) / 16, passes = (tiles + most - 1) / most, of_pass = (tiles + passes - 1) / passes;
+    if (!few && passes * of_pass > tiles) return 0;
+    const bool in_turns = r > 4 || (is_f32 && r > 2 && !few);
+    if (heads * channels * 16 * of_pass * passes > (in_turns ? (few ? 100000 : 60000) : (few ? 600000 : 270000))) return 0;
+    // kept small by the line above
+    const uint64_t query_bytes = (uint64_t)a.n_layers * (uint64_t)a.n_q_heads * (uint64_t)a.t_q * (uint64_t)a.head_dim * (is_f32 ? 4u : 2u);
+    if (!apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups))) return 0;
+    if (a.token_scores && !apart(a.q, query_bytes, a.token_scores, sizeof(float) * (uint64_t)a.n_layers * (uint64_t)a.t_q * (uint64_t)a.n_groups)) return 0;
+    return of_pass;
+}
+
 // ---- head_dim-axis store: who makes the summary keys ----------------------------------------
 constexpr int kTallBlock = 1024;  // threads of a workgroup that walks a tall tile
 constexpr int64_t kLowTile = 64 << 10, kTallTile = 128 << 10, kTallTile16Bit = 96 << 10;  // bytes of the input

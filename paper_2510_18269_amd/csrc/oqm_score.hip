@@ -9,7 +9,8 @@
 //   score_fold_query_kernel  both of these in one launch, for short questions.
 //   score_token_gemm_kernel  per-token scores [T_q x H_k*d] x [H_k*d x T] on the matrix
 //                            cores (v_mfma_f64_16x16x4_f64), then the token mean; small launches
-//                            split the contraction over waves (score_token_split_kernel).
+//                            split the contraction over waves (score_token_split_kernel), and
+//                            most of these fold the query themselves (score_token_fold_kernel).
 //
 // Everything accumulates in float64 (the CDNA vector and matrix pipes run it at
 // full rate), so the float32 scores handed to top-k agree with a float64
@@ -716,6 +717,163 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
     }
 }
 
+// Fold and split contraction in one launch, for small launches (fold_tiles in oqm_dispatch.h): the query is folded where it enters the MFMA registers.  Lane (fi, kk)
+// takes token fi of a tile and channels 8 kk .. 8 kk + 7 of a block of 32, loads 16 bytes of each of the r query heads that its KV head stands for, and averages them on the vector
+// pipe; blocks go round the eight waves, pieces past the end of the query are read as zero.  Every workgroup of a layer reads its question, at 2 r bytes an element against the 8 of a
+// folded one, so the launch of the fold (4.5 us and more) is saved for nothing up to four heads; with more the conversions and the loads of a block in RH heads at a time cost more than they save.  Bound by latency:
+// load, convert, MFMA, two blocks a wave at 512 channels.  Whole question on the device at 4 groups, bf16, before / now: one layer x 64 groups x 1 head of 64 x 13 tokens 11.6 / 8.7 us,
+// 28 x 280 x 1 of 128 x 64 18.9 / 13.5, 16 x 512 x 12 heads on 3 of 96 x 30 19.1 / 14.8, 28 x 130 x 16 on 4 of 128 x 64 24.7 / 19.5, 28 x 100 x 10 on 5 of 256 x 64 43.8 / 29.6, 28 on 4 of 128, one layer x 256 x 16 13.0 / 11.9.
+// MT tiles of 16 tokens a pass: 72 to 127 registers with one or two, 148 to 223 with three or four (one workgroup a compute unit).
+struct TokenFold {
+    uint32_t inv_head_dim;
+};
+
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, uint32_t off, Raw8<In_bf16>& x) {
+    x.a = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, uint32_t off, Raw8<In_f16>& x) {
+    x.a = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, uint32_t off, Raw8<In_f32>& x) {
+    x.a = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+    x.b = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 16, 0));
+}
+
+// Dynamic LDS with the cosine: H_k*d doubles, the sums of the folded query over its tokens.
+template <typename QT, int MT, int RH>
+__global__ void __launch_bounds__(kSplitThreads) score_token_fold_kernel(const ScoreArgs a, const TokenFold f) {
+    constexpr int EB = elem_bytes<QT>::value;
+    constexpr uint32_t kOutside = 0x80000000u;  // an offset past the end of any query (fold_tiles)
+    __shared__ double red[kSplitWaves][2 * 256];  // two 16 x 16 tiles of every wave
+    __shared__ double col[2][kSplitWaves][16];
+    __shared__ double wsum[kSplitWaves];
+    extern __shared__ __align__(16) double qsum[];
+    request(a);
+    const int unit = (int)(blockIdx.x & 7u) * a.gemm_units_per_xcd + (int)(blockIdx.x >> 3);
+    if (unit >= a.gemm_units) return;  // uniform per workgroup
+    const int li = div_by(unit, a.gemm_tiles_per_layer, a.inv_gemm_tiles_per_layer);
+    const int n0 = (unit - li * a.gemm_tiles_per_layer) * 16;
+    const int d = a.head_dim, HD = a.n_kv_heads * d;
+    const int T = a.n_groups, Tq = a.t_q, r = a.n_q_heads / a.n_kv_heads;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fi = lane & 15, kk = lane >> 4;
+    const int blocks = (HD + 31) >> 5;
+    const bool norm = a.sim == TOM_SIM_COSINE;
+    // groups past T repeat the last one and are dropped at the end
+    const float* const key = a.keys + ((int64_t)(a.layer0 + li) * a.capacity_groups + min(n0 + fi, T - 1)) * HD;
+    const uint32_t row_bytes = (uint32_t)d * EB, head_bytes = (uint32_t)Tq * row_bytes, layer_bytes = (uint32_t)a.n_q_heads * head_bytes;
+    const __amdgpu_buffer_rsrc_t q = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<char*>(static_cast<const char*>(a.q)) + (uint64_t)li * layer_bytes, 0, (int)layer_bytes, 0x00020000);
+    const double inv_r = 1.0 / (double)r;
+
+    double csum = 0.0, nk2 = 0.0;
+    for (int m0 = 0; m0 < Tq; m0 += 16 * MT) {
+        f64x4 acc[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int b = wave; b < blocks; b += kSplitWaves) {
+            const int k = b * 32 + kk * 8;
+            const bool in = k < HD;
+            const int h = div_by((uint32_t)k, (uint32_t)d, f.inv_head_dim);
+            const uint32_t first = in ? (uint32_t)(h * r) * head_bytes + (uint32_t)(k - h * d) * EB : kOutside;
+            double qt[MT][8];
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) qt[m][i] = 0.0;
+            f32x4 rb[2];
+            for (int g0 = 0; g0 < r; g0 += RH) {
+                Raw8<QT> raw[MT][RH];
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int g = 0; g < RH; ++g) {
+                        const int j = m0 + m * 16 + fi;
+                        load_row(q, j < Tq && g0 + g < r ? first + (uint32_t)(g0 + g) * head_bytes + (uint32_t)j * row_bytes : kOutside, raw[m][g]);
+                    }
+                if (g0 == 0) {
+                    const float* p = key + min(k, HD - 8);
+                    rb[0] = *reinterpret_cast<const f32x4*>(p);
+                    rb[1] = *reinterpret_cast<const f32x4*>(p + 4);
+                }
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int g = 0; g < RH; ++g) {
+                        float x[8];
+                        widen(raw[m][g], x);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) qt[m][i] += (double)x[i];
+                    }
+            }
+            if (!in) rb[0] = rb[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double bv = (double)rb[i >> 2][i & 3];
+                if (m0 == 0) nk2 = fma(bv, bv, nk2);
+                double s = 0.0;
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    qt[m][i] *= inv_r;
+                    s += qt[m][i];
+                    acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(qt[m][i], bv, acc[m], 0, 0, 0);
+                }
+                if (norm) {  // uniform; a block's channels are this wave's alone
+                    s = row16_sum_f64(s);
+                    if (fi == 0 && in) qsum[k + i] = m0 == 0 ? s : qsum[k + i] + s;
+                }
+            }
+        }
+        // add up the waves, two tiles at a time: thread (u, e) owns element e = v * 64 + lane of tile m + u
+#pragma unroll
+        for (int m = 0; m < MT; m += 2) {
+            if (m0 + m > 0) __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (m + u < MT) red[wave][u * 256 + v * 64 + lane] = acc[m + u < MT ? m + u : 0][v];
+            __syncthreads();
+            const int j = m0 + (m + (tid >> 8)) * 16 + mfma_d_row(lane, (tid >> 6) & 3);
+            if (m + (tid >> 8) < MT && j < Tq) {
+                double sum = 0.0;
+#pragma unroll
+                for (int w = 0; w < kSplitWaves; ++w) sum += red[w][tid];
+                csum += sum;
+                if (a.token_scores && n0 + fi < T) a.token_scores[((int64_t)li * Tq + j) * T + n0 + fi] = (float)sum;
+            }
+        }
+    }
+    if (norm) {  // the sums of all waves were put in front of the last barrier
+        double sq = 0.0;
+        const double share = 1.0 / (double)Tq;
+        for (int e = tid; e < HD; e += kSplitThreads) {
+            const double qb = qsum[e] * share;
+            sq = fma(qb, qb, sq);
+        }
+        put_wave_sum(sq, wsum);
+    }
+    // lanes fi, 16 + fi, 32 + fi, 48 + fi hold parts of group n0 + fi
+    csum = rows16_sum_f64(csum);
+    nk2 = rows16_sum_f64(nk2);
+    if (kk == 0) {
+        col[0][wave][fi] = csum;
+        col[1][wave][fi] = nk2;
+    }
+    __syncthreads();
+    if (tid < 16 && n0 + tid < T) {
+        double s = 0.0, n2 = 0.0;
+#pragma unroll
+        for (int w = 0; w < kSplitWaves; ++w) {
+            s += col[0][w][tid];
+            n2 += col[1][w][tid];
+        }
+        s = s / (double)Tq;
+        if (norm) s = s / (fmax(sqrt(total_of<kSplitWaves>(wsum)), 1e-12) * fmax(sqrt(n2), 1e-12));
+        a.scores[(int64_t)li * a.score_stride + n0 + tid] = (float)s;
+    }
+}
+
 }  // namespace
 
 static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStream_t s) {
@@ -812,9 +970,11 @@ hipError_t launch_score_mean_query(const ScoreArgs& a, hipStream_t s) {
 
 hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     if (args.n_layers == 0 || args.n_groups == 0) return hipSuccess;
-    if (hipError_t e = launch_query_fold(args, true, s)) return e;
     ScoreArgs a = args;
-    const int tiles = split_tiles(a);
+    const int folded = fold_tiles(a);
+    if (!folded)
+        if (hipError_t e = launch_query_fold(args, true, s)) return e;
+    const int tiles = folded ? folded : split_tiles(a);
     const int width = tiles > 0 ? 16 : kGemmN;
     a.gemm_tiles_per_layer = (a.n_groups + width - 1) / width;
     a.inv_gemm_tiles_per_layer = reciprocal_u32((uint32_t)a.gemm_tiles_per_layer);
@@ -823,6 +983,32 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     a.gemm_units = (int32_t)units;
     a.gemm_units_per_xcd = (int32_t)((units + 7) / 8);
     const dim3 grid(8u * (unsigned)a.gemm_units_per_xcd);
+    if (folded) {
+        const TokenFold f{reciprocal_u32((uint32_t)a.head_dim)};
+        const size_t lds = a.sim == TOM_SIM_COSINE ? (size_t)a.n_kv_heads * a.head_dim * sizeof(double) : 0;
+        const int r = a.n_q_heads / a.n_kv_heads;
+        auto go = [&](auto qt, auto mt, auto rh) {
+            launch(score_token_fold_kernel<decltype(qt), decltype(mt)::value, decltype(rh)::value>, grid, dim3(kSplitThreads), lds, s, a, f);
+            return hipGetLastError();
+        };
+        auto heads = [&](auto qt, auto mt) {
+            if (r == 1) return go(qt, mt, std::integral_constant<int, 1>{});
+            if constexpr (elem_bytes<decltype(qt)>::value == 2) {
+                if (r > 2) return go(qt, mt, std::integral_constant<int, 4>{});
+            }
+            return go(qt, mt, std::integral_constant<int, 2>{});
+        };
+        auto type = [&](auto mt) {
+            if (a.q_dtype == TOM_F32) return heads(In_f32{}, mt);
+            return a.q_dtype == TOM_BF16 ? heads(In_bf16{}, mt) : heads(In_f16{}, mt);
+        };
+        switch (folded) {
+            case 1: return type(std::integral_constant<int, 1>{});
+            case 2: return type(std::integral_constant<int, 2>{});
+            case 3: return type(std::integral_constant<int, 3>{});
+            default: return type(std::integral_constant<int, 4>{});
+        }
+    }
     switch (tiles) {
         case 0:
             if (a.t_q <= 16) launch(score_token_gemm_kernel<1>, grid, dim3(kBlock), 0, s, a);

@@ -174,6 +174,35 @@ static void split() {
     CHECK(tiles(512, 16, 1) == 1 && tiles(513, 16, 1) == 0);
     CHECK(tiles(4, 1024, 64) == 4 && tiles(4, 1024, 65) == 3 && tiles(4, 1024, 1 << 20) == 4);
     CHECK(tiles(65535, 0x7fffffff, 1) == 0);                     // far beyond, no overflow
+
+    // the fold inside: layers, groups, query tokens, KV heads, query heads of each, head_dim -> tiles of a pass, or 0
+    auto fold = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d, int type = TOM_BF16) {
+        ScoreArgs b{};
+        b.n_layers = n_layers, b.n_groups = n_groups, b.t_q = t_q, b.n_kv_heads = heads, b.n_q_heads = heads * r, b.head_dim = d, b.q_dtype = type;
+        b.score_stride = n_groups;
+        const uint64_t bytes = (uint64_t)n_layers * heads * r * t_q * d * (type == TOM_F32 ? 4 : 2);
+        const uint64_t out = 1ull << 40;
+        b.q = at(out - bytes), b.scores = reinterpret_cast<float*>(at(out)), b.token_scores = reinterpret_cast<float*>(at(1ull << 44));
+        const int n = fold_tiles(b);
+        b.q = at(out - bytes + 4);
+        CHECK(fold_tiles(b) == 0);                               // the scores share memory with the query
+        b.q = at((1ull << 44) - bytes);
+        CHECK(fold_tiles(b) == n);
+        b.q = at((1ull << 44) - bytes + 4);
+        CHECK(fold_tiles(b) == 0);
+        b.token_scores = nullptr;
+        CHECK(fold_tiles(b) == n);
+        return n;
+    };
+    CHECK(fold(1, 256, 16, 4, 7, 128) == 1 && fold(1, 256, 17, 4, 7, 128) == 0 && fold(28, 130, 64, 4, 4, 128) == 4 && fold(28, 100, 65, 5, 2, 256) == 3);
+    CHECK(fold(28, 60, 64, 8, 4, 256) == 4 && fold(28, 60, 65, 8, 4, 256) == 0);                      // 524 K and 655 K conversions
+    CHECK(fold(28, 256, 32, 4, 4, 128) == 2 && fold(28, 256, 33, 4, 4, 128) == 0 && fold(28, 256, 64, 4, 4, 128) == 2 && fold(28, 256, 45, 4, 2, 128) == 3);
+    CHECK(fold(28, 256, 16, 4, 7, 128) == 1 && fold(28, 256, 17, 4, 7, 128) == 0);                    // 57 K and 115 K
+    CHECK(fold(28, 100, 7, 8, 4, 256) == 0 && fold(28, 60, 8, 8, 4, 256) == 1 && fold(28, 130, 1, 4, 4, 128) == 1);
+    CHECK(fold(28, 300, 32, 4, 2, 128) == 2 && fold(28, 300, 33, 4, 2, 128) == 0 && fold(28, 300, 32, 4, 3, 128) == 0 && fold(28, 300, 32, 1, 1, 128) == 0);
+    CHECK(fold(1, 1100 * 16, 16, 4, 1, 128) == 1 && fold(1, 1100 * 16 + 1, 16, 4, 1, 128) == 0);
+    CHECK(fold(1, 500, 16, 4, 7, 128, TOM_F32) == 0 && fold(28, 130, 64, 4, 4, 128, TOM_F32) == 4 && fold(28, 256, 32, 4, 1, 128, TOM_F32) == 2);
+    CHECK(fold(1, 16, 8, 48, 1, 64) == 1 && fold(1, 16, 8, 49, 1, 64) == 0 && fold(65535, 1 << 26, 1 << 20, 1, 1, 8) == 0);
 }
 
 static void rows() {
