@@ -155,9 +155,6 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
 // 28 layers x 4 heads x 196 x 128 x 64 groups (944 MB), codes and pairs of random bits, one store, us: chunks 158, one piece 185, two 156.2, three 157, four 158.6; an arithmetic-free
 // kernel of the same order with nothing but this shape's constants 153.4 (two adjacent pieces 157; runs of 16 workgroups per XCD 155; 512 threads 156, 1024 172; index loads per lane 174).
 // 128 groups (quant-groups of 32, 2.0 GB) 337 -> 325; 37 x 256, 700 MB of output 162 -> 152; 61 x 96 168 -> 162.
-constexpr int kPieces = 2;
-constexpr uint32_t kXcds = 8;
-
 // What the kernel needs of a DequantArgs, made on the host.
 struct PieceArgs {
     const char *codes, *meta;  // of the first layer asked for
@@ -216,6 +213,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_pieces_kernel(const Pie
     // first item of the wave, of the first piece; below zero in front of the rows
     const uint32_t first = ((blockIdx.x & ~(kXcds - 1u)) * kPieces + (blockIdx.x & (kXcds - 1u))) * kBlock +
                            ((uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63u) - lead;
+    if ((int)first >= (int)(a.k_eff * ti)) return;  // uniform in a wave: the last workgroups of a head
     typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;  // not written by this launch where it is read
     typedef const __attribute__((address_space(4))) char* scalar_bytes;
     const scalar_bytes idx = (scalar_bytes)(uintptr_t)a.idx;
@@ -291,8 +289,7 @@ hipError_t launch_pieces(const DequantArgs& a, uint32_t prefix_blocks, hipStream
     f.sys_k = a.sys_k;
     f.sys_v = a.sys_v;
     f.prefix_bytes = (uint64_t)a.prefix_bytes;
-    const uint32_t pieces = (uint32_t)a.k_eff * a.tile_items / kBlock + 2;  // the first and the last one may be parts
-    f.blocks = (pieces + kXcds * kPieces - 1) / (kXcds * kPieces) * kXcds;
+    f.blocks = (uint32_t)piece_blocks(a);
     const dim3 grid(f.blocks + (prefix_blocks + kXcds - 1) / kXcds * kXcds, 2 * f.heads, a.n_layers);
     auto go = [&](auto bits, auto mb, auto past) {
         constexpr int B = decltype(bits)::value;

@@ -226,17 +226,35 @@ inline bool gather_past_caches(const DequantArgs& a) {
     return read + (keys < kKeysPastCaches ? keys : 0) > (a.k_eff == a.n_groups ? 265000000 : 210000000);
 }
 
+// Pieces of 4 KB that a workgroup of dequant_gather_pieces_kernel takes, one behind the pieces of the other XCDs' workgroups.
+constexpr int kPieces = 2;
+constexpr uint32_t kXcds = 8;
+
+// Pieces of the rows of a head: where not all heads' rows start at the start of a piece, the first one may be a part.
+inline int64_t pieces_of_head(const DequantArgs& a) {
+    constexpr uint64_t kPieceBytes = kBlock * 16;
+    const uint64_t prefix = (uint64_t)a.prefix_bytes;
+    const uint64_t starts = (reinterpret_cast<uintptr_t>(a.k_out) + prefix) | (reinterpret_cast<uintptr_t>(a.v_out) + prefix) | (uint64_t)a.head_out_bytes;
+    const int64_t part = starts % kPieceBytes ? kBlock - 1 : 0;
+    return ((int64_t)a.k_eff * a.tile_items + part + kBlock - 1) / kBlock;
+}
+// ... and its workgroups: whole rounds of the XCDs.
+inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + kXcds * kPieces - 1) / (kXcds * kPieces) * kXcds; }
+
 // Whether the gather goes by aligned pieces of its output instead of by tiles (dequant_gather_pieces_kernel).  Large launches on the head_dim axis alone: the pieces are
 // written in a better order, but a wave of them has a longer way to its first load, which smaller launches do not hide.  28 layers, 600 groups and more stored, us, by tiles / by pieces, three stores
 // in turn (the same question again): 4 heads of 196 x 128 bf16, 200 MB of output 47.7 / 49.8 (38.6 / 38.7), 300 70.0 / 69.8 (58.3 / 57.7), 450 106.2 / 105.7 (89.3 / 87.9), 700 156.3 / 154.2; 50 x 128 200 49.7 / 50.4
 // (40.1 / 40.5), 450 104.5 / 102.6 (89.6 / 87.2), 700 155.2 / 151.4; 61 x 96 450 108.7 / 104.9 (93.3 / 91.8), 700 167.8 / 162.4; 37 x 256 450 105.4 / 102.7, 700 162.3 / 152.2.  2-bit codes, 196 x 128 450 104.8 / 104.8 (80.4 / 79.6),
 // 61 x 96 112.0 / 107.4 (84.6 / 83.7), but with bfloat16 pairs 50 x 128 92.7 / 98.9.  float32 output of 2-bit codes: 196 x 128 400 71.7 / 61.2 (69.6 / 61.1), 700 138 / 110 with bfloat16 pairs, 149 / 152 (130 / 109) with float32
 // ones, 1400 265 / 282 (263 / 217); of 4-bit codes 700 151 / 158.
-// The pieces take 32-bit offsets, and a wave at most two tiles.
+// Not where the last round of a head's workgroups leaves more than a 64th of all idle: 8 heads, 50 tokens, 97 groups (304 pieces in 20 rounds of 16) 123.2 / 127.9, 92 groups (288 in 18) 117.3 / 114.8; 7 heads of 196, 28
+// groups (344 in 22) 119.9 / 122.0.  The pieces take 32-bit offsets, and a wave at most two tiles.
 inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t prefix_blocks) {
     const int64_t items = (int64_t)a.k_eff * a.tile_items, heads = 2 * (int64_t)a.n_layers * a.n_kv_heads, out = heads * items * 16;
     if (a.qaxis == TOM_QAXIS_TOKENS || a.tile_items < 64) return false;
     if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
+    const int64_t pieces = pieces_of_head(a);
+    if ((kPieces * piece_blocks(a) - pieces) * 64 > pieces) return false;
     constexpr int64_t kMost = 1LL << 31;
     const int64_t code_tile = (int64_t)a.tile_items * (is_16_bit ? 8 : 4) * a.bits / 8;
     return items < kMost / 16 && a.plane_tiles * code_tile < kMost && a.plane_tiles * a.tile_meta_bytes < kMost && (int64_t)a.n_layers * a.k < kMost / 4 &&

@@ -282,10 +282,10 @@ static void gather() {
     CHECK(!past(56, 200) && past(58, 200) && !past(40, 1024) && past(48, 1024) && !past(59, 3600) && past(60, 3600));
     CHECK(!past(64, 64) && past(64, 65 + 135) && !past(72, 72) && past(80, 80) && !past(64, 1024, 7) && past(256, 1024, 7));
 
-    // 400 MB of 16-bit output; with float32 output 2-bit codes between 300 MB and 1 GB
-    auto pieces = [&](int64_t k_eff, bool is_16_bit, int bits, bool meta_bf16 = false, int tokens = 196, int capacity = 1024, int k = 0, uint32_t prefix_blocks = 0) {
+    // 400 MB of 16-bit output; with float32 output 2-bit codes between 300 MB and 1 GB.  39 groups of 196 x 128: 478 pieces, two short of 30 rounds
+    auto pieces = [&](int64_t k_eff, bool is_16_bit, int bits, bool meta_bf16 = false, int n_layers = 28, int tokens = 196, int capacity = 1024, int k = 0, uint32_t prefix_blocks = 0) {
         DequantArgs q{};
-        q.n_layers = 28, q.n_kv_heads = 4, q.head_dim = 128, q.k_eff = (int32_t)k_eff, q.k = k ? k : (int32_t)k_eff, q.bits = bits, q.meta_bf16 = meta_bf16;
+        q.n_layers = n_layers, q.n_kv_heads = 4, q.head_dim = 128, q.k_eff = (int32_t)k_eff, q.k = k ? k : (int32_t)k_eff, q.bits = bits, q.meta_bf16 = meta_bf16;
         q.tile_items = (uint32_t)tokens * (is_16_bit ? 16u : 32u), q.tile_meta_bytes = (uint32_t)tokens * 2 * 8, q.plane_tiles = (int64_t)capacity * 4;
         q.qaxis = TOM_QAXIS_HEAD_DIM;
         const bool yes = gather_by_pieces(q, is_16_bit, prefix_blocks);
@@ -293,12 +293,25 @@ static void gather() {
         CHECK(!gather_by_pieces(q, is_16_bit, prefix_blocks));
         return yes;
     };
-    CHECK(!pieces(35, true, 4) && pieces(36, true, 4) && pieces(36, true, 4, true) && pieces(36, true, 2) && !pieces(36, true, 2, true));
-    CHECK(!pieces(13, false, 2) && pieces(14, false, 2) && pieces(44, false, 2, true) && !pieces(45, false, 2) && !pieces(20, false, 4));
-    CHECK(pieces(3000, true, 4, false, 4) && !pieces(3000, true, 4, false, 3));         // 64 items: a wave meets two tiles at most
-    CHECK(pieces(36, true, 4, false, 196, 42000) && !pieces(36, true, 4, false, 196, 43000));   // codes of a (layer, K|V) against 2^31 bytes
-    CHECK(!pieces(42800, true, 4) && pieces(42700, true, 4));                           // rows of a head
-    CHECK(!pieces(36, true, 4, false, 196, 1024, 1 << 25) && !pieces(36, true, 4, false, 196, 1024, 0, 1u << 23));
+    CHECK(!pieces(39, true, 4, false, 25) && pieces(39, true, 4, false, 26) && pieces(39, true, 4, true) && pieces(39, true, 2) && !pieces(39, true, 2, true));
+    CHECK(!pieces(37, true, 4) && !pieces(38, true, 4) && pieces(40, true, 4) && !pieces(41, true, 4));   // 454, 466, 490 and 503 pieces in 29 to 32 rounds
+    CHECK(!pieces(39, false, 2, false, 9) && pieces(39, false, 2, true, 10) && pieces(39, false, 2, false, 31) && !pieces(39, false, 2, false, 32) && !pieces(39, false, 4, false, 20));
+    CHECK(pieces(3000, true, 4, false, 28, 4) && !pieces(3000, true, 4, false, 28, 3));        // 64 items: a wave meets two tiles at most
+    CHECK(pieces(39, true, 4, false, 28, 196, 42000) && !pieces(39, true, 4, false, 28, 196, 43000));   // codes of a (layer, K|V) against 2^31 bytes
+    CHECK(!pieces(42800, true, 4) && pieces(42700, true, 4));                                  // rows of a head
+    CHECK(!pieces(39, true, 4, false, 28, 196, 1024, 1 << 25) && !pieces(39, true, 4, false, 28, 196, 1024, 0, 1u << 23));
+    // the first piece is a part where the rows of some head do not start on a piece
+    DequantArgs starts{};
+    starts.k_eff = 64, starts.tile_items = 196 * 16, starts.head_out_bytes = 64 * 196 * 256;
+    CHECK(pieces_of_head(starts) == 784 && piece_blocks(starts) == 392);
+    starts.k_out = at(1 << 24), starts.v_out = at((1 << 25) + 16);
+    CHECK(pieces_of_head(starts) == 785 && piece_blocks(starts) == 400);
+    starts.prefix_bytes = 4080;
+    CHECK(pieces_of_head(starts) == 785);
+    starts.k_out = at((1 << 24) + 16);
+    CHECK(pieces_of_head(starts) == 784);
+    starts.head_out_bytes += 16;
+    CHECK(pieces_of_head(starts) == 785);
 
     auto joins = [&](uint64_t sys_k, uint64_t sys_v) {
         a.n_layers = 2, a.n_kv_heads = 4;
