@@ -128,7 +128,9 @@ __device__ __forceinline__ void join_rows_of_wave(double (&acc)[8], int lpr, int
 // channels.  The r * T_q rows of a KV head are contiguous in Q: the mean alone is one sum over them.  TOKENS: every token's mean
 // over the r heads is wanted too, so a slot takes whole tokens.  Bound by latency and by what the few compute units that take part can
 // load, hence parts of 64 channels in small launches (fold_parts in oqm_dispatch.h).  28 layers x 28 heads of 128 in a graph of the whole question, 256 threads per head / 512 / 512
-// per part: 32 tokens 5.4 / 4.5 / 4.4 us, 64 7.5 / 5.7 / 5.0, 64 with every token kept 10.2 / 9.4 / 7.0.
+// per part: 32 tokens 5.4 / 4.5 / 4.4 us, 64 7.5 / 5.7 / 5.0, 64 with every token kept 10.2 / 9.4 / 7.0.  Rows that no slot of the workgroup has are not converted (8 rows
+// a trip, 0.1 us each): mean query of one token over 28 x 1024 groups 21.2 -> 19.6 us, fused with the scores of one layer x 256 groups 8.9 -> 8.3, 16 rows 12.1 -> 11.9.  (Not worth its branches in
+// score_token_fold_kernel, where the heads of a turn are few.)
 template <typename QT, bool TOKENS>
 __global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArgs a, const int parts) {
     constexpr int EB = elem_bytes<QT>::value;
@@ -166,6 +168,7 @@ __global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArg
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
+                if (base + u * jn >= rows) break;  // uniform: nothing but zeros from here on
                 float x[8];
                 widen(raw[u], x);
 #pragma unroll
@@ -188,8 +191,9 @@ __global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArg
                 }
 #pragma unroll
                 for (int g = 0; g < kRows; ++g) {
+                    if (g0 + g >= r) break;  // uniform
                     float x[8];
-                    widen(raw[g], x);  // heads past the block were zero-filled
+                    widen(raw[g], x);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) qt[i] += (double)x[i];
                 }
@@ -366,16 +370,17 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
         double acc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = 0.0;
-        for (int r0 = part; r0 < rows; r0 += kRows * f.slots) {
+        for (int r0 = 0; r0 < rows; r0 += kRows * (int)f.slots) {  // uniform
             Raw8<QT> raw[kRows];
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
                 zero_raw(raw[u]);
-                const int row = r0 + u * f.slots;
+                const int row = r0 + u * (int)f.slots + part;
                 if (row < rows) load_raw(q + (int64_t)row * d * EB, raw[u]);
             }
 #pragma unroll
             for (int u = 0; u < kRows; ++u) {
+                if (r0 + u * (int)f.slots >= rows) break;  // uniform: nothing but zeros from here on
                 float x[8];
                 widen(raw[u], x);
 #pragma unroll
