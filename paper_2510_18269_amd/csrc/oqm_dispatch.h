@@ -196,6 +196,22 @@ inline int row_waves(int lpr, int group_tokens, bool is_16_bit) {
     return is_16_bit && lpr < 32 && few <= 4 ? 4 : 0;
 }
 
+// The general form: rows that a lane holds between its two sweeps over a tile, at most.
+constexpr int kMostHeld = 8, kMostHeld16Bit = 13;
+
+// Rows per lane where `threads` of a workgroup share a tile.
+inline int held_rows(int lpr, int group_tokens, int threads) { return (group_tokens + threads / lpr - 1) / (threads / lpr); }
+
+// Threads of the general form where 256 cannot hold the tile, or 0: it is read twice.  As few as hold it: 512 leave two workgroups a compute unit,
+// so that one loads while the other packs; 1024 one.  28 layers x 4 heads, us per call, twice / 512 / 1024 / waves that hold the tile (8 of them): bf16 196 x 256, 6 frames (215 MB) 54.3 / 44.2 / 49.5 / 49.5, one 15.2 / 10.8 /
+// 10.3 / 12.2; 110 x 256, 16 77.6 / 61.8 / 71.3 / 70.2; 250 x 128, 16 87.2 / 67.6 / 80.8 / 69.1; float32 196 x 128, 16 114 / 87.5 / 104 / 82.7, two 15.7 / 11.5 / 14.3 / 11.9; 240 x 80 85.5 / 70.4 / 94.7; 196 x 96, one
+// 8.2 / 7.9 / 8.3; 196 x 256, 8 131 / - / 94.0 / 150; bf16 256 x 256 73.5 / - / 60.9 / 86.
+inline int tall_threads(int lpr, int group_tokens, bool is_16_bit) {
+    for (int threads : {512, 1024})
+        if (held_rows(lpr, group_tokens, threads) <= (is_16_bit ? kMostHeld16Bit : kMostHeld)) return threads;
+    return 0;
+}
+
 // ---- gather: the prefix rows, and the selection ---------------------------------------------
 // All ask about a launch whose sizes (from chunks to head_out_bytes) are filled in.
 

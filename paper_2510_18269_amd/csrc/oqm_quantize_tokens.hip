@@ -11,8 +11,9 @@
 // 8 running minima and maxima over its rows, the 256/(d/8) row slots of the workgroup are
 // combined through LDS, one thread per channel derives scale, reciprocal and zero point,
 // and a second sweep quantizes and packs.  When a lane's share of the tile fits a few
-// registers (HOLD rows: up to 13 x 16 B) the rows stay in registers between the sweeps;
-// otherwise the second sweep reads the tile again (from the caches: it was read a moment ago).
+// registers (HOLD rows: up to 13 x 16 B) the rows stay in registers between the sweeps: 256 threads where those hold the tile, otherwise
+// 512 or 1024 (tall_threads in oqm_dispatch.h); of still taller tiles
+// the second sweep reads the tile again (from the caches: it was read a moment ago), row by row behind one wait each.
 // HBM traffic per element: 2 B read + 0.5 B written + 8/G B of
 // (scale, zero) pairs.  The order of the grid, us before / after at 28 layers x 4 heads x 50 x 96 bf16: 8 frames 8.6 / 7.6, 32
 // 24.8 / 21.0.  Keys from another tensor, second pass / workgroups of their own: 100 x 80, 1 frame 6.1 / 4.1, 8 12.9 / 11.3; in the row
@@ -41,8 +42,8 @@ __device__ __forceinline__ Role role_of(const AppendArgs& a, uint32_t& id) {
     return (Role)role;
 }
 
-template <typename IN, bool SEP, int HOLD, int BITS, bool MB>
-__global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const AppendArgs a) {
+template <typename IN, bool SEP, int HOLD, int BITS, bool MB, int NT>
+__global__ void __launch_bounds__(NT) quantize_append_tokens_kernel(const AppendArgs a) {
     constexpr int EB = elem_bytes<IN>::value;
     constexpr uint32_t CW = BITS;  // bytes of packed codes per lane and row (8 channels)
     typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
@@ -64,7 +65,7 @@ __global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const Ap
     const uint32_t in_lane = (uint32_t)row0 * in_row_bytes + (uint32_t)slot * 8u * EB;
     const uint32_t code_lane = ((uint32_t)row0 * lpr + slot) * CW;
 
-    __shared__ double shared_buf[kBlock * 8];        // 16 KB: (min, max) per row slot, then key sums
+    __shared__ double shared_buf[NT * 8];            // (min, max) per row slot, then key sums
     extern __shared__ f32x2 fin[];                    // [d] (zero point, 1/scale) per channel
     f32x2* mm = reinterpret_cast<f32x2*>(shared_buf);
 
@@ -84,7 +85,7 @@ __global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const Ap
         }
         __syncthreads();
         float* key = t.key(a);
-        for (int q = tid; q < d; q += kBlock) {
+        for (int q = tid; q < d; q += NT) {
             double sum = 0.0;
             for (int r = 0; r < rpp; ++r) sum += shared_buf[r * d + q];
             key[(q % lpr) * 8 + q / lpr] = (float)(sum / (double)G);
@@ -155,7 +156,7 @@ __global__ void __launch_bounds__(kBlock) quantize_append_tokens_kernel(const Ap
     // ---- one thread per channel: Eq. 9 over the whole token axis.  The LDS arrays are indexed
     // by position q = i * lpr + slot (channel slot * 8 + i), so that the lanes of a wave touch
     // consecutive words instead of words 64 bytes apart (16-way bank conflicts otherwise).
-    for (int q = tid; q < d; q += kBlock) {
+    for (int q = tid; q < d; q += NT) {
         float cmn = mm[q][0], cmx = mm[q][1];
         for (int r = 1; r < rpp; ++r) {
             cmn = fminf(cmn, mm[r * d + q][0]);
@@ -390,16 +391,16 @@ hipError_t launch_rows(const QuantArgs& a, int waves, int rows, hipStream_t s) {
     return launch_rows_h<IN, LPR, kMostRows>(a, waves, s);
 }
 
-template <typename IN, int HOLD>
+template <typename IN, int HOLD, int NT = kBlock>
 hipError_t launch_h(const QuantArgs& q, hipStream_t s) {
     AppendArgs a = append_args(q, elem_bytes<IN>::value, (uint32_t)q.head_dim);
-    a.rows_per_pass = (int32_t)(kBlock / a.lanes_per_row);
+    a.rows_per_pass = (int32_t)(NT / a.lanes_per_row);
     const size_t lds = (size_t)q.head_dim * sizeof(f32x2);
     auto go = [&](auto bits, auto mb, auto sep) {
         constexpr int B = decltype(bits)::value;
         constexpr bool M = decltype(mb)::value, S = decltype(sep)::value;
-        return launch_blocks(a, (S ? 3 : 2) * set_items(a, q), kBlock, [&](dim3 grid, dim3 block) {
-            launch(quantize_append_tokens_kernel<IN, S, HOLD, B, M>, grid, block, lds, s, a);
+        return launch_blocks(a, (S ? 3 : 2) * set_items(a, q), NT, [&](dim3 grid, dim3 block) {
+            launch(quantize_append_tokens_kernel<IN, S, HOLD, B, M, NT>, grid, block, lds, s, a);
         });
     };
     return with_options(q, go);
@@ -415,12 +416,15 @@ hipError_t launch_t(const QuantArgs& a, hipStream_t s) {
         if (lpr == 16) return launch_rows<IN, 16>(a, waves, rows, s);
         return launch_rows<IN, 32>(a, waves, rows, s);
     }
-    const int rpp = kBlock / lpr;
-    const int trips = (a.group_tokens + rpp - 1) / rpp;  // rows per lane
+    constexpr bool is_16_bit = sizeof(Raw8<IN>) <= 16;
+    constexpr int kMost = is_16_bit ? kMostHeld16Bit : kMostHeld;
+    const int trips = held_rows(lpr, a.group_tokens, kBlock);  // rows per lane
     if (trips <= 4) return launch_h<IN, 4>(a, s);
     if (trips <= 8) return launch_h<IN, 8>(a, s);
-    if constexpr (sizeof(Raw8<IN>) <= 16) {  // 13 float32 rows would not fit the register budget
-        if (trips <= 13) return launch_h<IN, 13>(a, s);
+    if (trips <= kMost) return launch_h<IN, kMost>(a, s);
+    switch (tall_threads(lpr, a.group_tokens, is_16_bit)) {
+        case 512: return launch_h<IN, kMost, 512>(a, s);
+        case 1024: return held_rows(lpr, a.group_tokens, 1024) <= 8 ? launch_h<IN, 8, 1024>(a, s) : launch_h<IN, kMost, 1024>(a, s);
     }
     return launch_h<IN, 0>(a, s);
 }

@@ -233,6 +233,18 @@ static void rows() {
             }
 }
 
+static void tall() {
+    // 512 threads hold 13 rows a lane at 16 bits, eight of float32, then 1024; a taller tile is read twice
+    for (int lpr : {10, 12, 16, 32, 64, 256})
+        for (bool narrow : {false, true}) {
+            const int most = narrow ? kMostHeld16Bit : kMostHeld;
+            CHECK(tall_threads(lpr, most * (512 / lpr), narrow) == 512 && tall_threads(lpr, most * (512 / lpr) + 1, narrow) == 1024);
+            CHECK(tall_threads(lpr, most * (1024 / lpr), narrow) == 1024 && tall_threads(lpr, most * (1024 / lpr) + 1, narrow) == 0);
+            for (int tokens = 1; tokens < 2000; ++tokens)
+                if (const int threads = tall_threads(lpr, tokens, narrow)) CHECK(held_rows(lpr, tokens, threads) * (threads / lpr) >= tokens);
+        }
+}
+
 static void gather() {
     DequantArgs a{};
     a.n_kv_heads = 4, a.head_dim = 64, a.n_layers = 2, a.k = 10, a.k_eff = 10, a.n_groups = 200, a.chunks = 1;
@@ -337,6 +349,7 @@ int main() {
     append();
     split();
     rows();
+    tall();
     gather();
     if (failures) { std::fprintf(stderr, "%d failures\n", failures); return 2; }
     std::printf("dispatch driver: clean\n");
