@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
 }
 
 // ------------------------------------------------------------------ the gather by pieces of its output
-// Large launches of the head_dim axis (gather_by_pieces in oqm_dispatch.h).  What bounds them is the order in which memory is written: plain
+// Large launches of the head_dim axis, and those of the smallest tiles (gather_by_pieces in oqm_dispatch.h).  What bounds them is the order in which memory is written: plain
 // 16-byte stores of 755 MB take 112 us where every workgroup writes the next 4 KB, 124 where it writes 16 KB, 153 with 64 KB and 180 from
 // a persistent grid.  Tiles and their chunks are not multiples of 4 KB, so here the rows of a head are cut into aligned pieces of 4 KB whatever tile they belong to, and
 // a workgroup takes kPieces of them, eight pieces apart: workgroups go round-robin over the eight XCDs, so that the ones in flight write one dense window of which each
@@ -304,11 +304,9 @@ hipError_t launch_pieces(const DequantArgs& a, uint32_t prefix_blocks, hipStream
             return gather_past_caches(a) ? go(integral_constant<int, 4>{}, mb, std::true_type{}) : go(integral_constant<int, 4>{}, mb, std::false_type{});
         };
         if (a.bits == 4) return a.meta_bf16 ? four(std::true_type{}) : four(std::false_type{});
-        return go(integral_constant<int, 2>{}, std::false_type{}, std::false_type{});
-    } else {
-        return a.meta_bf16 ? go(integral_constant<int, 2>{}, std::true_type{}, std::false_type{})
-                           : go(integral_constant<int, 2>{}, std::false_type{}, std::false_type{});
     }
+    return a.meta_bf16 ? go(integral_constant<int, 2>{}, std::true_type{}, std::false_type{})
+                       : go(integral_constant<int, 2>{}, std::false_type{}, std::false_type{});
 }
 
 // The prefix alone.  grid (chunks, H_k * n_layers, 2).

@@ -263,14 +263,20 @@ inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + 
 // (40.1 / 40.5), 450 104.5 / 102.6 (89.6 / 87.2), 700 155.2 / 151.4; 61 x 96 450 108.7 / 104.9 (93.3 / 91.8), 700 167.8 / 162.4; 37 x 256 450 105.4 / 102.7, 700 162.3 / 152.2.  2-bit codes, 196 x 128 450 104.8 / 104.8 (80.4 / 79.6),
 // 61 x 96 112.0 / 107.4 (84.6 / 83.7), but with bfloat16 pairs 50 x 128 92.7 / 98.9.  float32 output of 2-bit codes: 196 x 128 400 71.7 / 61.2 (69.6 / 61.1), 700 138 / 110 with bfloat16 pairs, 149 / 152 (130 / 109) with float32
 // ones, 1400 265 / 282 (263 / 217); of 4-bit codes 700 151 / 158.
-// Not where the last round of a head's workgroups leaves more than a 64th of all idle: 8 heads, 50 tokens, 97 groups (304 pieces in 20 rounds of 16) 123.2 / 127.9, 92 groups (288 in 18) 117.3 / 114.8; 7 heads of 196, 28
+// A tile of one pass or less leaves lanes of its workgroup idle, and the workgroup has nothing to hide its loads behind: 20 x 64 (160 items), 30 MB of output 10.0 / 8.1 (9.8 / 6.3), 100 30.5 / 23.6, 350 125 / 81;
+// 20 x 80 (200) 29 8.9 / 8.8 (8.3 / 6.7), 150 51.1 / 44.9 (34.6 / 35.3); 28 x 64 (224) 59 14.3 / 16.1, 149 47.1 / 42.1 (31.9 / 33.3); 16 x 128 (256) 60 14.4 / 14.3, 150 44.6 / 41.3 (32.5 / 33.6), 350 96.1 / 87.2 (83.2 / 74.5).
+// Other tiles not where the last round of a head's workgroups leaves more than a 64th of all idle: 8 heads, 50 tokens, 97 groups (304 pieces in 20 rounds of 16) 123.2 / 127.9, 92 groups (288 in 18) 117.3 / 114.8; 7 heads of 196, 28
 // groups (344 in 22) 119.9 / 122.0.  The pieces take 32-bit offsets, and a wave at most two tiles.
 inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t prefix_blocks) {
     const int64_t items = (int64_t)a.k_eff * a.tile_items, heads = 2 * (int64_t)a.n_layers * a.n_kv_heads, out = heads * items * 16;
     if (a.qaxis == TOM_QAXIS_TOKENS || a.tile_items < 64) return false;
-    if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
-    const int64_t pieces = pieces_of_head(a);
-    if ((kPieces * piece_blocks(a) - pieces) * 64 > pieces) return false;
+    if (is_16_bit && a.tile_items <= kBlock) {
+        if (out < (a.tile_items <= 208 ? 30000000 : 150000000)) return false;
+    } else {
+        if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
+        const int64_t pieces = pieces_of_head(a);
+        if ((kPieces * piece_blocks(a) - pieces) * 64 > pieces) return false;
+    }
     constexpr int64_t kMost = 1LL << 31;
     const int64_t code_tile = (int64_t)a.tile_items * (is_16_bit ? 8 : 4) * a.bits / 8;
     return items < kMost / 16 && a.plane_tiles * code_tile < kMost && a.plane_tiles * a.tile_meta_bytes < kMost && (int64_t)a.n_layers * a.k < kMost / 4 &&
