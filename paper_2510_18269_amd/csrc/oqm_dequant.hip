@@ -353,7 +353,10 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     // 10 (2240) 20.5 / 20.5, 16 26.0 / 25.4, 64 65 / 74; 150 x 80 10 20.6 / 22.0; 100 x 128 (7) 6 17.7 / 16.4, 8 19.2 / 18.5; of 700 groups 8 25.3 / 23.7, 10 27.3 / 28.1, 32 45 / 48.
     const int64_t tiles = (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff;
     const bool many = tok && eb == 2 && tiles > 128;
-    const uint32_t whole = many ? (tiles <= 2048 ? 7 : 5) : 4, most = eb == 2 ? (many ? 5 : 3) : (tok ? 3 : 4);
+    // float32, token axis, chunks of at most 3 / 4, three stores in turn: 50 x 128 (7 passes) 600 MB 137 / 123, 250 45.1 / 43.9, 100 19.0 / 18.3 (the same question again 16.7 / 17.1); 80 x 128 (10) 600 MB 123 / 108;
+    // 112 x 128 (14) 107 / 111, 196 x 128 105 / 114.
+    const bool four = !tok || (passes <= 10 && tiles * a.tile_items * 16 >= 200000000);
+    const uint32_t whole = many ? (tiles <= 2048 ? 7 : 5) : 4, most = eb == 2 ? (many ? 5 : 3) : (four ? 4 : 3);
     const uint32_t fit = passes <= whole ? whole : most;
     a.chunks = passes <= whole ? 1 : (passes + most - 1) / most;
     while ((G + a.chunks - 1) / a.chunks * lpr > fit * a.step) ++a.chunks;

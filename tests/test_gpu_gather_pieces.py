@@ -3,7 +3,8 @@
 Tiles of 1 to 12 pieces that are and are not whole waves, whole pieces or aligned, prefix rows that move the rows off a
 piece's start, indices that name no stored group (their rows are left alone), repeated indices, and the one-call form that takes
 every group in order and writes the indices.  The launches by tiles are small ones of the same groups, which the oracle covers
-elsewhere; a launch above the line of the rule is large, hence the repeated groups."""
+elsewhere; a launch above the line of the rule is large, hence the repeated groups.  And float32 tiles of the token axis, whose chunks
+grow with the launch, the same way."""
 import pytest
 import torch
 
@@ -27,9 +28,9 @@ def oqm():
     return m
 
 
-def filled(oqm, L, heads, d, G, gs, T, out, bits, meta, seed):
+def filled(oqm, L, heads, d, G, gs, T, out, bits, meta, seed, qaxis=0):
     code, dt = H.DT[out]
-    cfg = oqm.make_config(L, heads, heads, d, G, gs, T, bits=bits, in_dtype=code, out_dtype=code,
+    cfg = oqm.make_config(L, heads, heads, d, G, gs, T, qaxis=qaxis, bits=bits, in_dtype=code, out_dtype=code,
                           meta_dtype=oqm.TOM_BF16 if meta == "bf16" else oqm.TOM_F32)
     mem = oqm.Memory.allocate(cfg)
     gen = torch.Generator(device="cuda").manual_seed(seed)
@@ -125,5 +126,25 @@ def test_every_group_in_order(oqm, G, d, gs, prefix, out, bits, meta):
             assert bool((body[:, :, T:] == -3.0).all())
             if prefix:
                 assert torch.equal(raw(g[:, :, :prefix].contiguous()), raw(s))
+    finally:
+        mem.close()
+
+
+@pytest.mark.parametrize("G, d", ((33, 128), (50, 128), (61, 96), (80, 128), (81, 128)))   # 5, 7, 7, 10 and 11 passes
+@pytest.mark.parametrize("bits, meta", ((4, "f32"), (2, "bf16")))
+def test_large_float32_token_axis(oqm, G, d, bits, meta):
+    """Tiles of up to ten passes go in chunks of four from 200 MB up, in chunks of three below."""
+    L, heads, T = 2, 3, 5
+    mem, dt = filled(oqm, L, heads, d, G, 8, T, "f32", bits, meta, G + d, qaxis=1)
+    try:
+        want = by_tiles(oqm, mem, dt, L, heads, d, G, T)
+        k = 200_000_000 // (2 * L * heads * G * d * 4) + 1
+        gen = torch.Generator(device="cuda").manual_seed(G)
+        idx = torch.randint(0, T, (L, k), generator=gen, device="cuda", dtype=torch.int32)
+        got = [torch.zeros((L, heads, k * G, d), dtype=dt, device="cuda") for _ in range(2)]
+        oqm.tom_oqm_dequant_gather(mem.handle, 0, L, idx, k, k, *got)
+        for g, w in zip(got, want):
+            for li in range(L):
+                assert torch.equal(raw(g[li].view(heads, k, G, d)), raw(w[li][:, idx[li].long()]))
     finally:
         mem.close()
