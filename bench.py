@@ -55,12 +55,12 @@ def bytes_topk(w, T, k_eff):
 
 
 # ------------------------------------------------------------------ committed counter summaries
-def traced_append_kernel(workload):
-    """The append kernel in the committed kernel trace of `bench.py --workload <workload>`: the library
-    chooses among several by rules of its own.  None if there is no trace."""
+def traced_kernel(workload, start):
+    """The kernel whose name begins with `start` in the committed kernel trace of `bench.py --workload
+    <workload>`: the library chooses among several by rules of its own.  None if there is none."""
     try:
         with open(os.path.join(ROOT, "profiles", f"kernel_trace_bench_{workload.lower()}.txt")) as f:
-            names = [l.split("<")[0].split()[0] for l in f if l.startswith("quantize_append")]
+            names = [l.split("<")[0].split()[0] for l in f if l.startswith(start)]
     except OSError:
         return None
     return names[0] if names else None
@@ -386,7 +386,8 @@ class Leg:
                     "frac_by_committed_kernel_trace": round(b / (traced * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4) if traced else None}
 
         tok = self.tok
-        append_kernel = (traced_append_kernel(w.name) if default_variant else None) or "quantize_append"
+        append_kernel = (traced_kernel(w.name, "quantize_append") if default_variant else None) or "quantize_append"
+        gather_kernel = (traced_kernel(w.name, "dequant_gather") if default_variant else None) or "dequant_gather_kernel"
         r = {
             "workload": f"{w.name}: {L} layers, {w.n_kv_heads} KV heads ({w.n_q_heads} query heads), "
                         f"head_dim {w.head_dim}, {w.dtype} K/V, {T} frames x {w.group_tokens} tokens stored, "
@@ -410,7 +411,7 @@ class Leg:
             "event_overhead_us": round(event_overhead_us, 2),
             "retrieval_ms_per_query": round(ms_retrieve_call, 4),
             "retrieval_ms_per_query_separate_calls": round(ms_score + ms_topk + ms_gather, 4),
-            "roofline": roof("dequant_gather_kernel", b_gat, ms_gather, probes.get("gather")),
+            "roofline": roof(gather_kernel, b_gat, ms_gather, probes.get("gather")),
             "roofline_append": roof(append_kernel, b_app, ms_append, probes.get("append")),
         }
         if self.path == self.oqm.TOM_SCORE_TOKEN_GEMM:
