@@ -94,9 +94,16 @@ inline int fold_parts(const ScoreArgs& a, bool want_tokens) {
 // at most three tiles (118 registers, two workgroups) 512 units run in one.  Fold and scores at 448 to 512 units, equal
 // passes of three / passes of four / 64 x 64 form: one head of 64 x 65 tokens 14.5 / 18.0 / 15.8 us, x 1024
 // tokens 92 / 117 / 107; 4 heads of 128 x 65 tokens 36 / 45 / 46, x 1024 tokens 370 / 390 / 470.
+// One tile of tokens on keys of 256 channels and more goes on beyond: there the 64 x 64 form is bound by its chain of chunks, a barrier and a load latency for 32
+// channels, with one or two workgroups a compute unit, and what the split form reads of the query grows with the tokens. Fold and scores, 64 x 64 form / this, three
+// stores in turn, at 1 / 4 / 8 / 12 tokens: 700 units of 512 channels 15.9 / 12.6, 15.9 / 13.0, 15.9 / 13.6, 16.0 / 14.8; 1232 units of 2048 67.2 / 44.0, 67.6 / 48.5, 68.7 / 54.7
+// (16: 70.1 / 66.9), of 1024 34.3 / 24.7, 33.7 / 25.7, 33.4 / 28.2 (16: 35.3 / 35.4), of 512 19.5 / 15.9, 19.6 / 16.7, 19.6 / 17.6 (16: 19.7 / 20.7), of 256 12.9 / 12.1, 13.0 / 12.5,
+// 12.9 / 12.9; 1484 units of 512 19.6 / 17.9, 19.7 / 18.7, 19.6 / 19.8, 19.8 / 22.1; 1596 of 1024 37.4 / 32.8, 38.0 / 34.9, 38.9 / 38.3; 2100 of 512 24.7 / 23.9, 24.7 / 24.7, 24.7 / 26.0;
+// 2632 of 1024 46.1 / 47.3 at 1; 1232 of 64 and 1792 of 128 channels lose 9 and 17 % at any number of tokens.
 inline int split_tiles(const ScoreArgs& a) {
     constexpr int64_t kSplitUnits = 512, kUnitsOfFourTiles = 256;
     const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers;
+    if (a.t_q <= 16 && units <= 1700 - 50 * a.t_q && a.n_kv_heads * a.head_dim >= 256) return 1;
     if (units > kSplitUnits) return 0;
     const int most = units > kUnitsOfFourTiles ? 3 : 4;
     const int tiles = (a.t_q + 15) / 16, passes = (tiles + most - 1) / most;

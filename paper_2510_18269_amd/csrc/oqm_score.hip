@@ -605,7 +605,7 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
     }
 }
 
-// The same contraction for launches of few units of 16 groups (split_tiles in oqm_dispatch.h), where the 64 x 64 form
+// The same contraction for launches of few units of 16 groups, or of few tokens on long keys (split_tiles in oqm_dispatch.h), where the 64 x 64 form
 // leaves compute units idle and each of its few workgroups walks the whole contraction through
 // barriers (1.2 us per 32 channels).  Unit of work = (layer, 16
 // consecutive groups), all query tokens in passes of 16 * MT: the eight waves of a workgroup split the contraction,

@@ -174,6 +174,12 @@ static void split() {
     CHECK(tiles(512, 16, 1) == 1 && tiles(513, 16, 1) == 0);
     CHECK(tiles(4, 1024, 64) == 4 && tiles(4, 1024, 65) == 3 && tiles(4, 1024, 1 << 20) == 4);
     CHECK(tiles(65535, 0x7fffffff, 1) == 0);                     // far beyond, no overflow
+    a.n_kv_heads = 2, a.head_dim = 128;                          // one tile of tokens on longer keys: up to 1700 - 50 t_q units
+    CHECK(tiles(28, 58 * 16, 1) == 1 && tiles(28, 59 * 16, 1) == 0 && tiles(28, 32 * 16, 16) == 1 && tiles(28, 33 * 16, 16) == 0);
+    CHECK(tiles(28, 28 * 16, 17) == 0 && tiles(65535, 0x7fffffff, 1) == 0);
+    a.n_kv_heads = 31, a.head_dim = 8;
+    CHECK(tiles(28, 58 * 16, 1) == 0);
+    a.n_kv_heads = a.head_dim = 0;
 
     // the fold inside: layers, groups, query tokens, KV heads, query heads of each, head_dim -> tiles of a pass, or 0
     auto fold = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d, int type = TOM_BF16) {

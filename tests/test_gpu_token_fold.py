@@ -90,3 +90,10 @@ def test_folds_of_their_own(oqm):
 def test_scores_over_the_question(oqm):
     for T, tq in ((40, 16), (700, 3)):
         _check(oqm, 2, 2, 2, 64, T, tq, overlap=True)
+
+
+# one tile of tokens, launches beyond two rounds of the chip: up to 1700 - 50 t_q units of 16 groups the contraction is split, from there on 64 x 64
+@pytest.mark.parametrize("tq, units", ((1, 1650), (8, 1300), (12, 1100), (16, 900)))
+def test_one_tile_of_tokens_on_long_keys(oqm, tq, units):
+    for heads, d, r, T in ((2, 128, 3, units // 10 * 16), (2, 128, 3, units // 10 * 16 + 1), (3, 80, 3, units // 10 * 16), (4, 136, 4, units // 10 * 16 - 5)):
+        _check(oqm, 10, heads, r, d, T, tq, cosine=tq != 8)
