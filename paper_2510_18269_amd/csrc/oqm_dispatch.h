@@ -84,6 +84,7 @@ inline int fold_parts(const ScoreArgs& a, bool want_tokens) {
 }
 
 // ---- per-token scores: the contraction is split over the waves of a workgroup -------------
+constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
 // Tiles of 16 query tokens per pass of score_token_split_kernel (1 to 4), or 0: the 64 x 64 form.
 // A whole question on the device (fold, this, top-k, gather of 4 groups) at 4 heads of 128, against the 64 x 64 form:
 // 1 layer x 256 groups x 32 tokens 18.1 / 28.0 us, x 64 tokens 25.8 / 39.3; 8 x 1024 (512 units)
@@ -100,13 +101,22 @@ inline int fold_parts(const ScoreArgs& a, bool want_tokens) {
 // (16: 70.1 / 66.9), of 1024 34.3 / 24.7, 33.7 / 25.7, 33.4 / 28.2 (16: 35.3 / 35.4), of 512 19.5 / 15.9, 19.6 / 16.7, 19.6 / 17.6 (16: 19.7 / 20.7), of 256 12.9 / 12.1, 13.0 / 12.5,
 // 12.9 / 12.9; 1484 units of 512 19.6 / 17.9, 19.7 / 18.7, 19.6 / 19.8, 19.8 / 22.1; 1596 of 1024 37.4 / 32.8, 38.0 / 34.9, 38.9 / 38.3; 2100 of 512 24.7 / 23.9, 24.7 / 24.7, 24.7 / 26.0;
 // 2632 of 1024 46.1 / 47.3 at 1; 1232 of 64 and 1792 of 128 channels lose 9 and 17 % at any number of tokens.
+// Two and three tiles whose last one is mostly empty go on as well (its lanes re-read one row here, the 64 x 64 form multiplies them), on keys of 512 channels and more, where the 64 x 64 form would
+// leave a third of one round of the chip or two fifths of two idle. 64 x 64 form / this at 17 / 25 / 33 / 38 tokens: 28 layers x 384 groups of 512 channels (168 units of 64) 21.3 / 18.2, 21.6 / 19.8, 28.0 / 24.4,
+// 28.2 / 25.5, of 2048 68.5 / 50.9, 70.8 / 59.7, 93.7 / 74.4, 95.0 / 80.4; 700 of 512 (308) 29.0 / 25.4, 29.3 / 27.9, 38.8 / 34.8, 38.8 / 36.7, of 1024 52.7 / 42.7, 53.1 / 48.3, 72.1 / 61.6, 72.5 / 66.0; but
+// 768 of 512 (336) 29.0 / 28.6, 29.4 / 31.6, 38.8 / 39.8, 38.9 / 41.9; 512 of 1024 (224) x 24 37.3 / 40.0; 1000 of 2048 (448) x 24 99.9 / 118.9; 320 of 1024 (140) x 32 37.8 / 36.4, 700 x 32 53.7 / 55.0.
 inline int split_tiles(const ScoreArgs& a) {
     constexpr int64_t kSplitUnits = 512, kUnitsOfFourTiles = 256;
     const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers;
     if (a.t_q <= 16 && units <= 1700 - 50 * a.t_q && a.n_kv_heads * a.head_dim >= 256) return 1;
-    if (units > kSplitUnits) return 0;
+    const int tiles = (a.t_q + 15) / 16;
+    if (units > kSplitUnits) {
+        const int64_t wide = ((int64_t)a.n_groups + kGemmN - 1) / kGemmN * a.n_layers;
+        const bool idle = wide <= 168 || (wide > 256 && wide <= 308);  // 256 compute units
+        return idle && tiles >= 2 && tiles <= 3 && 5 * a.t_q <= 64 * tiles && a.n_kv_heads * a.head_dim >= 512 ? tiles : 0;
+    }
     const int most = units > kUnitsOfFourTiles ? 3 : 4;
-    const int tiles = (a.t_q + 15) / 16, passes = (tiles + most - 1) / most;
+    const int passes = (tiles + most - 1) / most;
     return (tiles + passes - 1) / passes;
 }
 

@@ -436,7 +436,6 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
 // v_mfma_f64_16x16x4_f64 register layout (checked on hardware by the GPU tests through
 // the per-token score output): lane = 16*kk + i supplies A[i][kk] and B[kk][i]; lane
 // 16*g + j holds D[4*v + g][j] in accumulator register v.
-constexpr int kGemmN = 64;
 constexpr int kGemmM = 64;
 constexpr int kGemmK = 32;
 // Row pitches of the staged operands.  A fragment read takes element (row fi, column kk) per

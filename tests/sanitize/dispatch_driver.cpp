@@ -177,8 +177,13 @@ static void split() {
     a.n_kv_heads = 2, a.head_dim = 128;                          // one tile of tokens on longer keys: up to 1700 - 50 t_q units
     CHECK(tiles(28, 58 * 16, 1) == 1 && tiles(28, 59 * 16, 1) == 0 && tiles(28, 32 * 16, 16) == 1 && tiles(28, 33 * 16, 16) == 0);
     CHECK(tiles(28, 28 * 16, 17) == 0 && tiles(65535, 0x7fffffff, 1) == 0);
+    a.n_kv_heads = 4;                                            // two and three tiles, the last mostly empty: up to 168 and 257 to 308 units of 64
+    for (int t_q : {17, 25, 26, 32, 33, 38, 39, 48, 49, 64, 65})
+        for (int groups : {6 * 64, 6 * 64 + 1, 9 * 64, 9 * 64 + 1, 11 * 64, 11 * 64 + 1})
+            CHECK(tiles(28, groups, t_q) == ((groups <= 6 * 64 || (groups > 9 * 64 && groups <= 11 * 64)) ? (t_q <= 25 ? 2 : t_q >= 33 && t_q <= 38 ? 3 : 0) : 0));
+    CHECK(tiles(65535, 0x7fffffff, 17) == 0);
     a.n_kv_heads = 31, a.head_dim = 8;
-    CHECK(tiles(28, 58 * 16, 1) == 0);
+    CHECK(tiles(28, 58 * 16, 1) == 0 && tiles(28, 6 * 64, 17) == 0);
     a.n_kv_heads = a.head_dim = 0;
 
     // the fold inside: layers, groups, query tokens, KV heads, query heads of each, head_dim -> tiles of a pass, or 0

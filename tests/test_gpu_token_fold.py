@@ -97,3 +97,10 @@ def test_scores_over_the_question(oqm):
 def test_one_tile_of_tokens_on_long_keys(oqm, tq, units):
     for heads, d, r, T in ((2, 128, 3, units // 10 * 16), (2, 128, 3, units // 10 * 16 + 1), (3, 80, 3, units // 10 * 16), (4, 136, 4, units // 10 * 16 - 5)):
         _check(oqm, 10, heads, r, d, T, tq, cosine=tq != 8)
+
+
+# two and three tiles whose last is mostly empty, where the 64 x 64 form would leave a third of one round or two fifths of two idle: up to 168 and from 257 to 308 units of 64
+@pytest.mark.parametrize("tq", (17, 25, 26, 33, 38, 39))
+def test_nearly_empty_tiles_on_long_keys(oqm, tq):
+    for i, T in enumerate((6 * 64, 6 * 64 + 1, 9 * 64, 9 * 64 + 1, 11 * 64, 11 * 64 + 1)):
+        _check(oqm, 28, 4, 3, 128 + 8 * (i % 2), T, tq, tokens=i % 2 == 0, cosine=i != 2)

@@ -1,7 +1,7 @@
 """GPU: the per-token scores of small launches (the K-split form) against plain float64.
 
 A launch of at most 512 units of 16 groups splits the contraction over the waves of a workgroup, with
-1 to 4 tiles of 16 query tokens at a time (1 to 3 above 256 units); larger launches take the 64 x 64 form.  The cases sit on
+1 to 4 tiles of 16 query tokens at a time (1 to 3 above 256 units); larger launches take the 64 x 64 form, unless few tokens meet long keys.  The cases sit on
 both sides of every edge: token tiles, group tiles, contractions that end in half a block of 16
 channels or need several rounds of blocks, and the launch size itself."""
 import pytest
