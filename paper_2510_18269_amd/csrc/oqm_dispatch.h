@@ -99,7 +99,7 @@ constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
 // channels, with one or two workgroups a compute unit, and what the split form reads of the query grows with the tokens. Fold and scores, 64 x 64 form / this, three
 // stores in turn, at 1 / 4 / 8 / 12 tokens: 700 units of 512 channels 15.9 / 12.6, 15.9 / 13.0, 15.9 / 13.6, 16.0 / 14.8; 1232 units of 2048 67.2 / 44.0, 67.6 / 48.5, 68.7 / 54.7
 // (16: 70.1 / 66.9), of 1024 34.3 / 24.7, 33.7 / 25.7, 33.4 / 28.2 (16: 35.3 / 35.4), of 512 19.5 / 15.9, 19.6 / 16.7, 19.6 / 17.6 (16: 19.7 / 20.7), of 256 12.9 / 12.1, 13.0 / 12.5,
-// 12.9 / 12.9; 1484 units of 512 19.6 / 17.9, 19.7 / 18.7, 19.6 / 19.8, 19.8 / 22.1; 1596 of 1024 37.4 / 32.8, 38.0 / 34.9, 38.9 / 38.3; 2100 of 512 24.7 / 23.9, 24.7 / 24.7, 24.7 / 26.0;
+// 12.9 / 12.9; 1484 units of 512 19.6 / 17.9, 19.7 / 18.7, 19.6 / 19.8, 19.8 / 22.1; 1596 of 1024 37.4 / 32.8, 38.0 / 34.9, 38.9 / 38.3, of 2048 70.2 / 55.8, 69.6 / 61.5, 71.8 / 70.5 (the same question again 59.9 / 51.8, 60.4 / 56.5, 61.2 / 65.8); 1876 of 1024 40.0 / 36.9 at 1, of 2048 71.9 / 62.9; 2100 of 512 24.7 / 23.9, 24.7 / 24.7, 24.7 / 26.0;
 // 2632 of 1024 46.1 / 47.3 at 1; 1232 of 64 and 1792 of 128 channels lose 9 and 17 % at any number of tokens.
 // Two and three tiles whose last one is mostly empty go on as well (its lanes re-read one row here, the 64 x 64 form multiplies them), on keys of 512 channels and more, where the 64 x 64 form would
 // leave a third of one round of the chip or two fifths of two idle. 64 x 64 form / this at 17 / 25 / 33 / 38 tokens: 28 layers x 384 groups of 512 channels (168 units of 64) 21.3 / 18.2, 21.6 / 19.8, 28.0 / 24.4,
@@ -108,12 +108,13 @@ constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
 inline int split_tiles(const ScoreArgs& a) {
     constexpr int64_t kSplitUnits = 512, kUnitsOfFourTiles = 256;
     const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers;
-    if (a.t_q <= 16 && units <= 1700 - 50 * a.t_q && a.n_kv_heads * a.head_dim >= 256) return 1;
+    const int channels = a.n_kv_heads * a.head_dim;
+    if (a.t_q <= 16 && channels >= 256 && units <= (channels >= 1024 && a.t_q <= 12 ? 2000 - 75 * a.t_q : 1700 - 50 * a.t_q)) return 1;
     const int tiles = (a.t_q + 15) / 16;
     if (units > kSplitUnits) {
         const int64_t wide = ((int64_t)a.n_groups + kGemmN - 1) / kGemmN * a.n_layers;
         const bool idle = wide <= 168 || (wide > 256 && wide <= 308);  // 256 compute units
-        return idle && tiles >= 2 && tiles <= 3 && 5 * a.t_q <= 64 * tiles && a.n_kv_heads * a.head_dim >= 512 ? tiles : 0;
+        return idle && tiles >= 2 && tiles <= 3 && 5 * a.t_q <= 64 * tiles && channels >= 512 ? tiles : 0;
     }
     const int most = units > kUnitsOfFourTiles ? 3 : 4;
     const int passes = (tiles + most - 1) / most;

@@ -182,6 +182,8 @@ static void split() {
         for (int groups : {6 * 64, 6 * 64 + 1, 9 * 64, 9 * 64 + 1, 11 * 64, 11 * 64 + 1})
             CHECK(tiles(28, groups, t_q) == ((groups <= 6 * 64 || (groups > 9 * 64 && groups <= 11 * 64)) ? (t_q <= 25 ? 2 : t_q >= 33 && t_q <= 38 ? 3 : 0) : 0));
     CHECK(tiles(65535, 0x7fffffff, 17) == 0);
+    a.n_kv_heads = 8;                                            // 1024 channels: up to 2000 - 75 t_q, from 12 tokens on as before
+    CHECK(tiles(25, 77 * 16, 1) == 1 && tiles(25, 78 * 16, 1) == 0 && tiles(25, 44 * 16, 12) == 1 && tiles(25, 45 * 16, 12) == 0 && tiles(25, 42 * 16, 13) == 1 && tiles(25, 43 * 16, 13) == 0);
     a.n_kv_heads = 31, a.head_dim = 8;
     CHECK(tiles(28, 58 * 16, 1) == 0 && tiles(28, 6 * 64, 17) == 0);
     a.n_kv_heads = a.head_dim = 0;

@@ -92,11 +92,13 @@ def test_scores_over_the_question(oqm):
         _check(oqm, 2, 2, 2, 64, T, tq, overlap=True)
 
 
-# one tile of tokens, launches beyond two rounds of the chip: up to 1700 - 50 t_q units of 16 groups the contraction is split, from there on 64 x 64
+# one tile of tokens, launches beyond two rounds of the chip: up to 1700 - 50 t_q units of 16 groups the contraction is split (1024 channels, up to 12 tokens: 2000 - 75 t_q), from there on 64 x 64
 @pytest.mark.parametrize("tq, units", ((1, 1650), (8, 1300), (12, 1100), (16, 900)))
 def test_one_tile_of_tokens_on_long_keys(oqm, tq, units):
     for heads, d, r, T in ((2, 128, 3, units // 10 * 16), (2, 128, 3, units // 10 * 16 + 1), (3, 80, 3, units // 10 * 16), (4, 136, 4, units // 10 * 16 - 5)):
         _check(oqm, 10, heads, r, d, T, tq, cosine=tq != 8)
+    for T in ((2000 - 75 * tq) // 10 * 16, (2000 - 75 * tq) // 10 * 16 + 1):
+        _check(oqm, 10, 4, 3, 256, T, tq, tokens=False)
 
 
 # two and three tiles whose last is mostly empty, where the 64 x 64 form would leave a third of one round or two fifths of two idle: up to 168 and from 257 to 308 units of 64
