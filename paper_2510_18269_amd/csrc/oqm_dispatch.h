@@ -102,9 +102,9 @@ constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
 // 12.9 / 12.9; 1484 units of 512 19.6 / 17.9, 19.7 / 18.7, 19.6 / 19.8, 19.8 / 22.1; 1596 of 1024 37.4 / 32.8, 38.0 / 34.9, 38.9 / 38.3, of 2048 70.2 / 55.8, 69.6 / 61.5, 71.8 / 70.5 (the same question again 59.9 / 51.8, 60.4 / 56.5, 61.2 / 65.8); 1876 of 1024 40.0 / 36.9 at 1, of 2048 71.9 / 62.9; 2100 of 512 24.7 / 23.9, 24.7 / 24.7, 24.7 / 26.0;
 // 2632 of 1024 46.1 / 47.3 at 1; 1232 of 64 and 1792 of 128 channels lose 9 and 17 % at any number of tokens.
 // Two and three tiles whose last one is mostly empty go on as well (its lanes re-read one row here, the 64 x 64 form multiplies them), on keys of 512 channels and more, where the 64 x 64 form would
-// leave a third of one round of the chip or two fifths of two idle. 64 x 64 form / this at 17 / 25 / 33 / 38 tokens: 28 layers x 384 groups of 512 channels (168 units of 64) 21.3 / 18.2, 21.6 / 19.8, 28.0 / 24.4,
-// 28.2 / 25.5, of 2048 68.5 / 50.9, 70.8 / 59.7, 93.7 / 74.4, 95.0 / 80.4; 700 of 512 (308) 29.0 / 25.4, 29.3 / 27.9, 38.8 / 34.8, 38.8 / 36.7, of 1024 52.7 / 42.7, 53.1 / 48.3, 72.1 / 61.6, 72.5 / 66.0; but
-// 768 of 512 (336) 29.0 / 28.6, 29.4 / 31.6, 38.8 / 39.8, 38.9 / 41.9; 512 of 1024 (224) x 24 37.3 / 40.0; 1000 of 2048 (448) x 24 99.9 / 118.9; 320 of 1024 (140) x 32 37.8 / 36.4, 700 x 32 53.7 / 55.0.
+// leave a third of one round of the chip or, with three tiles, two fifths of two idle. 64 x 64 form / this at 17 / 25 / 33 / 38 tokens: 28 layers x 384 groups of 512 channels (168 units of 64) 21.3 / 18.2, 21.6 / 19.8, 28.0 / 24.4,
+// 28.2 / 25.5, of 2048 68.5 / 50.9, 70.8 / 59.7, 93.7 / 74.4, 95.0 / 80.4; 700 of 512 (308) at 33 / 38 38.8 / 34.8, 38.8 / 36.7, of 1024 72.1 / 61.6, 72.5 / 66.0; but
+// 768 of 512 (336) 38.8 / 39.8, 38.9 / 41.9; 512 of 1024 (224) x 24 37.3 / 40.0; 1000 of 2048 (448) x 24 99.9 / 118.9; 320 of 1024 (140) x 32 37.8 / 36.4, 700 x 32 53.7 / 55.0.
 inline int split_tiles(const ScoreArgs& a) {
     constexpr int64_t kSplitUnits = 512, kUnitsOfFourTiles = 256;
     const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers;
@@ -113,12 +113,22 @@ inline int split_tiles(const ScoreArgs& a) {
     const int tiles = (a.t_q + 15) / 16;
     if (units > kSplitUnits) {
         const int64_t wide = ((int64_t)a.n_groups + kGemmN - 1) / kGemmN * a.n_layers;
-        const bool idle = wide <= 168 || (wide > 256 && wide <= 308);  // 256 compute units
+        const bool idle = wide <= 168 || (tiles == 3 && wide > 256 && wide <= 308);  // 256 compute units
         return idle && tiles >= 2 && tiles <= 3 && 5 * a.t_q <= 64 * tiles && channels >= 512 ? tiles : 0;
     }
     const int most = units > kUnitsOfFourTiles ? 3 : 4;
     const int passes = (tiles + most - 1) / most;
     return (tiles + passes - 1) / passes;
+}
+
+// Groups of a unit of the 64 x 64 form: 64, or 32 where units of 64 need two rounds of the 256 compute units and units of 32 one and a half. The waves of a unit of 32 share out the token tiles in two
+// halves, so a pass of one or three tiles has an idle one. Fold and scores, units of 64 / 32, three stores in turn: 28 layers x 600 groups of 512 channels (280 units of 64) 32 tokens 30.2 / 26.7, 48 39.8 / 40.4, 64 48.4 / 41.7, 70
+// 62.0 / 59.5, 100 81.7 / 75.0, 300 214 / 186; 864 (378) of 64 to 2048 channels x 64 0.84 to 0.91, 620 of 64 x 20 0.96. Outside of that the query is staged more often for nothing: 1024 groups (448) x 32 30.4 / 31.7, x 64 49.1 / 55.7; 1300 (588, rounds
+// of 3 and 2.5) 39.5 / 37.2, 66.1 / 65.4, 100 112 / 121; 3600 x 64 141 / 150; up to one round 2 % are gained at 32 and 64, 3 to 4 lost at 100.
+inline int gemm_width(const ScoreArgs& a) {
+    const int64_t units = ((int64_t)a.n_groups + kGemmN - 1) / kGemmN * a.n_layers, halves = ((int64_t)a.n_groups + kGemmN / 2 - 1) / (kGemmN / 2) * a.n_layers;
+    const bool pairs = a.t_q > 16 && (a.t_q <= 32 || a.t_q > 48);
+    return pairs && units > 256 && halves <= 768 ? kGemmN / 2 : kGemmN;
 }
 
 // Tiles of 16 query tokens per pass of score_token_fold_kernel (1 to 4), or 0: the fold is a launch of its own, and split_tiles decides about the contraction.

@@ -424,7 +424,8 @@ __global__ void __launch_bounds__(kFoldThreads) score_fold_query_kernel(const Sc
 // ------------------------------------------------------------------ per-token GEMM
 // S[j][t] = sum_e qtok[j][e] * key[t][e], j < T_q query tokens, t < T groups, e < H_k*d.
 // Unit of work = (layer, 64 consecutive groups): one workgroup of 4 waves; wave w owns groups
-// n0 + 16w .. + 15 and up to four 16-token row tiles.  Operands are staged through LDS in
+// n0 + 16w .. + 15 and up to four 16-token row tiles.  With units of 32 groups (gemm_width in oqm_dispatch.h) waves w and w + 2
+// own the same groups and half of the row tiles each.  Operands are staged through LDS in
 // chunks of kGemmK along e.
 //
 // Workgroup id -> unit.  Ids go round-robin over the eight XCDs, each with its own L2, so
@@ -451,11 +452,11 @@ __device__ __forceinline__ int mfma_d_row(int lane, int v) { return 4 * v + (lan
 // of this wave.  No branches inside, so the LDS reads of a step are issued together.
 template <int MT>
 __device__ __forceinline__ void mma_chunk(const double* __restrict__ As, const float* __restrict__ Bs,
-                                          f64x4 (&acc)[MT], double& nk2c, int wave, int fi,
+                                          f64x4 (&acc)[MT], double& nk2c, int tile, int fi,
                                           int kk) {
 #pragma unroll
     for (int ks = 0; ks < kGemmK / 4; ++ks) {
-        const double bv = (double)Bs[(wave * 16 + fi) * kLdB + ks * 4 + kk];
+        const double bv = (double)Bs[(tile * 16 + fi) * kLdB + ks * 4 + kk];
         double av[MT];
 #pragma unroll
         for (int m = 0; m < MT; ++m) av[m] = As[(m * 16 + fi) * kLdA + ks * 4 + kk];
@@ -466,27 +467,29 @@ __device__ __forceinline__ void mma_chunk(const double* __restrict__ As, const f
     }
 }
 
-// One block of up to 64 query rows: the chunk loop with the row-tile count fixed at compile
+// One block of up to 64 query rows against NG group tiles: the chunk loop with the row-tile count fixed at compile
 // time, so the accumulators stay in place across the whole contraction.
-template <int MT, int SIZE>
-__device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SIZE], float (&Bs)[2][kGemmN * kLdB],
+template <int MT, int NG, int SIZE>
+__device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SIZE], float (&Bs)[2][NG * 16 * kLdB],
                                           const double* qtok, const float* keys, int m0, int n0, int li,
                                           double& colsum, double& nk2) {
     const int HD = a.n_kv_heads * a.head_dim;
     const int T = a.n_groups, Tq = a.t_q;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fi = lane & 15, kk = lane >> 4;
+    constexpr int kParts = 4 / NG, WT = MT / kParts;  // WT: row tiles of a wave
+    const int tile = wave % NG, part = wave / NG;
     const int n_chunks = (HD + kGemmK - 1) / kGemmK;
     constexpr int kALanes = kGemmK / 2, kBLanes = kGemmK / 4;
     constexpr int kAPass = kBlock / kALanes, kBPass = kBlock / kBLanes;
-    constexpr int kARows = (MT * 16 + kAPass - 1) / kAPass, kBRows = kGemmN / kBPass;
+    constexpr int kARows = (MT * 16 + kAPass - 1) / kAPass, kBRows = NG * 16 / kBPass;
     const int a_row = tid / kALanes, a_col = (tid % kALanes) * 2;
     const int b_row = tid / kBLanes, b_col = (tid % kBLanes) * 4;
     const int rows = min(kGemmM, Tq - m0);
 
-    f64x4 acc[MT];
+    f64x4 acc[WT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int m = 0; m < WT; ++m) acc[m] = f64x4{0.0, 0.0, 0.0, 0.0};
     double nk2c = 0.0;
     double ra[kARows][2];
     f32x4 rb[kBRows];
@@ -535,17 +538,17 @@ __device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SI
     for (int c = 0; c < n_chunks; ++c) {
         const int stage = c & 1;
         if (c + 1 < n_chunks) load_chunk(c + 1);  // in flight during the MFMAs below
-        mma_chunk<MT>(As[stage], Bs[stage], acc, nk2c, wave, fi, kk);
+        mma_chunk<WT>(As[stage] + part * WT * 16 * kLdA, Bs[stage], acc, nk2c, tile, fi, kk);
         if (c + 1 < n_chunks) store_chunk(stage ^ 1);  // that stage was consumed before the last barrier
         __syncthreads();
     }
     if (m0 == 0) nk2 = nk2c;
-    const int t = n0 + wave * 16 + fi;
+    const int t = n0 + tile * 16 + fi;
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
+    for (int m = 0; m < WT; ++m) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int j = m0 + m * 16 + mfma_d_row(lane, v);
+            const int j = m0 + (part * WT + m) * 16 + mfma_d_row(lane, v);
             colsum += acc[m][v];  // rows >= T_q were staged as zeros
             if (a.token_scores && j < Tq && t < T)
                 a.token_scores[((int64_t)li * Tq + j) * T + t] = (float)acc[m][v];
@@ -556,15 +559,15 @@ __device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SI
 // MOST: row tiles of a pass.  With one or two the whole question is one pass, and with registers and LDS for them alone six or four
 // workgroups share a compute unit instead of three: 28 layers x 2200 groups x 2 heads of 128 x 16 tokens 29.3 -> 26.5 us (whole question, k = 1), 32 tokens
 // 37.9 -> 35.3, 2000 x 1 head of 64 x 16 18.5 -> 16.6; up to one round of the chip 1 to 2 %.  Three tiles gain nothing.
-template <int MOST>
+template <int MOST, int NG>
 __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArgs a) {
     // two LDS stages: chunk c is multiplied while chunk c+1 travels global -> registers -> LDS
     __shared__ double As[2][MOST * 16 * kLdA];
-    __shared__ float Bs[2][kGemmN * kLdB];
+    __shared__ float Bs[2][NG * 16 * kLdB];
     const int unit = (int)(blockIdx.x & 7u) * a.gemm_units_per_xcd + (int)(blockIdx.x >> 3);
     if (unit >= a.gemm_units) return;  // uniform per workgroup
     const int li = div_by(unit, a.gemm_tiles_per_layer, a.inv_gemm_tiles_per_layer);
-    const int n0 = (unit - li * a.gemm_tiles_per_layer) * kGemmN;
+    const int n0 = (unit - li * a.gemm_tiles_per_layer) * (NG * 16);
     const int HD = a.n_kv_heads * a.head_dim;
     const int T = a.n_groups, Tq = a.t_q;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -577,25 +580,36 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
 
     double colsum = 0.0, nk2 = 0.0;
     if constexpr (MOST <= 2) {
-        gemm_rows<MOST>(a, As, Bs, qtok, keys, 0, n0, li, colsum, nk2);
+        gemm_rows<MOST, NG>(a, As, Bs, qtok, keys, 0, n0, li, colsum, nk2);
     } else {
         for (int m0 = 0; m0 < Tq; m0 += kGemmM) {
             const int mt = (min(kGemmM, Tq - m0) + 15) >> 4;
-            switch (mt) {  // uniform
-                case 1: gemm_rows<1>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
-                case 2: gemm_rows<2>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
-                case 3: gemm_rows<3>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
-                default: gemm_rows<4>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+            switch (mt) {  // uniform; halves of tiles need an even number of them
+                case 1:
+                    if constexpr (NG == 4) {
+                        gemm_rows<1, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2);
+                        break;
+                    }
+                case 2: gemm_rows<2, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
+                case 3:
+                    if constexpr (NG == 4) {
+                        gemm_rows<3, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2);
+                        break;
+                    }
+                default: gemm_rows<4, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
             }
         }
     }
     norm.put(wsum);
-    // lanes fi, 16 + fi, 32 + fi, 48 + fi hold the partial sums of group n0 + 16*wave + fi
+    // lanes fi, 16 + fi, 32 + fi, 48 + fi hold the partial sums of group n0 + 16 * tile + fi
     colsum = rows16_sum_f64(colsum);
     nk2 = rows16_sum_f64(nk2);
+    __shared__ double other[NG == 2 ? 32 : 1];  // of the waves with the upper half of the tokens
+    if (NG == 2 && wave >= 2 && kk == 0) other[(wave - 2) * 16 + fi] = colsum;
     __syncthreads();
     const int t = n0 + wave * 16 + fi;
-    if (kk == 0 && t < T) {
+    if (wave < NG && kk == 0 && t < T) {
+        if (NG == 2) colsum += other[wave * 16 + fi];
         double s = colsum / (double)Tq;
         if (a.sim == TOM_SIM_COSINE) {
             s = s / (fmax(sqrt(total_of<kBlock / 64>(wsum)), 1e-12) * fmax(sqrt(nk2), 1e-12));
@@ -979,7 +993,7 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     if (!folded)
         if (hipError_t e = launch_query_fold(args, true, s)) return e;
     const int tiles = folded ? folded : split_tiles(a);
-    const int width = tiles > 0 ? 16 : kGemmN;
+    const int width = tiles > 0 ? 16 : gemm_width(a);
     a.gemm_tiles_per_layer = (a.n_groups + width - 1) / width;
     a.inv_gemm_tiles_per_layer = reciprocal_u32((uint32_t)a.gemm_tiles_per_layer);
     const int64_t units = (int64_t)a.gemm_tiles_per_layer * a.n_layers;
@@ -1015,9 +1029,14 @@ hipError_t launch_score_token_gemm(const ScoreArgs& args, hipStream_t s) {
     }
     switch (tiles) {
         case 0:
-            if (a.t_q <= 16) launch(score_token_gemm_kernel<1>, grid, dim3(kBlock), 0, s, a);
-            else if (a.t_q <= 32) launch(score_token_gemm_kernel<2>, grid, dim3(kBlock), 0, s, a);
-            else launch(score_token_gemm_kernel<4>, grid, dim3(kBlock), 0, s, a);
+            if (width == kGemmN / 2) {
+                if (a.t_q <= 32) launch(score_token_gemm_kernel<2, 2>, grid, dim3(kBlock), 0, s, a);
+                else launch(score_token_gemm_kernel<4, 2>, grid, dim3(kBlock), 0, s, a);
+                break;
+            }
+            if (a.t_q <= 16) launch(score_token_gemm_kernel<1, 4>, grid, dim3(kBlock), 0, s, a);
+            else if (a.t_q <= 32) launch(score_token_gemm_kernel<2, 4>, grid, dim3(kBlock), 0, s, a);
+            else launch(score_token_gemm_kernel<4, 4>, grid, dim3(kBlock), 0, s, a);
             break;
         case 1: launch(score_token_split_kernel<1>, grid, dim3(kSplitThreads), 0, s, a); break;
         case 2: launch(score_token_split_kernel<2>, grid, dim3(kSplitThreads), 0, s, a); break;

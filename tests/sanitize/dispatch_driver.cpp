@@ -177,16 +177,25 @@ static void split() {
     a.n_kv_heads = 2, a.head_dim = 128;                          // one tile of tokens on longer keys: up to 1700 - 50 t_q units
     CHECK(tiles(28, 58 * 16, 1) == 1 && tiles(28, 59 * 16, 1) == 0 && tiles(28, 32 * 16, 16) == 1 && tiles(28, 33 * 16, 16) == 0);
     CHECK(tiles(28, 28 * 16, 17) == 0 && tiles(65535, 0x7fffffff, 1) == 0);
-    a.n_kv_heads = 4;                                            // two and three tiles, the last mostly empty: up to 168 and 257 to 308 units of 64
+    a.n_kv_heads = 4;                                            // two and three tiles, the last mostly empty: up to 168 units of 64, three from 257 to 308 too
     for (int t_q : {17, 25, 26, 32, 33, 38, 39, 48, 49, 64, 65})
         for (int groups : {6 * 64, 6 * 64 + 1, 9 * 64, 9 * 64 + 1, 11 * 64, 11 * 64 + 1})
-            CHECK(tiles(28, groups, t_q) == ((groups <= 6 * 64 || (groups > 9 * 64 && groups <= 11 * 64)) ? (t_q <= 25 ? 2 : t_q >= 33 && t_q <= 38 ? 3 : 0) : 0));
+            CHECK(tiles(28, groups, t_q) == (t_q >= 33 && t_q <= 38 && (groups <= 6 * 64 || (groups > 9 * 64 && groups <= 11 * 64)) ? 3 : t_q <= 25 && groups <= 6 * 64 ? 2 : 0));
     CHECK(tiles(65535, 0x7fffffff, 17) == 0);
     a.n_kv_heads = 8;                                            // 1024 channels: up to 2000 - 75 t_q, from 12 tokens on as before
     CHECK(tiles(25, 77 * 16, 1) == 1 && tiles(25, 78 * 16, 1) == 0 && tiles(25, 44 * 16, 12) == 1 && tiles(25, 45 * 16, 12) == 0 && tiles(25, 42 * 16, 13) == 1 && tiles(25, 43 * 16, 13) == 0);
     a.n_kv_heads = 31, a.head_dim = 8;
     CHECK(tiles(28, 58 * 16, 1) == 0 && tiles(28, 6 * 64, 17) == 0);
     a.n_kv_heads = a.head_dim = 0;
+    auto width = [&](int n_layers, int n_groups, int t_q) {      // units of 32 groups: more than 256 of 64, at most 768
+        a.n_layers = n_layers, a.n_groups = n_groups, a.t_q = t_q;
+        return gemm_width(a);
+    };
+    for (int t_q : {1, 16, 17, 32, 33, 48, 49, 64, 65, 1000}) {
+        const bool pairs = t_q > 16 && (t_q <= 32 || t_q > 48);
+        CHECK(width(1, 256 * 64, t_q) == 64 && width(1, 256 * 64 + 1, t_q) == (pairs ? 32 : 64) && width(1, 768 * 32, t_q) == (pairs ? 32 : 64) && width(1, 768 * 32 + 1, t_q) == 64);
+        CHECK(width(65535, 0x7fffffff, t_q) == 64);
+    }
 
     // the fold inside: layers, groups, query tokens, KV heads, query heads of each, head_dim -> tiles of a pass, or 0
     auto fold = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d, int type = TOM_BF16) {

@@ -101,8 +101,15 @@ def test_one_tile_of_tokens_on_long_keys(oqm, tq, units):
         _check(oqm, 10, 4, 3, 256, T, tq, tokens=False)
 
 
-# two and three tiles whose last is mostly empty, where the 64 x 64 form would leave a third of one round or two fifths of two idle: up to 168 and from 257 to 308 units of 64
+# two and three tiles whose last is mostly empty, where the 64 x 64 form would leave a third of one round idle, up to 168 units of 64, or, three tiles, two fifths of two, 257 to 308
 @pytest.mark.parametrize("tq", (17, 25, 26, 33, 38, 39))
 def test_nearly_empty_tiles_on_long_keys(oqm, tq):
     for i, T in enumerate((6 * 64, 6 * 64 + 1, 9 * 64, 9 * 64 + 1, 11 * 64, 11 * 64 + 1)):
         _check(oqm, 28, 4, 3, 128 + 8 * (i % 2), T, tq, tokens=i % 2 == 0, cosine=i != 2)
+
+
+# units of 32 groups: from 257 units of 64 to 768 of 32, one, two or four token tiles in the last pass; launches on both sides
+@pytest.mark.parametrize("tq", (17, 32, 33, 49, 64, 65, 96, 100, 130))
+def test_units_of_32_groups(oqm, tq):
+    for i, T in enumerate((25 * 64, 25 * 64 + 1, 26 * 64 - 31, 26 * 64 - 32, 76 * 32 - 1, 76 * 32, 76 * 32 + 1)):
+        _check(oqm, 10, (5, 3)[i % 2], 3, (8, 40)[i % 2], T, tq, cosine=i % 3 != 0, tokens=i != 1)
