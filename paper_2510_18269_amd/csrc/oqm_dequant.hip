@@ -155,6 +155,10 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
 // 28 layers x 4 heads x 196 x 128 x 64 groups (944 MB), codes and pairs of random bits, one store, us: chunks 158, one piece 185, two 156.2, three 157, four 158.6; an arithmetic-free
 // kernel of the same order with nothing but this shape's constants 153.4 (two adjacent pieces 157; runs of 16 workgroups per XCD 155; 512 threads 156, 1024 172; index loads per lane 174).
 // 128 groups (quant-groups of 32, 2.0 GB) 337 -> 325; 37 x 256, 700 MB of output 162 -> 152; 61 x 96 168 -> 162.
+// The last round of a head shares what is left of its pieces, first half and second half, among as few workgroups: with whole rounds alone a head of 785 pieces (64 groups behind a prefix)
+// left seven of 400 workgroups idle, one of 304 16 of 160.  Tiles / whole rounds / this, three stores in turn: 64 groups behind 14 rows 157.5 / 159.0 / 156.2, in buffers that start 512 bytes behind a
+// piece 157.5 / 157.0 / 156.0, 72 176.4 / 180.9 / 174.5; 8 heads of 50 x 128, 97 groups 123.8 / 126.7 / 120.2, behind 14 rows 125.5 / 120.8 / 119.8.  Rounds that start on 32 KB of every head, so that an XCD keeps
+// to the same eighth of memory over all heads: 159 at 64 groups behind 14 rows, 177.7 at 72.
 // What the kernel needs of a DequantArgs, made on the host.
 struct PieceArgs {
     const char *codes, *meta;  // of the first layer asked for
@@ -188,13 +192,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const char* base, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)bytes, 0x00020000);
 }
 
-// grid (a multiple of 8 workgroups for the pieces, then prefix blocks; K heads, then V heads; layer).  ALL: every stored group is taken in order, and
+// grid (a workgroup for two pieces, then prefix blocks; K heads, then V heads; layer).  ALL: every stored group is taken in order, and
 // these indices are written.
 template <typename OUT, int N, int BITS, bool MB, bool PAST_CACHES, bool ALL>
 __global__ void __launch_bounds__(kBlock) dequant_gather_pieces_kernel(const PieceArgs a) {
     constexpr uint32_t CW = BITS * N / 8;  // bytes of packed codes per item
     constexpr uint32_t CMASK = (1u << BITS) - 1u;
-    constexpr uint32_t kItemBytes = 16, kApart = kXcds * kBlock;  // items between a workgroup's pieces
+    constexpr uint32_t kItemBytes = 16;
     typedef typename MetaPair<MB>::type meta_pair;  // two float32, or two bfloat16 in one word
     // everything the addresses need is requested at once, not behind the index
     asm volatile("" ::"s"(a.codes), "s"(a.meta), "s"(a.idx), "s"(a.k_out), "s"(a.v_out), "s"(a.code_plane), "s"(a.meta_plane), "s"(a.head_out_bytes),
@@ -210,17 +214,19 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_pieces_kernel(const Pie
     const uint32_t lane = threadIdx.x & 63u, ti = a.tile_items, last = a.k_eff - 1u;
     // items between the start of the first piece and the rows
     const uint32_t lead = (((uint32_t)(uintptr_t)out0 + head * (uint32_t)a.head_out_bytes) & (kBlock * kItemBytes - 1u)) / kItemBytes;
+    // items between a workgroup's pieces; the last round of a head has what is left of its workgroups
+    const uint32_t round = blockIdx.x & ~(kXcds - 1u), apart = min(kXcds, a.blocks - round) * kBlock;
     // first item of the wave, of the first piece; below zero in front of the rows
-    const uint32_t first = ((blockIdx.x & ~(kXcds - 1u)) * kPieces + (blockIdx.x & (kXcds - 1u))) * kBlock +
+    const uint32_t first = (round * kPieces + (blockIdx.x & (kXcds - 1u))) * kBlock +
                            ((uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x) & ~63u) - lead;
-    if ((int)first >= (int)(a.k_eff * ti)) return;  // uniform in a wave: the last workgroups of a head
+    if ((int)first >= (int)(a.k_eff * ti)) return;  // uniform in a wave: a last piece that only other heads have
     typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;  // not written by this launch where it is read
     typedef const __attribute__((address_space(4))) char* scalar_bytes;
     const scalar_bytes idx = (scalar_bytes)(uintptr_t)a.idx;
     uint32_t r[kPieces], t[kPieces][2];  // rank of the wave's first tile; groups of it and of the next
 #pragma unroll
     for (int p = 0; p < kPieces; ++p) {
-        r[p] = min(div_by((uint32_t)max((int)(first + p * kApart), 0), ti, a.inv_tile_items), last);
+        r[p] = min(div_by((uint32_t)max((int)(first + p * apart), 0), ti, a.inv_tile_items), last);
         const uint32_t next = min(r[p] + 1u, last);
         t[p][0] = ALL ? r[p] : *(scalar_ptr)(idx + (li * a.k + r[p]) * 4u);
         t[p][1] = ALL ? next : *(scalar_ptr)(idx + (li * a.k + next) * 4u);
@@ -233,7 +239,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_pieces_kernel(const Pie
     meta_pair sm[kPieces];
 #pragma unroll
     for (int p = 0; p < kPieces; ++p) {
-        const uint32_t item = first + p * kApart + lane, at = item - r[p] * ti;
+        const uint32_t item = first + p * apart + lane, at = item - r[p] * ti;
         const bool second = (int)at >= (int)ti;
         // offsets of the tile that item 0 of the wave's first tile would have
         const uint32_t c0 = t[p][0] * a.code_group, c1 = t[p][1] * a.code_group - a.code_tile;
@@ -258,7 +264,7 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_pieces_kernel(const Pie
     if (ALL && blockIdx.y == 0) {
 #pragma unroll
         for (int p = 0; p < kPieces; ++p) {
-            const uint32_t item = first + p * kApart + lane, at = item - r[p] * ti, rank = r[p] + (at == ti ? 1u : 0u);
+            const uint32_t item = first + p * apart + lane, at = item - r[p] * ti, rank = r[p] + (at == ti ? 1u : 0u);
             if ((int)item >= 0 && (at == 0u || at == ti) && rank <= last) const_cast<int32_t*>(a.idx)[(uint64_t)li * a.k + rank] = (int32_t)rank;
         }
     }
@@ -290,7 +296,7 @@ hipError_t launch_pieces(const DequantArgs& a, uint32_t prefix_blocks, hipStream
     f.sys_v = a.sys_v;
     f.prefix_bytes = (uint64_t)a.prefix_bytes;
     f.blocks = (uint32_t)piece_blocks(a);
-    const dim3 grid(f.blocks + (prefix_blocks + kXcds - 1) / kXcds * kXcds, 2 * f.heads, a.n_layers);
+    const dim3 grid(f.blocks + prefix_blocks, 2 * f.heads, a.n_layers);
     auto go = [&](auto bits, auto mb, auto past) {
         constexpr int B = decltype(bits)::value;
         constexpr bool M = decltype(mb)::value, C = decltype(past)::value;

@@ -282,8 +282,8 @@ inline int64_t pieces_of_head(const DequantArgs& a) {
     const int64_t part = starts % kPieceBytes ? kBlock - 1 : 0;
     return ((int64_t)a.k_eff * a.tile_items + part + kBlock - 1) / kBlock;
 }
-// ... and its workgroups: whole rounds of the XCDs.
-inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + kXcds * kPieces - 1) / (kXcds * kPieces) * kXcds; }
+// ... and its workgroups.
+inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + kPieces - 1) / kPieces; }
 
 // Whether the gather goes by aligned pieces of its output instead of by tiles (dequant_gather_pieces_kernel).  Large launches on the head_dim axis alone: the pieces are
 // written in a better order, but a wave of them has a longer way to its first load, which smaller launches do not hide.  28 layers, 600 groups and more stored, us, by tiles / by pieces, three stores
@@ -293,8 +293,7 @@ inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + 
 // ones, 1400 265 / 282 (263 / 217); of 4-bit codes 700 151 / 158.
 // A tile of one pass or less leaves lanes of its workgroup idle, and the workgroup has nothing to hide its loads behind: 20 x 64 (160 items), 30 MB of output 10.0 / 8.1 (9.8 / 6.3), 100 30.5 / 23.6, 350 125 / 81;
 // 20 x 80 (200) 29 8.9 / 8.8 (8.3 / 6.7), 150 51.1 / 44.9 (34.6 / 35.3); 28 x 64 (224) 59 14.3 / 16.1, 149 47.1 / 42.1 (31.9 / 33.3); 16 x 128 (256) 60 14.4 / 14.3, 150 44.6 / 41.3 (32.5 / 33.6), 350 96.1 / 87.2 (83.2 / 74.5).
-// Other tiles not where the last round of a head's workgroups leaves more than a 64th of all idle: 8 heads, 50 tokens, 97 groups (304 pieces in 20 rounds of 16) 123.2 / 127.9, 92 groups (288 in 18) 117.3 / 114.8; 7 heads of 196, 28
-// groups (344 in 22) 119.9 / 122.0.  The pieces take 32-bit offsets, and a wave at most two tiles.
+// The pieces take 32-bit offsets, and a wave at most two tiles.
 inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t prefix_blocks) {
     const int64_t items = (int64_t)a.k_eff * a.tile_items, heads = 2 * (int64_t)a.n_layers * a.n_kv_heads, out = heads * items * 16;
     if (a.qaxis == TOM_QAXIS_TOKENS || a.tile_items < 64) return false;
@@ -302,8 +301,6 @@ inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t pref
         if (out < (a.tile_items <= 208 ? 30000000 : 150000000)) return false;
     } else {
         if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
-        const int64_t pieces = pieces_of_head(a);
-        if ((kPieces * piece_blocks(a) - pieces) * 64 > pieces) return false;
     }
     constexpr int64_t kMost = 1LL << 31;
     const int64_t code_tile = (int64_t)a.tile_items * (is_16_bit ? 8 : 4) * a.bits / 8;

@@ -3,6 +3,7 @@
 // overlap, adjoin or lie apart.  No device is touched: the addresses are fakes.  Exit status 0 = clean.
 #include <cstdio>
 #include <utility>
+#include <vector>
 
 #include "oqm_dispatch.h"
 
@@ -316,7 +317,7 @@ static void gather() {
     CHECK(!past(56, 200) && past(58, 200) && !past(40, 1024) && past(48, 1024) && !past(59, 3600) && past(60, 3600));
     CHECK(!past(64, 64) && past(64, 65 + 135) && !past(72, 72) && past(80, 80) && !past(64, 1024, 7) && past(256, 1024, 7));
 
-    // 400 MB of 16-bit output; with float32 output 2-bit codes between 300 MB and 1 GB.  39 groups of 196 x 128: 478 pieces, two short of 30 rounds
+    // 400 MB of 16-bit output; with float32 output 2-bit codes between 300 MB and 1 GB.  39 groups of 196 x 128: 438 MB
     auto pieces = [&](int64_t k_eff, bool is_16_bit, int bits, bool meta_bf16 = false, int n_layers = 28, int tokens = 196, int capacity = 1024, int k = 0, uint32_t prefix_blocks = 0) {
         DequantArgs q{};
         q.n_layers = n_layers, q.n_kv_heads = 4, q.head_dim = 128, q.k_eff = (int32_t)k_eff, q.k = k ? k : (int32_t)k_eff, q.bits = bits, q.meta_bf16 = meta_bf16;
@@ -328,7 +329,7 @@ static void gather() {
         return yes;
     };
     CHECK(!pieces(39, true, 4, false, 25) && pieces(39, true, 4, false, 26) && pieces(39, true, 4, true) && pieces(39, true, 2) && !pieces(39, true, 2, true));
-    CHECK(!pieces(37, true, 4) && !pieces(38, true, 4) && pieces(40, true, 4) && !pieces(41, true, 4));   // 454, 466, 490 and 503 pieces in 29 to 32 rounds
+    for (int k = 36; k < 129; ++k) CHECK(pieces(k, true, 4));                                  // whatever the last round of a head is left with
     CHECK(!pieces(39, false, 2, false, 9) && pieces(39, false, 2, true, 10) && pieces(39, false, 2, false, 31) && !pieces(39, false, 2, false, 32) && !pieces(39, false, 4, false, 20));
     CHECK(pieces(3000, true, 4, false, 28, 4) && !pieces(3000, true, 4, false, 28, 3));        // 64 items: a wave meets two tiles at most
     CHECK(pieces(39, true, 4, false, 28, 196, 42000) && !pieces(39, true, 4, false, 28, 196, 43000));   // codes of a (layer, K|V) against 2^31 bytes
@@ -341,13 +342,43 @@ static void gather() {
     starts.k_eff = 64, starts.tile_items = 196 * 16, starts.head_out_bytes = 64 * 196 * 256;
     CHECK(pieces_of_head(starts) == 784 && piece_blocks(starts) == 392);
     starts.k_out = at(1 << 24), starts.v_out = at((1 << 25) + 16);
-    CHECK(pieces_of_head(starts) == 785 && piece_blocks(starts) == 400);
+    CHECK(pieces_of_head(starts) == 785 && piece_blocks(starts) == 393);
     starts.prefix_bytes = 4080;
     CHECK(pieces_of_head(starts) == 785);
     starts.k_out = at((1 << 24) + 16);
     CHECK(pieces_of_head(starts) == 784);
     starts.head_out_bytes += 16;
     CHECK(pieces_of_head(starts) == 785);
+    // 64 groups behind 14 prefix rows, and in buffers that start 512 bytes behind a piece, as without either
+    DequantArgs behind{};
+    behind.n_layers = 28, behind.n_kv_heads = 4, behind.head_dim = 128, behind.k_eff = behind.k = 64, behind.bits = 4, behind.qaxis = TOM_QAXIS_HEAD_DIM;
+    behind.tile_items = 196 * 16, behind.tile_meta_bytes = 196 * 2 * 8, behind.plane_tiles = 1024 * 4;
+    behind.k_out = at(1 << 24), behind.v_out = at(1ull << 40);
+    for (int rows : {0, 1, 14, 16}) {
+        behind.prefix_bytes = rows * 256, behind.head_out_bytes = behind.prefix_bytes + 64 * 196 * 256;
+        for (int off : {0, 512}) {
+            behind.k_out = at((1 << 24) + off);
+            CHECK(gather_by_pieces(behind, true, 1));
+        }
+    }
+    // every piece of a head is taken once: rounds of 16 pieces by eight workgroups, the last one by what is left of them
+    for (int items : {1, 255, 256, 257, 784 * 256, 785 * 256, 13 * 256 + 1})
+        for (int more = 0; more < 40; ++more) {
+            starts = DequantArgs{};
+            starts.k_eff = 1, starts.tile_items = (uint32_t)(items + more * 256);
+            const int blocks = (int)piece_blocks(starts), pieces = (int)pieces_of_head(starts);
+            std::vector<int> taken(pieces + 1);
+            for (int x = 0; x < blocks; ++x) {
+                const int round = x & ~7, apart = blocks - round < 8 ? blocks - round : 8;
+                for (int q = 0; q < kPieces; ++q) {
+                    const int at_piece = round * kPieces + (x & 7) + q * apart;
+                    if (at_piece <= pieces) ++taken[at_piece];
+                    CHECK(at_piece <= pieces);
+                }
+            }
+            for (int q = 0; q < pieces; ++q) CHECK(taken[q] == 1);
+            CHECK(taken[pieces] == (pieces & 1));
+        }
 
     auto joins = [&](uint64_t sys_k, uint64_t sys_v) {
         a.n_layers = 2, a.n_kv_heads = 4;

@@ -1,6 +1,6 @@
 """The gather by 4 KB pieces of its output (large launches of the head_dim axis) against the gather by tiles, bit for bit.
 
-Tiles of 1 to 12 pieces that are and are not whole waves, whole pieces or aligned, prefix rows that move the rows off a
+Tiles of 1 to 12 pieces that are and are not whole waves, heads whose last round of pieces is whole, a part or a single piece, whole pieces or aligned, prefix rows that move the rows off a
 piece's start, indices that name no stored group (their rows are left alone), repeated indices, and the one-call form that takes
 every group in order and writes the indices.  The launches by tiles are small ones of the same groups, which the oracle covers
 elsewhere; a launch above the line of the rule is large, hence the repeated groups.  And float32 tiles of the token axis, whose chunks
@@ -97,6 +97,39 @@ def test_pieces_against_tiles(oqm, G, d, gs, L, heads, prefix, out, bits, meta):
                 expect = w[li][:, idx[li].clamp(0, T - 1).long()]
                 expect[:, ~stored[li]] = -3.0
                 assert torch.equal(raw(body.contiguous()), raw(expect))
+    finally:
+        mem.close()
+
+
+@pytest.mark.parametrize("prefix, off", ((0, 0), (14, 0), (0, 512), (3, 16)))
+def test_last_round_of_a_head(oqm, prefix, off):
+    """Whole rounds of 16 pieces and 1 to 15 left over, behind prefix rows and in buffers that start behind a piece's start."""
+    L, heads, G, d, T = 2, 3, 49, 128, 5     # 3.06 pieces a tile
+    mem, dt = filled(oqm, L, heads, d, G, 64, T, "bf16", 4, "f32", prefix + off)
+    try:
+        want = by_tiles(oqm, mem, dt, L, heads, d, G, T)
+        gen = torch.Generator(device="cuda").manual_seed(prefix)
+        k0 = line("bf16", G, d) // (2 * L * heads * G * d * 2) + 1
+        left = set()
+        for k in range(k0, k0 + 21):
+            idx = torch.randint(0, T, (L, k), generator=gen, device="cuda", dtype=torch.int32)
+            shape = (L, heads, prefix + k * G, d)
+            n = L * heads * (prefix + k * G) * d
+            room = [torch.full((n + off // 2 + 64,), -3.0, dtype=dt, device="cuda") for _ in range(2)]
+            got = [r[off // 2:off // 2 + n].view(shape) for r in room]
+            if prefix:
+                sys = [torch.randn((L, heads, prefix, d), generator=gen, device="cuda").to(dt) for _ in range(2)]
+                oqm.tom_oqm_assemble_active(mem.handle, 0, L, idx, k, k, prefix, *sys, *got)
+                for g, s in zip(got, sys):
+                    assert torch.equal(raw(g[:, :, :prefix].contiguous()), raw(s))
+            else:
+                oqm.tom_oqm_dequant_gather(mem.handle, 0, L, idx, k, k, *got)
+            for r, g, w in zip(room, got, want):
+                assert bool((r[:off // 2] == -3.0).all()) and bool((r[off // 2 + n:] == -3.0).all())
+                for li in range(L):
+                    assert torch.equal(raw(g[li, :, prefix:].view(heads, k, G, d)), raw(w[li][:, idx[li].long()]))
+            left.add((k * G * d * 2 // 4096 + (k * G * d * 2 % 4096 > 0)) % 16)
+        assert len(left) == 16
     finally:
         mem.close()
 
