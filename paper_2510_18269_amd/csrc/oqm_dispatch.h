@@ -291,14 +291,17 @@ inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + 
 // (40.1 / 40.5), 450 104.5 / 102.6 (89.6 / 87.2), 700 155.2 / 151.4; 61 x 96 450 108.7 / 104.9 (93.3 / 91.8), 700 167.8 / 162.4; 37 x 256 450 105.4 / 102.7, 700 162.3 / 152.2.  2-bit codes, 196 x 128 450 104.8 / 104.8 (80.4 / 79.6),
 // 61 x 96 112.0 / 107.4 (84.6 / 83.7), but with bfloat16 pairs 50 x 128 92.7 / 98.9.  float32 output of 2-bit codes: 196 x 128 400 71.7 / 61.2 (69.6 / 61.1), 700 138 / 110 with bfloat16 pairs, 149 / 152 (130 / 109) with float32
 // ones, 1400 265 / 282 (263 / 217); of 4-bit codes 700 151 / 158.
-// A tile of one pass or less leaves lanes of its workgroup idle, and the workgroup has nothing to hide its loads behind: 20 x 64 (160 items), 30 MB of output 10.0 / 8.1 (9.8 / 6.3), 100 30.5 / 23.6, 350 125 / 81;
-// 20 x 80 (200) 29 8.9 / 8.8 (8.3 / 6.7), 150 51.1 / 44.9 (34.6 / 35.3); 28 x 64 (224) 59 14.3 / 16.1, 149 47.1 / 42.1 (31.9 / 33.3); 16 x 128 (256) 60 14.4 / 14.3, 150 44.6 / 41.3 (32.5 / 33.6), 350 96.1 / 87.2 (83.2 / 74.5).
+// A tile of one pass or less leaves lanes of its workgroup idle, and the workgroup has nothing to hide its loads behind, hence lines of their own at 16-bit output, whatever the codes and pairs.
+//   Up to 208 items, 30 MB: 16 x 64 (128 items) 32 MB 12.5 / 7.6 (12.6 / 6.4), 390 147 / 85 (129 / 72); 13 x 128 (208) 32 8.9 / 8.2 (8.6 / 6.3), 390 123 / 88 (82 / 78); the worst, 20 x 80 (200) in quant-groups of 16, 32 9.5 / 9.5
+//     (8.9 / 6.8), 150 50.1 / 43.1 (34.8 / 35.6), 300 101.6 / 73.8 (68.1 / 69.0); in 2 bits 200 62.8 / 51.2 (45.1 / 43.2), with bfloat16 pairs 45.2 / 40.2 (44.5 / 39.9).
+//   Up to 256, 170 MB: below it the nearly full tiles lose in both columns, 31 x 64 (248) 150 MB 30.6 / 33.0 (29.5 / 33.4), 15 x 128 (240) 31.1 / 32.7 (29.7 / 32.8), 16 x 128 (256) 158 31.6 / 32.0 (30.3 / 33.2); above it three stores in turn
+//     gain more than the same question again loses: 31 x 64 174 38.6 / 36.6 (33.7 / 36.2), 200 51.2 / 41.4 (38.4 / 41.1), 390 107.5 / 88.3 (72.7 / 78.4), 600 160 / 139 (160 / 139); 16 x 128 200 46.2 / 40.8 (37.5 / 39.5), 390 104.6 / 84.1 (71.3 / 72.1).
 // The pieces take 32-bit offsets, and a wave at most two tiles.
 inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t prefix_blocks) {
     const int64_t items = (int64_t)a.k_eff * a.tile_items, heads = 2 * (int64_t)a.n_layers * a.n_kv_heads, out = heads * items * 16;
     if (a.qaxis == TOM_QAXIS_TOKENS || a.tile_items < 64) return false;
     if (is_16_bit && a.tile_items <= kBlock) {
-        if (out < (a.tile_items <= 208 ? 30000000 : 150000000)) return false;
+        if (out < (a.tile_items <= 208 ? 30000000 : 170000000)) return false;
     } else {
         if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
     }

@@ -335,8 +335,8 @@ static void gather() {
     CHECK(pieces(39, true, 4, false, 28, 196, 42000) && !pieces(39, true, 4, false, 28, 196, 43000));   // codes of a (layer, K|V) against 2^31 bytes
     CHECK(!pieces(42800, true, 4) && pieces(42700, true, 4));                                  // rows of a head
     CHECK(!pieces(39, true, 4, false, 28, 196, 1024, 1 << 25) && !pieces(39, true, 4, false, 28, 196, 1024, 0, 1u << 23));
-    // tiles of up to one pass: 208 items from 30 MB up, 256 from 150
-    CHECK(pieces(41, true, 2, true, 28, 13) && !pieces(40, true, 4, false, 28, 13) && pieces(164, true, 4, false, 28, 16) && !pieces(163, true, 4, false, 28, 16) && !pieces(164, true, 4, false, 28, 17));
+    // tiles of up to one pass: 208 items from 30 MB up, 256 from 170
+    CHECK(pieces(41, true, 2, true, 28, 13) && !pieces(40, true, 4, false, 28, 13) && pieces(186, true, 4, false, 28, 16) && !pieces(185, true, 4, false, 28, 16) && !pieces(186, true, 4, false, 28, 17));
     // the first piece is a part where the rows of some head do not start on a piece
     DequantArgs starts{};
     starts.k_eff = 64, starts.tile_items = 196 * 16, starts.head_out_bytes = 64 * 196 * 256;

@@ -18,7 +18,7 @@ LINE = {"f32": 300_000_000, "bf16": 400_000_000, "f16": 400_000_000}
 def line(out, G, d):
     """Bytes of output from which on the launch goes by pieces."""
     items = G * d // 8
-    return LINE[out] if out == "f32" or items > 256 else 30_000_000 if items <= 208 else 150_000_000
+    return LINE[out] if out == "f32" or items > 256 else 30_000_000 if items <= 208 else 170_000_000
 
 
 @pytest.fixture(scope="module")
