@@ -132,15 +132,30 @@ inline int gemm_width(const ScoreArgs& a) {
 }
 
 // Tiles of 16 query tokens per pass of score_token_fold_kernel (1 to 4), or 0: the fold is a launch of its own, and split_tiles decides about the contraction.
-// What a workgroup has to convert (query heads per KV head x tokens of all passes x channels, twice that in float32) against the launch that is saved.  Whole question of bf16 at 4 groups, launch of its own / inside.
-// Up to 256 (layer, 16-group) units, one workgroup a compute unit: 16 heads on 4 of 128 x 64 tokens (131 K) 24.7 / 19.5 us, 32 on 8 of 256 x 64 (524 K) 62.0 / 51.5; more than four heads, loaded in turns: 28 on 4 of 128 x 16 (57 K)
-// 13.0 / 11.9, 32 (115 K) 15.1 / 15.4, 64 21.7 / 25.4; float32 16 (115 K) 13.7 / 16.1.  257 to 512, two workgroups of at most two tiles a compute unit, three of up to two heads: 16 on 4 of 128 x 32 (66 K) 22.2 / 19.6, 64 (131 K) 34.1 / 31.2, but
-// three tiles in two passes of two 26.6 / 30.3; 8 on 4 45 tokens in one pass of three 26.5 / 23.0; 28 on 4 x 16 (57 K) 17.0 / 16.5, 24 20.3 / 24.0; 14 on 2 of 128 x 32 (57 K) 17.4 / 16.7.  Above, short questions of up to two heads on keys that are not the shortest: 4 on 4 of 128
-// x 32, 588 units 27.9 / 21.9, 1064 35.5 / 30.0, 1792 35.9 / 38.7; 2 on 2 of 96, 900 20.7 / 19.1; 2 on 1 of 64, 1064 14.4 / 15.6.  A few tokens on long keys read less folded: 1 token, 32 on 8 of 256 21.3 / 24.1, 16 on 8 of 128 (504 units) 22.3 / 23.3, 10 on 5 of 256 17.4 / 17.0.
+// What a workgroup has to convert (query heads per KV head x tokens of all passes x channels, twice that in float32) is set against the launch that is saved. With the
+// cosine a workgroup also sums what it folded over the tokens; a fold of its own is cut into parts where 64 divides the head (`cut`), and takes longer
+// with more workgroups (`fold_blocks`).  Fold and scores alone, us, launch of its own / inside; a line stands between the last two of each row.
+//   up to 256 (layer, 16-group) units, one workgroup a compute unit
+//     one and two heads, and three and four in 16 bits without the cosine or not `cut`, 600 K: never slower as far as measured (16 on 8 of 256 x 55 tokens, 262 K, 41.7 / 34.7)
+//     three and four in 16 bits, cosine, `cut`: 16 on 4 of 128 x 123 (262 K) 21 % gained, 24 on 8 of 128 x 91 (295 K) 34.9 / 36.2, 12 on 3 of 256 x 98 (393 K) 33.1 / 36.8.  From 1024 channels on: 32 on 8 of 128 x 14 (65 K) 10 % gained, 24 on 8 of
+//       128 x 18 (98 K) 14.0 / 14.4; behind a fold of more than 256 workgroups 32 on 8 of 128 x 60 (262 K) 24 % gained
+//     more than four in 16 bits, in turns, 100 K; cosine, `cut`, from 1024 channels on: 40 on 8 of 128 x 9 (82 K) 10.8 / 12.7
+//     three and four in float32, in turns: `cut` 8 on 2 of 128 x 49 (131 K) 11.6 / 10.9, 12 on 3 of 128 x 47 (147 K) 12.9 / 13.1, 16 on 4 of 128 x 38 (197 K) 13.2 / 15.1, cosine, from 1024 channels on 24 on 8 of 128 x 16 (98 K) 12.0 / 12.7; not `cut`
+//       12 on 3 of 112 x 105 (344 K) 23.2 / 18.7, 20 on 5 of 88 x 117 (451 K) 11 % lost, behind a fold of 224 workgroups 24 on 8 of 80 x 119 (492 K) 38.1 / 31.3, of whole blocks of 32 channels 32 on 8 of 96 x 26 (197 K) 14.0 / 14.6; behind a fold of 208 workgroups 16 on 4 of 256 x 25 (262 K)
+//       15.9 / 17.6, of 280 15 on 5 of 128 x 63 (246 K) 26.9 / 20.9
+//     more than four in float32, 100 K: 21 on 3 of 112 x 11 (75 K) 8.8 / 7.2; cosine, `cut`, from 288 channels on 18 on 3 of 128 x 10 (74 K) 8.6 / 7.7, 24 on 4 of 128 x 12 (98 K) 9.1 / 9.6; an odd one leaves a turn half empty: 15 on 3 of 128 x
+//       5 (61 K) 8.3 / 7.1, 35 on 5 of 64 x 13 (72 K) 8.0 / 8.2
+//   257 to 512, two workgroups of at most two tiles a compute unit, three of up to two heads; not where a pass would be partly idle (16 on 4 of 128 x 45, in two passes of two, whole question 26.6 / 30.3)
+//     up to four heads 270 K; cosine, `cut`, three and four from 768 channels on: 32 on 8 of 128 x 14 (66 K) gained, 12 on 3 of 256 x 20 (98 K) 18.6 / 19.2, behind a fold of more than 112 workgroups 32 on 8 of 128 x 22 (131 K) 25.6 / 23.6
+//     in turns 60 K; 16 bits, cosine, `cut`: 16 on 2 of 128 x 8 (33 K) 9.3 / 8.1, 12 on 1 of 128 x 28 (49 K) 9.5 / 10.1
+//   above, short questions of up to two heads on keys that are not the shortest, whole question: 4 on 4 of 128 x 32, 588 units 27.9 / 21.9, 1064 35.5 / 30.0, 1792 35.9 / 38.7; 2 on 2 of 96, 900 20.7 / 19.1; 2 on 1 of 64, 1064 14.4 / 15.6
+// Few tokens on long keys: a tile is folded whole however empty it is.  1 token, 32 on 8 of 256 21.3 / 24.1, 16 on 8 of 128 (504 units) 22.3 / 23.3, 10 on 5 of 256 17.4 / 17.0; 9 to 11 tokens, cosine, 16 on 8 of 256 15.2 / 16.6 (dot
+// 15.0 / 12.4), 8 on 8 of 256 behind a fold of 896 workgroups 19.2 / 16.1.
 // Scores that share memory with the query need the separate fold, as above.
 inline int fold_tiles(const ScoreArgs& a) {
     const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers, channels = (int64_t)a.n_kv_heads * a.head_dim;
     const bool is_f32 = a.q_dtype == TOM_F32, few = units <= 256, most_units = units <= 512;
+    const bool cosine = a.sim == TOM_SIM_COSINE, cut = a.head_dim % 64 == 0;
     const int r = a.n_q_heads / a.n_kv_heads, heads = is_f32 ? 2 * r : r;
     if (units > 1100 || channels > 3072) return 0;  // q-bar sums: at most 24 KB of LDS
     if (!most_units && (heads > 2 || a.t_q > 32 || channels < 192)) return 0;
@@ -148,8 +163,26 @@ inline int fold_tiles(const ScoreArgs& a) {
     const int most = few ? 4 : heads <= 2 && most_units ? 3 : 2;
     const int tiles = (a.t_q + 15) / 16, passes = (tiles + most - 1) / most, of_pass = (tiles + passes - 1) / passes;
     if (!few && passes * of_pass > tiles) return 0;
-    const bool in_turns = r > 4 || (is_f32 && r > 2 && !few);
-    if (heads * channels * 16 * of_pass * passes > (in_turns ? (few ? 100000 : 60000) : (few ? 600000 : 270000))) return 0;
+    const int64_t converted = heads * channels * 16 * of_pass * passes;
+    const int64_t fold_blocks = (int64_t)a.n_layers * a.n_kv_heads * (cut ? a.head_dim / 64 : 1);  // of the launch that is saved
+    if (a.t_q < 16 && cosine && channels >= 2048 && fold_blocks <= 512) return 0;
+    int64_t most_converted = 600000;
+    if (!few) {
+        if (r > 4 || (is_f32 && r > 2)) most_converted = cosine && cut && !is_f32 ? 45000 : 60000;
+        else most_converted = cosine && cut && r > 2 && channels >= 768 && fold_blocks <= 112 ? 90000 : 270000;
+    } else if (is_f32 && r > 2) {
+        if (r > 4) most_converted = !cosine || !cut || channels < 288 ? 100000 : r % 2 ? 66000 : 76000;
+        else if (a.head_dim % 32 != 0) most_converted = fold_blocks > 210 ? 600000 : 400000;
+        else if (fold_blocks > 210) most_converted = 280000;
+        else if (cut) most_converted = cosine && channels >= 1024 ? 90000 : 140000;
+        else most_converted = 190000;
+    } else if (r > 4) {
+        most_converted = cosine && cut && channels >= 1024 ? 80000 : 100000;
+    } else if (r > 2 && cosine && cut) {
+        if (channels >= 1024) most_converted = fold_blocks > 256 ? 270000 : 80000;
+        else most_converted = fold_blocks > 112 ? 600000 : 290000;
+    }
+    if (converted > most_converted) return 0;
     // kept small by the line above
     const uint64_t query_bytes = (uint64_t)a.n_layers * (uint64_t)a.n_q_heads * (uint64_t)a.t_q * (uint64_t)a.head_dim * (is_f32 ? 4u : 2u);
     if (!apart(a.q, query_bytes, a.scores, score_span(a.score_stride, a.n_layers, a.n_groups))) return 0;

@@ -199,9 +199,9 @@ static void split() {
     }
 
     // the fold inside: layers, groups, query tokens, KV heads, query heads of each, head_dim -> tiles of a pass, or 0
-    auto fold = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d, int type = TOM_BF16) {
+    auto fold = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d, int type = TOM_BF16, int sim = TOM_SIM_DOT) {
         ScoreArgs b{};
-        b.n_layers = n_layers, b.n_groups = n_groups, b.t_q = t_q, b.n_kv_heads = heads, b.n_q_heads = heads * r, b.head_dim = d, b.q_dtype = type;
+        b.n_layers = n_layers, b.n_groups = n_groups, b.t_q = t_q, b.n_kv_heads = heads, b.n_q_heads = heads * r, b.head_dim = d, b.q_dtype = type, b.sim = sim;
         b.score_stride = n_groups;
         const uint64_t bytes = (uint64_t)n_layers * heads * r * t_q * d * (type == TOM_F32 ? 4 : 2);
         const uint64_t out = 1ull << 40;
@@ -225,6 +225,21 @@ static void split() {
     CHECK(fold(28, 300, 32, 4, 2, 128) == 2 && fold(28, 300, 33, 4, 2, 128) == 0 && fold(28, 300, 32, 4, 3, 128) == 0 && fold(28, 300, 32, 1, 1, 128) == 0);
     CHECK(fold(1, 1100 * 16, 16, 4, 1, 128) == 1 && fold(1, 1100 * 16 + 1, 16, 4, 1, 128) == 0);
     CHECK(fold(1, 500, 16, 4, 7, 128, TOM_F32) == 0 && fold(28, 130, 64, 4, 4, 128, TOM_F32) == 4 && fold(28, 256, 32, 4, 1, 128, TOM_F32) == 2);
+    auto cosine = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d, int type = TOM_BF16) { return fold(n_layers, n_groups, t_q, heads, r, d, type, TOM_SIM_COSINE); };
+    // three and four query heads in float32: heads that the fold of its own cuts or not, and one of many workgroups
+    CHECK(fold(1, 100, 17, 4, 4, 128, TOM_F32) == 2 && cosine(1, 100, 33, 3, 4, 128, TOM_F32) == 0 && cosine(1, 100, 16, 8, 3, 128, TOM_F32) == 0 && fold(1, 100, 16, 8, 4, 128, TOM_F32) == 1 && cosine(1, 100, 16, 7, 4, 128, TOM_F32) == 1);
+    CHECK(cosine(1, 100, 32, 8, 4, 80, TOM_F32) == 2 && cosine(1, 100, 48, 8, 4, 80, TOM_F32) == 3 && cosine(1, 100, 65, 8, 4, 80, TOM_F32) == 0 && cosine(28, 40, 63, 8, 4, 72, TOM_F32) == 4 && cosine(28, 40, 105, 8, 3, 80, TOM_F32) == 4 && cosine(1, 40, 105, 8, 3, 80, TOM_F32) == 0 && fold(1, 100, 32, 8, 4, 96, TOM_F32) == 0 && fold(1, 100, 32, 7, 4, 96, TOM_F32) == 2);
+    CHECK(cosine(22, 40, 61, 5, 3, 128, TOM_F32) == 4 && cosine(21, 40, 61, 5, 3, 128, TOM_F32) == 0);
+    // more than four in float32
+    CHECK(cosine(1, 100, 12, 3, 6, 128, TOM_F32) == 1 && cosine(1, 100, 12, 5, 5, 64, TOM_F32) == 1 && cosine(1, 100, 12, 4, 6, 128, TOM_F32) == 0 && cosine(1, 100, 16, 5, 7, 64, TOM_F32) == 0 && fold(1, 100, 16, 5, 7, 64, TOM_F32) == 1 && cosine(1, 100, 32, 3, 7, 64, TOM_F32) == 2 && cosine(1, 100, 11, 3, 7, 112, TOM_F32) == 1 &&
+          cosine(1, 100, 17, 3, 7, 96, TOM_F32) == 0);
+    // 16 bits with the cosine
+    CHECK(cosine(1, 100, 144, 4, 4, 128) == 0 && fold(1, 100, 144, 4, 4, 128) == 3 && cosine(1, 100, 128, 4, 4, 128) == 4 && cosine(28, 100, 145, 4, 4, 128) == 4);
+    CHECK(cosine(1, 100, 16, 8, 4, 128) == 1 && cosine(1, 100, 17, 8, 4, 128) == 0 && cosine(28, 60, 64, 8, 4, 128) == 4 && cosine(28, 60, 65, 8, 4, 128) == 0 && cosine(1, 100, 17, 8, 4, 136) == 2);
+    CHECK(cosine(1, 100, 9, 8, 5, 128) == 0 && fold(1, 100, 9, 8, 5, 128) == 1 && cosine(1, 100, 9, 7, 5, 128) == 1);
+    CHECK(cosine(1, 4100, 17, 4, 4, 128) == 2 && cosine(1, 4100, 17, 3, 4, 256) == 0 && cosine(10, 410, 17, 3, 4, 256) == 2 && cosine(1, 4100, 17, 1, 12, 128) == 0 && cosine(1, 4100, 16, 1, 12, 128) == 1);
+    // a tile that is partly empty on the longest keys
+    CHECK(cosine(1, 100, 15, 8, 1, 256) == 0 && cosine(1, 100, 16, 8, 1, 256) == 1 && fold(1, 100, 15, 8, 1, 256) == 1 && cosine(1, 100, 15, 8, 1, 248) == 1 && cosine(17, 100, 15, 8, 1, 256) == 1 && cosine(16, 100, 15, 8, 1, 256) == 0);
     CHECK(fold(1, 16, 8, 48, 1, 64) == 1 && fold(1, 16, 8, 49, 1, 64) == 0 && fold(65535, 1 << 26, 1 << 20, 1, 1, 8) == 0);
 }
 
