@@ -85,6 +85,24 @@ inline int fold_parts(const ScoreArgs& a, bool want_tokens) {
 
 // ---- per-token scores: the contraction is split over the waves of a workgroup -------------
 constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
+// More than 512 units of 16 groups (`wide`: of 64): whether up to 16 query tokens split the contraction.  The 64 x 64 form is bound by its chain of chunks, a barrier and a load latency for 32 channels, with one
+// or two workgroups a compute unit; its time steps up behind 256 units of 64 (1024 of 16). The split form steps up with every 256 units, a workgroup more on each
+// compute unit, and grows with the tokens, which it reads once a unit.  So per step up to c - k / channels tokens.  Fold and scores, 64 x 64 form / this, at the last tokens kept and some behind them:
+//   513 to 768 units: 256 channels x 8 tokens 0.98 to 0.99, x 15 11.1 / 11.7; 288 x 10 12.1 / 11.6; 320 x 13 0.95; 400 x 15 15.0 / 13.6; 512 x 16 0.97; 1024 x 16 0.95
+//   769 to 1024 (with more than 256 units of 64 as the next row: 1012 of 256 x 1 13.1 / 11.1): 256 x 1 1.00 to 1.03; 288 x 3 12.1 / 11.6; 320 x 5 0.97, x 8 12.8 / 13.4; 480 x 6 15.9 / 15.1; 512 x 7 0.98, x 12 16.3 / 17.9; 1024 x 9 0.97, x 14 25.1 / 27.1; 2048 x 9 0.91, x 12 1.02
+//   1025 to 1280: 256 x 7 0.98, x 12 1.04; 320 x 9 15.2 / 14.3; 400 x 11 0.97; 512 x 9 0.91, x 14 1.01; 1024 x 11 0.92, x 15 1.01; 2048 x 15 0.99
+//   1281 to 1536: 256 x 1 13.3 / 14.0; 320 x 1 1.00, x 5 1.04; 400 x 4 18.1 / 16.6; 512 x 5 19.7 / 18.7, x 8 1.03; 640 x 6 24.0 / 22.7; 768 x 8 1.00; 1024 x 9 0.96, x 11 1.02; 2048 x 8 0.94
+//   1537 to 1792: 512 x 1 1.01; 768 x 3 1.00, x 7 1.06; 1024 x 3 38.6 / 34.5, x 5 38.5 / 35.6; 2048 x 5 0.95, x 16 1.34
+//   1793 to 2048: 512 x 2 1.12; 1024 x 1 40.3 / 37.6, x 2 1.02; 2048 x 1 71.9 / 62.9, x 9 1.21
+// Three stores in turn; with the same question again within 4 % of it, mostly 1 to 3 % in favour of this form (1024 channels from 1537 units on 4 to 8 % against it: x 3 33.6 / 31.8, x 1 at 1863 33.9 / 34.3).
+inline bool one_tile_splits(int64_t units, int64_t wide, int t_q, int channels) {
+    static constexpr struct { int c, k, channels; } kLine[] = {{40, 8192, 256}, {11, 1800, 288}, {17, 2400, 256}, {13, 3600, 352}, {10, 5000, 256}, {6, 5000, 256}};  // three to eight units a compute unit
+    int64_t step = (units + 255) / 256 - 3;
+    if (step == 1 && wide > 256) step = 2;
+    if (t_q > 16 || step < 0 || step > 5 || channels < kLine[step].channels) return false;
+    return (int64_t)(kLine[step].c - t_q) * channels >= kLine[step].k;
+}
+
 // Tiles of 16 query tokens per pass of score_token_split_kernel (1 to 4), or 0: the 64 x 64 form.
 // A whole question on the device (fold, this, top-k, gather of 4 groups) at 4 heads of 128, against the 64 x 64 form:
 // 1 layer x 256 groups x 32 tokens 18.1 / 28.0 us, x 64 tokens 25.8 / 39.3; 8 x 1024 (512 units)
@@ -95,12 +113,7 @@ constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
 // at most three tiles (118 registers, two workgroups) 512 units run in one.  Fold and scores at 448 to 512 units, equal
 // passes of three / passes of four / 64 x 64 form: one head of 64 x 65 tokens 14.5 / 18.0 / 15.8 us, x 1024
 // tokens 92 / 117 / 107; 4 heads of 128 x 65 tokens 36 / 45 / 46, x 1024 tokens 370 / 390 / 470.
-// One tile of tokens on keys of 256 channels and more goes on beyond: there the 64 x 64 form is bound by its chain of chunks, a barrier and a load latency for 32
-// channels, with one or two workgroups a compute unit, and what the split form reads of the query grows with the tokens. Fold and scores, 64 x 64 form / this, three
-// stores in turn, at 1 / 4 / 8 / 12 tokens: 700 units of 512 channels 15.9 / 12.6, 15.9 / 13.0, 15.9 / 13.6, 16.0 / 14.8; 1232 units of 2048 67.2 / 44.0, 67.6 / 48.5, 68.7 / 54.7
-// (16: 70.1 / 66.9), of 1024 34.3 / 24.7, 33.7 / 25.7, 33.4 / 28.2 (16: 35.3 / 35.4), of 512 19.5 / 15.9, 19.6 / 16.7, 19.6 / 17.6 (16: 19.7 / 20.7), of 256 12.9 / 12.1, 13.0 / 12.5,
-// 12.9 / 12.9; 1484 units of 512 19.6 / 17.9, 19.7 / 18.7, 19.6 / 19.8, 19.8 / 22.1; 1596 of 1024 37.4 / 32.8, 38.0 / 34.9, 38.9 / 38.3, of 2048 70.2 / 55.8, 69.6 / 61.5, 71.8 / 70.5 (the same question again 59.9 / 51.8, 60.4 / 56.5, 61.2 / 65.8); 1876 of 1024 40.0 / 36.9 at 1, of 2048 71.9 / 62.9; 2100 of 512 24.7 / 23.9, 24.7 / 24.7, 24.7 / 26.0;
-// 2632 of 1024 46.1 / 47.3 at 1; 1232 of 64 and 1792 of 128 channels lose 9 and 17 % at any number of tokens.
+// One tile of tokens on keys of 256 channels and more goes on beyond (one_tile_splits).
 // Two and three tiles whose last one is mostly empty go on as well (its lanes re-read one row here, the 64 x 64 form multiplies them), on keys of 512 channels and more, where the 64 x 64 form would
 // leave a third of one round of the chip or, with three tiles, two fifths of two idle. 64 x 64 form / this at 17 / 25 / 33 / 38 tokens: 28 layers x 384 groups of 512 channels (168 units of 64) 21.3 / 18.2, 21.6 / 19.8, 28.0 / 24.4,
 // 28.2 / 25.5, of 2048 68.5 / 50.9, 70.8 / 59.7, 93.7 / 74.4, 95.0 / 80.4; 700 of 512 (308) at 33 / 38 38.8 / 34.8, 38.8 / 36.7, of 1024 72.1 / 61.6, 72.5 / 66.0; but
@@ -109,10 +122,10 @@ inline int split_tiles(const ScoreArgs& a) {
     constexpr int64_t kSplitUnits = 512, kUnitsOfFourTiles = 256;
     const int64_t units = ((int64_t)a.n_groups + 15) / 16 * a.n_layers;
     const int channels = a.n_kv_heads * a.head_dim;
-    if (a.t_q <= 16 && channels >= 256 && units <= (channels >= 1024 && a.t_q <= 12 ? 2000 - 75 * a.t_q : 1700 - 50 * a.t_q)) return 1;
     const int tiles = (a.t_q + 15) / 16;
     if (units > kSplitUnits) {
         const int64_t wide = ((int64_t)a.n_groups + kGemmN - 1) / kGemmN * a.n_layers;
+        if (one_tile_splits(units, wide, a.t_q, channels)) return 1;
         const bool idle = wide <= 168 || (tiles == 3 && wide > 256 && wide <= 308);  // 256 compute units
         return idle && tiles >= 2 && tiles <= 3 && 5 * a.t_q <= 64 * tiles && channels >= 512 ? tiles : 0;
     }

@@ -175,16 +175,24 @@ static void split() {
     CHECK(tiles(512, 16, 1) == 1 && tiles(513, 16, 1) == 0);
     CHECK(tiles(4, 1024, 64) == 4 && tiles(4, 1024, 65) == 3 && tiles(4, 1024, 1 << 20) == 4);
     CHECK(tiles(65535, 0x7fffffff, 1) == 0);                     // far beyond, no overflow
-    a.n_kv_heads = 2, a.head_dim = 128;                          // one tile of tokens on longer keys: up to 1700 - 50 t_q units
-    CHECK(tiles(28, 58 * 16, 1) == 1 && tiles(28, 59 * 16, 1) == 0 && tiles(28, 32 * 16, 16) == 1 && tiles(28, 33 * 16, 16) == 0);
+    // one tile of tokens on keys of 256 channels and more: the most tokens, by units a compute unit
+    const struct { int channels, most[8]; } one_tile[] = {{248, {16}}, {256, {16, 8, 0, 7}}, {280, {16, 10, 0, 8}}, {288, {16, 11, 4, 8}}, {320, {16, 14, 5, 9}}, {344, {16, 16, 5, 10}}, {352, {16, 16, 5, 10, 2}}, {400, {16, 16, 6, 11, 4}},
+                                                          {512, {16, 16, 7, 12, 5, 0, 0, 0}}, {768, {16, 16, 8, 13, 8, 3, 0, 0}}, {1024, {16, 16, 9, 14, 9, 5, 1, 0}},
+                                                          {2048, {16, 16, 10, 15, 11, 7, 3, 0}}, {1 << 20, {16, 16, 10, 16, 12, 9, 5, 0}}};
+    for (const auto& w : one_tile)
+        for (int i = 0; i < 8; ++i)
+            for (int units : {i ? 256 * (i + 1) + 1 : 1, 256 * (i + 2)}) {
+                a.n_kv_heads = w.channels / 8, a.head_dim = 8;
+                for (int t_q = 1; t_q <= 16; ++t_q) CHECK(tiles(1, units * 16, t_q) == (t_q <= w.most[i]));
+                CHECK(tiles(units, 16, 1) == (w.most[i == 2 ? 3 : i] > 0));   // one group tile a layer: as many units of 64
+            }
+    a.n_kv_heads = 2, a.head_dim = 128;
     CHECK(tiles(28, 28 * 16, 17) == 0 && tiles(65535, 0x7fffffff, 1) == 0);
     a.n_kv_heads = 4;                                            // two and three tiles, the last mostly empty: up to 168 units of 64, three from 257 to 308 too
     for (int t_q : {17, 25, 26, 32, 33, 38, 39, 48, 49, 64, 65})
         for (int groups : {6 * 64, 6 * 64 + 1, 9 * 64, 9 * 64 + 1, 11 * 64, 11 * 64 + 1})
             CHECK(tiles(28, groups, t_q) == (t_q >= 33 && t_q <= 38 && (groups <= 6 * 64 || (groups > 9 * 64 && groups <= 11 * 64)) ? 3 : t_q <= 25 && groups <= 6 * 64 ? 2 : 0));
     CHECK(tiles(65535, 0x7fffffff, 17) == 0);
-    a.n_kv_heads = 8;                                            // 1024 channels: up to 2000 - 75 t_q, from 12 tokens on as before
-    CHECK(tiles(25, 77 * 16, 1) == 1 && tiles(25, 78 * 16, 1) == 0 && tiles(25, 44 * 16, 12) == 1 && tiles(25, 45 * 16, 12) == 0 && tiles(25, 42 * 16, 13) == 1 && tiles(25, 43 * 16, 13) == 0);
     a.n_kv_heads = 31, a.head_dim = 8;
     CHECK(tiles(28, 58 * 16, 1) == 0 && tiles(28, 6 * 64, 17) == 0);
     a.n_kv_heads = a.head_dim = 0;

@@ -92,13 +92,26 @@ def test_scores_over_the_question(oqm):
         _check(oqm, 2, 2, 2, 64, T, tq, overlap=True)
 
 
-# one tile of tokens, launches beyond two rounds of the chip: up to 1700 - 50 t_q units of 16 groups the contraction is split (1024 channels, up to 12 tokens: 2000 - 75 t_q), from there on 64 x 64
+# one tile of tokens, launches beyond two rounds of the chip: the contraction is split or, at more tokens and units, 64 x 64
 @pytest.mark.parametrize("tq, units", ((1, 1650), (8, 1300), (12, 1100), (16, 900)))
 def test_one_tile_of_tokens_on_long_keys(oqm, tq, units):
     for heads, d, r, T in ((2, 128, 3, units // 10 * 16), (2, 128, 3, units // 10 * 16 + 1), (3, 80, 3, units // 10 * 16), (4, 136, 4, units // 10 * 16 - 5)):
         _check(oqm, 10, heads, r, d, T, tq, cosine=tq != 8)
     for T in ((2000 - 75 * tq) // 10 * 16, (2000 - 75 * tq) // 10 * 16 + 1):
         _check(oqm, 10, 4, 3, 256, T, tq, tokens=False)
+
+
+# ... and both sides of its lines, which step with every 256 units of 16 groups and go by channels and tokens
+@pytest.mark.parametrize("heads, d, units, tq", ((2, 128, 768, 8), (2, 128, 768, 9), (2, 128, 769, 1), (2, 128, 1025, 7), (2, 128, 1280, 8), (3, 96, 1024, 4), (3, 96, 1024, 5), (5, 80, 1536, 4), (5, 80, 1281, 5),
+                                                 (4, 128, 1024, 7), (4, 128, 1024, 8), (4, 128, 1280, 12), (4, 128, 1281, 5), (4, 128, 1281, 6), (4, 256, 1792, 5), (4, 256, 1537, 6), (4, 256, 1793, 1), (4, 256, 1793, 2)))
+def test_steps_of_one_tile(oqm, heads, d, units, tq):
+    _check(oqm, 1, heads, 3, d, units * 16 - units % 3, tq, tokens=tq % 2 == 0, cosine=units % 2 == 0)
+
+
+# the same units cut into 16 or 64 groups by short layers: 260 units of 64 step as 1025 of 16 do
+def test_short_layers_of_one_tile(oqm):
+    for T in (17, 65):
+        _check(oqm, 260, 4, 2, 64, T, 2)
 
 
 # two and three tiles whose last is mostly empty, where the 64 x 64 form would leave a third of one round idle, up to 168 units of 64, or, three tiles, two fifths of two, 257 to 308
