@@ -342,6 +342,9 @@ inline int64_t piece_blocks(const DequantArgs& a) { return (pieces_of_head(a) + 
 //     (8.9 / 6.8), 150 50.1 / 43.1 (34.8 / 35.6), 300 101.6 / 73.8 (68.1 / 69.0); in 2 bits 200 62.8 / 51.2 (45.1 / 43.2), with bfloat16 pairs 45.2 / 40.2 (44.5 / 39.9).
 //   Up to 256, 170 MB: below it the nearly full tiles lose in both columns, 31 x 64 (248) 150 MB 30.6 / 33.0 (29.5 / 33.4), 15 x 128 (240) 31.1 / 32.7 (29.7 / 32.8), 16 x 128 (256) 158 31.6 / 32.0 (30.3 / 33.2); above it three stores in turn
 //     gain more than the same question again loses: 31 x 64 174 38.6 / 36.6 (33.7 / 36.2), 200 51.2 / 41.4 (38.4 / 41.1), 390 107.5 / 88.3 (72.7 / 78.4), 600 160 / 139 (160 / 139); 16 x 128 200 46.2 / 40.8 (37.5 / 39.5), 390 104.6 / 84.1 (71.3 / 72.1).
+// Tiles of three passes are one workgroup each that loads them whole, and heads of few pieces change the window often: 4-bit codes of 513 to 768 items, 400 to 800 MB, by pieces over by tiles with stores in turn (the same question again),
+//   means of random launches: heads of up to 500 pieces 1.02 (1.04), 768 1.01 (1.03), 1000 0.99 (1.01), 1500 1.00 (1.01), above 0.98 (0.99).  Tiles of two passes 0.96 to 1.00 (0.97 to 1.01), of four and more 0.95 to 1.00 (0.96 to 1.01),
+//   single launches up to 1.08; 2-bit codes of three 0.99 (1.00).
 // The pieces take 32-bit offsets, and a wave at most two tiles.
 inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t prefix_blocks) {
     const int64_t items = (int64_t)a.k_eff * a.tile_items, heads = 2 * (int64_t)a.n_layers * a.n_kv_heads, out = heads * items * 16;
@@ -350,6 +353,8 @@ inline bool gather_by_pieces(const DequantArgs& a, bool is_16_bit, uint32_t pref
         if (out < (a.tile_items <= 208 ? 30000000 : 170000000)) return false;
     } else {
         if (is_16_bit ? out < 400000000 || (a.bits == 2 && a.meta_bf16) : out < 300000000 || out > 1000000000 || a.bits != 2) return false;
+        const bool three_passes = a.tile_items > 2 * kBlock && a.tile_items <= 3 * kBlock;
+        if (is_16_bit && a.bits == 4 && three_passes && pieces_of_head(a) < 768) return false;
     }
     constexpr int64_t kMost = 1LL << 31;
     const int64_t code_tile = (int64_t)a.tile_items * (is_16_bit ? 8 : 4) * a.bits / 8;

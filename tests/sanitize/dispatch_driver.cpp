@@ -360,6 +360,10 @@ static void gather() {
     CHECK(!pieces(39, true, 4, false, 28, 196, 1024, 1 << 25) && !pieces(39, true, 4, false, 28, 196, 1024, 0, 1u << 23));
     // tiles of up to one pass: 208 items from 30 MB up, 256 from 170
     CHECK(pieces(41, true, 2, true, 28, 13) && !pieces(40, true, 4, false, 28, 13) && pieces(186, true, 4, false, 28, 16) && !pieces(185, true, 4, false, 28, 16) && !pieces(186, true, 4, false, 28, 17));
+    // 4-bit tiles of three passes: heads of 768 pieces and more
+    for (int tokens : {33, 48})
+        CHECK(!pieces(196351 / (tokens * 16), true, 4, false, 21, tokens) && pieces(196353 / (tokens * 16) + 1, true, 4, false, 21, tokens) && pieces(196351 / (tokens * 16), true, 2, false, 21, tokens));
+    CHECK(pieces(383, true, 4, false, 21, 32) && pieces(250, true, 4, false, 21, 49));
     // the first piece is a part where the rows of some head do not start on a piece
     DequantArgs starts{};
     starts.k_eff = 64, starts.tile_items = 196 * 16, starts.head_out_bytes = 64 * 196 * 256;
