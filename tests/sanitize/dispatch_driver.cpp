@@ -248,6 +248,31 @@ static void split() {
     CHECK(cosine(1, 4100, 17, 4, 4, 128) == 2 && cosine(1, 4100, 17, 3, 4, 256) == 0 && cosine(10, 410, 17, 3, 4, 256) == 2 && cosine(1, 4100, 17, 1, 12, 128) == 0 && cosine(1, 4100, 16, 1, 12, 128) == 1);
     // a tile that is partly empty on the longest keys
     CHECK(cosine(1, 100, 15, 8, 1, 256) == 0 && cosine(1, 100, 16, 8, 1, 256) == 1 && fold(1, 100, 15, 8, 1, 256) == 1 && cosine(1, 100, 15, 8, 1, 248) == 1 && cosine(17, 100, 15, 8, 1, 256) == 1 && cosine(16, 100, 15, 8, 1, 256) == 0);
+    // the launches that ask the split form itself (tests/test_gpu_token_split.py): the scores start where the question does
+    auto split_alone = [&](int n_layers, int n_groups, int t_q, int heads, int r, int d) {
+        ScoreArgs b{};
+        b.n_layers = n_layers, b.n_groups = n_groups, b.t_q = t_q, b.n_kv_heads = heads, b.n_q_heads = heads * r, b.head_dim = d, b.q_dtype = TOM_BF16;
+        b.score_stride = n_groups + 3, b.q = at(1 << 20), b.scores = reinterpret_cast<float*>(at(1 << 20)), b.token_scores = reinterpret_cast<float*>(at(1ull << 44));
+        CHECK(fold_tiles(b) == 0);
+        b.sim = TOM_SIM_COSINE;
+        CHECK(fold_tiles(b) == 0);
+        return split_tiles(b);
+    };
+    const int channels[][2] = {{1, 8}, {3, 8}, {1, 72}, {1, 128}, {17, 8}, {33, 8}, {65, 8}};
+    const int tokens[][2] = {{1, 1}, {16, 1}, {17, 2}, {33, 3}, {48, 3}, {49, 4}, {64, 4}, {65, 3}, {113, 4}, {130, 3}};   // tiles of a pass: 1, 2, 3, 4, 2 x 3, 2 x 4, 3 x 3
+    for (const auto& c : channels)
+        for (const auto& t : tokens)
+            for (int groups : {1, 15, 16, 17})
+                for (int r : {1, 2}) CHECK(split_alone(2, groups, t[0], c[0], r, c[1]) == t[1]);
+    const int shapes[][3] = {{1, 24, 3}, {1, 40, 33}, {3, 8, 49}, {5, 24, 64}, {1, 24, 97}};
+    const struct { int layers, groups, tiles[5]; } launches[] = {{1, 4096, {1, 3, 4, 4, 4}}, {1, 4097, {1, 3, 2, 2, 3}}, {16, 512, {1, 3, 2, 2, 3}}, {16, 513, {}}, {1, 8191, {1, 3, 2, 2, 3}}, {3, 2720, {1, 3, 2, 2, 3}}, {3, 2721, {}}};
+    for (const auto& l : launches)
+        for (int i = 0; i < 5; ++i) CHECK(split_alone(l.layers, l.groups, shapes[i][2], shapes[i][0], 1, shapes[i][1]) == l.tiles[i]);
+    for (int groups : {9600, 9601}) {
+        CHECK(split_alone(1, groups, 8, 1, 3, 264) == 1 && split_alone(1, groups, 9, 1, 3, 264) == 0 && split_alone(1, groups, 16, 65, 3, 8) == 1 && split_alone(1, groups, 20, 65, 3, 8) == 2 && split_alone(1, groups, 26, 65, 3, 8) == 0 &&
+              split_alone(1, groups, 36, 65, 3, 8) == 3);
+        CHECK(fold(1, groups, 8, 1, 3, 264) == 0 && fold(1, groups, 16, 65, 3, 8) == 0);   // apart from the question too
+    }
     CHECK(fold(1, 16, 8, 48, 1, 64) == 1 && fold(1, 16, 8, 49, 1, 64) == 0 && fold(65535, 1 << 26, 1 << 20, 1, 1, 8) == 0);
 }
 

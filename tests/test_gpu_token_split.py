@@ -1,7 +1,9 @@
-"""GPU: the per-token scores of small launches (the K-split form) against plain float64.
+"""GPU: the per-token scores of small launches against plain float64.
 
 A launch of at most 512 units of 16 groups splits the contraction over the waves of a workgroup, with
-1 to 4 tiles of 16 query tokens at a time (1 to 3 above 256 units); larger launches take the 64 x 64 form, unless few tokens meet long keys.  The cases sit on
+1 to 4 tiles of 16 query tokens at a time (1 to 3 above 256 units); larger launches take the 64 x 64 form, unless few tokens meet long keys.  Most small ones
+fold the query inside that launch, and so do the cases of the first tests here but for the largest. Scores that share memory with the question keep the
+fold a launch of its own: the last tests ask the split form itself in this way.  The cases sit on
 both sides of every edge: token tiles, group tiles, contractions that end in half a block of 16
 channels or need several rounds of blocks, and the launch size itself."""
 import pytest
@@ -17,7 +19,7 @@ def oqm():
     return m
 
 
-def _check(oqm, L, H, r, d, T, tq, cosine, seed):
+def _check(oqm, L, H, r, d, T, tq, cosine, seed, overlap=False):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     cfg = oqm.make_config(L, H, H * r, d, 1, 8, T, in_dtype=oqm.TOM_BF16, out_dtype=oqm.TOM_BF16,
                           sim=oqm.TOM_SIM_COSINE if cosine else oqm.TOM_SIM_DOT)
@@ -28,12 +30,18 @@ def _check(oqm, L, H, r, d, T, tq, cosine, seed):
         q = torch.randn((L, H * r, tq, d), generator=gen, device="cuda").to(torch.bfloat16)
         ws = torch.empty(oqm.tom_oqm_score_workspace_bytes(mem.handle, L, tq, oqm.TOM_SCORE_TOKEN_GEMM, True),
                          dtype=torch.uint8, device="cuda")
-        scores = torch.full((L, T + 3), 7.0, device="cuda")
+        qt = q.double().view(L, H, r, tq, d).mean(2).permute(0, 2, 1, 3).reshape(L, tq, H * d).cpu()
+        if overlap:     # the scores go where the question is
+            room = torch.full((max(q.numel() * 2 // 4, L * (T + 3)) + 4,), 7.0, device="cuda")
+            inside = room.view(torch.bfloat16)[:q.numel()].view(q.shape)
+            inside.copy_(q)
+            q, scores = inside, room[:L * (T + 3)].view(L, T + 3)
+        else:
+            scores = torch.full((L, T + 3), 7.0, device="cuda")
         tok = torch.full((L * tq * T + 64,), 7.0, device="cuda")
         oqm.tom_oqm_score_groups(mem.handle, 0, L, q, tq, scores, T + 3, tok[:L * tq * T].view(L, tq, T),
                                  oqm.TOM_SCORE_TOKEN_GEMM, ws)
         keys = mem.keys.double().view(L, T, H * d).cpu()
-        qt = q.double().view(L, H, r, tq, d).mean(2).permute(0, 2, 1, 3).reshape(L, tq, H * d).cpu()
         want = qt @ keys.transpose(1, 2)
         # one rounding to float32 (2^-24) on sums whose float64 error is far below the absolute term
         size = qt.norm(dim=-1)[:, :, None] * keys.norm(dim=-1)[:, None, :]
@@ -45,7 +53,7 @@ def _check(oqm, L, H, r, d, T, tq, cosine, seed):
         slack = size.max(1).values if not cosine else torch.ones_like(group)
         got = scores[:, :T].double().cpu()
         assert ((got - group).abs() <= group.abs() * 2.0 ** -24 + slack * 1e-13).all()
-        assert (scores[:, T:] == 7.0).all() and (tok[L * tq * T:] == 7.0).all()   # nothing outside the outputs
+        assert (overlap or (scores[:, T:] == 7.0).all()) and (tok[L * tq * T:] == 7.0).all()   # nothing outside the outputs
     finally:
         mem.close()
 
@@ -73,3 +81,25 @@ def test_launch_size_of_the_split_form(oqm, L, T):
 def test_passes_above_256_units(oqm, tq):
     for T in (4096, 4097):
         _check(oqm, 1, 1, 1, 24, T, tq, T == 4096, tq + T)
+
+
+# The split form itself.  Tiles of a pass: one to four up to 256 units, up to three above; channels: half a block alone, half a block behind whole ones, fewer blocks than
+# waves, one a wave and a half more, rounds of two and a rest.
+@pytest.mark.parametrize("tq", (1, 16, 17, 33, 48, 49, 64, 65, 113, 130))
+@pytest.mark.parametrize("H, d", ((1, 8), (3, 8), (1, 72), (1, 128), (17, 8), (33, 8), (65, 8)))
+def test_split_form_at_the_tile_edges(oqm, H, d, tq):
+    for i, T in enumerate((1, 15, 16, 17)):
+        _check(oqm, 2, H, 1 + i % 2, d, T, tq, i % 2 == 0, 10 * tq + T, overlap=True)
+
+
+@pytest.mark.parametrize("L, T", ((1, 4096), (1, 4097), (16, 512), (16, 513), (1, 8191), (3, 2720), (3, 2721)))   # 256 and 257, 512 and 528, 512, 510 and 513 units
+def test_split_form_at_the_launch_sizes(oqm, L, T):
+    for H, d, tq in ((1, 24, 3), (1, 40, 33), (3, 8, 49), (5, 24, 64), (1, 24, 97)):
+        _check(oqm, L, H, 1, d, T, tq, tq % 2 == 0, L + T + tq, overlap=True)
+
+
+# beyond 512 units, few tokens on long keys that end in half a block
+@pytest.mark.parametrize("H, d, tq", ((1, 264, 8), (1, 264, 9), (65, 8, 16), (65, 8, 20), (65, 8, 26), (65, 8, 36)))
+def test_split_form_of_long_keys(oqm, H, d, tq):
+    for T in (9600, 9601):
+        _check(oqm, 1, H, 3, d, T, tq, T == 9600, H + T + tq)
