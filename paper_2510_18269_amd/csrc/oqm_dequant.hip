@@ -1,7 +1,7 @@
 // Reconstruction of the selected frame-groups into the bounded active KV buffer
 // (paper Sec. 3.4, Eq. 11 and Eq. 13; supplement "Cache reconstruction for decoding").
 //
-// Grid (rank * chunks + chunk, then prefix blocks; K|V * H_k + head; layer): a workgroup of 256
+// dequant_gather_kernel, by tiles: grid (rank * chunks + chunk, then prefix blocks; K|V * H_k + head; layer).  A workgroup of 256
 // threads owns one head tile of one selected group where few passes cover it, otherwise an equal share of
 // it (launch_t); consecutive workgroups
 // write consecutive row blocks of the active buffer.  It reads the group index from device memory
@@ -9,10 +9,11 @@
 // and writes them to token rows [rank*G, (rank+1)*G) of the layer's active buffer.  A lane turns the codes of
 // 16 bytes of output (8 channels, 4 in float32) into one 128-bit non-temporal store, so each store
 // instruction of a wave writes 1 KB of contiguous memory.  HBM-bound: 0.5 + 8/gs bytes
-// read and 2 bytes written per element.
+// read and 2 bytes written per element.  It serves the token axis, every launch that selects its groups itself, and those of the head_dim axis
+// below the lines of gather_by_pieces (oqm_dispatch.h); above them dequant_gather_pieces_kernel cuts the output into pieces instead.
 //
-// Measured at 28 layers x 64 random groups x 196 x 128 (944 MB): cards differ, the benchmark's kernel
-// trace averages 163 us (5.8 TB/s) on the fastest one seen and 169 (5.6) on another, where an
+// What its form was chosen by, measured at 28 layers x 64 random groups x 196 x 128 (944 MB), which goes by pieces now (156 us): 163 us
+// (5.8 TB/s) in a kernel trace on the fastest card seen and 169 (5.6) on another, where an
 // arithmetic-free linear stream of the same byte mix reaches 6.1 TB/s.  Before the stores stopped waiting for each other (below) a
 // workgroup lived 3.5 us (index 0.2, loads 1.5, stores 1.7) and 1520 of 2048 slots were taken at any time; one to
 // five passes per workgroup, 256 or 512 threads and a barrier between loads and stores
@@ -122,9 +123,9 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
                 sm[u] = *reinterpret_cast<const meta_pair*>(meta_t + (item >> a.lpg_shift) * (uint32_t)sizeof(meta_pair));
         }
     }
-    // One wait for all loads.  Without it each item waits for its own, which after the first store is a wait for
-    // that store as well: 28 layers x 64 groups x 196 x 128 163.5 -> 162 us, 73 tokens x 13 groups 3 % less; but the token axis, with more items a lane,
-    // and float32 output are 2 to 5 % slower with it.
+    // One wait for all loads.  Without it each item waits for its own, which after the first store is a wait for that store as well: 28 layers x 64
+    // groups x 196 x 128 (by pieces now) 163.5 -> 162 us, 73 tokens x 13 groups 3 % less; but the token axis, with more items a lane, and float32
+    // output are 2 to 5 % slower with it.
     if constexpr (!TOKEN_AXIS && EB == 2) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0) alone
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
@@ -146,19 +147,21 @@ __global__ void __launch_bounds__(kBlock) dequant_gather_kernel(const DequantArg
 }
 
 // ------------------------------------------------------------------ the gather by pieces of its output
-// Large launches of the head_dim axis, and those of the smallest tiles (gather_by_pieces in oqm_dispatch.h).  What bounds them is the order in which memory is written: plain
-// 16-byte stores of 755 MB take 112 us where every workgroup writes the next 4 KB, 124 where it writes 16 KB, 153 with 64 KB and 180 from
-// a persistent grid.  Tiles and their chunks are not multiples of 4 KB, so here the rows of a head are cut into aligned pieces of 4 KB whatever tile they belong to, and
-// a workgroup takes kPieces of them, eight pieces apart: workgroups go round-robin over the eight XCDs, so that the ones in flight write one dense window of which each
-// XCD has every eighth piece.  Two pieces hide the loads; with one a wave lives too short for them, three or four open the window.
-// A wave's 64 items lie in at most two tiles.  Buffer instructions drop what lies outside of the rows, so nothing branches.
-// 28 layers x 4 heads x 196 x 128 x 64 groups (944 MB), codes and pairs of random bits, one store, us: chunks 158, one piece 185, two 156.2, three 157, four 158.6; an arithmetic-free
-// kernel of the same order with nothing but this shape's constants 153.4 (two adjacent pieces 157; runs of 16 workgroups per XCD 155; 512 threads 156, 1024 172; index loads per lane 174).
-// 128 groups (quant-groups of 32, 2.0 GB) 337 -> 325; 37 x 256, 700 MB of output 162 -> 152; 61 x 96 168 -> 162.
-// The last round of a head shares what is left of its pieces, first half and second half, among as few workgroups: with whole rounds alone a head of 785 pieces (64 groups behind a prefix)
-// left seven of 400 workgroups idle, one of 304 16 of 160.  Tiles / whole rounds / this, three stores in turn: 64 groups behind 14 rows 157.5 / 159.0 / 156.2, in buffers that start 512 bytes behind a
-// piece 157.5 / 157.0 / 156.0, 72 176.4 / 180.9 / 174.5; 8 heads of 50 x 128, 97 groups 123.8 / 126.7 / 120.2, behind 14 rows 125.5 / 120.8 / 119.8.  Rounds that start on 32 KB of every head, so that an XCD keeps
-// to the same eighth of memory over all heads: 159 at 64 groups behind 14 rows, 177.7 at 72.
+// Large launches of the head_dim axis, and those of the smallest tiles (gather_by_pieces in oqm_dispatch.h).  What bounds them is the order in which
+// memory is written: plain 16-byte stores of 755 MB take 112 us where every workgroup writes the next 4 KB, 124 where it writes 16 KB, 153 with 64 KB
+// and 180 from a persistent grid.  Tiles and their chunks are not multiples of 4 KB, so here the rows of a head are cut into aligned pieces of 4 KB
+// whatever tile they belong to, and a workgroup takes kPieces of them, eight pieces apart: workgroups go round-robin over the eight XCDs, so that the
+// ones in flight write one dense window of which each XCD has every eighth piece.  Two pieces hide the loads; with one a wave lives too short for
+// them, three or four open the window. A wave's 64 items lie in at most two tiles.  Buffer instructions drop what lies outside of the rows, so
+// nothing branches. 28 layers x 4 heads x 196 x 128 x 64 groups (944 MB), codes and pairs of random bits, one store, us: chunks 158, one piece 185,
+// two 156.2, three 157, four 158.6; an arithmetic-free kernel of the same order with nothing but this shape's constants 153.4 (two adjacent pieces
+// 157; runs of 16 workgroups per XCD 155; 512 threads 156, 1024 172; index loads per lane 174). 128 groups (quant-groups of 32, 2.0 GB) 337 -> 325;
+// 37 x 256, 700 MB of output 162 -> 152; 61 x 96 168 -> 162. The last round of a head shares what is left of its pieces, first half and second half,
+// among as few workgroups: with whole rounds alone a head of 785 pieces (64 groups behind a prefix) left seven of 400 workgroups idle, one of 304 16
+// of 160.  Tiles / whole rounds / this, three stores in turn: 64 groups behind 14 rows 157.5 / 159.0 / 156.2, in buffers that start 512 bytes behind
+// a piece 157.5 / 157.0 / 156.0, 72 176.4 / 180.9 / 174.5; 8 heads of 50 x 128, 97 groups 123.8 / 126.7 / 120.2, behind 14 rows 125.5 / 120.8 /
+// 119.8.  Rounds that start on 32 KB of every head, so that an XCD keeps to the same eighth of memory over all heads: 159 at 64 groups behind 14
+// rows, 177.7 at 72.
 // What the kernel needs of a DequantArgs, made on the host.
 struct PieceArgs {
     const char *codes, *meta;  // of the first layer asked for
@@ -348,19 +351,21 @@ hipError_t launch_t(const DequantArgs& args, hipStream_t s) {
     a.step = tok ? kBlock / lpr * lpr : kBlock;
     a.tile_items = G * lpr;  // G * d * 4 < 2^31 is checked by the API layer
     const uint32_t passes = (a.tile_items + a.step - 1) / a.step;
-    // Up to `whole` passes one workgroup takes the tile, above that equal chunks (whole rows) of at most `most`.  On the token axis every
-    // lane first loads the pairs of its channels, 64 bytes at 16-bit output against 16 stored per pass, so it takes more passes, but for
-    // launches that leave most compute units without a tile.  28 layers, us per question (200 stored groups, 10 to 60 selected), chunks of at most 3 / 4 / 5
-    // passes: head_dim axis bf16 109.0 / 110.6 / 111.8, float32 105 / 101.7 / 112; token axis float32 88.7 / 97 / 100.  Token axis bf16, 64 of 200 groups,
-    // chunks of at most 3 / 4 / 5 passes and the tile whole, three stores in turn: 80 x 128 (5 passes) 85 / 85 / 74, 100 x 128 (7) 109 / 93 / 93 / 94, 112 x 128 (7) 113 / 101 /
-    // 101 / 105, 196 x 128 (13) 182 / 172 / 161; the same question again: 58 / 58 / 62, 72 / 68 / 68 / 77, 75 / 80 / 80 / 88, 163 / 143 / 148; 32 groups 35 / 35 / 34, 43 / 39 / 39 / 42,
-    // 45 / 44 / 44 / 46, 65 / 66 / 71.  One group of one layer, 8 tiles: 9.0 / 9.0 / 9.5, 9.0 / 9.3 / 9.3 / 9.9, 9.1 / 9.3 / 9.3 / 9.9, 9.0 / 9.3 / 9.5; 64 tiles 0.1 to 0.4 apart, 256 level.
-    // Six and seven passes in two workgroups / whole, while a round of the chip (2048) holds the whole tiles: 96 x 128 (6 passes) 5 groups (1120 tiles) 15.4 / 13.9, 8 (1792) 17.3 / 16.9,
-    // 10 (2240) 20.5 / 20.5, 16 26.0 / 25.4, 64 65 / 74; 150 x 80 10 20.6 / 22.0; 100 x 128 (7) 6 17.7 / 16.4, 8 19.2 / 18.5; of 700 groups 8 25.3 / 23.7, 10 27.3 / 28.1, 32 45 / 48.
+    // Up to `whole` passes one workgroup takes the tile, above that equal chunks (whole rows) of at most `most`.  On the token axis every lane first
+    // loads the pairs of its channels, 64 bytes at 16-bit output against 16 stored per pass, so it takes more passes, but for launches that leave
+    // most compute units without a tile.  28 layers, us per question (200 stored groups, 10 to 60 selected), chunks of at most 3 / 4 / 5 passes:
+    // head_dim axis bf16 109.0 / 110.6 / 111.8, float32 105 / 101.7 / 112; token axis float32 88.7 / 97 / 100.  Token axis bf16, 64 of 200 groups,
+    // chunks of at most 3 / 4 / 5 passes and the tile whole, three stores in turn: 80 x 128 (5 passes) 85 / 85 / 74, 100 x 128 (7) 109 / 93 / 93 /
+    // 94, 112 x 128 (7) 113 / 101 / 101 / 105, 196 x 128 (13) 182 / 172 / 161; the same question again: 58 / 58 / 62, 72 / 68 / 68 / 77, 75 / 80 / 80
+    // / 88, 163 / 143 / 148; 32 groups 35 / 35 / 34, 43 / 39 / 39 / 42, 45 / 44 / 44 / 46, 65 / 66 / 71.  One group of one layer, 8 tiles: 9.0 / 9.0
+    // / 9.5, 9.0 / 9.3 / 9.3 / 9.9, 9.1 / 9.3 / 9.3 / 9.9, 9.0 / 9.3 / 9.5; 64 tiles 0.1 to 0.4 apart, 256 level. Six and seven passes in two
+    // workgroups / whole, while a round of the chip (2048) holds the whole tiles: 96 x 128 (6 passes) 5 groups (1120 tiles) 15.4 / 13.9, 8 (1792)
+    // 17.3 / 16.9, 10 (2240) 20.5 / 20.5, 16 26.0 / 25.4, 64 65 / 74; 150 x 80 10 20.6 / 22.0; 100 x 128 (7) 6 17.7 / 16.4, 8 19.2 / 18.5; of 700
+    // groups 8 25.3 / 23.7, 10 27.3 / 28.1, 32 45 / 48.
     const int64_t tiles = (int64_t)a.n_layers * 2 * a.n_kv_heads * a.k_eff;
     const bool many = tok && eb == 2 && tiles > 128;
-    // float32, token axis, chunks of at most 3 / 4, three stores in turn: 50 x 128 (7 passes) 600 MB 137 / 123, 250 45.1 / 43.9, 100 19.0 / 18.3 (the same question again 16.7 / 17.1); 80 x 128 (10) 600 MB 123 / 108;
-    // 112 x 128 (14) 107 / 111, 196 x 128 105 / 114.
+    // float32, token axis, chunks of at most 3 / 4, three stores in turn: 50 x 128 (7 passes) 600 MB 137 / 123, 250 45.1 / 43.9, 100 19.0 / 18.3 (the
+    // same question again 16.7 / 17.1); 80 x 128 (10) 600 MB 123 / 108; 112 x 128 (14) 107 / 111, 196 x 128 105 / 114.
     const bool four = !tok || (passes <= 10 && tiles * a.tile_items * 16 >= 200000000);
     const uint32_t whole = many ? (tiles <= 2048 ? 7 : 5) : 4, most = eb == 2 ? (many ? 5 : 3) : (four ? 4 : 3);
     const uint32_t fit = passes <= whole ? whole : most;

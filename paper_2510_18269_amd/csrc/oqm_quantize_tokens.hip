@@ -216,19 +216,17 @@ __global__ void __launch_bounds__(NT) quantize_append_tokens_kernel(const Append
     write_key();
 }
 
-// The form for d = 64, 128, 256 (LPR = d/8 lanes per token row divides a wave).  As few waves as
-// can hold the tile at eight rows per lane (13 where that would be more than four waves) own it; a wave reduces its rows with lane swaps, several
-// exchange one (min, max) per channel through LDS behind a barrier, one
-// alone needs neither.  Each phase of a launch this short is latency or vector work, not
-// bandwidth: fewer threads per tile mean more tiles in flight and fewer of the per-channel steps.
-// The keys are summed while the codes are packed, from the same widened rows and behind the exchange that the codes wait for.
-// A key taken from another tensor has workgroups of its own, which hold that tensor's tile.
-// Grid: those, then all K tiles, then all V tiles, so that one dense stream of addresses is read at a time and the
-// longer workgroups start first.  Measured, us: 28 layers x 4 heads x 50 x 128 (two waves of seven rows), K and V of a layer in turn with the sums in front
-// of the exchange / in turn / V first / K first: 8 FP16 frames 9.2 / 9.3 / 8.8 / 8.6, 32 bf16 frames (124 MB) 25.6 / 25.9 / 25.3 / 24.3 (5.1
-// TB/s), 16 13.5 / 13.2 / 12.9 / 12.0; 196 tokens x 4 frames 15.2 / 14.0 / 13.3 / 12.9.  It takes 88 registers, five waves per SIMD; forcing fewer spills and loses.  At 32 frames one wave of 13 rows takes
-// 29.1 us, three waves of five 28.4, four of four 29.8, skipping the dead rows by a branch per row
-// 27.5 (no v_min3 across rows), where this form took 25.9; the 256-thread form below 30.1.
+// The form for d = 64, 128, 256 (LPR = d/8 lanes per token row divides a wave).  As few waves as can hold the tile at eight rows per lane (13 where
+// that would be more than four waves) own it; a wave reduces its rows with lane swaps, several exchange one (min, max) per channel through LDS behind
+// a barrier, one alone needs neither.  Each phase of a launch this short is latency or vector work, not bandwidth: fewer threads per tile mean more
+// tiles in flight and fewer of the per-channel steps. The keys are summed while the codes are packed, from the same widened rows and behind the
+// exchange that the codes wait for. A key taken from another tensor has workgroups of its own, which hold that tensor's tile. Grid: those, then all K
+// tiles, then all V tiles, so that one dense stream of addresses is read at a time and the longer workgroups start first.  Measured, us: 28 layers x
+// 4 heads x 50 x 128 (two waves of seven rows), K and V of a layer in turn with the sums in front of the exchange / in turn / V first / K first: 8
+// FP16 frames 9.2 / 9.3 / 8.8 / 8.6, 32 bf16 frames (124 MB) 25.6 / 25.9 / 25.3 / 24.3 (5.1 TB/s), 16 13.5 / 13.2 / 12.9 / 12.0; 196 tokens x 4
+// frames 15.2 / 14.0 / 13.3 / 12.9.  It takes 88 registers, five waves per SIMD; forcing fewer spills and loses.  At 32 frames one wave of 13 rows
+// takes 29.1 us, three waves of five 28.4, four of four 29.8, skipping the dead rows by a branch per row 27.5 (no v_min3 across rows), where this
+// form took 25.9; the 256-thread form below 30.1.
 template <typename IN, int LPR, int HOLD, int BITS, bool MB, bool SEP>
 __global__ void __launch_bounds__(256) quantize_append_rows_kernel(const AppendArgs a, const int waves) {
     constexpr int EB = elem_bytes<IN>::value;

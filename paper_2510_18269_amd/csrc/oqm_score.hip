@@ -85,10 +85,9 @@ __device__ __forceinline__ double total_of(const double* wsum) {
     for (int w = 0; w < WAVES; ++w) v += wsum[w];
     return v;
 }
-// |q-bar|^2 of a layer, from what query_fold_kernel has left: the first elements are requested where this is made, and
-// put() behind the work that their latency shall not hold up (summed in front of it, 2000 of the 10800 cycles of a split workgroup with one tile of
-// tokens: 28 layers x 100 groups x 10 tokens 13.8 -> 13.3 us, 17 x 167 x 10 at 5 heads of 256 18.3 -> 17.5, 28 x 1024 x 64 62.9 -> 62.3, with the sums over
-// lanes by swaps).
+// |q-bar|^2 of a layer, from what query_fold_kernel has left: the first elements are requested where this is made, and put() behind the work that
+// their latency shall not hold up (summed in front of it, 2000 of the 10800 cycles of a split workgroup with one tile of tokens: 28 layers x 100
+// groups x 10 tokens 13.8 -> 13.3 us, 17 x 167 x 10 at 5 heads of 256 18.3 -> 17.5, 28 x 1024 x 64 62.9 -> 62.3, with the sums over lanes by swaps).
 template <int THREADS>
 struct QueryNorm2 {
     const double* qbar;
@@ -124,13 +123,13 @@ __device__ __forceinline__ void join_rows_of_wave(double (&acc)[8], int lpr, int
 }
 
 // ------------------------------------------------------------------ query fold
-// grid (H_k * parts, n_layers); a workgroup owns d / parts channels of a KV head: kFoldThreads threads = row slots x lanes of 8
-// channels.  The r * T_q rows of a KV head are contiguous in Q: the mean alone is one sum over them.  TOKENS: every token's mean
-// over the r heads is wanted too, so a slot takes whole tokens.  Bound by latency and by what the few compute units that take part can
-// load, hence parts of 64 channels in small launches (fold_parts in oqm_dispatch.h).  28 layers x 28 heads of 128 in a graph of the whole question, 256 threads per head / 512 / 512
-// per part: 32 tokens 5.4 / 4.5 / 4.4 us, 64 7.5 / 5.7 / 5.0, 64 with every token kept 10.2 / 9.4 / 7.0.  Rows that no slot of the workgroup has are not converted (8 rows
-// a trip, 0.1 us each): mean query of one token over 28 x 1024 groups 21.2 -> 19.6 us, fused with the scores of one layer x 256 groups 8.9 -> 8.3, 16 rows 12.1 -> 11.9.  (Not worth its branches in
-// score_token_fold_kernel, where the heads of a turn are few.)
+// grid (H_k * parts, n_layers); a workgroup owns d / parts channels of a KV head: kFoldThreads threads = row slots x lanes of 8 channels.  The r *
+// T_q rows of a KV head are contiguous in Q: the mean alone is one sum over them.  TOKENS: every token's mean over the r heads is wanted too, so a
+// slot takes whole tokens.  Bound by latency and by what the few compute units that take part can load, hence parts of 64 channels in small launches
+// (fold_parts in oqm_dispatch.h).  28 layers x 28 heads of 128 in a graph of the whole question, 256 threads per head / 512 / 512 per part: 32 tokens
+// 5.4 / 4.5 / 4.4 us, 64 7.5 / 5.7 / 5.0, 64 with every token kept 10.2 / 9.4 / 7.0.  Rows that no slot of the workgroup has are not converted (8
+// rows a trip, 0.1 us each): mean query of one token over 28 x 1024 groups 21.2 -> 19.6 us, fused with the scores of one layer x 256 groups 8.9 ->
+// 8.3, 16 rows 12.1 -> 11.9.  (Not worth its branches in score_token_fold_kernel, where the heads of a turn are few.)
 template <typename QT, bool TOKENS>
 __global__ void __launch_bounds__(kFoldThreads) query_fold_kernel(const ScoreArgs a, const int parts) {
     constexpr int EB = elem_bytes<QT>::value;
@@ -556,9 +555,9 @@ __device__ __forceinline__ void gemm_rows(const ScoreArgs& a, double (&As)[2][SI
     }
 }
 
-// MOST: row tiles of a pass.  With one or two the whole question is one pass, and with registers and LDS for them alone six or four
-// workgroups share a compute unit instead of three: 28 layers x 2200 groups x 2 heads of 128 x 16 tokens 29.3 -> 26.5 us (whole question, k = 1), 32 tokens
-// 37.9 -> 35.3, 2000 x 1 head of 64 x 16 18.5 -> 16.6; up to one round of the chip 1 to 2 %.  Three tiles gain nothing.
+// MOST: row tiles of a pass.  With one or two the whole question is one pass, and with registers and LDS for them alone six or four workgroups share
+// a compute unit instead of three: 28 layers x 2200 groups x 2 heads of 128 x 16 tokens 29.3 -> 26.5 us (whole question, k = 1), 32 tokens 37.9 ->
+// 35.3, 2000 x 1 head of 64 x 16 18.5 -> 16.6; up to one round of the chip 1 to 2 %.  Three tiles gain nothing.
 template <int MOST, int NG>
 __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArgs a) {
     // two LDS stages: chunk c is multiplied while chunk c+1 travels global -> registers -> LDS
@@ -590,12 +589,14 @@ __global__ void __launch_bounds__(kBlock) score_token_gemm_kernel(const ScoreArg
                         gemm_rows<1, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2);
                         break;
                     }
+                    [[fallthrough]];
                 case 2: gemm_rows<2, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
                 case 3:
                     if constexpr (NG == 4) {
                         gemm_rows<3, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2);
                         break;
                     }
+                    [[fallthrough]];
                 default: gemm_rows<4, NG>(a, As, Bs, qtok, keys, m0, n0, li, colsum, nk2); break;
             }
         }
@@ -735,13 +736,15 @@ __global__ void __launch_bounds__(kSplitThreads) score_token_split_kernel(const 
     }
 }
 
-// Fold and split contraction in one launch, for small launches (fold_tiles in oqm_dispatch.h): the query is folded where it enters the MFMA registers.  Lane (fi, kk)
-// takes token fi of a tile and channels 8 kk .. 8 kk + 7 of a block of 32, loads 16 bytes of each of the r query heads that its KV head stands for, and averages them on the vector
-// pipe; blocks go round the eight waves, pieces past the end of the query are read as zero.  Every workgroup of a layer reads its question, at 2 r bytes an element against the 8 of a
-// folded one, so the launch of the fold (4.5 us and more) is saved for nothing up to four heads; with more the conversions and the loads of a block in RH heads at a time cost more than they save.  Bound by latency:
-// load, convert, MFMA, two blocks a wave at 512 channels.  Whole question on the device at 4 groups, bf16, before / now: one layer x 64 groups x 1 head of 64 x 13 tokens 11.6 / 8.7 us,
-// 28 x 280 x 1 of 128 x 64 18.9 / 13.5, 16 x 512 x 12 heads on 3 of 96 x 30 19.1 / 14.8, 28 x 130 x 16 on 4 of 128 x 64 24.7 / 19.5, 28 x 100 x 10 on 5 of 256 x 64 43.8 / 29.6, 28 on 4 of 128, one layer x 256 x 16 13.0 / 11.9.
-// MT tiles of 16 tokens a pass: 72 to 127 registers with one or two, 148 to 223 with three or four (one workgroup a compute unit).
+// Fold and split contraction in one launch, for small launches (fold_tiles in oqm_dispatch.h): the query is folded where it enters the MFMA
+// registers.  Lane (fi, kk) takes token fi of a tile and channels 8 kk .. 8 kk + 7 of a block of 32, loads 16 bytes of each of the r query heads that
+// its KV head stands for, and averages them on the vector pipe; blocks go round the eight waves, pieces past the end of the query are read as zero.
+// Every workgroup of a layer reads its question, at 2 r bytes an element against the 8 of a folded one, so the launch of the fold (4.5 us and more)
+// is saved for nothing up to four heads of 16 bits; with more the conversions and the loads of a block in RH heads at a time cost more than they save.  Bound by
+// latency: load, convert, MFMA, two blocks a wave at 512 channels.  Whole question on the device at 4 groups, bf16, before / now: one layer x 64
+// groups x 1 head of 64 x 13 tokens 11.6 / 8.7 us, 28 x 280 x 1 of 128 x 64 18.9 / 13.5, 16 x 512 x 12 heads on 3 of 96 x 30 19.1 / 14.8, 28 x 130 x
+// 16 on 4 of 128 x 64 24.7 / 19.5, 28 x 100 x 10 on 5 of 256 x 64 43.8 / 29.6, 28 on 4 of 128, one layer x 256 x 16 13.0 / 11.9. MT tiles of 16
+// tokens a pass: 78 to 128 registers with one or two, 144 to 223 with three or four (one workgroup a compute unit).
 struct TokenFold {
     uint32_t inv_head_dim;
 };
@@ -912,9 +915,9 @@ static hipError_t launch_query_fold(const ScoreArgs& a, bool want_tokens, hipStr
     }
 }
 
-// Calls go with the pieces of 4 * W key channels that a lane loads together and what they leave, as types,
-// and the bytes of a staged q-bar: one trip of up to eight pieces, or the fewest equal trips if they leave nothing.  Exactly as many pieces as the key has
-// instead of two, four or eight: 28 layers x 1024 groups x 5 heads of 128 24.2 -> 21.1 us (whole question, k = 1), 3 of 96 18.5 -> 17.3.
+// Calls go with the pieces of 4 * W key channels that a lane loads together and what they leave, as types, and the bytes of a staged q-bar: one trip
+// of up to eight pieces, or the fewest equal trips if they leave nothing.  Exactly as many pieces as the key has instead of two, four or eight: 28
+// layers x 1024 groups x 5 heads of 128 24.2 -> 21.1 us (whole question, k = 1), 3 of 96 18.5 -> 17.3.
 template <int W, typename GO>
 static hipError_t with_pieces(int HD, GO go) {
     const int pieces = (HD + 4 * W - 1) / (4 * W), trips = (pieces + kScoreChunks - 1) / kScoreChunks;
