@@ -95,19 +95,23 @@ constexpr int kGemmN = 64;  // groups of a unit of the 64 x 64 form
 //   513 to 768 units: 256 channels x 8 tokens 0.98 to 0.99, x 15 11.1 / 11.7; 288 x 10 12.1 / 11.6; 320 x 13 0.95; 400 x 15 15.0 / 13.6; 512 x 16
 //     0.97; 1024 x 16 0.95
 //   769 to 1024 (with more than 256 units of 64 as the next row: 1012 of 256 x 1 13.1 / 11.1): 256 x 1 1.00 to 1.03; 288 x 3 12.1 / 11.6; 320 x 5
-//     0.97, x 8 12.8 / 13.4; 480 x 6 15.9 / 15.1; 512 x 7 0.98, x 12 16.3 / 17.9; 1024 x 9 0.97, x 14 25.1 / 27.1; 2048 x 9 0.91, x 12 1.02
-//   1025 to 1280: 256 x 7 0.98, x 12 1.04; 320 x 9 15.2 / 14.3; 400 x 11 0.97; 512 x 9 0.91, x 14 1.01; 1024 x 11 0.92, x 15 1.01; 2048 x 15 0.99
+//     0.97, x 8 12.8 / 13.4; 480 x 6 15.9 / 15.1; 512 x 7 0.98, x 12 16.3 / 17.9; 1024 x 9 0.97, x 14 25.1 / 27.1; 1280 x 11 1.00, x 14 1.07; 2048 x 12
+//     0.83 (again 1.02), x 14 0.87 (1.07).  Keys of 1280 channels and more go on by a second line.
+//   1025 to 1280: 256 x 7 0.98, x 12 1.04; 320 x 9 15.2 / 14.3; 400 x 10 0.95; 512 x 11 0.97, x 14 1.01; 1024 x 11 0.92, x 15 1.01; 1280 x 13 1.02 to 1.06
+//     (0.93), x 16 1.12 to 1.16 (1.03); 2048 x 14 0.92 (0.96)
 //   1281 to 1536: 256 x 1 13.3 / 14.0; 320 x 1 1.00, x 5 1.04; 400 x 4 18.1 / 16.6; 512 x 5 19.7 / 18.7, x 8 1.03; 640 x 6 24.0 / 22.7; 768 x 8 1.00;
-//     1024 x 9 0.96, x 11 1.02; 2048 x 8 0.94
-//   1537 to 1792: 512 x 1 1.01; 768 x 3 1.00, x 7 1.06; 1024 x 3 38.6 / 34.5, x 5 38.5 / 35.6; 2048 x 5 0.95, x 16 1.34
-//   1793 to 2048: 512 x 2 1.12; 1024 x 1 40.3 / 37.6, x 2 1.02; 2048 x 1 71.9 / 62.9, x 9 1.21
-// Three stores in turn; with the same question again within 4 % of it, mostly 1 to 3 % in favour of this form (1024 channels from 1537 units on 4 to
-// 8 % against it: x 3 33.6 / 31.8, x 1 at 1863 33.9 / 34.3).
+//     1024 x 9 0.96, x 11 1.02; 1280 x 9 1.04 to 1.07 (0.95), x 11 1.13 (1.03); 2048 x 10 0.94 (0.98), x 14 1.03 (1.11)
+//   1537 to 1792: 512 x 1 1.01; 768 x 3 1.00, x 7 1.06; 1024 x 3 38.6 / 34.5, x 5 38.5 / 35.6; 1280 x 5 1.00 to 1.02 (0.96), x 9 1.16 (1.08); 2048 x 7
+//     0.96 (1.02), x 11 1.05 (1.16)
+//   1793 to 2048: 512 x 2 1.12; 1024 x 1 40.3 / 37.6, x 2 1.02; 1280 x 1 0.87 to 0.94 (0.79 to 0.98), x 5 1.01 to 1.07; 2048 x 3 0.93 (0.78 to 0.99), x
+//     7 1.00 to 1.03 (0.89 to 1.14)
+// Three stores in turn (the same question again, where it differs by more than 4 %; 1024 channels from 1537 units on gain 4 to 8 % less again).
 inline bool one_tile_splits(int64_t units, int64_t wide, int t_q, int channels) {
-    static constexpr struct { int c, k, channels; } kLine[] = {{40, 8192, 256}, {11, 1800, 288}, {17, 2400, 256}, {13, 3600, 352}, {10, 5000, 256}, {6, 5000, 256}};  // three to eight units a compute unit
+    static constexpr struct { int c, k, channels; } kLine[] = {{40, 8192, 256}, {11, 1800, 288}, {15, 1900, 256}, {12, 3000, 352}, {9, 4000, 576}, {6, 5000, 256}};  // three to eight units a compute unit
     int64_t step = (units + 255) / 256 - 3;
     if (step == 1 && wide > 256) step = 2;
     if (t_q > 16 || step < 0 || step > 5 || channels < kLine[step].channels) return false;
+    if (step == 1 && (int64_t)(16 - t_q) * channels >= 6400) return true;
     return (int64_t)(kLine[step].c - t_q) * channels >= kLine[step].k;
 }
 

@@ -176,9 +176,9 @@ static void split() {
     CHECK(tiles(4, 1024, 64) == 4 && tiles(4, 1024, 65) == 3 && tiles(4, 1024, 1 << 20) == 4);
     CHECK(tiles(65535, 0x7fffffff, 1) == 0);                     // far beyond, no overflow
     // one tile of tokens on keys of 256 channels and more: the most tokens, by units a compute unit
-    const struct { int channels, most[8]; } one_tile[] = {{248, {16}}, {256, {16, 8, 0, 7}}, {280, {16, 10, 0, 8}}, {288, {16, 11, 4, 8}}, {320, {16, 14, 5, 9}}, {344, {16, 16, 5, 10}}, {352, {16, 16, 5, 10, 2}}, {400, {16, 16, 6, 11, 4}},
-                                                          {512, {16, 16, 7, 12, 5, 0, 0, 0}}, {768, {16, 16, 8, 13, 8, 3, 0, 0}}, {1024, {16, 16, 9, 14, 9, 5, 1, 0}},
-                                                          {2048, {16, 16, 10, 15, 11, 7, 3, 0}}, {1 << 20, {16, 16, 10, 16, 12, 9, 5, 0}}};
+    const struct { int channels, most[8]; } one_tile[] = {{248, {16}}, {256, {16, 8, 0, 7}}, {280, {16, 10, 0, 8}}, {288, {16, 11, 4, 8}}, {320, {16, 14, 5, 9}}, {344, {16, 16, 5, 9}}, {352, {16, 16, 5, 9, 3}}, {400, {16, 16, 6, 10, 4}},
+                                                          {512, {16, 16, 7, 11, 6, 0, 0, 0}}, {576, {16, 16, 7, 11, 6, 2, 0, 0}}, {768, {16, 16, 8, 12, 8, 3, 0, 0}}, {1024, {16, 16, 9, 13, 9, 5, 1, 0}},
+                                                          {1280, {16, 16, 11, 13, 9, 5, 2, 0}}, {2048, {16, 16, 12, 14, 10, 7, 3, 0}}, {3072, {16, 16, 13, 14, 11, 7, 4, 0}}};
     for (const auto& w : one_tile)
         for (int i = 0; i < 8; ++i)
             for (int units : {i ? 256 * (i + 1) + 1 : 1, 256 * (i + 2)}) {
